@@ -1,16 +1,22 @@
 // gather_pool: embedding-row gather with per-bag sum pooling.
 //
-// A wave owns 64 consecutive bags.  First every lane loads the bounds and the first kIdsInRegs
-// indices of ONE bag (coalesced: the bags of a wave are neighbours in `offsets` and in the index
-// array).  Then the wave walks its bags in rounds: a group of lanes (dim/4 rounded up to a power of
-// two, at most the whole wave) takes one bag per round, gets the bag's indices from the owner lane by
-// shuffle, reads the rows (one coalesced access per row, kIdsInRegs of them in flight) and writes the
-// pooled row once, in full lines.  Rows wider than 256 elements are walked in segments of 256 by the
-// whole wave.  The few bags longer than kIdsInRegs read their remaining indices from memory.  A wave
-// whose bags all hold at most two IDs (one-hot slots) issues four rounds of row reads together instead
-// (81 -> 69 us on the workload with one ID per bag).
-// Measured on MI355X the earlier one-group-per-bag kernel spent half its time
-// on the dependent offset -> index -> row chain issued by eight times as many waves.
+// A wave owns a few consecutive bags, at most 64.  First every lane loads the bounds and the first
+// kIdsInRegs indices of ONE bag (coalesced: the bags of a wave are neighbours in `offsets` and in the
+// index array).  Then the wave walks its bags in rounds: a group of lanes takes one bag per round, gets
+// the bag's indices from the owner lane by shuffle, reads the rows (one coalesced access of 16 bytes per
+// lane and row, kIdsInRegs rows in flight) and writes the pooled row once, in full lines.  Rows wider than
+// 64 lanes hold are walked in segments by the whole wave.  A bag longer than kIdsInRegs goes on in steps
+// of kIdsInRegs indices, the next step's indices requested before this step's rows are waited for (bags
+// of 23 IDs on average, dim 36: 144 us per launch when the rest of a long bag was read one row at a time,
+// 20 us so).  A wave whose bags all hold at most two IDs (one-hot slots) issues four rounds of row reads
+// together instead (81 -> 69 us on the workload with one ID per bag).
+//
+// How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
+// thousand of them: 64 where that still leaves kWavesWanted waves (the index loads are then as coalesced
+// as they can be), else as few as one round needs (33 K bags of dim 512: one wave per 64 bags was 512
+// waves on 256 compute units).
+// Large batches are bound by the rows and pooled rows that move behind the L2 (4.1-4.2 TB/s at 6.8 M and
+// 26 M IDs, of the 4.9 TB/s a plain copy reaches).
 // Summation is in occurrence order, in fp32.
 //
 // Where the rows come from is a policy of the kernel:
@@ -25,72 +31,124 @@
 namespace mono {
 
 constexpr int kIdsInRegs = 8;
+constexpr uint64_t kWavesWanted = 4096;  // half of what the chip can hold: enough loads in flight to hide their latency
 
-template <typename E>
-__device__ inline float4 load4(const E* rows, uint64_t row, uint32_t dim, uint32_t col);
-
+// N consecutive elements of a row as they are stored (one load), and their sum in fp32.
+template <typename E, int N>
+struct Piece;
 template <>
-__device__ inline float4 load4<float>(const float* rows, uint64_t row, uint32_t dim, uint32_t col) {
-  return *reinterpret_cast<const float4*>(rows + row * dim + col);
-}
-template <>
-__device__ inline float4 load4<uint16_t>(const uint16_t* rows, uint64_t row, uint32_t dim, uint32_t col) {
-  uint2 u = *reinterpret_cast<const uint2*>(rows + row * dim + col);
+struct Piece<float, 4> {
   float4 v;
-  v.x = __uint_as_float(u.x << 16);
-  v.y = __uint_as_float(u.x & 0xFFFF0000u);
-  v.z = __uint_as_float(u.y << 16);
-  v.w = __uint_as_float(u.y & 0xFFFF0000u);
-  return v;
+  __device__ void clear() { v = make_float4(0.f, 0.f, 0.f, 0.f); }
+  __device__ void add_to(float* a) const {
+    a[0] += v.x;
+    a[1] += v.y;
+    a[2] += v.z;
+    a[3] += v.w;
+  }
+};
+__device__ inline void add_bf16_pair(uint32_t u, float* a) {
+  a[0] += __uint_as_float(u << 16);
+  a[1] += __uint_as_float(u & 0xFFFF0000u);
+}
+template <>
+struct Piece<uint16_t, 4> {
+  uint2 v;
+  __device__ void clear() { v = make_uint2(0u, 0u); }
+  __device__ void add_to(float* a) const {
+    add_bf16_pair(v.x, a);
+    add_bf16_pair(v.y, a + 2);
+  }
+};
+template <>
+struct Piece<uint16_t, 8> {
+  uint4 v;
+  __device__ void clear() { v = make_uint4(0u, 0u, 0u, 0u); }
+  __device__ void add_to(float* a) const {
+    add_bf16_pair(v.x, a);
+    add_bf16_pair(v.y, a + 2);
+    add_bf16_pair(v.z, a + 4);
+    add_bf16_pair(v.w, a + 6);
+  }
+};
+
+template <typename E, int N>
+__device__ inline void load_piece(Piece<E, N>& p, const E* rows, uint64_t row, uint32_t dim, uint32_t col) {
+  p.v = *reinterpret_cast<const decltype(p.v)*>(rows + row * dim + col);
 }
 
-__device__ inline void add4(float4& a, const float4& b) {
-  a.x += b.x;
-  a.y += b.y;
-  a.z += b.z;
-  a.w += b.w;
-}
-
-template <typename E>
+template <typename E, int N_>
 struct TableRows {
+  static constexpr int N = N_;
   using Id = int32_t;
   const E* rows;
   const int32_t* idx;
   uint32_t cap;
+  struct Row {
+    Piece<E, N> p;
+    __device__ void clear() { p.clear(); }
+    __device__ void add_to(float* a) const { p.add_to(a); }
+  };
   __device__ Id none() const { return -1; }
   __device__ Id at(int64_t i) const { return idx[i]; }
   __device__ bool present(Id r) const { return (uint32_t)r < cap; }
-  __device__ float4 fetch(Id r, uint32_t dim, uint32_t col) const { return load4<E>(rows, (uint32_t)r, dim, col); }
+  __device__ void fetch(Row& x, Id r, uint32_t dim, uint32_t col) const { load_piece(x.p, rows, (uint32_t)r, dim, col); }
 };
 
-template <typename E>
+template <typename E, int N_>
 struct QuotRemRows {
+  static constexpr int N = N_;
   using Id = int64_t;
   const E* rem;    // E_r: 2^m rows
   const E* quot;   // E_q: 2^m rows
   const int64_t* ids;
   uint32_t m;
+  struct Row {
+    Piece<E, N> r, q;
+    __device__ void clear() {
+      r.clear();
+      q.clear();
+    }
+    __device__ void add_to(float* a) const {  // E_r + E_q first, then the bag's sum
+      float e[N];
+#pragma unroll
+      for (int i = 0; i < N; ++i) e[i] = 0.f;
+      r.add_to(e);
+      q.add_to(e);
+#pragma unroll
+      for (int i = 0; i < N; ++i) a[i] += e[i];
+    }
+  };
   __device__ Id none() const { return -1; }
   __device__ Id at(int64_t i) const { return ids[i]; }
   __device__ bool present(Id id) const { return ((uint64_t)id >> (2 * m)) == 0; }
-  __device__ float4 fetch(Id id, uint32_t dim, uint32_t col) const {
-    float4 a = load4<E>(rem, (uint64_t)id & ((1ull << m) - 1), dim, col);
-    add4(a, load4<E>(quot, (uint64_t)id >> m, dim, col));
-    return a;
+  __device__ void fetch(Row& x, Id id, uint32_t dim, uint32_t col) const {
+    load_piece(x.r, rem, (uint64_t)id & ((1ull << m) - 1), dim, col);
+    load_piece(x.q, quot, (uint64_t)id >> m, dim, col);
   }
 };
 
+template <int N>
+__device__ inline void store_pooled(float* out, const float* a) {
+#pragma unroll
+  for (int i = 0; i < N; i += 4) *reinterpret_cast<float4*>(out + i) = make_float4(a[i], a[i + 1], a[i + 2], a[i + 3]);
+}
+
+// group_log2: log2 of the lanes that share a row; bags_log2: log2 of the bags a wave owns (64 >> group_log2 at least)
 template <typename Src>
 __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t* __restrict__ offsets,
                                                           uint64_t n_bags, uint64_t n, uint32_t dim,
-                                                          uint32_t group_log2, float* __restrict__ out) {
+                                                          uint32_t group_log2, uint32_t bags_log2,
+                                                          float* __restrict__ out) {
   using Id = typename Src::Id;
+  using Row = typename Src::Row;
+  constexpr int N = Src::N;
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const uint64_t bag_base = wave * 64;
+  const uint64_t bag_base = wave << bags_log2;
   if (bag_base >= n_bags) return;  // wave-uniform
   const uint32_t lane = lane_id();
   // phase 1: lane <-> bag
-  const bool mine = bag_base + lane < n_bags;
+  const bool mine = lane < (1u << bags_log2) && bag_base + lane < n_bags;
   // offsets and indices are the caller's: both are bounded (to the n indices, to the table's
   // rows) so that a malformed input gives zeros, not an access out of range
   int64_t s = mine ? offsets[bag_base + lane] : 0;
@@ -103,102 +161,118 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   for (int j = 0; j < kIdsInRegs; ++j) id[j] = j < len ? src.at(s + j) : src.none();
   // phase 2: group <-> bag, one bag per group and round
   const uint32_t group = 1u << group_log2, l = lane & (group - 1u), g = lane >> group_log2;
-  const uint32_t bags_per_round = 64u >> group_log2;
-  const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
+  const uint32_t bags_per_round = 64u >> group_log2, rounds = (1u << bags_log2) >> (6u - group_log2);
   // Short bags (one or two IDs each, as in one-hot slots): a round keeps only one or two rows per
   // lane in flight, so four rounds are issued together instead.
   constexpr int kShort = 2, kRoundsTogether = kIdsInRegs / kShort;
   int longest = len;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) longest = max(longest, __shfl_xor(longest, d));
-  if (longest <= kShort && dim <= 256) {  // wave-uniform
-    const bool active = l * 4 < dim;
-    for (uint32_t q0 = 0; q0 < group; q0 += kRoundsTogether) {
-      float4 v[kRoundsTogether][kShort];
+  if (longest <= kShort && dim <= 64 * N) {  // wave-uniform
+    const bool active = l * N < dim;
+    for (uint32_t q0 = 0; q0 < rounds; q0 += kRoundsTogether) {
+      Row v[kRoundsTogether][kShort];
 #pragma unroll
       for (int rr = 0; rr < kRoundsTogether; ++rr) {
         const int from = (int)((q0 + rr) * bags_per_round + g) & 63;
 #pragma unroll
         for (int j = 0; j < kShort; ++j) {
           const Id r = __shfl(id[j], from);
-          v[rr][j] = (q0 + rr < group && src.present(r) && active) ? src.fetch(r, dim, l * 4) : zero;
+          v[rr][j].clear();
+          if (q0 + rr < rounds && src.present(r) && active) src.fetch(v[rr][j], r, dim, l * N);
         }
       }
 #pragma unroll
       for (int rr = 0; rr < kRoundsTogether; ++rr) {
-        float4 acc = v[rr][0];
-        add4(acc, v[rr][1]);
+        float acc[N] = {0.f};
+        v[rr][0].add_to(acc);
+        v[rr][1].add_to(acc);
         const uint64_t bag = bag_base + (q0 + rr) * bags_per_round + g;
-        if (q0 + rr < group && bag < n_bags && active) *reinterpret_cast<float4*>(out + bag * dim + l * 4) = acc;
+        if (q0 + rr < rounds && bag < n_bags && active) store_pooled<N>(out + bag * dim + l * N, acc);
       }
     }
     return;
   }
-  for (uint32_t q = 0; q < group; ++q) {
+  for (uint32_t q = 0; q < rounds; ++q) {
     const int from = (int)(q * bags_per_round + g);
     const int blen = __shfl(len, from);
     const int64_t bs = __shfl(s, from);
-    Id rid[kIdsInRegs];
-#pragma unroll
-    for (int j = 0; j < kIdsInRegs; ++j) rid[j] = __shfl(id[j], from);
     const uint64_t bag = bag_base + (uint32_t)from;
-    for (uint32_t col = l * 4; col < dim; col += 256) {  // one trip for rows of at most 256 elements
-      float4 v[kIdsInRegs];
+    for (uint32_t col0 = 0; col0 < dim; col0 += 64 * N) {  // one trip unless the row is wider than the wave
+      const uint32_t col = col0 + l * N;
+      const bool active = col < dim;
+      float acc[N] = {0.f};
+      Id rid[kIdsInRegs];
 #pragma unroll
-      for (int j = 0; j < kIdsInRegs; ++j) v[j] = src.present(rid[j]) ? src.fetch(rid[j], dim, col) : zero;
-      float4 acc = zero;
+      for (int j = 0; j < kIdsInRegs; ++j) rid[j] = __shfl(id[j], from);
+      for (int c = 0;;) {
+        Row v[kIdsInRegs];
 #pragma unroll
-      for (int j = 0; j < kIdsInRegs; ++j) add4(acc, v[j]);
-      for (int j = kIdsInRegs; j < blen; ++j) {  // long bag: the rest of its indices straight from memory
-        const Id r = src.at(bs + j);
-        if (src.present(r)) add4(acc, src.fetch(r, dim, col));
+        for (int j = 0; j < kIdsInRegs; ++j) {
+          v[j].clear();
+          if (src.present(rid[j]) && active) src.fetch(v[j], rid[j], dim, col);
+        }
+        c += kIdsInRegs;
+        const bool more = c < blen;
+        if (more) {  // a long bag: its next indices, straight from memory (the group's lanes ask for the same words)
+#pragma unroll
+          for (int j = 0; j < kIdsInRegs; ++j) rid[j] = c + j < blen ? src.at(bs + c + j) : src.none();
+        }
+#pragma unroll
+        for (int j = 0; j < kIdsInRegs; ++j) v[j].add_to(acc);
+        if (!more) break;
       }
-      if (bag < n_bags) *reinterpret_cast<float4*>(out + bag * dim + col) = acc;
+      if (bag < n_bags && active) store_pooled<N>(out + bag * dim + col, acc);
     }
   }
 }
 
-static uint32_t lane_group_log2(uint32_t dim) {
-  uint32_t g = 0;
-  while (g < 6 && (4u << g) < dim) ++g;
-  return g;
+// lanes per row, bags per wave and the grid of a launch
+struct GatherShape {
+  uint32_t group_log2 = 0, bags_log2 = 6;
+  dim3 grid;
+  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags) {
+    while (group_log2 < 6 && (n_per_lane << group_log2) < dim) ++group_log2;
+    while (bags_log2 > 6 - group_log2 && (n_bags >> bags_log2) < kWavesWanted) --bags_log2;
+    const uint64_t waves = (n_bags + (1ull << bags_log2) - 1) >> bags_log2;
+    grid = dim3((unsigned)((waves + 3) / 4));
+  }
+};
+
+template <typename Src>
+static hipError_t queue_gather(const Src& src, const int64_t* d_offsets, uint64_t n_bags, uint64_t n, uint32_t dim,
+                               float* d_out, hipStream_t stream, Profiler* prof) {
+  const GatherShape sh(dim, Src::N, n_bags);
+  MONO_LAUNCH(prof, K_GATHER_POOL, stream, gather_pool_kernel<Src>, sh.grid, dim3(256), src, d_offsets, n_bags, n, dim,
+              sh.group_log2, sh.bags_log2, d_out);
+  return hipGetLastError();
 }
 
+// bf16 rows are read eight elements per lane wherever a row is a whole number of such pieces (dim 512: one
+// access of the wave per row instead of two), else four
 hipError_t launch_gather_pool(const TableView& t, const int32_t* d_rows, uint64_t n, const int64_t* d_offsets,
                               uint64_t n_bags, float* d_out, hipStream_t stream, Profiler* prof) {
   if (n_bags == 0) return hipSuccess;
-  const uint32_t group_log2 = lane_group_log2(t.dim);
-  const uint64_t waves = (n_bags + 63) / 64;
-  const dim3 block(256), grid((unsigned)((waves + 3) / 4));
-  if (t.bf16) {
-    const TableRows<uint16_t> src{(const uint16_t*)t.rows, d_rows, (uint32_t)t.capacity};
-    MONO_LAUNCH(prof, K_GATHER_POOL, stream, gather_pool_kernel<TableRows<uint16_t>>, grid, block, src, d_offsets, n_bags,
-                n, t.dim, group_log2, d_out);
-  } else {
-    const TableRows<float> src{(const float*)t.rows, d_rows, (uint32_t)t.capacity};
-    MONO_LAUNCH(prof, K_GATHER_POOL, stream, gather_pool_kernel<TableRows<float>>, grid, block, src, d_offsets, n_bags, n,
-                t.dim, group_log2, d_out);
-  }
-  return hipGetLastError();
+  const uint32_t cap = (uint32_t)t.capacity;
+  if (!t.bf16)
+    return queue_gather(TableRows<float, 4>{(const float*)t.rows, d_rows, cap}, d_offsets, n_bags, n, t.dim, d_out, stream,
+                        prof);
+  const uint16_t* rows = (const uint16_t*)t.rows;
+  if (t.dim % 8 == 0)
+    return queue_gather(TableRows<uint16_t, 8>{rows, d_rows, cap}, d_offsets, n_bags, n, t.dim, d_out, stream, prof);
+  return queue_gather(TableRows<uint16_t, 4>{rows, d_rows, cap}, d_offsets, n_bags, n, t.dim, d_out, stream, prof);
 }
 
 hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t log2_rows, uint32_t dim, bool bf16,
                                  const int64_t* d_ids, uint64_t n, const int64_t* d_offsets, uint64_t n_bags,
                                  float* d_out, hipStream_t stream) {
   if (n_bags == 0) return hipSuccess;
-  const uint32_t group_log2 = lane_group_log2(dim);
-  const uint64_t waves = (n_bags + 63) / 64;
-  const dim3 block(256), grid((unsigned)((waves + 3) / 4));
-  if (bf16) {
-    const QuotRemRows<uint16_t> src{(const uint16_t*)d_rem, (const uint16_t*)d_quot, d_ids, log2_rows};
-    hipLaunchKernelGGL(gather_pool_kernel<QuotRemRows<uint16_t>>, grid, block, 0, stream, src, d_offsets, n_bags, n, dim,
-                       group_log2, d_out);
-  } else {
-    const QuotRemRows<float> src{(const float*)d_rem, (const float*)d_quot, d_ids, log2_rows};
-    hipLaunchKernelGGL(gather_pool_kernel<QuotRemRows<float>>, grid, block, 0, stream, src, d_offsets, n_bags, n, dim,
-                       group_log2, d_out);
-  }
-  return hipGetLastError();
+  if (!bf16)
+    return queue_gather(QuotRemRows<float, 4>{(const float*)d_rem, (const float*)d_quot, d_ids, log2_rows}, d_offsets,
+                        n_bags, n, dim, d_out, stream, nullptr);
+  const uint16_t *rem = (const uint16_t*)d_rem, *quot = (const uint16_t*)d_quot;
+  return queue_gather(QuotRemRows<uint16_t, 4>{rem, quot, d_ids, log2_rows}, d_offsets, n_bags, n, dim, d_out, stream,
+                      nullptr);
 }
 
 }  // namespace mono
