@@ -39,6 +39,9 @@ constexpr int kExportCount = 1;             // Control::scratch slot: elements f
 constexpr int kValidPairs = 2;              // Control::scratch slot: (row, bag) pairs kept by the sort
 constexpr int kRefusedRecords = 3;          // Control::scratch slot: records refused by the running restore call
 
+constexpr int kSmallMisses = 4;             // Control::scratch slots of the one-kernel lookup (zero between calls):
+constexpr int kSmallDone = 5;               // missing occurrences so far, blocks that have finished their probes
+
 struct StashEntry {
   uint64_t key;
   uint32_t row;

@@ -76,6 +76,11 @@ struct RestoreSource {
 hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, uint64_t n, uint32_t step, uint32_t epoch,
                                    int32_t* d_rows_out, const RestoreSource& src, hipStream_t stream, Profiler* prof);
 
+// The same in one kernel, for batches of at most kSmallLookup keys that are not a restore call.
+constexpr uint64_t kSmallLookup = 4096;
+hipError_t launch_lookup_small(const TableView& t, const int64_t* d_keys, uint64_t n, uint32_t step, uint32_t epoch,
+                               int32_t* d_rows_out, hipStream_t stream, Profiler* prof);
+
 // Re-inserts every element of src into dst (dst empty, same dim and storage type, capacity >= src's),
 // carries the free-row stack over and spreads the occurrence counters; rows are copied by the caller.
 hipError_t launch_migrate(const TableView& dst, const TableView& src, int32_t src_free_n, hipStream_t stream);

@@ -1,7 +1,7 @@
 // lookup_or_insert: cuckoo probe, count-before-admit, insertion with bounded eviction chain,
 // resolve (paper section 2.1; batch semantics of the build's contract).
 //
-// Four kernels per call:
+// Four kernels per call (small batches have one kernel of their own: lookup_small.hip):
 //   probe_count   (thread per occurrence) hit -> row index + last-seen stamp; miss -> touch the
 //                 key's occurrence counter
 //   admit_elect   (thread per occurrence, after ALL counts) miss with counter >= threshold -> one
@@ -19,58 +19,11 @@
 // admission whose row, accumulator and last-seen step come from the caller instead of from
 // init(seed, key) / the current step; a record whose key is already stored is refused.  The
 // migrate kernel re-inserts every stored element of one table into another (rehash / grow).
-//
-// Slot protocol (no 128-bit atomics, no fences): a slot's `meta` word doubles as its lock.
-//   free slot:   key == EMPTY, meta == kNoMeta
-//   claim:       CAS key EMPTY -> k (wait for the result); then store meta (publishes row + stamp)
-//   evict:       old = exch(meta, kNoMeta); row(old) == kNoRow -> slot is free or mid-write, try
-//                another; else the caller owns the slot: vk = exch(key, k) (wait), then store meta.
-//                The victim (vk, old) continues in its other sub-table.
-// Every access in the protocol is an agent-scope atomic performed at the coherence point, and each
-// step consumes the result of the previous one, so no ordering fence is needed.  No thread ever
-// waits for another one; every loop is bounded.
 #include "common.h"
 #include "kernels.h"
+#include "table_ops.h"
 
 namespace mono {
-
-// Counts are kept unsaturated in the low half of a counter word and read as min(count, 255).  Where
-// counters age, the first touch of a batch cuts the count back to 255; where they do not, a reader
-// does so once the count has passed kCountGuard (a batch adds less than 2^28).
-constexpr uint32_t kCountGuard = 1u << 30;
-
-// one counter word: `times` occurrences at `step`
-__device__ inline void touch_word(const TableView& t, unsigned long long* w, uint32_t step, uint32_t times) {
-  if (t.expire_steps == 0) {
-    // nothing ever ages: the stamp only moves forward and the count only grows, so two atomics
-    // whose results nobody waits for do it (low half = count, high half = last step)
-    uint32_t* half = reinterpret_cast<uint32_t*>(w);
-    atomicMax(half + 1, step);
-    atomicAdd(half, times);
-    return;
-  }
-  unsigned long long cur = ld_agent(w);
-  for (;;) {
-    if ((uint32_t)(cur >> 32) == step) {  // already touched in this batch: increments only
-      atomicAdd(w, (unsigned long long)times);  // unsaturated; read as min(count, 255)
-      return;
-    }
-    // first toucher of the batch: ages the word, stamps the step and adds its occurrences in one exchange
-    uint32_t last = (uint32_t)(cur >> 32), cnt = (uint32_t)cur;
-    if (cnt > 255u) cnt = 255u;  // the unsaturated count is cut back once per batch: it can never wrap
-    if (step - last >= t.expire_steps) cnt = 0;
-    const unsigned long long want = ((unsigned long long)step << 32) | (unsigned long long)(cnt + times);
-    const unsigned long long old = atomicCAS(w, cur, want);
-    if (old == cur) return;
-    cur = old;
-  }
-}
-
-// every counter of the key (section 2.1's probabilistic filter read as a counting filter with
-// filter_hashes hashes; two hashes of a key that fall on one counter touch it twice, as the oracle does)
-__device__ inline void touch_counter(const TableView& t, uint64_t key, uint32_t step, uint32_t times) {
-  for (uint32_t j = 0; j < t.filter_hashes; ++j) touch_word(t, &t.filter[filter_index(t, key, j)], step, times);
-}
 
 // Cooperative probe.  A lane owns one key; the eight lanes of a group then visit the group's eight
 // buckets one after another, each lane reading 16 bytes, so that a bucket line (eight keys + eight
@@ -325,127 +278,6 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
 
 // ---- insertion ---------------------------------------------------------------------------------
 
-__device__ inline void wait_all_memory_ops() {
-  __asm__ volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0);  // every load, store and atomic of this wave has been performed
-  __asm__ volatile("" ::: "memory");
-}
-
-// The bucket's bit in the occupancy bitmap.  Read first, with an ordinary load: most buckets that take a
-// key hold one already, and a stale copy can only show a bit as clear that another compute unit has set
-// in this very kernel (bits are cleared by the sweep alone, in a kernel of its own), which costs one
-// redundant atomic.
-__device__ inline void mark_occupied(const TableView& t, const Bucket* b) {
-  const uint64_t idx = (uint64_t)(b - t.buckets);
-  unsigned long long* w = &t.occupied[idx >> 6];
-  const unsigned long long bit = 1ull << (idx & 63);
-  if (!(*w & bit)) atomicOr(w, bit);
-}
-
-__device__ inline bool try_claim(const TableView& t, Bucket* b, uint64_t k, unsigned long long meta) {
-  // snapshot of the eight keys (may be stale: a slot seen free may be taken by now; the CAS decides)
-  const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(b->key);
-  const ulonglong2 a0 = kp[0], a1 = kp[1], a2 = kp[2], a3 = kp[3];
-  const uint64_t snap[kBucket] = {a0.x, a0.y, a1.x, a1.y, a2.x, a2.y, a3.x, a3.y};
-#pragma unroll
-  for (int l = 0; l < kBucket; ++l) {
-    if (snap[l] != kEmptyKey) continue;
-    if (atomicCAS((unsigned long long*)&b->key[l], (unsigned long long)kEmptyKey, (unsigned long long)k) ==
-        (unsigned long long)kEmptyKey) {
-      st_agent(&b->meta[l], meta);  // issued after the CAS has returned: publishes the slot
-      mark_occupied(t, b);
-      return true;
-    }
-  }
-  return false;
-}
-
-__device__ inline bool has_empty_key(const Bucket* b) {
-  const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(b->key);
-  const ulonglong2 a0 = kp[0], a1 = kp[1], a2 = kp[2], a3 = kp[3];
-  return a0.x == kEmptyKey || a0.y == kEmptyKey || a1.x == kEmptyKey || a1.y == kEmptyKey || a2.x == kEmptyKey ||
-         a2.y == kEmptyKey || a3.x == kEmptyKey || a3.y == kEmptyKey;
-}
-
-// Which resident of the full bucket b (in sub-table `side`) to evict.  A victim whose OTHER bucket has
-// a free slot ends the chain after one move, so the other buckets of the eight residents are looked
-// at first (eight independent line reads) and the first such resident from `start` on is chosen;
-// if there is none, `start` itself.  Only a hint: the snapshot may be stale, the protocol decides.
-// Measured on the streaming configuration at load 0.92: a random victim gave chains of up to 20
-// evictions, each five dependent memory round trips long, and the slowest chain is the kernel's time.
-__device__ inline uint32_t pick_victim(const TableView& t, const Bucket* b, int side, uint32_t start) {
-  const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(b->key);
-  const ulonglong2 a0 = kp[0], a1 = kp[1], a2 = kp[2], a3 = kp[3];
-  const uint64_t res[kBucket] = {a0.x, a0.y, a1.x, a1.y, a2.x, a2.y, a3.x, a3.y};
-  uint32_t good = 0;  // bit l: resident l could move out at once
-#pragma unroll
-  for (int l = 0; l < kBucket; ++l) {
-    if (res[l] == kEmptyKey) continue;
-    if (has_empty_key(&t.buckets[bucket_index(t, 1 - side, res[l])])) good |= 1u << l;
-  }
-  if (good == 0) return start;
-  const uint32_t rotated = ((good >> start) | (good << (kBucket - start))) & 0xFFu;  // bit 0 = slot `start`
-  return (start + (uint32_t)__ffs((int)rotated) - 1u) & (kBucket - 1);
-}
-
-// Inserts (k, meta); k is not in the table and no other thread inserts the same key.
-__device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long meta) {
-  int side = 0;
-  uint32_t chain = 0;
-#pragma unroll 1
-  for (int kick = 0; kick < kMaxKicks; ++kick) {
-    Bucket* b = &t.buckets[bucket_index(t, side, k)];
-    if (try_claim(t, b, k, meta)) goto done;
-    if (kick == 0 && try_claim(t, &t.buckets[bucket_index(t, 1, k)], k, meta)) goto done;
-    // evict: take the lock of a published slot
-    const uint32_t v0 = pick_victim(t, b, side, (uint32_t)(mix64(k + (uint64_t)kick) >> 61));
-#pragma unroll 1
-    for (int tries = 0; tries < kBucket; ++tries) {
-      const int l = (int)((v0 + (uint32_t)tries) & (kBucket - 1));
-      const unsigned long long old = atomicExch(&b->meta[l], kNoMeta);
-      if (meta_row(old) == kNoRow) continue;  // free or mid-write: not ours
-      const uint64_t vk = atomicExch((unsigned long long*)&b->key[l], (unsigned long long)k);
-      wait_all_memory_ops();  // the key exchange is performed before the slot is published again
-      st_agent(&b->meta[l], meta);
-      k = vk;
-      meta = old;
-      side = 1 - side;  // the victim continues in its other sub-table
-      ++chain;
-      break;
-    }
-  }
-  {  // chain bound hit: keep the homeless element aside
-    const uint32_t s = atomicAdd(&t.ctl->stash_n, 1u);
-    atomicAdd(&t.ctl->n_insert_failed, 1ull);
-    if (s < kStashCap) {
-      t.stash[s].key = k;
-      t.stash[s].row = meta_row(meta);
-      t.stash[s].seen = meta_seen(meta);
-    } else {
-      atomicAdd(&t.ctl->n_lost, 1ull);
-    }
-  }
-done:
-  // (read first: an atomic on this one word from every insertion that evicted serialises at ~12 ns each,
-  // which at load 0.8 was most of the kernel's time)
-  if (chain && (unsigned long long)chain > ld_agent(&t.ctl->max_chain))
-    atomicMax(&t.ctl->max_chain, (unsigned long long)chain);
-}
-
-template <typename E>
-__device__ inline void store_init4(E* rows, uint64_t idx, float4 v);
-template <>
-__device__ inline void store_init4<float>(float* rows, uint64_t idx, float4 v) {
-  *reinterpret_cast<float4*>(rows + idx) = v;
-}
-template <>
-__device__ inline void store_init4<uint16_t>(uint16_t* rows, uint64_t idx, float4 v) {
-  uint2 u;
-  u.x = (uint32_t)f32_to_bf16(v.x) | ((uint32_t)f32_to_bf16(v.y) << 16);
-  u.y = (uint32_t)f32_to_bf16(v.z) | ((uint32_t)f32_to_bf16(v.w) << 16);
-  *reinterpret_cast<uint2*>(rows + idx) = u;
-}
-
 // Dense over the elected occurrences: winner number w of the call takes free_rows[free_n - 1 - w].
 template <typename E>
 __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step, int32_t* rows_out,
@@ -462,7 +294,6 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
   const int32_t free0 = t.ctl->free_n;  // settled by the resolve kernel, constant here
   // all of the call's new keys fit under the fill limit, or none of them is placed
   const bool room = (int64_t)total <= rows_on_offer(t.capacity, free0);
-  E* rows = reinterpret_cast<E*>(t.rows);
   const uint32_t stride = gridDim.x * blockDim.x;
   for (uint32_t w0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); w0 < total; w0 += stride) {
     const uint32_t w = w0 + lane;
@@ -502,33 +333,7 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
         }
       }
     }
-    // the wave initialises its new rows together: a group of dim/4 lanes per row (at most the whole
-    // wave, which then walks the row in pieces of 256 elements), four elements per lane, 64/group rows
-    // at a time, stored as whole 16-byte (fp32) or 8-byte (bf16) pieces
-    uint32_t glog = 0;
-    while (glog < 6 && (4u << glog) < t.dim) ++glog;
-    const uint32_t group = 1u << glog, per_round = 64u >> glog, l = lane & (group - 1u), gi = lane >> glog;
-    const int ok = valid && row != kNoRow;
-    if (__ballot(ok) == 0) continue;  // wave-uniform
-    for (uint32_t q = 0; q < group; ++q) {
-      const int from = (int)(q * per_round + gi);
-      const uint64_t kk = __shfl(k, from);
-      const uint32_t rr = __shfl(row, from);
-      const uint32_t oo = __shfl(occ, from);
-      if (!__shfl(ok, from)) continue;
-      for (uint32_t col = l * 4; col < t.dim; col += 256) {
-        float4 v;
-        if (src.values) {
-          v = *reinterpret_cast<const float4*>(src.values + (uint64_t)oo * t.dim + col);
-        } else {
-          const uint64_t base_h = mix64(kk ^ t.s_init);
-          v = make_float4(init_value(base_h, col), init_value(base_h, col + 1), init_value(base_h, col + 2),
-                          init_value(base_h, col + 3));
-        }
-        store_init4<E>(rows, (uint64_t)rr * t.dim + col, v);
-      }
-      if (l == 0) t.state[rr] = RowState{src.acc ? src.acc[oo] : 0.0f, 0u};
-    }
+    init_new_rows<E>(t, valid && row != kNoRow, k, row, occ, src);
   }
 }
 
@@ -544,17 +349,7 @@ __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, i
       total += t.win_cnt[l * kWinStride];
       t.win_cnt[l * kWinStride] = 0;
     }
-    const int32_t free0 = t.ctl->free_n;
-    const uint32_t offer = (uint32_t)rows_on_offer(t.capacity, free0);
-    const uint32_t got = total <= offer ? total : 0u;  // all of the call's new keys or none
-    t.ctl->free_n = free0 - (int32_t)got;
-    const uint32_t in_use = (uint32_t)t.capacity - (uint32_t)(free0 - (int32_t)got);
-    if (in_use > t.ctl->hwm) t.ctl->hwm = in_use;  // rows are handed out in ascending order
-    if (t.hwm_mail)  // the host reads this word when it pleases; the mark only ever grows, so a stale value is a safe one
-      __hip_atomic_store(t.hwm_mail, ((unsigned long long)epoch << 32) | (unsigned long long)t.ctl->hwm, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_SYSTEM);
-    t.ctl->n_admitted += got;
-    t.ctl->n_full += total - got;
+    settle_call(t, total, t.ctl->free_n, epoch);
   }
 }
 
@@ -569,6 +364,7 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
                                    int32_t* d_rows_out, const RestoreSource& src, hipStream_t stream, Profiler* prof) {
   if (n == 0) return hipSuccess;
   const int restore = src.values != nullptr;
+  if (!restore && n <= kSmallLookup) return launch_lookup_small(t, d_keys, n, step, epoch, d_rows_out, stream, prof);
   const dim3 block(256), grid((unsigned)((n + 255) / 256));
   const dim3 igrid(grid.x < 2048u ? grid.x : 2048u);
   if (t.expire_steps == 0)

@@ -12,6 +12,7 @@ enum KernelId {
   K_ADMIT_ELECT,
   K_INSERT,
   K_RESOLVE,
+  K_LOOKUP_SMALL,
   K_GATHER_POOL,
   K_SORT_HIST,
   K_SORT_SCAN,
@@ -26,9 +27,9 @@ enum KernelId {
 };
 
 inline const char* kernel_name(int id) {
-  static const char* names[K_COUNT] = {"probe_count", "admit_elect", "insert", "resolve", "gather_pool",
-                                       "sort_hist",   "sort_scan",    "sort_scatter", "seg_reduce",  "combine",
-                                       "sweep_begin", "sweep_find", "sweep_remove", "sweep_end"};
+  static const char* names[K_COUNT] = {"probe_count", "admit_elect", "insert", "resolve",   "lookup_small",
+                                       "gather_pool", "sort_hist",   "sort_scan",    "sort_scatter", "seg_reduce",
+                                       "combine",     "sweep_begin", "sweep_find",   "sweep_remove", "sweep_end"};
   return id >= 0 && id < K_COUNT ? names[id] : "?";
 }
 
