@@ -238,6 +238,16 @@ int mono_table_stats(mono_table* t, mono_stats* h_out, void* stream);
 int mono_table_export(mono_table* t, int64_t* d_keys, int32_t* d_row, uint32_t* d_last_seen, int64_t* d_slot,
                       float* d_values, float* d_acc, uint64_t max_n, uint64_t* h_n, void* stream);
 
+/* mono_table_export (touched_only == 0) or mono_export_touched (!= 0) in ascending order of the keys as
+ * unsigned 64-bit numbers, sorted on the device.  d_keys and d_row must be given; the others may be NULL.  If more
+ * than max_n elements qualify, *h_n says how many, nothing is written and a synchronisation window stays open.
+ * d_work: scratch of at least mono_export_sorted_bytes(max_n) bytes, 256-byte aligned (max_n < 2^32).
+ * Synchronises `stream` to learn the count; the outputs are complete once the stream has passed the call. */
+size_t mono_export_sorted_bytes(uint64_t max_n);
+int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t* d_row, uint32_t* d_last_seen,
+                       int64_t* d_slot, float* d_values, float* d_acc, uint64_t max_n, void* d_work, size_t work_bytes,
+                       uint64_t* h_n, void* stream);
+
 /* Occurrence counters [first, first + count) in canonical form (step & 0xFFFFFF) << 8 | min(count, 255).
  * There are 4 * capacity counters unless mono_table_create_ex said otherwise. */
 int mono_filter_export(mono_table* t, uint32_t* d_words, uint64_t first, uint64_t count, void* stream);

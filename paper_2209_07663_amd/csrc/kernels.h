@@ -113,6 +113,23 @@ hipError_t launch_export(const TableView& t, int64_t* d_keys, int32_t* d_row, ui
                          uint64_t max_n, bool touched_only, hipStream_t stream);
 hipError_t launch_export_values(const TableView& t, const int32_t* d_row, uint64_t n, float* d_values, float* d_acc,
                                 hipStream_t stream);
+
+// Scratch of a sorted export of at most n elements: the elements as the scan finds them, and the sort's buffers.
+struct ExportWorkspace {
+  uint64_t* key[2];          // [n] ping, pong; the scan writes key[0]
+  uint32_t* idx[2];          // [n] position of the element in row / seen / slot
+  int32_t* row;              // [n]
+  uint32_t* seen;            // [n]
+  int64_t* slot;             // [n]
+  uint32_t* hist;            // [256 * (export_sort_units(n) + 1)]
+  unsigned long long* bits;  // OR and AND of all keys
+};
+uint64_t export_sort_units(uint64_t n);
+hipError_t launch_export_bits(const ExportWorkspace& ws, uint64_t n, hipStream_t stream);
+// varying: the bits in which the keys differ
+hipError_t launch_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t varying, int64_t* d_keys, int32_t* d_row,
+                              uint32_t* d_last_seen, int64_t* d_slot, hipStream_t stream);
+
 hipError_t launch_filter_export(const TableView& t, uint32_t* d_words, uint64_t first, uint64_t count,
                                 hipStream_t stream);
 hipError_t launch_filter_import(const TableView& t, const uint32_t* d_words, uint64_t first, uint64_t count,

@@ -192,6 +192,22 @@ hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
   return hipSuccess;
 }
 
+// Carves the scratch of a sorted export of at most n elements; with base == nullptr only measures.
+size_t export_workspace(ExportWorkspace* ws, char* base, uint64_t n) {
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* p = base ? base + off : nullptr;
+    off += align_up(bytes);
+    return p;
+  };
+  char *k0 = take(n * 8), *k1 = take(n * 8), *i0 = take(n * 4), *i1 = take(n * 4), *row = take(n * 4), *seen = take(n * 4),
+       *slot = take(n * 8), *hist = take(256 * (export_sort_units(n) + 1) * 4), *bits = take(2 * 8);
+  if (ws)
+    *ws = ExportWorkspace{{(uint64_t*)k0, (uint64_t*)k1}, {(uint32_t*)i0, (uint32_t*)i1}, (int32_t*)row,
+                          (uint32_t*)seen, (int64_t*)slot, (uint32_t*)hist, (unsigned long long*)bits};
+  return off;
+}
+
 void note_call(mono_table* t, uint32_t tag, uint64_t n) {
   t->recent_tag[tag % mono_table::kRecentCalls] = tag;
   t->recent_n[tag % mono_table::kRecentCalls] = n;
@@ -465,6 +481,39 @@ int mono_table_export(mono_table* t, int64_t* d_keys, int32_t* d_row, uint32_t* 
     if (launch_export_values(t->view, d_row, wrote, d_values, d_acc, s) != hipSuccess) return MONO_EHIP;
     if (hipStreamSynchronize(s) != hipSuccess) return MONO_EHIP;
   }
+  return MONO_OK;
+}
+
+size_t mono_export_sorted_bytes(uint64_t max_n) {
+  return max_n >> 32 ? 0 : export_workspace(nullptr, nullptr, max_n ? max_n : 1);
+}
+
+int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t* d_row, uint32_t* d_last_seen,
+                       int64_t* d_slot, float* d_values, float* d_acc, uint64_t max_n, void* d_work, size_t work_bytes,
+                       uint64_t* h_n, void* stream) {
+  if (!t || !h_n || !d_work || ((uintptr_t)d_work & 255) || max_n >> 32 || (max_n && (!d_keys || !d_row)))
+    return MONO_EINVAL;
+  ExportWorkspace ws;
+  if (export_workspace(&ws, (char*)d_work, max_n ? max_n : 1) > work_bytes) return MONO_EINVAL;
+  hipStream_t s = (hipStream_t)stream;
+  if (launch_export(t->view, (int64_t*)ws.key[0], ws.row, d_last_seen ? ws.seen : nullptr, d_slot ? ws.slot : nullptr,
+                    max_n, touched_only != 0, s) != hipSuccess)
+    return MONO_EHIP;
+  unsigned long long n = 0, bits[2] = {0, 0};
+  if (hipMemcpyAsync(&n, &t->view.ctl->scratch[kExportCount], sizeof(n), hipMemcpyDeviceToHost, s) != hipSuccess ||
+      hipStreamSynchronize(s) != hipSuccess)
+    return MONO_EHIP;
+  *h_n = n;
+  if (n > max_n) return MONO_OK;  // the caller's buffers are too small: nothing is written, a window stays open
+  if (n) {
+    if (launch_export_bits(ws, n, s) != hipSuccess ||
+        hipMemcpyAsync(bits, ws.bits, sizeof(bits), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+      return MONO_EHIP;
+    if (launch_export_sort(ws, n, bits[0] & ~bits[1], d_keys, d_row, d_last_seen, d_slot, s) != hipSuccess) return MONO_EHIP;
+    if ((d_values || d_acc) && launch_export_values(t->view, d_row, n, d_values, d_acc, s) != hipSuccess) return MONO_EHIP;
+  }
+  if (touched_only) t->view.sync_epoch += 1;  // a new window, as mono_export_touched starts one
   return MONO_OK;
 }
 

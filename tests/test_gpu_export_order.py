@@ -1,0 +1,51 @@
+"""Exports come sorted by key as unsigned numbers, by a radix sort on the device over the bits in which the keys
+differ: the numbers of elements at the edges of its units, keys that differ everywhere, in the low bits only, in the
+top bits only, and a single key; attributes and rows stay with their key."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import Oracle
+from tests import table_checks as tc
+
+pytestmark = pytest.mark.gpu
+
+
+def _keys(kind, n, rng):
+    k = np.unique(rng.integers(0, 1 << 63, n + 64).astype(np.uint64))
+    k = rng.permutation(k)[:n]
+    if kind == "low":
+        return (np.arange(n, dtype=np.uint64) * np.uint64(3)) | np.uint64(1 << 62)
+    if kind == "top":
+        return np.arange(n, dtype=np.uint64) << np.uint64(64 - 17)
+    return k ^ (k << np.uint64(1))                                      # all 64 bits
+
+
+@pytest.mark.parametrize("kind", ["all", "low", "top"])
+@pytest.mark.parametrize("n", [0, 1, 2, 2047, 2048, 2049, 70001])
+def test_exports_are_in_key_order(kind, n):
+    from paper_2209_07663_amd.binding import Table
+    dev, seed = torch.device("cuda:0"), 5
+    tab = Table(1 << 17, 8, seed, max_ids=1 << 17, device=dev)
+    orc = Oracle(1 << 17, 8, seed, 1, 0, False, kind="cuckoo")
+    keys = _keys(kind, n, np.random.default_rng(n)).astype(np.int64)
+    if n:
+        rows = tab.mono_lookup_or_insert(torch.from_numpy(keys).to(dev), 3)
+        orc.lookup_or_insert(keys, 3)
+    d = tab.mono_table_export()
+    assert (np.diff(d["keys"].view(np.uint64).astype(object)) > 0).all() if n < 3000 else \
+        (d["keys"].view(np.uint64)[1:] > d["keys"].view(np.uint64)[:-1]).all()
+    tc.assert_same_table(d, orc.dump(), exact_rows=True)
+    tc.check_placement(d, tab.capacity, 8, seed)
+    if not n:
+        assert tab.mono_export_touched()["n"] == 0
+        return
+    assert dict(zip(d["keys"].tolist(), d["row"].tolist())) == dict(zip(keys.tolist(), rows.cpu().tolist()))
+    offs = torch.arange(n + 1, dtype=torch.int64, device=dev)
+    tab.mono_apply_grad_adagrad(rows, offs, torch.ones((n, 8), device=dev), 0.1, 1e-8)
+    assert tab.mono_export_touched(max_n=n - 1) == {"n": n}             # too small: nothing is taken
+    touched, dump = tab.mono_export_touched(), tab.mono_table_export()
+    for name in ("keys", "row", "rows", "acc"):
+        assert (touched[name] == dump[name]).all()
+    assert tab.mono_export_touched(with_values=False)["n"] == 0
+    tab.close()
