@@ -17,20 +17,30 @@ struct UpdateWorkspace {
   uint32_t* part_row;   // [2 * tiles] row (+ head flag) of each partial, kNoRow if unused
 };
 
-// The sort comes in two shapes, chosen per call by the host from its bound on the rows in use:
-//   narrow  digits of at most 8 bits, blocks of 256 threads that own 2048 elements: three passes up to 2^24 rows
-//   wide    digits of at most 9 bits, blocks of 512 threads that own 4096 elements (so that a block's share of a
-//           bin still leaves as pieces of eight elements): three passes up to 2^27 rows, where narrow needs four.
-//           A wide pass takes a quarter longer than a narrow one (measured: 56 us against 45 us on 6.8 M pairs),
-//           so wide is taken only where it saves a pass: 1.33 -> 1.30 ms per step on the streaming workload
-//           (25 M rows in use), 5.78 -> 5.70 ms on the 26 M-ID workload.
+// The sort comes in several shapes, chosen per call by the host.  From its bound on the rows in use:
+//   narrow  digits of at most 8 bits, blocks of 256 threads: three passes up to 2^24 rows
+//   wide    digits of at most 9 bits, blocks of 512 threads: three passes up to 2^27 rows, where narrow needs four.
+//           A wide pass takes a quarter longer than a narrow one (measured on 6.8 M pairs), so wide is taken only
+//           where it saves a pass: 1.33 -> 1.30 ms per step on the streaming workload (25 M rows in use), 5.78 ->
+//           5.70 ms on the 26 M-ID workload.
+// From the size of the batch: how many elements a block owns.  Large batches want long shares of a bin (8
+// elements on average: 2048 per narrow block, 4096 per wide one).  Small ones are bound by the chain of
+// latencies of one block, which its elements lengthen, and have too few blocks to fill the chip: a scatter of
+// 26 K pairs takes 11.1 / 8.2 / 6.4 us with 2048 / 1024 / 512 elements per block, one of 204 K 10.8 / 8.0 / 7.0,
+// one of 690 K 12.0 / 9.9 / 10.5 (there the histograms, one word per bin and block, begin to cost more), one
+// of 1 M 12.9 / 12.5 / 12.8.
+// And batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch instead of nine.
 struct SortShape {
-  uint32_t max_bits, block, items;
+  uint32_t max_bits, items;
 };
-constexpr SortShape kSortNarrow = {8, 256, 2048};
-constexpr SortShape kSortWide = {9, 512, 4096};
+constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9;
 constexpr uint32_t kSortNarrowMaxRows = 1u << 24;  // beyond this many rows in use the wide shape saves a pass
-inline SortShape sort_shape_for(uint32_t hwm_bound) { return hwm_bound > kSortNarrowMaxRows ? kSortWide : kSortNarrow; }
+constexpr uint64_t kSortItems512 = 400000, kSortItems1024 = 1u << 20;  // largest batches of those block sizes
+constexpr uint64_t kSortSmall = 8192;
+inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
+  if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, n <= kSortItems1024 ? 1024u : 4096u};
+  return {kSortNarrowBits, n <= kSortItems512 ? 512u : (n <= kSortItems1024 ? 1024u : 2048u)};
+}
 constexpr int kPairsPerLane = 16;                  // sorted pairs per lane of a lane group in seg_reduce
 constexpr uint32_t kReduceTile = 256 * kPairsPerLane;  // sorted pairs reduced by one block
 
@@ -39,12 +49,19 @@ constexpr uint32_t kReduceTile = 256 * kPairsPerLane;  // sorted pairs reduced b
 #endif
 
 inline uint64_t sort_units(uint64_t n, uint32_t items) { return (n + items - 1) / items; }
-// words of the histogram workspace for batches of at most n elements: one histogram per unit, then the bin
-// totals, for whichever shape needs more
+inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // of a bin's counts: whole 16-byte pieces
+// words of the histogram workspace for batches of at most n elements, whatever the shape: one histogram per
+// unit, then the bin totals
 inline uint64_t sort_hist_words(uint64_t n) {
-  const uint64_t narrow = (1ull << kSortNarrow.max_bits) * (sort_units(n, kSortNarrow.items) + 1);
-  const uint64_t wide = (1ull << kSortWide.max_bits) * (sort_units(n, kSortWide.items) + 1);
-  return narrow > wide ? narrow : wide;
+  uint64_t most = 0;
+  const uint64_t sizes[] = {n, n < kSortItems512 ? n : kSortItems512, n < kSortItems1024 ? n : kSortItems1024};
+  for (const uint64_t m : sizes)
+    for (const uint32_t rows : {kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
+      const SortShape s = sort_shape_for(rows, m);
+      const uint64_t words = (1ull << s.max_bits) * (sort_stride(sort_units(m, s.items)) + 1);
+      most = words > most ? words : most;
+    }
+  return most;
 }
 inline uint64_t reduce_tiles(uint64_t n) { return (n + 255) / 256; }  // most tiles a batch can need (one pair per lane)
 

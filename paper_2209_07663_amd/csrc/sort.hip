@@ -3,9 +3,7 @@
 //
 // The key width is decided ON THE DEVICE: row indices are handed out in ascending order, so every
 // row in use is below the high-water mark `hwm` kept in the control block.  bit_length(hwm - 1)
-// bits are sorted in the fewest passes of equal width that the call's shape allows (digits of at most eight
-// bits in blocks of 2048 elements up to 16 M rows, of at most nine bits in blocks of 4096 elements beyond:
-// either way a block's share of a bin leaves as pieces of eight elements on average); the host picks the
+// bits are sorted in the fewest passes of equal width that the call's shape allows (kernels.h); the host picks the
 // shape and launches the passes that an upper bound of `hwm` needs (it keeps one without waiting for the
 // device: see the table's host side) and the superfluous ones return at once.  Pass p reads buffer (p even ? a : b)
 // and writes the other one.  Pass 0 reads the row indices as the caller holds them and finds the bag
@@ -14,16 +12,20 @@
 // (kValidPairs slot of the control block's scratch).
 //
 // Unit of work: one block owns kItems consecutive elements, an equal share per wave.  Per pass:
-//   hist     per-unit digit histogram (LDS atomics), written bin-major: hist[bin * units + unit]
+//   hist     per-unit digit histogram (LDS atomics), written bin-major: hist[bin * stride + unit]
 //   scan     one block per bin: exclusive scan along the units; bin totals to `totals`
-//   scatter  the block loads its elements into registers (all loads independent), counts the digits
-//            per wave in LDS, turns the counts into start offsets inside the block, then every wave
-//            ranks its elements 64 at a time by digit matching with ballots (stable: rank = number
-//            of lower lanes with the same digit) and puts them IN ORDER into an LDS copy of the
-//            block; the copy is then written out with neighbouring threads on neighbouring
-//            elements of a bin.  (Scattering straight from the registers sends one 8-byte write
-//            per element to the L2: measured, that request rate was what bounded the pass.)
+//   scatter  the block loads its elements into registers (all loads independent); every wave ranks its elements
+//            64 at a time by digit matching with ballots (stable: rank = the wave's earlier elements of the digit
+//            + lower lanes with it; what the ranking leaves behind are the wave's digit counts, which a loop
+//            of LDS atomics counted before: 46 -> 41 us a pass at 5.8 M pairs); the counts become start
+//            offsets inside the block, and the elements go IN ORDER into an LDS copy of the block, which is
+//            written out with neighbouring threads on neighbouring elements of a bin.  (Scattering
+//            straight from the registers sends one 8-byte write per element to the L2: measured, that
+//            request rate was what bounded the pass.)
 // No kernel spins or waits for another block.
+// Measured at 5.8 M pairs of 24-bit rows, per pass: hist 20-24 us (neither its LDS atomics nor its scattered words
+// bound it alone: ballots instead of atomics, or four units per block and 16-byte pieces, change it by a
+// microsecond), scan 5.4 (9.1 with single-word loads), scatter 33-35, the first one 51 with its walk of the bags.
 #include "common.h"
 #include "kernels.h"
 
@@ -41,13 +43,17 @@ struct Shape {
   static_assert(kBlock >= (int)kBins && kBlock % 64 == 0 && kItems % (uint32_t)kBlock == 0, "one thread per bin");
 };
 
-// Lanes of the wave that hold the same digit as this lane (among the lanes with valid == true).
+// Lanes of the wave that hold the same digit (of `bits` <= kBits bits) as this lane, among the lanes with valid == true.
+template <uint32_t kBits>
 __device__ inline uint64_t same_digit_lanes(uint32_t digit, uint32_t bits, bool valid) {
   uint64_t peers = __ballot(valid);
-  for (uint32_t b = 0; b < bits; ++b) {
-    const bool bit = (digit >> b) & 1u;
-    const uint64_t vote = __ballot(bit);
-    peers &= bit ? vote : ~vote;
+#pragma unroll
+  for (uint32_t b = 0; b < kBits; ++b) {
+    if (b < bits) {  // wave-uniform
+      const bool bit = (digit >> b) & 1u;
+      const uint64_t vote = __ballot(bit);
+      peers &= bit ? vote : ~vote;
+    }
   }
   return peers;
 }
@@ -82,70 +88,90 @@ __device__ inline uint32_t bag_holding(const int64_t* offsets, uint64_t n_bags, 
   return (uint32_t)lo;
 }
 
-// Pass 0 also notes, for the scatter kernel of the same pass, the bag that holds the unit's first
-// occurrence (the last wave of the block searches while the others count).
-template <uint32_t kBits, int kBlock, uint32_t kItems>
+// A block counts kUnits consecutive units.  Pass 0 has more blocks than that, in front: for the scatter kernel of
+// the same pass, their waves find the bag that holds a unit's first occurrence, a unit each (four dependent
+// memory round trips, beside the counting instead of after it).
+template <uint32_t kBits, int kBlock, uint32_t kItems, uint32_t kUnits>
 __global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __restrict__ ctl, uint32_t pass,
                                                                const int32_t* __restrict__ rows,
                                                                const uint2* __restrict__ src, uint64_t n,
-                                                               uint64_t units, uint32_t* __restrict__ hist,
+                                                               uint64_t stride, uint32_t* __restrict__ hist,
                                                                const int64_t* __restrict__ offsets, uint64_t n_bags,
-                                                               uint32_t* __restrict__ unit_bag) {
+                                                               uint32_t* __restrict__ unit_bag,
+                                                               uint32_t search_blocks) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   if (pass >= plan.passes) return;
   using S = Shape<kBits, kBlock, kItems>;
-  __shared__ uint32_t cnt[S::kBins];
-  const uint64_t unit = blockIdx.x;
+  __shared__ uint32_t cnt[kUnits][S::kBins];
+  if (blockIdx.x < search_blocks) {
+    const uint64_t unit = (uint64_t)blockIdx.x * S::kWaves + (threadIdx.x >> 6);
+    if (unit * kItems < n) {  // wave-uniform
+      const uint32_t b0 = bag_holding(offsets, n_bags, n, unit * kItems);
+      if (lane_id() == 0) unit_bag[unit] = b0;
+    }
+    return;
+  }
+  const uint64_t block = blockIdx.x - search_blocks;
   const uint32_t shift = plan.shift(pass), nbins = 1u << plan.width(pass), mask = nbins - 1;
-  for (uint32_t b = threadIdx.x; b < nbins; b += kBlock) cnt[b] = 0;
+  for (uint32_t b = threadIdx.x; b < S::kBins * kUnits; b += kBlock) cnt[0][b] = 0;
   __syncthreads();
-  const uint64_t base = unit * kItems;
+  const uint64_t base = block * kUnits * kItems;
   if (pass > 0) n = ctl->scratch[kValidPairs];
   // every key of the thread is requested before the first one is counted (left to itself the compiler
-  // keeps each load behind the LDS atomic before it: eight memory round trips in a row)
+  // keeps each load behind the LDS atomic before it: a memory round trip for each)
   constexpr uint32_t kPerThread = kItems / kBlock;
-  uint32_t key[kPerThread];
+  uint32_t key[kPerThread * kUnits];
 #pragma unroll
-  for (uint32_t r = 0; r < kPerThread; ++r) {
+  for (uint32_t r = 0; r < kPerThread * kUnits; ++r) {
     const uint64_t i = base + (uint64_t)r * kBlock + threadIdx.x;
     key[r] = plan.hwm;
     if (i < n) key[r] = pass == 0 ? first_key(rows, i, plan.hwm) : src[i].x;
   }
 #pragma unroll
-  for (uint32_t r = 0; r < kPerThread; ++r)
-    if (key[r] < plan.hwm) atomicAdd(&cnt[(key[r] >> shift) & mask], 1u);
+  for (uint32_t r = 0; r < kPerThread * kUnits; ++r)
+    if (key[r] < plan.hwm) atomicAdd(&cnt[r / kPerThread][(key[r] >> shift) & mask], 1u);
   __syncthreads();
-  for (uint32_t b = threadIdx.x; b < nbins; b += kBlock) hist[(uint64_t)b * units + unit] = cnt[b];
-  if (pass == 0 && (threadIdx.x >> 6) == S::kWaves - 1) {  // wave-uniform; after the last barrier: nobody waits for it
-    const uint32_t b0 = bag_holding(offsets, n_bags, n, unit * kItems);
-    if (lane_id() == 0) unit_bag[unit] = b0;
+  for (uint32_t b = threadIdx.x; b < nbins; b += kBlock) {
+    uint32_t* to = hist + (uint64_t)b * stride + block * kUnits;
+    if constexpr (kUnits == 4)
+      *reinterpret_cast<uint4*>(to) = make_uint4(cnt[0][b], cnt[1][b], cnt[2][b], cnt[3][b]);
+    else
+      *to = cnt[0][b];
   }
 }
 
-// exclusive scan of hist[bin * units + 0 .. units) in place; total of the bin to totals[bin].
-// One block per bin; thread t owns a run of consecutive units (loaded at once, summed serially),
+// exclusive scan of hist[bin * stride + 0 .. units) in place; total of the bin to totals[bin].
+// One block per bin; thread t owns a run of consecutive units (loaded at once in 16-byte pieces, summed serially),
 // the thread sums are scanned across the block, and the run is written back.
-constexpr uint32_t kScanPerThread = 16;  // units per thread and round
+constexpr uint32_t kScanQuads = 4;  // pieces of four units per thread and round
 template <uint32_t kBits>
 __global__ __launch_bounds__(256) void sort_scan_kernel(const Control* __restrict__ ctl, uint32_t pass,
                                                         uint32_t* __restrict__ hist, uint64_t units,
-                                                        uint32_t* __restrict__ totals) {
+                                                        uint64_t stride, uint32_t* __restrict__ totals) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   if (pass >= plan.passes || blockIdx.x >= (1u << plan.width(pass))) return;
   __shared__ uint32_t wave_sum[4];
-  __shared__ uint32_t carry_s;
-  uint32_t* row = hist + (uint64_t)blockIdx.x * units;
+  uint4* row = reinterpret_cast<uint4*>(hist + (uint64_t)blockIdx.x * stride);
+  const uint64_t quads = stride / 4;
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (threadIdx.x == 0) carry_s = 0;
-  __syncthreads();
-  for (uint64_t t0 = 0; t0 < units; t0 += 256ull * kScanPerThread) {
-    const uint64_t first = t0 + (uint64_t)threadIdx.x * kScanPerThread;
-    uint32_t v[kScanPerThread];
+  // (few units: as few pieces per thread as cover them, so that more threads load)
+  const uint32_t per = quads >= 256 * kScanQuads ? kScanQuads : (uint32_t)((quads + 255) / 256);
+  uint32_t carry = 0;
+  for (uint64_t t0 = 0; t0 < quads; t0 += 256ull * per) {
+    const uint64_t first = t0 + (uint64_t)threadIdx.x * per;
+    uint4 v[kScanQuads];
     uint32_t sum = 0;
 #pragma unroll
-    for (uint32_t j = 0; j < kScanPerThread; ++j) {
-      v[j] = first + j < units ? row[first + j] : 0;
-      sum += v[j];
+    for (uint32_t j = 0; j < kScanQuads; ++j) {
+      v[j] = j < per && first + j < quads ? row[first + j] : make_uint4(0u, 0u, 0u, 0u);
+      if ((first + j) * 4 + 4 > units) {  // the words after the last unit hold nothing
+        const uint64_t left = (first + j) * 4 < units ? units - (first + j) * 4 : 0;
+        if (left < 1) v[j].x = 0;
+        if (left < 2) v[j].y = 0;
+        if (left < 3) v[j].z = 0;
+        v[j].w = 0;
+      }
+      sum += v[j].x + v[j].y + v[j].z + v[j].w;
     }
     uint32_t x = sum;  // inclusive wave scan of the thread sums
 #pragma unroll
@@ -155,18 +181,22 @@ __global__ __launch_bounds__(256) void sort_scan_kernel(const Control* __restric
     }
     if (lane == 63) wave_sum[wave] = x;
     __syncthreads();
-    uint32_t run = carry_s + x - sum;
-    for (uint32_t w = 0; w < wave; ++w) run += wave_sum[w];
+    uint32_t run = carry + x - sum;
 #pragma unroll
-    for (uint32_t j = 0; j < kScanPerThread; ++j) {
-      if (first + j < units) row[first + j] = run;
-      run += v[j];
+    for (uint32_t w = 0; w < 4; ++w) {
+      if (w < wave) run += wave_sum[w];
+      carry += wave_sum[w];
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kScanQuads; ++j) {
+      const uint4 c = v[j];
+      const uint4 o = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
+      if (j < per && first + j < quads) row[first + j] = o;
+      run = o.w + c.w;
     }
     __syncthreads();
-    if (threadIdx.x == 255) carry_s = run;
-    __syncthreads();
   }
-  if (threadIdx.x == 0) totals[blockIdx.x] = carry_s;
+  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
 template <uint32_t kBits, int kBlock, uint32_t kItems>
@@ -176,7 +206,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
                                                                   uint64_t n_bags,
                                                                   const uint32_t* __restrict__ unit_bag,
                                                                   const uint2* __restrict__ src,
-                                                                  uint64_t n, uint64_t units,
+                                                                  uint64_t n, uint64_t stride,
                                                                   const uint32_t* __restrict__ hist,
                                                                   const uint32_t* __restrict__ totals,
                                                                   uint2* __restrict__ dst) {
@@ -197,7 +227,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   uint32_t tot = 0, before_me = 0;  // the bin in the whole batch / in the units before this one
   if (bin_thread && bin < nbins) {
     tot = totals[bin];
-    before_me = hist[(uint64_t)bin * units + unit];
+    before_me = hist[(uint64_t)bin * stride + unit];
   }
   // 1. this wave's elements -> registers (independent, coalesced loads)
   if (pass > 0) n = ctl->scratch[kValidPairs];
@@ -244,11 +274,23 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
     for (uint32_t r = 0; r < S::kRounds; ++r) kv[r].y = min(bag_here[wave * S::kPerWave + r * 64 + lane], last_bag);
   }
   __syncthreads();
-  // 2. per-wave digit counts
+  // 2. rank of every element among the wave's elements of its digit (stable), 64 at a time; what is left in
+  //    `lds` is the wave's digit counts
+  uint32_t rank[S::kRounds];  // digit << 16 | rank
+  {
+    volatile uint32_t* off = lds[wave];
 #pragma unroll
-  for (uint32_t r = 0; r < S::kRounds; ++r) {
-    if (kv[r].x != 0xFFFFFFFFu) atomicAdd(&lds[wave][(kv[r].x >> shift) & mask], 1u);
+    for (uint32_t r = 0; r < S::kRounds; ++r) {
+      const bool valid = kv[r].x != 0xFFFFFFFFu;
+      const uint32_t digit = (kv[r].x >> shift) & mask;
+      const uint64_t peers = same_digit_lanes<kBits>(digit, bits, valid);
+      rank[r] = (digit << 16) | (off[digit] + (uint32_t)__popcll(peers & lanes_below()));
+      __builtin_amdgcn_wave_barrier();
+      if (valid && (peers & lanes_below()) == 0) off[digit] += (uint32_t)__popcll(peers);
+      __builtin_amdgcn_wave_barrier();
+    }
   }
+  static_assert(kItems <= 0x10000, "rank and digit share a word");
   __syncthreads();
   // 3. thread b < S::kBins owns bin b: exclusive scans of the bin totals, once within the block
   //    (positions in `stage`) and once over all bins of the pass (start of the bin in dst)
@@ -295,18 +337,10 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
     }
   }
   __syncthreads();
-  // 4. rank (stable) into `stage`, 64 elements at a time
-  volatile uint32_t* off = lds[wave];
+  // 4. into `stage`, in sorted order
 #pragma unroll
-  for (uint32_t r = 0; r < S::kRounds; ++r) {
-    const bool valid = kv[r].x != 0xFFFFFFFFu;
-    const uint32_t digit = (kv[r].x >> shift) & mask;
-    const uint64_t peers = same_digit_lanes(digit, bits, valid);
-    if (valid) stage[off[digit] + (uint32_t)__popcll(peers & lanes_below())] = kv[r];
-    __builtin_amdgcn_wave_barrier();
-    if (valid && (peers & lanes_below()) == 0) off[digit] += (uint32_t)__popcll(peers);
-    __builtin_amdgcn_wave_barrier();
-  }
+  for (uint32_t r = 0; r < S::kRounds; ++r)
+    if (kv[r].x != 0xFFFFFFFFu) stage[lds[wave][rank[r] >> 16] + (rank[r] & 0xFFFFu)] = kv[r];
   __syncthreads();
   // 5. out: neighbouring threads write neighbouring elements of a bin
   uint32_t total = 0;
@@ -319,22 +353,128 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   }
 }
 
+// The whole sort of a batch of at most kSortSmall pairs by one block, all passes in LDS: 9 us for 8192 pairs where the
+// three kernels of three passes and the gaps between them take 55.  The result goes where the passes over
+// memory would have left it.
+constexpr int kSmallBlock = 1024;
+constexpr uint32_t kSmallWaves = kSmallBlock / 64, kSmallRounds = (uint32_t)kSortSmall / kSmallBlock;
+__global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __restrict__ ctl, uint32_t max_bits,
+                                                                 const int32_t* __restrict__ rows, uint32_t n,
+                                                                 const int64_t* __restrict__ offsets, uint64_t n_bags,
+                                                                 uint2* __restrict__ pair_a, uint2* __restrict__ pair_b) {
+  constexpr uint32_t kBins = 1u << kSortNarrowBits;
+  const SortPlan real = make_sort_plan(ctl->hwm, max_bits), plan = make_sort_plan(ctl->hwm, kSortNarrowBits);
+  __shared__ uint2 pairs[kSortSmall];
+  __shared__ uint32_t cnt[kSmallWaves][kBins];
+  __shared__ uint32_t wave_sum[kBins / 64];
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
+  const uint32_t rounds = (n + kSmallBlock - 1) / kSmallBlock;  // a wave owns 64 * rounds consecutive pairs
+  const uint32_t i0 = wave * 64 * rounds + lane;
+  uint2 kv[kSmallRounds];
+#pragma unroll
+  for (uint32_t r = 0; r < kSmallRounds; ++r) {
+    const uint32_t i = i0 + r * 64;
+    kv[r] = make_uint2(0xFFFFFFFFu, 0u);
+    if (r < rounds && i < n) kv[r].x = first_key(rows, i, plan.hwm);
+    if (kv[r].x >= plan.hwm) kv[r].x = 0xFFFFFFFFu;  // dropped occurrence (or past the end): left out
+  }
+  {  // every bag writes its number over its occurrences (all bags: a small batch has few)
+    uint32_t* bag_here = reinterpret_cast<uint32_t*>(pairs);
+    for (uint64_t b = tid; b < n_bags; b += kSmallBlock) {
+      const uint64_t from = bounded_offset(offsets, b, n), to = bounded_offset(offsets, b + 1, n);
+      for (uint64_t i = from; i < to; ++i) bag_here[i] = (uint32_t)b;
+    }
+    __syncthreads();
+    const uint32_t last_bag = (uint32_t)(n_bags - 1);  // (an occurrence outside every bag reads whatever the LDS held)
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; ++r)
+      if (r < rounds) kv[r].y = min(bag_here[i0 + r * 64], last_bag);
+  }
+  uint32_t count = n;  // elements that the pass reads: all occurrences, then the pairs that remain
+#pragma unroll 1
+  for (uint32_t pass = 0; pass < plan.passes; ++pass) {
+    const uint32_t shift = plan.shift(pass), bits = plan.width(pass), mask = (1u << bits) - 1;
+    if (pass > 0) {
+#pragma unroll
+      for (uint32_t r = 0; r < kSmallRounds; ++r)
+        kv[r] = r < rounds && i0 + r * 64 < count ? pairs[i0 + r * 64] : make_uint2(0xFFFFFFFFu, 0u);
+    }
+    volatile uint32_t* off = cnt[wave];
+#pragma unroll
+    for (uint32_t b = 0; b < kBins; b += 64) off[b + lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    uint32_t rank[kSmallRounds];  // digit << 16 | rank among the wave's elements of the digit
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; ++r) {
+      rank[r] = 0;
+      if (r < rounds) {  // block-uniform
+        const bool valid = kv[r].x != 0xFFFFFFFFu;
+        const uint32_t digit = (kv[r].x >> shift) & mask;
+        const uint64_t peers = same_digit_lanes<kSortNarrowBits>(digit, bits, valid);
+        rank[r] = (digit << 16) | (off[digit] + (uint32_t)__popcll(peers & lanes_below()));
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (peers & lanes_below()) == 0) off[digit] += (uint32_t)__popcll(peers);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();  // every wave has counted, and has its pairs in registers
+    uint32_t mine = 0;
+    if (tid < kBins) {
+#pragma unroll
+      for (uint32_t w = 0; w < kSmallWaves; ++w) mine += cnt[w][tid];
+    }
+    uint32_t x = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t y = __shfl_up(x, d);
+      if ((int)lane >= d) x += y;
+    }
+    if (tid < kBins && lane == 63) wave_sum[wave] = x;
+    __syncthreads();
+    if (tid < kBins) {
+      uint32_t at = x - mine;
+      for (uint32_t w = 0; w < wave; ++w) at += wave_sum[w];
+#pragma unroll
+      for (uint32_t w = 0; w < kSmallWaves; ++w) {
+        const uint32_t c = cnt[w][tid];
+        cnt[w][tid] = at;
+        at += c;
+      }
+    }
+    count = wave_sum[0] + wave_sum[1] + wave_sum[2] + wave_sum[3];
+    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < kSmallRounds; ++r)
+      if (kv[r].x != 0xFFFFFFFFu) pairs[cnt[wave][rank[r] >> 16] + (rank[r] & 0xFFFFu)] = kv[r];
+    __syncthreads();
+  }
+  uint2* dst = real.passes % 2 ? pair_b : pair_a;
+  for (uint32_t i = tid; i < count; i += kSmallBlock) dst[i] = pairs[i];
+  if (tid == 0) ctl->scratch[kValidPairs] = count;
+}
+
 template <uint32_t kBits, int kBlock, uint32_t kItems>
 static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                               const int64_t* d_offsets, uint64_t n_bags, uint32_t passes, hipStream_t stream,
                               Profiler* prof) {
-  const uint64_t units = sort_units(n, kItems);
-  uint32_t* totals = ws.hist + (uint64_t)(1u << kBits) * units;
+  const uint64_t units = sort_units(n, kItems), stride = sort_stride(units);
+  uint32_t* totals = ws.hist + (uint64_t)(1u << kBits) * stride;
   const dim3 block(kBlock), grid((unsigned)units);
   for (uint32_t p = 0; p < passes; ++p) {
     const uint2* src = p % 2 == 0 ? ws.pair_a : ws.pair_b;
     uint2* dst = p % 2 == 0 ? ws.pair_b : ws.pair_a;
-    MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems>), grid, block, t.ctl, p, d_rows, src, n,
-                units, ws.hist, d_offsets, n_bags, ws.unit_bag);
+    const uint32_t search = p == 0 ? (uint32_t)((units + kBlock / 64 - 1) / (kBlock / 64)) : 0u;
+    if (kItems >= 2048 && units >= 1024)
+      MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems, 4>),
+                  dim3((unsigned)(stride / 4) + search), block, t.ctl, p, d_rows, src, n, stride, ws.hist, d_offsets, n_bags,
+                  ws.unit_bag, search);
+    else
+      MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems, 1>), dim3((unsigned)units + search),
+                  block, t.ctl, p, d_rows, src, n, stride, ws.hist, d_offsets, n_bags, ws.unit_bag, search);
     MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3(1u << kBits), dim3(256), t.ctl, p, ws.hist, units,
-                totals);
+                stride, totals);
     MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems>), grid, block, t.ctl, p, d_rows,
-                d_offsets, n_bags, ws.unit_bag, src, n, units, ws.hist, totals, dst);
+                d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, totals, dst);
   }
 }
 
@@ -344,17 +484,32 @@ hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, cons
   // the shape and as many passes as the largest high-water mark the table can have by now needs (the device
   // knows the real mark: passes beyond its plan return at once)
   const uint32_t bound = hwm_bound < (uint32_t)t.capacity ? hwm_bound : (uint32_t)t.capacity;
-  const SortShape shape = sort_shape_for(bound);
+  const SortShape shape = sort_shape_for(bound, n);
   const SortPlan worst = make_sort_plan(bound, shape.max_bits);
   if (launched) *launched = worst.passes;
   if (max_bits) *max_bits = shape.max_bits;
   if (n == 0) return hipSuccess;
-  if (shape.max_bits == kSortWide.max_bits)
-    queue_sort_passes<kSortWide.max_bits, (int)kSortWide.block, kSortWide.items>(t, ws, d_rows, n, d_offsets, n_bags,
-                                                                                 worst.passes, stream, prof);
-  else
-    queue_sort_passes<kSortNarrow.max_bits, (int)kSortNarrow.block, kSortNarrow.items>(t, ws, d_rows, n, d_offsets,
-                                                                                       n_bags, worst.passes, stream, prof);
+  if (n <= kSortSmall && n_bags <= 2 * kSortSmall) {  // (one block walks all bags: not for a million empty ones)
+    MONO_LAUNCH(prof, K_SORT_SCATTER, stream, sort_small_kernel, dim3(1), dim3(kSmallBlock), t.ctl, shape.max_bits, d_rows,
+                (uint32_t)n, d_offsets, n_bags, ws.pair_a, ws.pair_b);
+    return hipGetLastError();
+  }
+#define MONO_SORT(bits, block, items) \
+  queue_sort_passes<bits, block, items>(t, ws, d_rows, n, d_offsets, n_bags, worst.passes, stream, prof)
+  if (shape.max_bits == kSortWideBits) {
+    if (shape.items == 1024)
+      MONO_SORT(kSortWideBits, 512, 1024);
+    else
+      MONO_SORT(kSortWideBits, 512, 4096);
+  } else {
+    if (shape.items == 512)
+      MONO_SORT(kSortNarrowBits, 256, 512);
+    else if (shape.items == 1024)
+      MONO_SORT(kSortNarrowBits, 256, 1024);
+    else
+      MONO_SORT(kSortNarrowBits, 256, 2048);
+  }
+#undef MONO_SORT
   return hipGetLastError();
 }
 
