@@ -15,6 +15,7 @@ struct UpdateWorkspace {
   uint32_t* hist;       // [sort_hist_words(max_ids)]: per-unit digit histograms (bin-major), then the bin totals
   float* part;          // [2 * tiles * dim] partial gradient sums of runs that cross tile borders
   uint32_t* part_row;   // [2 * tiles] row (+ head flag) of each partial, kNoRow if unused
+  uint64_t tiles;       // what part and part_row are for
 };
 
 // The sort comes in several shapes, chosen per call by the host.  From its bound on the rows in use:
@@ -41,8 +42,18 @@ inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
   if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, n <= kSortItems1024 ? 1024u : 4096u};
   return {kSortNarrowBits, n <= kSortItems512 ? 512u : (n <= kSortItems1024 ? 1024u : 2048u)};
 }
-constexpr int kPairsPerLane = 16;                  // sorted pairs per lane of a lane group in seg_reduce
-constexpr uint32_t kReduceTile = 256 * kPairsPerLane;  // sorted pairs reduced by one block
+// Pairs of a tile of the reduction: kReduceTile, halved while that leaves fewer than kTilesWanted tiles, as long as a
+// lane group (gpb of them in a block) keeps eight pairs to have in flight together.
+// (Large tiles only hold more LDS and leave fewer blocks to a compute unit: seg_reduce + combine of 5.8 M pairs of
+// dim 32 take 225 / 228 / 214 / 220 us with tiles of 4096 / 2048 / 1024 / 512 pairs.)
+constexpr uint32_t kReduceTile = 1024;
+constexpr uint64_t kTilesWanted = 2048;
+inline uint32_t reduce_tile(uint64_t n, uint32_t gpb) {
+  const uint32_t least = 8 * gpb < 256 ? 8 * gpb : 256;
+  uint32_t tile = kReduceTile;
+  while (tile > least && (n + tile - 1) / tile < kTilesWanted) tile >>= 1;
+  return tile;
+}
 
 #ifndef MONO_NOALLOC_MAX_IDS
 #define MONO_NOALLOC_MAX_IDS (1ull << 18)
@@ -63,7 +74,12 @@ inline uint64_t sort_hist_words(uint64_t n) {
     }
   return most;
 }
-inline uint64_t reduce_tiles(uint64_t n) { return (n + 255) / 256; }  // most tiles a batch can need (one pair per lane)
+// most tiles that a batch of at most n pairs can be cut into: tiles of fewer than 256 pairs (32 at least) only
+// where 256 would make fewer than kTilesWanted of them
+inline uint64_t reduce_tiles(uint64_t n) {
+  const uint64_t fine = (n + 31) / 32 < 2 * kTilesWanted ? (n + 31) / 32 : 2 * kTilesWanted, coarse = (n + 255) / 256;
+  return fine > coarse ? fine : coarse;
+}
 
 // How many bits of the row index are sorted, in how many passes (computed alike on host and device).
 struct SortPlan {

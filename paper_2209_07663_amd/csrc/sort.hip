@@ -464,7 +464,7 @@ static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, con
     const uint2* src = p % 2 == 0 ? ws.pair_a : ws.pair_b;
     uint2* dst = p % 2 == 0 ? ws.pair_b : ws.pair_a;
     const uint32_t search = p == 0 ? (uint32_t)((units + kBlock / 64 - 1) / (kBlock / 64)) : 0u;
-    if (kItems >= 2048 && units >= 1024)
+    if (kItems == 2048 && units >= 1024)
       MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems, 4>),
                   dim3((unsigned)(stride / 4) + search), block, t.ctl, p, d_rows, src, n, stride, ws.hist, d_offsets, n_bags,
                   ws.unit_bag, search);

@@ -37,11 +37,12 @@ struct mono_table {
 constexpr uint64_t kStaticMaxIds = MONO_NOALLOC_MAX_IDS;  // largest batch of the allocation-free entry point
 constexpr uint32_t kStaticMaxDim = 1024;
 constexpr size_t static_part(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+constexpr uint64_t kStaticTiles = 2 * kTilesWanted;  // tiles of the reduction: reduce_tiles(kStaticMaxIds), checked below
+constexpr size_t kStaticPartFloats = 2 * ((kStaticMaxIds + 255) / 256) * kStaticMaxDim;  // for wide rows: tiles of 256 pairs
 constexpr size_t kStaticScratchBytes =
     static_part(kStaticMaxIds * 4) + 2 * static_part(kStaticMaxIds * sizeof(uint2)) +
     static_part((size_t)256 * ((kStaticMaxIds + 511) / 512 + 4) * 4) +  // (at least sort_hist_words: checked below)
-    static_part(2 * ((kStaticMaxIds + 255) / 256) * kStaticMaxDim * sizeof(float)) +
-    static_part(2 * ((kStaticMaxIds + 255) / 256) * sizeof(uint32_t));
+    static_part(kStaticPartFloats * sizeof(float)) + static_part(2 * kStaticTiles * sizeof(uint32_t));
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 namespace {
@@ -148,6 +149,7 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
     t->ws.hist = (uint32_t*)hist;
     t->ws.part = (float*)part;
     t->ws.part_row = (uint32_t*)part_row;
+    t->ws.tiles = tiles;
   }
   return off;
 }
@@ -159,6 +161,7 @@ std::mutex g_scratch_mutex;
 
 hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
   if (sort_hist_words(kStaticMaxIds) > (size_t)256 * ((kStaticMaxIds + 511) / 512 + 4)) return hipErrorInvalidValue;
+  if (reduce_tiles(kStaticMaxIds) > kStaticTiles) return hipErrorInvalidValue;
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
   void* base = nullptr;
   {
@@ -182,13 +185,13 @@ hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
     at += static_part(bytes);
     return p;
   };
-  const uint64_t tiles = reduce_tiles(kStaticMaxIds);
   ws->unit_bag = (uint32_t*)take(kStaticMaxIds * 4);
   ws->pair_a = (uint2*)take(kStaticMaxIds * sizeof(uint2));
   ws->pair_b = (uint2*)take(kStaticMaxIds * sizeof(uint2));
-  ws->hist = (uint32_t*)take(sort_hist_words(kStaticMaxIds) * 4);
-  ws->part = (float*)take(2 * tiles * dim * sizeof(float));
-  ws->part_row = (uint32_t*)((char*)base + kStaticScratchBytes - static_part(2 * tiles * sizeof(uint32_t)));
+  ws->hist = (uint32_t*)take((size_t)256 * ((kStaticMaxIds + 511) / 512 + 4) * 4);
+  ws->part = (float*)take(kStaticPartFloats * sizeof(float));
+  ws->part_row = (uint32_t*)take(2 * kStaticTiles * sizeof(uint32_t));
+  ws->tiles = kStaticPartFloats / (2 * (uint64_t)dim) < kStaticTiles ? kStaticPartFloats / (2 * (uint64_t)dim) : kStaticTiles;
   return hipSuccess;
 }
 

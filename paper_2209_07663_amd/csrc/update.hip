@@ -4,8 +4,8 @@
 //                pooled gradient of bag b is the gradient of each of its occurrences; the first pass
 //                finds the bag of every occurrence from the offsets); dropped occurrences (row -1) are
 //                left out
-//   seg_reduce   the sorted sequence is cut into chunks of 16 pairs per lane of a lane group (dim/4
-//                lanes, four elements each); the group loads its chunk's pairs at once, then walks
+//   seg_reduce   the sorted sequence is cut into tiles, a block each, and a tile into chunks, one for each lane
+//                group of the block (dim/4 lanes, four elements each); the group loads its chunk's pairs at once, then walks
 //                them with eight gradient rows in flight, summing grad[bag] along each run.  A run that lies
 //                inside the chunk is complete: Adagrad is applied at once.  A run that crosses a
 //                chunk border leaves a partial sum in LDS; the groups of a block then join the
@@ -142,21 +142,20 @@ __device__ inline void adagrad_row(const TableView& t, uint32_t row, const RowVe
   if (l == 0) t.state[row] = RowState{acc, t.sync_epoch};  // trained in this window
 }
 
-// GLOG = log2(lanes per row), SEG = pieces of four elements per lane (1 unless GLOG == 6).  A group
-// owns ppl << GLOG consecutive sorted pairs (ppl = pairs per lane, at most kPairsPerLane), so a block of
-// 256 threads always owns a tile of 256 * ppl pairs; the host picks ppl so that small batches still
-// fill the machine.
+// GLOG = log2(lanes per row), SEG = pieces of four elements per lane (1 unless GLOG == 6).  A block of 256
+// threads owns a tile of `tile` consecutive sorted pairs, a group an equal chunk of it; the host picks the size
+// of the tile so that small batches still fill the machine.
 template <typename E, int GLOG, int SEG>
 __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint2* __restrict__ pair_a,
                                                          const uint2* __restrict__ pair_b, uint64_t n,
                                                          const float* __restrict__ grad, float lr, float eps,
                                                          float* __restrict__ part, uint32_t* __restrict__ part_row,
-                                                         uint32_t ppl, uint32_t launched, uint32_t max_bits) {
+                                                         uint32_t tile, uint32_t launched, uint32_t max_bits) {
   static_assert(SEG == 1 || GLOG == 6, "rows wider than 256 elements are held by a whole wave");
-  extern __shared__ float4 s_mem[];  // [2 * groups_per_block][dim / 4] vectors, then the slot rows
+  extern __shared__ float4 s_mem[];  // [2 * groups_per_block][dim / 4] vectors, the slot rows, the tile's pairs
   using Vec = RowVec<SEG>;
   constexpr uint32_t group = 1u << GLOG, gpb = 256u >> GLOG;  // groups (= chunks) per block
-  const uint32_t chunk = ppl << GLOG, tile = 256u * ppl;
+  const uint32_t chunk = tile >> (8 - GLOG);
   constexpr int kWide = (int)group < 8 ? (int)group : 8;
   constexpr int kBatch = kWide / SEG > 0 ? kWide / SEG : 1;   // gradient rows in flight per lane
   const SortPlan plan = make_sort_plan(t.ctl->hwm, max_bits);
@@ -183,13 +182,18 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   const float4* g4 = reinterpret_cast<const float4*>(grad);
 
   // ---- phase 0: the tile's sorted pairs -> LDS (coalesced) ---------------------------------------
-  __shared__ uint2 s_pairs[SEG > 1 ? kReduceTile / 2 : kReduceTile];  // (wide rows: half the pairs, see the launcher)
+  uint2* s_pairs = reinterpret_cast<uint2*>(s_row + 2 * gpb);
+  __shared__ uint32_t s_edge[2];  // rows of the pairs before and after the tile (asked for with the pairs, not after them)
   {
     const uint64_t t0 = (uint64_t)blockIdx.x * tile;
+    if (threadIdx.x < 2) {
+      const uint64_t at = threadIdx.x == 0 ? t0 - 1 : t0 + tile;  // (t0 - 1 of the first tile is beyond every n)
+      s_edge[threadIdx.x] = at < n ? sp[at].x : kNoRow;
+    }
 #pragma unroll
-    for (int m = 0; m < kPairsPerLane; ++m) {
-      const uint32_t j = (uint32_t)m * 256u + threadIdx.x;
-      if ((uint32_t)m < ppl) s_pairs[j] = t0 + j < n ? sp[t0 + j] : make_uint2(kNoRow, 0u);
+    for (uint32_t m = 0; m < kReduceTile / 256; ++m) {
+      const uint32_t j = m * 256u + threadIdx.x;
+      if (j < tile) s_pairs[j] = t0 + j < n ? sp[t0 + j] : make_uint2(kNoRow, 0u);
     }
   }
   __syncthreads();
@@ -200,8 +204,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     const uint64_t cs = c * chunk;
     const uint32_t count = (uint32_t)(n - cs < chunk ? n - cs : chunk);
     const uint2* mine = s_pairs + g * chunk;  // this group's chunk
-    const uint32_t before = cs > 0 ? sp[cs - 1].x : kNoRow;
-    const uint32_t after = cs + count < n ? sp[cs + count].x : kNoRow;
+    const uint32_t before = g == 0 ? s_edge[0] : mine[-1].x;
+    const uint32_t after = g == gpb - 1 ? s_edge[1] : mine[chunk].x;  // (kNoRow past the last pair)
     const uint32_t first = mine[0].x;
     const bool first_head_in = cs == 0 || before != first;
     uint32_t run = first;
@@ -322,18 +326,24 @@ __global__ __launch_bounds__(256) void combine_kernel(TableView t, uint64_t n_ti
   const uint32_t head = part_row[2 * c + 1];
   if (head == kNoRow || !(head & kHeadFlag)) return;  // block-uniform
   const uint32_t row = head & ~kHeadFlag;
-  // number of tiles after c that lie entirely inside the run
-  uint64_t mid = 0;
-  for (;;) {
-    const uint64_t cc = c + 1 + mid + (threadIdx.x & 63);
-    const bool is_mid = cc < n_tiles && part_row[2 * cc + 1] == row;
-    const uint64_t m = __ballot(is_mid);
-    if (m == ~0ull) {
-      mid += 64;
-      continue;
+  // number of tiles after c that lie entirely inside the run: nearly always none; where the first 64 all do, 512
+  // are looked at together (a row with a tenth of a batch of 26 M spans 2500 of them)
+  const auto full_tiles = [&](uint64_t first) {  // leading tiles among the 64 from `first` on (wave-uniform)
+    const uint64_t cc = first + (threadIdx.x & 63);
+    const uint64_t m = __ballot(cc < n_tiles && part_row[2 * cc + 1] == row);
+    return m == ~0ull ? 64u : (uint32_t)(__ffsll((unsigned long long)~m) - 1);
+  };
+  uint64_t mid = full_tiles(c + 1);
+  for (bool more = mid == 64; more;) {
+    constexpr int kLook = 8;
+    uint32_t full[kLook];
+#pragma unroll
+    for (int u = 0; u < kLook; ++u) full[u] = full_tiles(c + 1 + mid + (uint64_t)u * 64);
+#pragma unroll
+    for (int u = 0; u < kLook; ++u) {
+      if (more) mid += full[u];
+      more = more && full[u] == 64;
     }
-    mid += (uint64_t)(__ffsll((unsigned long long)~m) - 1);
-    break;
   }
   const uint64_t tail = c + 1 + mid;
   const bool has_tail = tail < n_tiles && part_row[2 * tail] == row;
@@ -345,10 +355,18 @@ __global__ __launch_bounds__(256) void combine_kernel(TableView t, uint64_t n_ti
   const float4* part4 = reinterpret_cast<const float4*>(part);
   Vec sum;
   sum.zero();
-  for (uint64_t p = g; p < pieces; p += gpb) {
-    const uint64_t slot = p <= mid ? 2 * (c + p) + 1 : 2 * tail;
-    sum.add(load_vec<SEG>(part4 + slot * dim4, l, active));
+  const auto slot_of = [&](uint64_t p) { return p <= mid ? 2 * (c + p) + 1 : 2 * tail; };
+  // (a hot row leaves a piece per tile: eight of them in flight)
+  constexpr int kPieces = 8 / SEG;
+  uint64_t p = g;
+  for (; p + (uint64_t)gpb * (kPieces - 1) < pieces; p += (uint64_t)gpb * kPieces) {
+    Vec v[kPieces];
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) v[u] = load_vec<SEG>(part4 + slot_of(p + (uint64_t)gpb * u) * dim4, l, active);
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) sum.add(v[u]);
   }
+  for (; p < pieces; p += gpb) sum.add(load_vec<SEG>(part4 + slot_of(p) * dim4, l, active));
   store_vec<SEG>(s_mem + g * dim4, l, active, sum);
   __syncthreads();
   if (g == 0) {
@@ -371,17 +389,16 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
   while (group_log2 < 6 && (4u << group_log2) < t.dim) ++group_log2;
   const uint32_t seg = t.dim > 256 ? t.dim / 256 : 1;  // pieces of four elements per lane
   const uint32_t gpb = 256u >> group_log2;
-  // pairs per lane: fewer for small batches (at least ~2048 tiles), and at most half the maximum for rows wider
-  // than 256 elements, whose partial sums take the LDS that the pairs would
-  uint32_t ppl = seg > 1 ? kPairsPerLane / 2 : kPairsPerLane;
-  while (ppl > 1 && (n + 256ull * ppl - 1) / (256ull * ppl) < 2048) ppl >>= 1;
-  const uint64_t n_tiles = (n + 256ull * ppl - 1) / (256ull * ppl);
+  uint32_t tile = reduce_tile(n, gpb);
+  while (tile < kReduceTile && (n + tile - 1) / tile > ws.tiles) tile <<= 1;
+  const uint64_t n_tiles = (n + tile - 1) / tile;
+  if (n_tiles > ws.tiles) return hipErrorInvalidValue;  // (cannot happen: the workspace is made for this rule)
   const dim3 block(256), grid((unsigned)n_tiles);
-  const size_t lds_reduce = 2 * gpb * (t.dim / 4) * sizeof(float4) + 2 * gpb * sizeof(uint32_t);
+  const size_t lds_reduce = 2 * gpb * (t.dim / 4) * sizeof(float4) + 2 * gpb * sizeof(uint32_t) + tile * sizeof(uint2);
   const size_t lds_combine = gpb * (t.dim / 4) * sizeof(float4);
 #define MONO_SEG_REDUCE(E, GLOG, SEG)                                                                                  \
   MONO_LAUNCH_SMEM(prof, K_SEG_REDUCE, stream, (seg_reduce_kernel<E, GLOG, SEG>), grid, block, lds_reduce, t, ws.pair_a, \
-                   ws.pair_b, n, d_grad, lr, eps, ws.part, ws.part_row, ppl, launched, max_bits)
+                   ws.pair_b, n, d_grad, lr, eps, ws.part, ws.part_row, tile, launched, max_bits)
 #define MONO_COMBINE(E, SEG)                                                                                     \
   MONO_LAUNCH_SMEM(prof, K_COMBINE, stream, (combine_kernel<E, SEG>), grid, block, lds_combine, t, n_tiles, ws.part, \
                    ws.part_row, lr, eps, group_log2)
