@@ -41,6 +41,7 @@ constexpr int kRefusedRecords = 3;          // Control::scratch slot: records re
 
 constexpr int kSmallMisses = 4;             // Control::scratch slots of the one-kernel lookup (zero between calls):
 constexpr int kSmallDone = 5;               // missing occurrences so far, blocks that have finished their probes
+constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
 
 struct StashEntry {
   uint64_t key;
@@ -68,7 +69,7 @@ struct Control {
   int32_t free_n;            // rows on the free stack
   uint32_t stash_n;          // elements pushed to the stash (may exceed kStashCap: then some were lost)
   uint32_t hwm;              // every row index ever handed out is below this high-water mark
-  uint32_t pad_;
+  uint32_t swept;            // step of the latest sweep
   unsigned long long n_admitted, n_expired, n_insert_failed, n_lost, n_full, max_chain;
   unsigned long long scratch[8];  // per-call scalars, indexed by the constants above
 };
@@ -87,11 +88,15 @@ struct TableView {
   Winner* win_list;          // [kWinLists * win_cap] elected occurrences
   uint32_t* win_cnt;         // [kWinLists * kWinStride] fill of each sub-list (zero between calls)
   uint64_t win_cap;
-  unsigned long long* occupied;  // [capacity / 512, at least 1] one bit per bucket: set when a slot of the bucket is
-                                 // taken; a clear bit proves the bucket empty (the sweep skips it), a set bit
-                                 // proves nothing (the sweep clears it when it finds the bucket empty)
-  uint32_t* sweep_list;      // [kWinLists * sweep_cap] slots found expired by the running sweep
-  uint32_t* sweep_cnt;       // [kWinLists * kWinStride]
+  // (tables with expiry) per bucket, for the sweep: a lower bound of the last-seen steps of its keys, in units of
+  // 1 << sweep_q steps (see sweep_unit); kAgeEmpty: the bucket holds nothing; kAgeLook: nothing is known.
+  // One bit per bucket beside it, set while the byte is not kAgeEmpty: small enough to stay in the caches
+  // of a probe.
+  uint32_t* oldest;          // [2 * n_buckets] bytes, handled as words
+  unsigned long long* occupied;  // [capacity / 512, at least 1]
+  uint32_t* sweep_list;      // [kWinLists * sweep_cap] rows (or slots) of the keys that the running sweep removes
+  uint32_t* sweep_cnt;       // [kWinLists * kWinStride] fill of each sub-list, and in the word beside it the blocks that are
+                             // done with it (all zero between calls)
   uint64_t sweep_cap;
   uint64_t capacity;
   uint64_t n_buckets;        // per sub-table
@@ -104,6 +109,7 @@ struct TableView {
   uint32_t dim;
   uint32_t freq_threshold;
   uint32_t expire_steps;
+  uint32_t sweep_q;          // log2 of the unit of `oldest`, so that expire_steps are at most kAgeUnits of them
   uint32_t bf16;
   uint32_t filter_hashes;    // counters per key (1..4); the key's count is their minimum
   uint32_t sync_epoch;       // current synchronisation window (>= 1); rows with touch == sync_epoch are "touched"
@@ -131,8 +137,15 @@ __host__ __device__ inline int64_t rows_on_offer(uint64_t capacity, int32_t free
   return offer > 0 ? offer : 0;
 }
 
-constexpr int kSweepSlotsPerThread = 8;     // a wave of the sweep owns 64 buckets = one word of the occupancy bitmap
-constexpr uint64_t kSweepSlotsPerBlock = 256ull * kSweepSlotsPerThread;
+constexpr uint32_t kAgeEmpty = 0xFFu, kAgeLook = 0u, kAgeModulus = 254u;  // other values of a byte of `oldest`: 1 + unit mod 254
+constexpr uint32_t kAgeUnits = 100;
+__host__ __device__ inline uint32_t sweep_unit(uint32_t step, uint32_t sweep_q) { return 1u + (step >> sweep_q) % kAgeModulus; }
+
+// A wave of the sweep owns 256 buckets, or 1024 of a large table.
+constexpr uint64_t kSweepSmallWave = 256, kSweepLargeWave = 1024, kSweepLargeTable = 1ull << 26;  // buckets, buckets, slots
+__host__ __device__ inline uint64_t sweep_wave_buckets(uint64_t capacity) {
+  return capacity >= kSweepLargeTable ? kSweepLargeWave : kSweepSmallWave;
+}
 __host__ __device__ inline uint64_t occupancy_words(uint64_t capacity) { return (capacity + 511) / 512; }
 
 __device__ inline uint64_t shr_or_zero(uint64_t h, uint32_t shift) { return shift >= 64 ? 0 : h >> shift; }

@@ -10,8 +10,8 @@
 //                 append counter would serialise at ~12 ns per atomic on this machine)
 //   insert        (dense, grid-stride over the elected occurrences) if all of them fit under the
 //                 table's fill limit (else none is placed): take a row from the free stack by rank
-//                 (no atomics), insert the key (CAS on 64-bit key slots, eviction chain), mark the
-//                 bucket in the occupancy bitmap, initialise the row with the whole wave
+//                 (no atomics), insert the key (CAS on 64-bit key slots, eviction chain), note it
+//                 in its bucket's bound for the sweep, initialise the row with the whole wave
 //   resolve       duplicates of an admitted key pick up the row of the elected occurrence; one
 //                 thread settles the counters and reports the high-water mark of rows to the host
 //
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
       t.dset_row[e.pos] = row == kNoRow ? kRowAbsent : (int32_t)row;
       rows_out[e.occ] = row == kNoRow ? kRowAbsent : (int32_t)row;
       if (row != kNoRow) {
-        cuckoo_insert(t, k, make_meta(row, src.seen ? src.seen[e.occ] : step));
+        cuckoo_insert(t, k, make_meta(row, src.seen ? src.seen[e.occ] : step), src.seen ? kAgeLook : sweep_unit(step, t.sweep_q));
         if (src.values && t.expire_steps == 0) {
           // a restored key counts as seen freq_threshold times: its counters are raised to that
           // (records may come without their counters, and a counter below the threshold would
@@ -402,11 +402,11 @@ __global__ __launch_bounds__(256) void migrate_kernel(TableView dst, TableView s
   if (g < src.capacity) {
     const Bucket* b = &src.buckets[g >> 3];
     const unsigned long long m = b->meta[g & 7];
-    if (meta_row(m) != kNoRow) cuckoo_insert(dst, b->key[g & 7], m);
+    if (meta_row(m) != kNoRow) cuckoo_insert(dst, b->key[g & 7], m, kAgeLook);
   } else if (g < src.capacity + kStashCap) {
     const uint32_t s = (uint32_t)(g - src.capacity);
     const uint32_t sn = src.ctl->stash_n < kStashCap ? src.ctl->stash_n : kStashCap;
-    if (s < sn) cuckoo_insert(dst, src.stash[s].key, make_meta(src.stash[s].row, src.stash[s].seen));
+    if (s < sn) cuckoo_insert(dst, src.stash[s].key, make_meta(src.stash[s].row, src.stash[s].seen), kAgeLook);
   }
 }
 

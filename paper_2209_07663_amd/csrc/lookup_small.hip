@@ -245,7 +245,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
         const uint32_t x = s.f.slot[w];
         key = s.f.key[x];
         row = (uint32_t)s.f.row[x];
-        cuckoo_insert(t, key, make_meta(row, step));
+        cuckoo_insert(t, key, make_meta(row, step), sweep_unit(step, t.sweep_q));
       }
       init_new_rows<E>(t, w < total, key, row, 0u, none);
     }

@@ -10,102 +10,153 @@ __device__ inline bool is_expired(const TableView& t, uint32_t now, uint32_t see
   return t.expire_steps > 0 && now >= seen && now - seen >= t.expire_steps;
 }
 
-// Sweep in four kernels:
-//   sweep_begin  one thread: walks the (normally empty) stash; scratch[kSweepRemoved] = keys removed so far
-//   sweep_find   eight slots per thread, only in buckets that the occupancy bitmap does not prove empty:
-//                slots whose stamp is too old are appended to one of kWinLists lists (one atomic per
-//                block, spread over the lists)
-//   sweep_remove dense over the found slots: pushes the row on the free stack by rank, reports the
-//                key, clears the slot
-//   sweep_end    one thread settles the counters
-__global__ void sweep_begin_kernel(TableView t, uint32_t now, int64_t* expired_keys, uint64_t max_expired) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+// Sweep in two kernels:
+//   sweep_find    reads the bound of every bucket (a byte each, kept by insertions and by the sweep itself) and looks
+//                 only at buckets that may hold a key that is too old; takes such keys out of their slots,
+//                 appends their rows to one of kWinLists lists (one atomic per wave and 64 buckets, spread
+//                 over the lists) and writes the bucket's new bound.  A key that nobody sees again is looked
+//                 at once, when it expires; a bucket of keys that stay in use about once in expire_steps.
+//                 (Before there were bounds a sweep read every bucket that was not empty: 129 us of a
+//                 2^25-slot table at load 0.7, 81 us of 2^28 slots with 3.6 M keys.)  One thread also walks the
+//                 (normally empty) stash.
+//   sweep_remove  dense over the lists: pushes the rows on the free stack by rank; the block that finishes last settles
+//                 the counters.  Where the caller wants the removed keys, the lists hold slots and this
+//                 kernel reports the keys and clears the slots.
+__device__ inline void sweep_stash(const TableView& t, uint32_t now, int64_t* expired_keys, uint64_t max_expired) {
   Control* c = t.ctl;
   unsigned long long removed = 0;
   uint32_t sn = c->stash_n < kStashCap ? c->stash_n : kStashCap;
-  for (uint32_t s = 0; s < sn;) {
-    if (is_expired(t, now, t.stash[s].seen)) {
-      if (expired_keys && removed < max_expired) expired_keys[removed] = (int64_t)t.stash[s].key;
-      t.free_rows[c->free_n] = t.stash[s].row;
-      c->free_n += 1;
-      t.stash[s] = t.stash[sn - 1];
-      --sn;
-      ++removed;
-    } else {
-      ++s;
+  if (c->stash_n) {
+    for (uint32_t s = 0; s < sn;) {
+      if (is_expired(t, now, t.stash[s].seen)) {
+        if (expired_keys && removed < max_expired) expired_keys[removed] = (int64_t)t.stash[s].key;
+        t.free_rows[c->free_n] = t.stash[s].row;
+        c->free_n += 1;
+        t.stash[s] = t.stash[sn - 1];
+        --sn;
+        ++removed;
+      } else {
+        ++s;
+      }
     }
+    c->stash_n = sn;
   }
-  c->stash_n = sn;
   c->scratch[kSweepRemoved] = removed;
 }
 
-// A wave looks at 512 consecutive slots = 64 buckets = one word of the occupancy bitmap at a time; a lane
-// looks at one slot of eight of those buckets (eight independent 8-byte loads, the eight lanes of a group
-// covering a bucket's meta words as one 64-byte access), and only at buckets whose bit is set: a sweep
-// over a sparsely filled table reads the bitmap and little else.  A bucket found empty gets its bit
-// cleared.  A wave walks `iters` consecutive words (a large table would otherwise need 10^5 blocks that do
-// next to nothing each) and asks for all of them at once, one per lane.  Waves never wait for each other:
-// a wave that found expired slots reserves its room in a sub-list with one atomic of its own.
-constexpr uint32_t kSweepMaxIters = 64;
-__global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t now, uint32_t iters) {
-  const uint32_t lane = lane_id(), grp = lane >> 3, l8 = lane & 7;
-  const uint64_t n_words = occupancy_words(t.capacity);
-  const uint64_t word0 = (((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6) * iters;
-  if (word0 >= n_words) return;  // wave-uniform
-  // a table that is at least a quarter full has hardly an empty bucket: its sweep does not wait for the
-  // bitmap words before it asks for the buckets (and leaves the bitmap alone)
-  const int32_t free_n = t.ctl->free_n;
-  const bool dense = ((uint64_t)t.capacity - (uint64_t)(free_n < 0 ? 0 : free_n)) * 4 > t.capacity;
-  unsigned long long mine = 0;  // lane i: the bitmap word of the wave's i-th turn
-  if (lane < iters && word0 + lane < n_words) mine = dense ? ~0ull : t.occupied[word0 + lane];
-#pragma unroll 1
-  for (uint32_t i = 0; i < iters; ++i) {
-    const unsigned long long bits = __shfl(mine, (int)i);
-    if (bits == 0) continue;  // wave-uniform: no bucket of these 64 holds anything (or past the end)
-    const uint64_t word = word0 + i;
-    const uint64_t slot0 = word * 512;
-    unsigned long long m[kSweepSlotsPerThread];
+// kWords: words of four bounds per lane, so that a wave owns 256 * kWords buckets.  Four of them (16-byte loads) on
+// large tables, whose bounds are then a plain stream and whose waves are not too many to launch; one on small
+// tables, which would have too few waves.
+// keep_slots: the lists take slots and the slots stay as they are (see sweep_remove).
+template <int kWords>
+__global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t now, int keep_slots, int64_t* expired_keys,
+                                                         uint64_t max_expired) {
+  constexpr uint32_t kBuckets = 256u * kWords;
+  __shared__ uint16_t s_list[4][kBuckets];
+  if (blockIdx.x == 0 && threadIdx.x == 0) sweep_stash(t, now, expired_keys, max_expired);
+  const uint32_t lane = lane_id(), grp = lane >> 3, l8 = lane & 7, wave = threadIdx.x >> 6;
+  const uint64_t wave_id = (uint64_t)blockIdx.x * 4 + wave, bucket0 = wave_id * kBuckets, n = 2 * t.n_buckets;
+  if (bucket0 >= n) return;  // wave-uniform (no barriers below)
+  // Bounds are unambiguous while every key's last-seen step lies in the last kAgeModulus units: all keys that the
+  // latest sweep left were seen less than expire_steps before it.  Beyond that every bucket is looked at.
+  const uint32_t unit_now = now >> t.sweep_q, swept = t.ctl->swept;
+  const uint32_t unit_least = (swept > t.expire_steps ? swept - t.expire_steps : 0u) >> t.sweep_q;
+  const bool look_all = unit_now - unit_least >= kAgeModulus - 1 || now < swept;
+  const uint64_t first = bucket0 + (uint64_t)lane * (4 * kWords);  // the lane's buckets
+  uint32_t word[kWords];
 #pragma unroll
-    for (int s = 0; s < kSweepSlotsPerThread; ++s) {
-      const uint32_t bucket_here = 8u * (uint32_t)s + grp;
-      const uint64_t slot = slot0 + (uint64_t)bucket_here * 8 + l8;
-      m[s] = kNoMeta;
-      if (((bits >> bucket_here) & 1ull) && slot < t.capacity) m[s] = t.buckets[slot >> 3].meta[l8];
+  for (int w = 0; w < kWords; ++w) word[w] = 0xFFFFFFFFu;
+  if (first + 4 * kWords <= n) {
+    if constexpr (kWords == 4) {
+      const uint4 q = *reinterpret_cast<const uint4*>(t.oldest + (first >> 2));
+      word[0] = q.x;
+      word[1] = q.y;
+      word[2] = q.z;
+      word[3] = q.w;
+    } else {
+      word[0] = t.oldest[first >> 2];
     }
-    uint64_t found[kSweepSlotsPerThread];
-    unsigned long long now_empty = 0;  // buckets of this word that are flagged but hold nothing
-    uint32_t total = 0;
-#pragma unroll
-    for (int s = 0; s < kSweepSlotsPerThread; ++s) {
-      const bool live = meta_row(m[s]) != kNoRow;
-      const uint64_t live_mask = __ballot(live);
-      const uint32_t bucket_here = 8u * (uint32_t)s + grp;
-      if (!dense && ((bits >> bucket_here) & 1ull) && ((live_mask >> (8 * grp)) & 0xFFull) == 0)
-        now_empty |= 1ull << bucket_here;
-      found[s] = __ballot(live && is_expired(t, now, meta_seen(m[s])));
-      total += (uint32_t)__popcll(found[s]);
+  } else {
+    for (uint32_t j = 0; j < 4 * kWords && first + j < n; ++j) {  // (tables of fewer than 2048 slots)
+      const uint32_t byte = reinterpret_cast<const uint8_t*>(t.oldest)[first + j];
+      word[j >> 2] = (word[j >> 2] & ~(0xFFu << (8 * (j & 3)))) | (byte << (8 * (j & 3)));
     }
-    // every lane of a group computed the same verdict for its eight buckets: one lane clears for the wave
+  }
+  uint32_t look = 0;  // bit j: bucket first + j may hold a key that is too old
 #pragma unroll
-    for (int d = 8; d < 64; d <<= 1) now_empty |= __shfl_xor(now_empty, d);
-    if (lane == 0 && now_empty) atomicAnd(&t.occupied[word], ~now_empty);
-    if (total == 0) continue;  // wave-uniform
-    const uint32_t list = (uint32_t)(word >> 2) & (kWinLists - 1);  // (the list of the 2048-slot chunk the word lies in)
+  for (uint32_t j = 0; j < 4u * kWords; ++j) {
+    const uint32_t b = (word[j >> 2] >> (8 * (j & 3))) & 0xFFu;
+    const uint32_t age = (unit_now + kAgeModulus - (b - 1u)) % kAgeModulus;  // of the bound, in units (b >= 1)
+    const uint32_t bound = (unit_now - age) << t.sweep_q;                   // no key was last seen before this step
+    const bool young = b != kAgeLook && age <= unit_now && !look_all && now - bound < t.expire_steps;
+    if (b != kAgeEmpty && !young) look |= 1u << j;
+  }
+  uint32_t inc = (uint32_t)__popc(look);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(inc, d);
+    if ((int)lane >= d) inc += y;
+  }
+  const uint32_t total = __shfl(inc, 63);
+  if (total == 0) return;  // wave-uniform
+  volatile uint16_t* list = s_list[wave];  // the buckets to look at, of the wave's
+  {
+    uint32_t at = inc - (uint32_t)__popc(look);
+    for (uint32_t m = look; m; m &= m - 1) list[at++] = (uint16_t)(lane * (4 * kWords) + (uint32_t)__ffs((int)m) - 1u);
+  }
+  __builtin_amdgcn_wave_barrier();
+  const uint32_t out = (uint32_t)wave_id & (kWinLists - 1);  // sub-list of this wave
+  constexpr int kTurns = 8;  // buckets per group of eight lanes with their meta words (64 bytes) in flight
+  for (uint32_t e0 = 0; e0 < total; e0 += 8 * kTurns) {
+    unsigned long long m[kTurns];
+#pragma unroll
+    for (int r = 0; r < kTurns; ++r) {
+      const uint32_t e = e0 + 8u * (uint32_t)r + grp;
+      m[r] = kNoMeta;
+      if (e < total) m[r] = t.buckets[bucket0 + list[e]].meta[l8];
+    }
+    uint64_t gone[kTurns];
+    uint32_t found = 0;
+#pragma unroll
+    for (int r = 0; r < kTurns; ++r) {
+      const uint32_t e = e0 + 8u * (uint32_t)r + grp;
+      const bool live = meta_row(m[r]) != kNoRow, old = live && is_expired(t, now, meta_seen(m[r]));
+      gone[r] = __ballot(old);
+      found += (uint32_t)__popcll(gone[r]);
+      uint32_t least = live && !old ? meta_seen(m[r]) : 0xFFFFFFFFu;  // over the keys that stay
+#pragma unroll
+      for (int d = 1; d < 8; d <<= 1) least = min(least, __shfl_xor(least, d));
+      if (e < total && l8 == 0) {
+        const uint64_t b = bucket0 + list[e];
+        // (a key from the future, seen after `now`: nothing is known)
+        const uint32_t age = least == 0xFFFFFFFFu ? kAgeEmpty : (least > now ? kAgeLook : sweep_unit(least, t.sweep_q));
+        reinterpret_cast<uint8_t*>(t.oldest)[b] = (uint8_t)age;
+        if (age == kAgeEmpty) atomicAnd(&t.occupied[b >> 6], ~(1ull << (b & 63)));
+      }
+    }
+    if (found == 0) continue;  // wave-uniform
     uint32_t p = 0;
-    if (lane == 0) p = atomicAdd(&t.sweep_cnt[list * kWinStride], total);
+    if (lane == 0) p = atomicAdd(&t.sweep_cnt[out * kWinStride], found);
     p = __shfl(p, 0);
 #pragma unroll
-    for (int s = 0; s < kSweepSlotsPerThread; ++s) {
-      if ((found[s] >> lane) & 1ull) {
-        const uint64_t slot = slot0 + (uint64_t)(8u * (uint32_t)s + grp) * 8 + l8;
-        t.sweep_list[(uint64_t)list * t.sweep_cap + p + (uint32_t)__popcll(found[s] & lanes_below())] = (uint32_t)slot;
+    for (int r = 0; r < kTurns; ++r) {
+      if ((gone[r] >> lane) & 1ull) {
+        const uint64_t b = bucket0 + list[e0 + 8u * (uint32_t)r + grp];
+        t.sweep_list[(uint64_t)out * t.sweep_cap + p + (uint32_t)__popcll(gone[r] & lanes_below())] =
+            keep_slots ? (uint32_t)(b * kBucket + l8) : meta_row(m[r]);
+        if (!keep_slots) {
+          t.buckets[b].meta[l8] = kNoMeta;
+          t.buckets[b].key[l8] = kEmptyKey;
+        }
       }
-      p += (uint32_t)__popcll(found[s]);
+      p += (uint32_t)__popcll(gone[r]);
     }
   }
 }
 
-__global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, int64_t* expired_keys, uint64_t max_expired) {
+// expired_keys != nullptr: the lists hold slots, which are cleared here.
+__global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, uint32_t now, int64_t* expired_keys,
+                                                           uint64_t max_expired, uint64_t* n_expired) {
   const uint32_t lane = lane_id();
   uint32_t inc = t.sweep_cnt[lane * kWinStride];
 #pragma unroll
@@ -114,7 +165,7 @@ __global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, int64_t*
     if ((int)lane >= d) inc += y;
   }
   const uint32_t total = __shfl(inc, 63);
-  const int32_t free0 = t.ctl->free_n;                     // constant during this kernel
+  const int32_t free0 = t.ctl->free_n;                     // settled by the last block, constant until then
   const unsigned long long out0 = t.ctl->scratch[kSweepRemoved];       // keys already reported from the stash
   const uint32_t stride = gridDim.x * blockDim.x;
   for (uint32_t w0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); w0 < total; w0 += stride) {
@@ -131,27 +182,32 @@ __global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, int64_t*
     const uint32_t before = __shfl(inc, (int)(lo > 0 ? lo - 1 : 0));
     if (w < total) {
       const uint32_t p = w - (lo > 0 ? before : 0u);
-      const uint32_t g = t.sweep_list[(uint64_t)lo * t.sweep_cap + p];
-      Bucket* b = &t.buckets[g >> 3];
-      const int l = (int)(g & 7);
-      t.free_rows[free0 + (int32_t)w] = meta_row(b->meta[l]);
-      if (expired_keys && out0 + w < max_expired) expired_keys[out0 + w] = (int64_t)b->key[l];
-      b->meta[l] = kNoMeta;
-      b->key[l] = kEmptyKey;
+      uint32_t g = t.sweep_list[(uint64_t)lo * t.sweep_cap + p];
+      if (expired_keys) {
+        Bucket* b = &t.buckets[g >> 3];
+        const int l = (int)(g & 7);
+        g = meta_row(b->meta[l]);
+        if (out0 + w < max_expired) expired_keys[out0 + w] = (int64_t)b->key[l];
+        b->meta[l] = kNoMeta;
+        b->key[l] = kEmptyKey;
+      }
+      t.free_rows[free0 + (int32_t)w] = g;
     }
   }
-  // (which block finishes last cannot be known cheaply: the counters are settled by sweep_end)
-}
-
-__global__ void sweep_end_kernel(TableView t, uint64_t* n_expired) {
-  if (blockIdx.x != 0 || threadIdx.x != 0) return;
-  uint32_t total = 0;
-  for (int l = 0; l < kWinLists; ++l) {
-    total += t.sweep_cnt[l * kWinStride];
-    t.sweep_cnt[l * kWinStride] = 0;
-  }
-  t.ctl->free_n += (int32_t)total;
-  const unsigned long long removed = t.ctl->scratch[kSweepRemoved] + total;
+  // The block that finishes last settles the counters: the others have read them.  (Blocks count themselves on the
+  // counters' 64 lines first, and the last of each line on one word: one word alone would serialise thousands
+  // of them at ~12 ns each.)
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const uint32_t line = blockIdx.x & (kWinLists - 1);
+  const uint32_t of_line = (gridDim.x - line + kWinLists - 1) / kWinLists, lines = gridDim.x < kWinLists ? gridDim.x : kWinLists;
+  if (atomicAdd(&t.sweep_cnt[line * kWinStride + 1], 1u) != of_line - 1) return;
+  if (atomicAdd(&t.ctl->scratch[kSweepDone], 1ull) != (unsigned long long)lines - 1) return;
+  for (int l = 0; l < kWinLists; ++l) *reinterpret_cast<uint2*>(&t.sweep_cnt[l * kWinStride]) = make_uint2(0u, 0u);
+  t.ctl->scratch[kSweepDone] = 0;
+  t.ctl->free_n = free0 + (int32_t)total;
+  t.ctl->swept = now;
+  const unsigned long long removed = out0 + total;
   t.ctl->n_expired += removed;
   if (n_expired) *n_expired = removed;
 }
@@ -166,16 +222,15 @@ hipError_t launch_expire_sweep(const TableView& t, uint32_t now, uint64_t* d_n_e
     if (d_n_expired) MONO_LAUNCH(prof, K_SWEEP_END, stream, sweep_nothing_kernel, dim3(1), dim3(64), d_n_expired);
     return hipGetLastError();
   }
-  MONO_LAUNCH(prof, K_SWEEP_BEGIN, stream, sweep_begin_kernel, dim3(1), dim3(64), t, now, d_expired_keys, max_expired);
-  const uint64_t words = occupancy_words(t.capacity);
-  uint64_t iters = (words + 32767) / 32768;  // about 32 K waves, at most kSweepMaxIters bitmap words each
-  iters = iters < 1 ? 1 : (iters > kSweepMaxIters ? kSweepMaxIters : iters);
-  const uint64_t waves = (words + iters - 1) / iters;
+  const uint64_t waves = (2 * t.n_buckets + sweep_wave_buckets(t.capacity) - 1) / sweep_wave_buckets(t.capacity);
   const dim3 block(256), grid((unsigned)((waves + 3) / 4));
-  MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel, grid, block, t, now, (uint32_t)iters);
-  MONO_LAUNCH(prof, K_SWEEP_REMOVE, stream, sweep_remove_kernel, dim3(grid.x < 2048u ? grid.x : 2048u), block, t,
-              d_expired_keys, max_expired);
-  MONO_LAUNCH(prof, K_SWEEP_END, stream, sweep_end_kernel, dim3(1), dim3(64), t, d_n_expired);
+  const int keep_slots = d_expired_keys != nullptr;
+  if (t.capacity >= kSweepLargeTable)
+    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<4>, grid, block, t, now, keep_slots, d_expired_keys, max_expired);
+  else
+    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<1>, grid, block, t, now, keep_slots, d_expired_keys, max_expired);
+  MONO_LAUNCH(prof, K_SWEEP_REMOVE, stream, sweep_remove_kernel, dim3(grid.x < 1024u ? grid.x : 1024u), block, t, now,
+              d_expired_keys, max_expired, d_n_expired);
   return hipGetLastError();
 }
 
@@ -367,6 +422,7 @@ hipError_t launch_table_init(const TableView& t, uint64_t dset_size, hipStream_t
   if ((e = hipMemsetAsync(t.ctl, 0, sizeof(Control), stream)) != hipSuccess) return e;
   if ((e = hipMemsetAsync(t.win_cnt, 0, kWinLists * kWinStride * sizeof(uint32_t), stream)) != hipSuccess) return e;
   if ((e = hipMemsetAsync(t.sweep_cnt, 0, kWinLists * kWinStride * sizeof(uint32_t), stream)) != hipSuccess) return e;
+  if ((e = hipMemsetAsync(t.oldest, 0xFF, (2 * t.n_buckets + 15) & ~15ull, stream)) != hipSuccess) return e;
   if ((e = hipMemsetAsync(t.occupied, 0, occupancy_words(t.capacity) * sizeof(unsigned long long), stream)) != hipSuccess)
     return e;
   if ((e = hipMemsetAsync(t.dset, 0, dset_size * sizeof(unsigned long long), stream)) != hipSuccess) return e;

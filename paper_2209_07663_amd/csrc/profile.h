@@ -19,7 +19,6 @@ enum KernelId {
   K_SORT_SCATTER,
   K_SEG_REDUCE,
   K_COMBINE,
-  K_SWEEP_BEGIN,
   K_SWEEP,
   K_SWEEP_REMOVE,
   K_SWEEP_END,
@@ -29,7 +28,7 @@ enum KernelId {
 inline const char* kernel_name(int id) {
   static const char* names[K_COUNT] = {"probe_count", "admit_elect", "insert", "resolve",   "lookup_small",
                                        "gather_pool", "sort_hist",   "sort_scan",    "sort_scatter", "seg_reduce",
-                                       "combine",     "sweep_begin", "sweep_find",   "sweep_remove", "sweep_end"};
+                                       "combine",     "sweep_find",  "sweep_remove", "sweep_end"};
   return id >= 0 && id < K_COUNT ? names[id] : "?";
 }
 

@@ -110,11 +110,13 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
   // a sub-list takes the winners of every kWinLists-th block of the election kernel, whose blocks hold 256 or
   // 1024 occurrences: sized for the larger, which also covers the smaller
   const uint64_t win_cap = ((max_ids + 1023) / 1024 + kWinLists - 1) / kWinLists * 1024;
-  const uint64_t sweep_blocks = (capacity + kSweepSlotsPerBlock - 1) / kSweepSlotsPerBlock;
-  const uint64_t sweep_cap = (sweep_blocks + kWinLists - 1) / kWinLists * kSweepSlotsPerBlock;
+  // (every kWinLists-th wave of the sweep appends to one sub-list, at most all the slots of its buckets)
+  const uint64_t wave_slots = sweep_wave_buckets(capacity) * kBucket;
+  const uint64_t sweep_cap = ((capacity + wave_slots - 1) / wave_slots + kWinLists - 1) / kWinLists * wave_slots;
   char* win_list = take(kWinLists * win_cap * sizeof(Winner));
   char* win_cnt = take(kWinLists * kWinStride * sizeof(uint32_t));
   char* occupied = take(occupancy_words(capacity) * sizeof(unsigned long long));
+  char* oldest = take((2 * n_buckets + 15) & ~15ull);
   char* sweep_list = take(kWinLists * sweep_cap * sizeof(uint32_t));
   char* sweep_cnt = take(kWinLists * kWinStride * sizeof(uint32_t));
   const uint64_t tiles = reduce_tiles(max_ids);
@@ -140,6 +142,7 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
     v.win_cnt = (uint32_t*)win_cnt;
     v.win_cap = win_cap;
     v.occupied = (unsigned long long*)occupied;
+    v.oldest = (uint32_t*)oldest;
     v.sweep_list = (uint32_t*)sweep_list;
     v.sweep_cnt = (uint32_t*)sweep_cnt;
     v.sweep_cap = sweep_cap;
@@ -319,6 +322,8 @@ int mono_table_create_ex(mono_table** out, uint64_t capacity, uint32_t dim, uint
   v.dim = dim;
   v.freq_threshold = freq_threshold;
   v.expire_steps = expire_steps;
+  v.sweep_q = 0;
+  while ((expire_steps >> v.sweep_q) > kAgeUnits) ++v.sweep_q;
   v.bf16 = flags == MONO_ROWS_BF16;
   v.sync_epoch = 1;
   t->max_ids = max_ids;
@@ -610,6 +615,7 @@ int mono_table_migrate(mono_table* dst, mono_table* src, uint32_t generation, vo
   d.stash_n = 0;  // stash elements get a new chance under the new hash functions
   d.free_n = c.free_n + (int32_t)(b.capacity - a.capacity);
   for (auto& x : d.scratch) x = 0;
+  d.swept = 0;  // (dst's buckets are all to be looked at)
   if (hipMemcpyAsync(b.ctl, &d, sizeof(Control), hipMemcpyHostToDevice, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)  // `d` is a local: the copy must have left it
     return MONO_EHIP;

@@ -61,18 +61,23 @@ __device__ inline void wait_all_memory_ops() {
   __asm__ volatile("" ::: "memory");
 }
 
-// The bucket's bit in the occupancy bitmap.  Read first, with an ordinary load: most buckets that take a
-// key hold one already, and a stale copy can only show a bit as clear that another compute unit has set
-// in this very kernel (bits are cleared by the sweep alone, in a kernel of its own), which costs one
-// redundant atomic.
-__device__ inline void mark_occupied(const TableView& t, const Bucket* b) {
+// Notes for the sweep that bucket b has taken a key (tables with expiry).  `unit`: the unit of the current step if the
+// key's last-seen step is that (no key can be newer, so a bucket that holds something keeps its bound), or
+// kAgeLook for a key that was seen earlier or at an unknown time.  The byte is read first, with an ordinary load:
+// a stale copy can only show kAgeEmpty where another compute unit has noted a key in this very kernel
+// (bytes become kAgeEmpty in the sweep alone, in a kernel of its own).  Bits are only ever cleared here: all who
+// note the current unit write the same one, and kAgeLook wins over any.
+__device__ inline void note_key(const TableView& t, const Bucket* b, uint32_t unit) {
+  if (t.expire_steps == 0) return;
   const uint64_t idx = (uint64_t)(b - t.buckets);
-  unsigned long long* w = &t.occupied[idx >> 6];
-  const unsigned long long bit = 1ull << (idx & 63);
-  if (!(*w & bit)) atomicOr(w, bit);
+  const uint32_t at = 8u * (uint32_t)(idx & 3);
+  uint32_t* w = &t.oldest[idx >> 2];
+  const uint32_t have = (*w >> at) & 0xFFu;
+  if (have == kAgeEmpty) atomicOr(&t.occupied[idx >> 6], 1ull << (idx & 63));
+  if (have == kAgeEmpty || (unit == kAgeLook && have != kAgeLook)) atomicAnd(w, (unit << at) | ~(0xFFu << at));
 }
 
-__device__ inline bool try_claim(const TableView& t, Bucket* b, uint64_t k, unsigned long long meta) {
+__device__ inline bool try_claim(const TableView& t, Bucket* b, uint64_t k, unsigned long long meta, uint32_t unit) {
   // snapshot of the eight keys (may be stale: a slot seen free may be taken by now; the CAS decides)
   const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(b->key);
   const ulonglong2 a0 = kp[0], a1 = kp[1], a2 = kp[2], a3 = kp[3];
@@ -83,7 +88,7 @@ __device__ inline bool try_claim(const TableView& t, Bucket* b, uint64_t k, unsi
     if (atomicCAS((unsigned long long*)&b->key[l], (unsigned long long)kEmptyKey, (unsigned long long)k) ==
         (unsigned long long)kEmptyKey) {
       st_agent(&b->meta[l], meta);  // issued after the CAS has returned: publishes the slot
-      mark_occupied(t, b);
+      note_key(t, b, unit);
       return true;
     }
   }
@@ -118,15 +123,15 @@ __device__ inline uint32_t pick_victim(const TableView& t, const Bucket* b, int 
   return (start + (uint32_t)__ffs((int)rotated) - 1u) & (kBucket - 1);
 }
 
-// Inserts (k, meta); k is not in the table and no other thread inserts the same key.
-__device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long meta) {
+// Inserts (k, meta); k is not in the table and no other thread inserts the same key.  unit: see note_key.
+__device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long meta, uint32_t unit) {
   int side = 0;
   uint32_t chain = 0;
 #pragma unroll 1
   for (int kick = 0; kick < kMaxKicks; ++kick) {
     Bucket* b = &t.buckets[bucket_index(t, side, k)];
-    if (try_claim(t, b, k, meta)) goto done;
-    if (kick == 0 && try_claim(t, &t.buckets[bucket_index(t, 1, k)], k, meta)) goto done;
+    if (try_claim(t, b, k, meta, unit)) goto done;
+    if (kick == 0 && try_claim(t, &t.buckets[bucket_index(t, 1, k)], k, meta, unit)) goto done;
     // evict: take the lock of a published slot
     const uint32_t v0 = pick_victim(t, b, side, (uint32_t)(mix64(k + (uint64_t)kick) >> 61));
 #pragma unroll 1
@@ -137,8 +142,10 @@ __device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long
       const uint64_t vk = atomicExch((unsigned long long*)&b->key[l], (unsigned long long)k);
       wait_all_memory_ops();  // the key exchange is performed before the slot is published again
       st_agent(&b->meta[l], meta);
+      if (unit == kAgeLook) note_key(t, b, unit);  // (a key of the current step leaves the bound of a full bucket as it is)
       k = vk;
       meta = old;
+      unit = kAgeLook;
       side = 1 - side;  // the victim continues in its other sub-table
       ++chain;
       break;
