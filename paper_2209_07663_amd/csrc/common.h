@@ -14,8 +14,8 @@ constexpr int kReserveShift = 5;            // capacity >> 5 rows are never hand
 constexpr uint32_t kStashCap = 4096;        // homeless elements kept aside after a failed chain
 constexpr int32_t kRowAbsent = -1;          // rows_out: key not in the table
 constexpr int32_t kRowMiss = -2;            // rows_out, between the kernels of one call: missed, undecided
-// rows_out values <= -3 between the kernels of one call: duplicate of an admitted key, encodes the
-// position of that key in the per-call dedup set
+// rows_out values <= -3 between the kernels of one call: duplicate of an admitted key, -occ - 3 of the occurrence
+// that was elected for it
 
 // One bucket = one 128-byte line (the unit the memory system fetches): eight keys, then eight
 // `meta` words = last-seen step << 32 | row index.  A probe costs one line per bucket; the row and
@@ -41,6 +41,8 @@ constexpr int kRefusedRecords = 3;          // Control::scratch slot: records re
 
 constexpr int kSmallMisses = 4;             // Control::scratch slots of the one-kernel lookup (zero between calls):
 constexpr int kSmallDone = 5;               // missing occurrences so far, blocks that have finished their probes
+constexpr int kMissTag = 7;                 // Control::scratch slots: tag of the latest call in which an occurrence missed,
+constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
 
 struct StashEntry {
@@ -61,7 +63,7 @@ struct alignas(8) RowState {
 struct alignas(16) Winner {
   uint64_t key;
   uint32_t occ;   // occurrence index in the batch
-  uint32_t pos;   // position of the key in the per-call dedup set
+  uint32_t pad;
 };
 
 // Counters that live on the device for the whole life of the table.
@@ -71,7 +73,7 @@ struct Control {
   uint32_t hwm;              // every row index ever handed out is below this high-water mark
   uint32_t swept;            // step of the latest sweep
   unsigned long long n_admitted, n_expired, n_insert_failed, n_lost, n_full, max_chain;
-  unsigned long long scratch[8];  // per-call scalars, indexed by the constants above
+  unsigned long long scratch[16];  // per-call scalars, indexed by the constants above
 };
 
 // Everything a kernel needs to know about a table; passed by value.
@@ -84,7 +86,6 @@ struct TableView {
   Control* ctl;
   StashEntry* stash;         // [kStashCap]
   unsigned long long* dset;  // [dset_size] per-call dedup set: epoch << 32 | occurrence index
-  int32_t* dset_row;         // [dset_size] row of the key that owns the dedup-set position
   Winner* win_list;          // [kWinLists * win_cap] elected occurrences
   uint32_t* win_cnt;         // [kWinLists * kWinStride] fill of each sub-list (zero between calls)
   uint64_t win_cap;

@@ -61,38 +61,37 @@ __device__ inline void probe_side(const TableView& t, uint64_t k, uint64_t bucke
   }
 }
 
-// Threads (= keys) per block of probe_count.  The block's missing keys are gathered in an LDS set with
-// their multiplicities and each distinct one touches its counter once: a hot ID that is not (yet)
-// admitted would otherwise hit one counter word with 10^5 atomics, which serialise at ~12 ns each.
-// The larger the block, the fewer touches such a key makes (one per block that holds it), but a block
-// lives as long as its slowest wave and the waves of a large block wait for each other at its barriers.
-//   kProbeBlockStatic: tables that never expire keys.  A key misses only until it is admitted, so hot
-//     missing keys are rare after the first steps (measured on the default workload: 0.200 ms per
-//     launch with 256, 0.225 ms with 1024).
-//   kProbeBlockAgeing: tables with expiry, whose counters age and whose hot set may drift: every step
-//     brings hot IDs that are new (measured on the streaming workload: 0.55 ms with 1024, 1.5 ms with 256
-//     from an empty table; 0.43 / 0.72 / 1.10 ms with 1024 / 512 / 256 on a table at load 0.77).
-constexpr int kProbeBlockStatic = 256;
-constexpr int kProbeBlockAgeing = 1024;
-// Keys per thread on tables with expiry: two turns halve the touches of a hot missing key once more
-// (streaming workload at load 0.77: 0.424 ms per launch with one key per thread, 0.380 with two, 0.391
-// with four, whose 96 KB set of missing keys leaves one block per compute unit; blocks of 512 and 256
-// threads with one key each take 0.72 and 1.10 ms: the kernel's time follows the number of blocks that
-// touch the hottest counters, ~12 ns per touch of one word).
-constexpr int kProbeTurnsAgeing = 2;
+// Threads (= keys of a turn) per block of probe_count.  The block's missing keys are gathered in an LDS set with
+// their multiplicities and each distinct one touches its counter once: a hot ID that is not (yet) admitted
+// would otherwise hit one counter word with 10^5 atomics, which serialise at ~12 ns each.  The more keys a block
+// takes, the fewer touches such a key makes (one per block that holds it), but a block lives as long as its
+// slowest wave, and large blocks whose waves wait for each other leave the memory idle.
+//   Tables that never expire keys take one turn: a key misses only until it is admitted, so hot missing keys are
+//   rare after the first steps.
+//   On tables with expiry counters age and the hot set may drift: every step brings hot IDs that are new.  A
+//   block takes up to kProbeMaxTurns turns, one after the other without a barrier, as many as leave about
+//   kProbeBlocksWanted blocks.  The set then has room for the missing keys of two turns: a hot key finds its
+//   slot in the first of them; a key that finds the set full touches its counter itself.
+//   (Blocks of 1024 threads that met at a barrier after two turns: 329 us per launch of 6.8 M keys where few missing
+//   keys are hot, 228 us now, 272 with sixteen turns; 372 -> 349 us, 325 with sixteen, where the hot set drifts.)
+constexpr int kProbeBlock = 256;
+constexpr uint64_t kProbeBlocksWanted = 1024, kProbeMaxTurns = 8;
+constexpr int kProbeTries = 8;  // slots of the set that a missing key looks at
 
 // restore != 0: the keys are snapshot records; a stored key is marked absent (its record is refused)
 // and nothing is stamped or counted.
-// kTurns: keys per thread.  A block owns kProbeBlock * kTurns consecutive keys and takes them in kTurns
-// turns of one key per thread; the LDS set of missing keys spans all turns, so that a hot missing key
-// costs one counter touch per kProbeBlock * kTurns keys.
-template <int kProbeBlock, int kTurns>
+// A block owns kProbeBlock * turns consecutive keys and takes them in turns of one key per thread.
+template <bool kManyTurns>
 __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, const int64_t* __restrict__ keys,
                                                                   uint64_t n, uint32_t step,
-                                                                  int32_t* __restrict__ rows_out, int restore) {
-  constexpr int kMissSlots = 2 * kProbeBlock * kTurns;  // slots of the block's LDS set of missing keys
+                                                                  int32_t* __restrict__ rows_out, int restore,
+                                                                  uint32_t turns_, uint32_t epoch) {
+  constexpr int kMissSlots = (kManyTurns ? 4 : 2) * kProbeBlock;  // slots of the block's LDS set of missing keys
+  const uint32_t turns = kManyTurns ? turns_ : 1u;
   __shared__ unsigned long long miss_key[kMissSlots];
   __shared__ uint32_t miss_cnt[kMissSlots];
+  __shared__ int any_miss;
+  if (threadIdx.x == 0) any_miss = 0;
   for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock) {
     miss_key[s] = kEmptyKey;
     miss_cnt[s] = 0;
@@ -105,8 +104,8 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
     sparse = ((uint64_t)t.capacity - (uint64_t)(free_n < 0 ? 0 : free_n)) * 4 <= t.capacity;
   }
 #pragma unroll 1
-  for (int turn = 0; turn < kTurns; ++turn) {
-    const uint64_t i = ((uint64_t)blockIdx.x * kTurns + (uint64_t)turn) * kProbeBlock + threadIdx.x;
+  for (uint32_t turn = 0; turn < turns; ++turn) {
+    const uint64_t i = ((uint64_t)blockIdx.x * turns + turn) * kProbeBlock + threadIdx.x;
     const uint64_t k = i < n ? (uint64_t)keys[i] : kEmptyKey;
     const bool live = k != kEmptyKey;
     // Negative lookup through the admission counters.  When nothing ages (expire_steps == 0) a
@@ -168,27 +167,36 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
         if (miss) rows_out[i] = kRowMiss;
       }
     }
+    if (miss) any_miss = 1;
     if (miss && !restore) {  // (records of a restore call are not occurrences: nothing is counted)
       uint32_t pos = (uint32_t)(mix64(k ^ t.s_dedup) >> 40) & (kMissSlots - 1);
-      for (;;) {  // at most half of the slots are ever taken: a free slot always turns up
+      int tries = 0;
+      for (; tries < kProbeTries; ++tries) {
         const unsigned long long old = atomicCAS(&miss_key[pos], (unsigned long long)kEmptyKey, (unsigned long long)k);
         if (old == kEmptyKey || old == k) break;
         pos = (pos + 1) & (kMissSlots - 1);
       }
-      atomicAdd(&miss_cnt[pos], 1u);
+      if (tries < kProbeTries)
+        atomicAdd(&miss_cnt[pos], 1u);
+      else
+        touch_counter(t, k, step, 1u);
     }
   }
-  if (restore) return;  // block-uniform
   __syncthreads();
+  // (an ordinary store: it stays in the XCD's L2 until the kernel ends; atomic ones to one word from 26 K blocks took
+  // 1.5 ms)
+  if (threadIdx.x == 0 && any_miss) t.ctl->scratch[kMissTag] = epoch;
+  if (restore || !any_miss) return;  // block-uniform
   for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock)
     if (miss_cnt[s]) touch_counter(t, miss_key[s], step, miss_cnt[s]);
 }
 
 // ---- election ------------------------------------------------------------------------------------
 
-// kElectBlock: occurrences (= threads) per block.  256 on tables that never expire keys; 1024 on tables
-// with expiry, where an ID that turns hot before it is admitted is led by one occurrence per block, and
-// all those leaders meet at one position of the dedup set.
+// kElectBlock: occurrences (= threads) per block.  256 on tables that never expire keys and for batches of at most
+// kElectSmall; 1024 for larger ones on tables with expiry, where an ID that turns hot before it is admitted is
+// led by one occurrence per block, and all those leaders meet at one position of the dedup set.
+constexpr uint64_t kElectSmall = 1u << 19;
 template <int kElectBlock>
 __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, const int64_t* __restrict__ keys,
                                                                   uint64_t n, uint32_t epoch, int32_t* rows_out,
@@ -201,7 +209,8 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   // that turns hot before it is admitted arrives here in thousands of occurrences, and each of them
   // re-reading the counter and competing for the same position of the dedup set serialised.
   __shared__ unsigned long long s_key[kElectSlots];
-  __shared__ int32_t s_res[kElectSlots];  // what the leader found: kRowAbsent, or the dedup-set position as -(pos) - 3
+  __shared__ int32_t s_res[kElectSlots];  // what the leader found: kRowAbsent, or the elected occurrence as -occ - 3
+  if (t.ctl->scratch[kMissTag] != epoch) return;  // block-uniform: no occurrence of the call missed
   for (int s = threadIdx.x; s < kElectSlots; s += kElectBlock) s_key[s] = kEmptyKey;
   __syncthreads();
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -219,7 +228,6 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     }
   }
   bool winner = false;
-  uint64_t pos = 0;
   if (leader) {
     // A snapshot record is admitted whatever its counter says, and with a threshold of 0 or 1 every
     // missing key is admissible (its count is at least 1 by now): no counter is read for either.
@@ -233,7 +241,8 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     int32_t found = kRowAbsent;
     if (cnt >= t.freq_threshold) {
       // one occurrence per distinct key wins its position of the per-call dedup set
-      pos = mix64(k ^ t.s_dedup) & t.dset_mask;
+      uint64_t pos = mix64(k ^ t.s_dedup) & t.dset_mask;
+      uint64_t owner = i;
       const unsigned long long mine = ((unsigned long long)epoch << 32) | (unsigned long long)i;
       for (;;) {
         unsigned long long e = ld_agent(&t.dset[pos]);
@@ -241,22 +250,29 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
           const unsigned long long old = atomicCAS(&t.dset[pos], e, mine);
           if (old == e) {
             winner = true;
+            owner = i;
             break;
           }
           e = old;  // someone wrote this position in this call
           if ((uint32_t)(e >> 32) != epoch) continue;
         }
-        if ((uint64_t)keys[(uint32_t)e] == k) break;  // duplicate of the owner
+        owner = (uint32_t)e;
+        if ((uint64_t)keys[owner] == k) break;  // duplicate of the owner
         pos = (pos + 1) & t.dset_mask;
       }
       // (a second record of the same key in one restore call is refused like a stored key)
-      found = restore ? kRowAbsent : -(int32_t)pos - 3;
+      found = restore ? kRowAbsent : -(int32_t)owner - 3;
     }
     s_res[ls] = found;
     if (!winner) rows_out[i] = found;  // the winner keeps kRowMiss until the insertion gives it its row
   }
   __syncthreads();
-  if (miss && !leader) rows_out[i] = s_res[ls];
+  bool duplicate = leader && !winner && s_res[ls] <= -3;
+  if (miss && !leader) {
+    rows_out[i] = s_res[ls];
+    duplicate = s_res[ls] <= -3;
+  }
+  if (__ballot(duplicate) && lane_id() == 0) t.ctl->scratch[kDuplicateTag] = epoch;
   // block-aggregated append to sub-list (blockIdx mod kWinLists)
   const uint32_t wave = threadIdx.x >> 6;
   const uint64_t wmask = __ballot(winner);
@@ -272,7 +288,7 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   if (winner) {
     uint32_t p = block_base + (uint32_t)__popcll(wmask & lanes_below());
     for (uint32_t w = 0; w < wave; ++w) p += wave_cnt[w];
-    t.win_list[(uint64_t)list * t.win_cap + p] = Winner{k, (uint32_t)i, (uint32_t)pos};
+    t.win_list[(uint64_t)list * t.win_cap + p] = Winner{k, (uint32_t)i, 0u};
   }
 }
 
@@ -317,7 +333,6 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
       occ = e.occ;
       k = e.key;
       if (room) row = t.free_rows[free0 - 1 - (int32_t)w];
-      t.dset_row[e.pos] = row == kNoRow ? kRowAbsent : (int32_t)row;
       rows_out[e.occ] = row == kNoRow ? kRowAbsent : (int32_t)row;
       if (row != kNoRow) {
         cuckoo_insert(t, k, make_meta(row, src.seen ? src.seen[e.occ] : step), src.seen ? kAgeLook : sweep_unit(step, t.sweep_q));
@@ -338,18 +353,19 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
 }
 
 __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, int32_t* rows_out, uint32_t epoch) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) {
-    const int32_t v = rows_out[i];
-    if (v <= -3) rows_out[i] = t.dset_row[(uint64_t)(-(v + 3))];
-  }
-  if (i == 0) {  // settle the counters of this call (the insert kernel has finished)
-    uint32_t total = 0;
-    for (int l = 0; l < kWinLists; ++l) {
-      total += t.win_cnt[l * kWinStride];
-      t.win_cnt[l * kWinStride] = 0;
+  if (t.ctl->scratch[kDuplicateTag] == epoch) {  // (else every missing key of the call occurred once, or was not admitted)
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+      const int32_t v = rows_out[i];
+      if (v <= -3) rows_out[i] = rows_out[-(int64_t)(v + 3)];  // (the elected occurrence has its row, or kRowAbsent, by now)
     }
-    settle_call(t, total, t.ctl->free_n, epoch);
+  }
+  if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // settle the counters of this call (the insert kernel has finished)
+    uint32_t total = t.win_cnt[threadIdx.x * kWinStride];
+    t.win_cnt[threadIdx.x * kWinStride] = 0;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
+    if (threadIdx.x == 0) settle_call(t, total, t.ctl->free_n, epoch);
   }
 }
 
@@ -367,17 +383,19 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
   if (!restore && n <= kSmallLookup) return launch_lookup_small(t, d_keys, n, step, epoch, d_rows_out, stream, prof);
   const dim3 block(256), grid((unsigned)((n + 255) / 256));
   const dim3 igrid(grid.x < 2048u ? grid.x : 2048u);
-  if (t.expire_steps == 0)
-    MONO_LAUNCH(prof, K_PROBE_COUNT, stream, (probe_count_kernel<kProbeBlockStatic, 1>),
-                dim3((unsigned)((n + kProbeBlockStatic - 1) / kProbeBlockStatic)), dim3(kProbeBlockStatic), t, d_keys, n,
-                step, d_rows_out, restore);
-  else {
-    constexpr uint64_t per_block = (uint64_t)kProbeBlockAgeing * kProbeTurnsAgeing;
-    MONO_LAUNCH(prof, K_PROBE_COUNT, stream, (probe_count_kernel<kProbeBlockAgeing, kProbeTurnsAgeing>),
-                dim3((unsigned)((n + per_block - 1) / per_block)), dim3(kProbeBlockAgeing), t, d_keys, n, step, d_rows_out,
-                restore);
+  {
+    uint64_t turns = t.expire_steps == 0 ? 1 : n / ((uint64_t)kProbeBlock * kProbeBlocksWanted);
+    turns = turns < 1 ? 1 : (turns > kProbeMaxTurns ? kProbeMaxTurns : turns);
+    const uint64_t per_block = (uint64_t)kProbeBlock * turns;
+    const dim3 pgrid((unsigned)((n + per_block - 1) / per_block));
+    if (turns == 1)
+      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, probe_count_kernel<false>, pgrid, dim3(kProbeBlock), t, d_keys, n, step,
+                  d_rows_out, restore, 1u, epoch);
+    else
+      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, probe_count_kernel<true>, pgrid, dim3(kProbeBlock), t, d_keys, n, step,
+                  d_rows_out, restore, (uint32_t)turns, epoch);
   }
-  if (t.expire_steps == 0)
+  if (t.expire_steps == 0 || n <= kElectSmall)
     MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<256>, grid, block, t, d_keys, n, epoch, d_rows_out, restore);
   else
     MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<1024>, dim3((unsigned)((n + 1023) / 1024)), dim3(1024), t,
@@ -386,7 +404,7 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
     MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<uint16_t>, igrid, block, t, step, d_rows_out, src);
   else
     MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<float>, igrid, block, t, step, d_rows_out, src);
-  MONO_LAUNCH(prof, K_RESOLVE, stream, resolve_kernel, grid, block, t, n, d_rows_out, epoch);
+  MONO_LAUNCH(prof, K_RESOLVE, stream, resolve_kernel, igrid, block, t, n, d_rows_out, epoch);
   if (restore) hipLaunchKernelGGL(count_refused_kernel, grid, block, 0, stream, t, n, d_rows_out);
   return hipGetLastError();
 }

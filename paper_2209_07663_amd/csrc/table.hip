@@ -106,7 +106,6 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
   char* ctl = take(sizeof(Control));
   char* stash = take(kStashCap * sizeof(StashEntry));
   char* dset_p = take(dset * sizeof(unsigned long long));
-  char* dset_row = take(dset * sizeof(int32_t));
   // a sub-list takes the winners of every kWinLists-th block of the election kernel, whose blocks hold 256 or
   // 1024 occurrences: sized for the larger, which also covers the smaller
   const uint64_t win_cap = ((max_ids + 1023) / 1024 + kWinLists - 1) / kWinLists * 1024;
@@ -137,7 +136,6 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
     v.ctl = (Control*)ctl;
     v.stash = (StashEntry*)stash;
     v.dset = (unsigned long long*)dset_p;
-    v.dset_row = (int32_t*)dset_row;
     v.win_list = (Winner*)win_list;
     v.win_cnt = (uint32_t*)win_cnt;
     v.win_cap = win_cap;
