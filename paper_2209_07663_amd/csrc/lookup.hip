@@ -193,15 +193,17 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
 
 // ---- election ------------------------------------------------------------------------------------
 
-// kElectBlock: occurrences (= threads) per block.  256 on tables that never expire keys and for batches of at most
-// kElectSmall; 1024 for larger ones on tables with expiry, where an ID that turns hot before it is admitted is
-// led by one occurrence per block, and all those leaders meet at one position of the dedup set.
+// kPer: occurrences per thread.  Four for large batches: the kernel is a chain of dependent accesses (occurrence ->
+// key -> dedup set -> exchange), and four of them side by side keep the memory busier than more blocks
+// with one would; and an ID that turns hot before it is admitted is led by one occurrence per block, and all those
+// leaders meet at one position of the dedup set.  One for batches of at most kElectSmall, which are short of blocks.
 constexpr uint64_t kElectSmall = 1u << 19;
-template <int kElectBlock>
+constexpr int kElectBlock = 256;
+template <int kPer>
 __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, const int64_t* __restrict__ keys,
                                                                   uint64_t n, uint32_t epoch, int32_t* rows_out,
                                                                   int restore) {
-  constexpr int kElectSlots = 2 * kElectBlock;  // slots of a block's LDS set of missing keys
+  constexpr int kElectSlots = 2 * kElectBlock * kPer;  // slots of a block's LDS set of missing keys
   constexpr int kElectWaves = kElectBlock / 64;
   __shared__ uint32_t wave_cnt[kElectWaves];
   __shared__ uint32_t block_base;
@@ -211,72 +213,109 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   __shared__ unsigned long long s_key[kElectSlots];
   __shared__ int32_t s_res[kElectSlots];  // what the leader found: kRowAbsent, or the elected occurrence as -occ - 3
   if (t.ctl->scratch[kMissTag] != epoch) return;  // block-uniform: no occurrence of the call missed
+  const uint64_t i0 = (uint64_t)blockIdx.x * (kElectBlock * kPer) + threadIdx.x;
+  bool miss[kPer];
+  uint64_t k[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint64_t i = i0 + (uint64_t)j * kElectBlock;
+    miss[j] = i < n && rows_out[i] == kRowMiss;
+  }
   for (int s = threadIdx.x; s < kElectSlots; s += kElectBlock) s_key[s] = kEmptyKey;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) k[j] = miss[j] ? (uint64_t)keys[i0 + (uint64_t)j * kElectBlock] : kEmptyKey;
   __syncthreads();
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool miss = i < n && rows_out[i] == kRowMiss;
-  const uint64_t k = miss ? (uint64_t)keys[i] : kEmptyKey;
-  bool leader = false;
-  uint32_t ls = 0;
-  if (miss) {
-    ls = (uint32_t)(mix64(k ^ t.s_dedup) >> 32) & (kElectSlots - 1);
-    for (;;) {  // at most half of the slots are ever taken: a free slot always turns up
-      const unsigned long long old = atomicCAS(&s_key[ls], (unsigned long long)kEmptyKey, (unsigned long long)k);
-      if (old == kEmptyKey) leader = true;
-      if (old == kEmptyKey || old == k) break;
-      ls = (ls + 1) & (kElectSlots - 1);
+  bool leader[kPer];
+  uint32_t ls[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    leader[j] = false;
+    ls[j] = 0;
+    if (miss[j]) {
+      ls[j] = (uint32_t)(mix64(k[j] ^ t.s_dedup) >> 32) & (kElectSlots - 1);
+      for (;;) {  // at most half of the slots are ever taken: a free slot always turns up
+        const unsigned long long old = atomicCAS(&s_key[ls[j]], (unsigned long long)kEmptyKey, (unsigned long long)k[j]);
+        if (old == kEmptyKey) leader[j] = true;
+        if (old == kEmptyKey || old == k[j]) break;
+        ls[j] = (ls[j] + 1) & (kElectSlots - 1);
+      }
     }
   }
-  bool winner = false;
-  if (leader) {
-    // A snapshot record is admitted whatever its counter says, and with a threshold of 0 or 1 every
-    // missing key is admissible (its count is at least 1 by now): no counter is read for either.
-    uint32_t cnt = 255u;
-    if (!restore && t.freq_threshold > 1u) {
-      for (uint32_t j = 0; j < t.filter_hashes; ++j) {  // smallest of the key's counters
-        const uint32_t c = reinterpret_cast<const uint32_t*>(&t.filter[filter_index(t, k, j)])[0];
+  // A snapshot record is admitted whatever its counter says, and with a threshold of 0 or 1 every
+  // missing key is admissible (its count is at least 1 by now): no counter is read for either.
+  bool admissible[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    uint32_t cnt = leader[j] ? 255u : 0u;
+    if (!restore && t.freq_threshold > 1u && leader[j]) {
+      for (uint32_t h = 0; h < t.filter_hashes; ++h) {  // smallest of the key's counters
+        const uint32_t c = reinterpret_cast<const uint32_t*>(&t.filter[filter_index(t, k[j], h)])[0];
         cnt = c < cnt ? c : cnt;  // (counts are kept unsaturated and read as min(count, 255))
       }
     }
+    admissible[j] = leader[j] && cnt >= t.freq_threshold;
+  }
+  // one occurrence per distinct key wins its position of the per-call dedup set: a first look and a first exchange
+  // for all of the thread's leaders together, then whatever is left to do for each
+  unsigned long long e[kPer], old[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    e[j] = 0;
+    if (admissible[j]) e[j] = ld_agent(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask]);
+  }
+  const unsigned long long tag = (unsigned long long)epoch << 32;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    old[j] = e[j];
+    if (admissible[j] && (uint32_t)(e[j] >> 32) != epoch)
+      old[j] = atomicCAS(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask], e[j], tag | (i0 + (uint64_t)j * kElectBlock));
+  }
+  bool winner[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    winner[j] = false;
+    if (!leader[j]) continue;
+    const uint64_t i = i0 + (uint64_t)j * kElectBlock;
     int32_t found = kRowAbsent;
-    if (cnt >= t.freq_threshold) {
-      // one occurrence per distinct key wins its position of the per-call dedup set
-      uint64_t pos = mix64(k ^ t.s_dedup) & t.dset_mask;
-      uint64_t owner = i;
-      const unsigned long long mine = ((unsigned long long)epoch << 32) | (unsigned long long)i;
-      for (;;) {
-        unsigned long long e = ld_agent(&t.dset[pos]);
-        if ((uint32_t)(e >> 32) != epoch) {
-          const unsigned long long old = atomicCAS(&t.dset[pos], e, mine);
-          if (old == e) {
-            winner = true;
-            owner = i;
-            break;
-          }
-          e = old;  // someone wrote this position in this call
-          if ((uint32_t)(e >> 32) != epoch) continue;
+    if (admissible[j]) {
+      uint64_t pos = mix64(k[j] ^ t.s_dedup) & t.dset_mask, owner = i;
+      unsigned long long seen = old[j];
+      winner[j] = (uint32_t)(e[j] >> 32) != epoch && old[j] == e[j];
+      while (!winner[j]) {
+        if ((uint32_t)(seen >> 32) == epoch) {  // someone wrote this position in this call
+          owner = (uint32_t)seen;
+          if ((uint64_t)keys[owner] == k[j]) break;  // duplicate of the owner
+          pos = (pos + 1) & t.dset_mask;
+          seen = ld_agent(&t.dset[pos]);
+          continue;
         }
-        owner = (uint32_t)e;
-        if ((uint64_t)keys[owner] == k) break;  // duplicate of the owner
-        pos = (pos + 1) & t.dset_mask;
+        const unsigned long long was = atomicCAS(&t.dset[pos], seen, tag | i);
+        winner[j] = was == seen;
+        if (winner[j]) owner = i;
+        seen = was;
       }
       // (a second record of the same key in one restore call is refused like a stored key)
       found = restore ? kRowAbsent : -(int32_t)owner - 3;
     }
-    s_res[ls] = found;
-    if (!winner) rows_out[i] = found;  // the winner keeps kRowMiss until the insertion gives it its row
+    s_res[ls[j]] = found;
+    if (!winner[j]) rows_out[i] = found;  // the winner keeps kRowMiss until the insertion gives it its row
   }
   __syncthreads();
-  bool duplicate = leader && !winner && s_res[ls] <= -3;
-  if (miss && !leader) {
-    rows_out[i] = s_res[ls];
-    duplicate = s_res[ls] <= -3;
+  bool duplicate = false;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    if (!miss[j] || winner[j]) continue;
+    const int32_t found = s_res[ls[j]];
+    if (!leader[j]) rows_out[i0 + (uint64_t)j * kElectBlock] = found;
+    duplicate = duplicate || found <= -3;
   }
   if (__ballot(duplicate) && lane_id() == 0) t.ctl->scratch[kDuplicateTag] = epoch;
   // block-aggregated append to sub-list (blockIdx mod kWinLists)
   const uint32_t wave = threadIdx.x >> 6;
-  const uint64_t wmask = __ballot(winner);
-  if (lane_id() == 0) wave_cnt[wave] = (uint32_t)__popcll(wmask);
+  uint32_t mine = 0;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) mine += (uint32_t)__popcll(__ballot(winner[j]));
+  if (lane_id() == 0) wave_cnt[wave] = mine;
   __syncthreads();
   const uint32_t list = blockIdx.x & (kWinLists - 1);
   if (threadIdx.x == 0) {
@@ -285,10 +324,15 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     block_base = total ? atomicAdd(&t.win_cnt[list * kWinStride], total) : 0u;
   }
   __syncthreads();
-  if (winner) {
-    uint32_t p = block_base + (uint32_t)__popcll(wmask & lanes_below());
-    for (uint32_t w = 0; w < wave; ++w) p += wave_cnt[w];
-    t.win_list[(uint64_t)list * t.win_cap + p] = Winner{k, (uint32_t)i, 0u};
+  uint32_t p = block_base;
+  for (uint32_t w = 0; w < wave; ++w) p += wave_cnt[w];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const uint64_t m = __ballot(winner[j]);
+    if (winner[j])
+      t.win_list[(uint64_t)list * t.win_cap + p + (uint32_t)__popcll(m & lanes_below())] =
+          Winner{k[j], (uint32_t)(i0 + (uint64_t)j * kElectBlock), 0u};
+    p += (uint32_t)__popcll(m);
   }
 }
 
@@ -296,9 +340,17 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
 
 // Dense over the elected occurrences: winner number w of the call takes free_rows[free_n - 1 - w].
 template <typename E>
-__global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step, int32_t* rows_out,
+__global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint32_t step, int32_t* rows_out,
                                                      RestoreSource src) {
+  // Keys that find both of their buckets full wait here until the block has placed the others: an eviction is a
+  // dozen dependent accesses, and one lane in twenty that needs it (load 0.7) would hold up every wave.
+  constexpr uint32_t kWaiting = 256;
+  __shared__ unsigned long long s_key[kWaiting], s_meta[kWaiting];
+  __shared__ uint32_t s_waiting;
+  if (threadIdx.x == 0) s_waiting = 0;
+  __syncthreads();
   const uint32_t lane = lane_id();
+  const uint32_t unit = src.seen ? kAgeLook : sweep_unit(step, t.sweep_q);
   // inclusive prefix of the sub-list fills, one list per lane
   uint32_t inc = t.win_cnt[lane * kWinStride];
 #pragma unroll
@@ -335,7 +387,16 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
       if (room) row = t.free_rows[free0 - 1 - (int32_t)w];
       rows_out[e.occ] = row == kNoRow ? kRowAbsent : (int32_t)row;
       if (row != kNoRow) {
-        cuckoo_insert(t, k, make_meta(row, src.seen ? src.seen[e.occ] : step), src.seen ? kAgeLook : sweep_unit(step, t.sweep_q));
+        const unsigned long long meta = make_meta(row, src.seen ? src.seen[e.occ] : step);
+        if (!claim_free(t, k, meta, unit)) {
+          const uint32_t at = atomicAdd(&s_waiting, 1u);
+          if (at < kWaiting) {
+            s_key[at] = k;
+            s_meta[at] = meta;
+          } else {
+            cuckoo_insert(t, k, meta, unit);
+          }
+        }
         if (src.values && t.expire_steps == 0) {
           // a restored key counts as seen freq_threshold times: its counters are raised to that
           // (records may come without their counters, and a counter below the threshold would
@@ -350,6 +411,9 @@ __global__ __launch_bounds__(256) void insert_kernel(TableView t, uint32_t step,
     }
     init_new_rows<E>(t, valid && row != kNoRow, k, row, occ, src);
   }
+  __syncthreads();
+  const uint32_t waiting = s_waiting < kWaiting ? s_waiting : kWaiting;
+  for (uint32_t w = threadIdx.x; w < waiting; w += blockDim.x) cuckoo_insert(t, s_key[w], s_meta[w], unit);
 }
 
 __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, int32_t* rows_out, uint32_t epoch) {
@@ -395,11 +459,11 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
       MONO_LAUNCH(prof, K_PROBE_COUNT, stream, probe_count_kernel<true>, pgrid, dim3(kProbeBlock), t, d_keys, n, step,
                   d_rows_out, restore, (uint32_t)turns, epoch);
   }
-  if (t.expire_steps == 0 || n <= kElectSmall)
-    MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<256>, grid, block, t, d_keys, n, epoch, d_rows_out, restore);
+  if (n <= kElectSmall)
+    MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<1>, grid, block, t, d_keys, n, epoch, d_rows_out, restore);
   else
-    MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<1024>, dim3((unsigned)((n + 1023) / 1024)), dim3(1024), t,
-                d_keys, n, epoch, d_rows_out, restore);
+    MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<4>, dim3((unsigned)((n + 1023) / 1024)), block, t, d_keys, n,
+                epoch, d_rows_out, restore);
   if (t.bf16)
     MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<uint16_t>, igrid, block, t, step, d_rows_out, src);
   else

@@ -123,6 +123,12 @@ __device__ inline uint32_t pick_victim(const TableView& t, const Bucket* b, int 
   return (start + (uint32_t)__ffs((int)rotated) - 1u) & (kBucket - 1);
 }
 
+// Takes a free slot of either bucket of k, if there is one (see cuckoo_insert).
+__device__ inline bool claim_free(const TableView& t, uint64_t k, unsigned long long meta, uint32_t unit) {
+  return try_claim(t, &t.buckets[bucket_index(t, 0, k)], k, meta, unit) ||
+         try_claim(t, &t.buckets[bucket_index(t, 1, k)], k, meta, unit);
+}
+
 // Inserts (k, meta); k is not in the table and no other thread inserts the same key.  unit: see note_key.
 __device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long meta, uint32_t unit) {
   int side = 0;
@@ -195,20 +201,20 @@ __device__ inline void init_new_rows(const TableView& t, bool ok_lane, uint64_t 
   uint32_t glog = 0;
   while (glog < 6 && (4u << glog) < t.dim) ++glog;
   const uint32_t group = 1u << glog, per_round = 64u >> glog, l = lane & (group - 1u), gi = lane >> glog;
-  const int ok = ok_lane;
-  if (__ballot(ok) == 0) return;  // wave-uniform
+  if (__ballot(ok_lane) == 0) return;  // wave-uniform
+  const uint64_t mine = mix64(k ^ t.s_init);
+  const uint32_t row_or_none = ok_lane ? row : kNoRow;
   for (uint32_t q = 0; q < group; ++q) {
     const int from = (int)(q * per_round + gi);
-    const uint64_t kk = __shfl(k, from);
-    const uint32_t rr = __shfl(row, from);
-    const uint32_t oo = __shfl(occ, from);
-    if (!__shfl(ok, from)) continue;
+    const uint64_t base_h = __shfl(mine, from);
+    const uint32_t rr = __shfl(row_or_none, from);
+    const uint32_t oo = src.values || src.acc ? __shfl(occ, from) : 0u;
+    if (rr == kNoRow) continue;
     for (uint32_t col = l * 4; col < t.dim; col += 256) {
       float4 v;
       if (src.values) {
         v = *reinterpret_cast<const float4*>(src.values + (uint64_t)oo * t.dim + col);
       } else {
-        const uint64_t base_h = mix64(kk ^ t.s_init);
         v = make_float4(init_value(base_h, col), init_value(base_h, col + 1), init_value(base_h, col + 2),
                         init_value(base_h, col + 3));
       }
