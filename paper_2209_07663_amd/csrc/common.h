@@ -36,6 +36,7 @@ constexpr int kWinStride = 32;              // u32 words between two sub-list co
 
 constexpr int kSweepRemoved = 0;            // Control::scratch slot: keys removed so far by the running sweep
 constexpr int kExportCount = 1;             // Control::scratch slot: elements found by the running export
+constexpr int kExportBits = 9;              // Control::scratch slots (two): OR and AND of the keys it found
 constexpr int kValidPairs = 2;              // Control::scratch slot: (row, bag) pairs kept by the sort
 constexpr int kRefusedRecords = 3;          // Control::scratch slot: records refused by the running restore call
 

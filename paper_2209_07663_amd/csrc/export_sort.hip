@@ -4,7 +4,7 @@
 // rows in that order on the host took 3 ms of a 6.3 ms synchronisation step.  Stable LSD radix sort of (key,
 // index) pairs, eight bits a pass, over the bits in which the keys differ at all (IDs of a 2^40 space: five
 // passes).  Per pass:
-//   hist     digit histogram of every unit of kUnit elements, bin-major
+//   hist     digit histogram of every unit of elements, bin-major
 //   scan     one block per bin: exclusive scan along the units, total of the bin
 //   scatter  a block ranks its unit (stable, by ballot matching within a wave) into LDS and writes it out
 // Then `emit` writes keys and attributes in order; the rows follow through the ordinary export_values kernel.
@@ -16,13 +16,23 @@
 namespace mono {
 
 constexpr int kThreads = 256, kWaves = kThreads / 64;
-constexpr uint32_t kUnit = 2048, kRounds = kUnit / kThreads;  // elements per block; per lane of a wave
+// Elements per block: many, so that a bin's share leaves in long pieces, or few where the export is small and a pass
+// is the latency of one block.
+constexpr uint32_t kUnitLarge = 2048, kUnitSmall = 512;
+constexpr uint64_t kSmallExport = 400000;
 
-uint64_t export_sort_units(uint64_t n) { return (n + kUnit - 1) / kUnit; }
+uint64_t export_sort_units(uint64_t n) {
+  const uint64_t large = (n + kUnitLarge - 1) / kUnitLarge, m = n < kSmallExport ? n : kSmallExport;
+  const uint64_t small = (m + kUnitSmall - 1) / kUnitSmall;
+  return large > small ? large : small;
+}
 
-// bits[0] = OR, bits[1] = AND of all keys
-__global__ __launch_bounds__(kThreads) void export_bits_kernel(const uint64_t* __restrict__ keys, uint64_t n,
-                                                               unsigned long long* __restrict__ bits) {
+// OR and AND of the keys that the scan has found (at most max_n were written)
+__global__ __launch_bounds__(kThreads) void export_bits_kernel(const uint64_t* __restrict__ keys, uint64_t max_n,
+                                                               Control* __restrict__ ctl) {
+  __shared__ unsigned long long s_any[kWaves], s_all[kWaves];
+  const unsigned long long found = ctl->scratch[kExportCount];
+  const uint64_t n = found < max_n ? found : max_n;
   unsigned long long any = 0, all = ~0ull;
   for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (uint64_t)gridDim.x * kThreads) {
     any |= keys[i];
@@ -34,11 +44,21 @@ __global__ __launch_bounds__(kThreads) void export_bits_kernel(const uint64_t* _
     all &= __shfl_xor(all, d);
   }
   if (lane_id() == 0) {
-    atomicOr(&bits[0], any);
-    atomicAnd(&bits[1], all);
+    s_any[threadIdx.x >> 6] = any;
+    s_all[threadIdx.x >> 6] = all;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {  // (one pair of atomics per block: they serialise)
+    for (int w = 1; w < kWaves; ++w) {
+      any |= s_any[w];
+      all &= s_all[w];
+    }
+    atomicOr(&ctl->scratch[kExportBits], any);
+    atomicAnd(&ctl->scratch[kExportBits + 1], all);
   }
 }
 
+template <uint32_t kUnit>
 __global__ __launch_bounds__(kThreads) void export_hist_kernel(const uint64_t* __restrict__ keys, uint64_t n,
                                                                uint32_t shift, uint64_t units,
                                                                uint32_t* __restrict__ hist) {
@@ -47,7 +67,7 @@ __global__ __launch_bounds__(kThreads) void export_hist_kernel(const uint64_t* _
   __syncthreads();
   const uint64_t base = (uint64_t)blockIdx.x * kUnit;
 #pragma unroll
-  for (uint32_t r = 0; r < kRounds; ++r) {
+  for (uint32_t r = 0; r < kUnit / kThreads; ++r) {
     const uint64_t i = base + (uint64_t)r * kThreads + threadIdx.x;
     if (i < n) atomicAdd(&cnt[(keys[i] >> shift) & 255u], 1u);
   }
@@ -87,6 +107,7 @@ __global__ __launch_bounds__(kThreads) void export_scan_kernel(uint32_t* __restr
 }
 
 // src_idx == nullptr: first pass, an element's index is its position
+template <uint32_t kUnit>
 __global__ __launch_bounds__(kThreads) void export_scatter_kernel(const uint64_t* __restrict__ src_key,
                                                                   const uint32_t* __restrict__ src_idx, uint64_t n,
                                                                   uint32_t shift, uint64_t units,
@@ -94,6 +115,7 @@ __global__ __launch_bounds__(kThreads) void export_scatter_kernel(const uint64_t
                                                                   const uint32_t* __restrict__ totals,
                                                                   uint64_t* __restrict__ dst_key,
                                                                   uint32_t* __restrict__ dst_idx) {
+  constexpr uint32_t kRounds = kUnit / kThreads;  // elements per lane of a wave
   __shared__ uint64_t s_key[kUnit];
   __shared__ uint32_t s_idx[kUnit];
   __shared__ uint32_t cnt[kWaves][256];  // per-wave digit counts, then local start offsets
@@ -194,34 +216,38 @@ __global__ __launch_bounds__(kThreads) void export_emit_kernel(ExportWorkspace w
   if (slot) slot[i] = ws.slot[from];
 }
 
-hipError_t launch_export_bits(const ExportWorkspace& ws, uint64_t n, hipStream_t stream) {
-  hipError_t e = hipMemsetAsync(&ws.bits[0], 0x00, sizeof(unsigned long long), stream);
-  if (e == hipSuccess) e = hipMemsetAsync(&ws.bits[1], 0xFF, sizeof(unsigned long long), stream);
-  if (e != hipSuccess) return e;
-  const uint64_t blocks = (n + kThreads - 1) / kThreads;
-  hipLaunchKernelGGL(export_bits_kernel, dim3((unsigned)(blocks < 256 ? blocks : 256)), dim3(kThreads), 0, stream,
-                     ws.key[0], n, ws.bits);
+hipError_t launch_export_bits(const TableView& t, const ExportWorkspace& ws, uint64_t max_n, hipStream_t stream) {
+  const uint64_t blocks = (max_n + kThreads - 1) / kThreads;
+  hipLaunchKernelGGL(export_bits_kernel, dim3((unsigned)(blocks < 64 ? (blocks ? blocks : 1) : 64)), dim3(kThreads), 0, stream,
+                     ws.key[0], max_n, t.ctl);
   return hipGetLastError();
 }
 
-hipError_t launch_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t varying, int64_t* d_keys, int32_t* d_row,
-                              uint32_t* d_last_seen, int64_t* d_slot, hipStream_t stream) {
-  const uint64_t units = export_sort_units(n);
+template <uint32_t kUnit>
+static hipError_t queue_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t varying, int64_t* d_keys, int32_t* d_row,
+                                    uint32_t* d_last_seen, int64_t* d_slot, hipStream_t stream) {
+  const uint64_t units = (n + kUnit - 1) / kUnit;
   uint32_t* totals = ws.hist + 256 * units;
   const dim3 block(kThreads), grid((unsigned)units);
   int side = 0;
   const uint32_t* idx = nullptr;
   for (uint32_t shift = varying ? (uint32_t)__builtin_ctzll(varying) : 64; shift < 64 && (varying >> shift); shift += 8) {
-    hipLaunchKernelGGL(export_hist_kernel, grid, block, 0, stream, ws.key[side], n, shift, units, ws.hist);
+    hipLaunchKernelGGL(export_hist_kernel<kUnit>, grid, block, 0, stream, ws.key[side], n, shift, units, ws.hist);
     hipLaunchKernelGGL(export_scan_kernel, dim3(256), block, 0, stream, ws.hist, units, totals);
-    hipLaunchKernelGGL(export_scatter_kernel, grid, block, 0, stream, ws.key[side], idx, n, shift, units, ws.hist, totals,
-                       ws.key[1 - side], ws.idx[1 - side]);
+    hipLaunchKernelGGL(export_scatter_kernel<kUnit>, grid, block, 0, stream, ws.key[side], idx, n, shift, units, ws.hist,
+                       totals, ws.key[1 - side], ws.idx[1 - side]);
     side = 1 - side;
     idx = ws.idx[side];
   }
   hipLaunchKernelGGL(export_emit_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), block, 0, stream, ws,
                      ws.key[side], idx, n, d_keys, d_row, d_last_seen, d_slot);
   return hipGetLastError();
+}
+
+hipError_t launch_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t varying, int64_t* d_keys, int32_t* d_row,
+                              uint32_t* d_last_seen, int64_t* d_slot, hipStream_t stream) {
+  return n <= kSmallExport ? queue_export_sort<kUnitSmall>(ws, n, varying, d_keys, d_row, d_last_seen, d_slot, stream)
+                           : queue_export_sort<kUnitLarge>(ws, n, varying, d_keys, d_row, d_last_seen, d_slot, stream);
 }
 
 }  // namespace mono

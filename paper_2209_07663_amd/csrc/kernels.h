@@ -30,15 +30,21 @@ struct UpdateWorkspace {
 // 26 K pairs takes 11.1 / 8.2 / 6.4 us with 2048 / 1024 / 512 elements per block, one of 204 K 10.8 / 8.0 / 7.0,
 // one of 690 K 12.0 / 9.9 / 10.5 (there the histograms, one word per bin and block, begin to cost more), one
 // of 1 M 12.9 / 12.5 / 12.8.
+// Where the batch is small and two digits of up to 11 bits save a pass of narrow ones (2^16 to 2^22 rows in use),
+// they are taken: all sort kernels of 100 K pairs 42 -> 36 us and three launches fewer, but 44 -> 45 at 204 K, 57 ->
+// 68 at 690 K (2048 histogram words per block).
 // And batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch instead of nine.
 struct SortShape {
   uint32_t max_bits, items;
 };
-constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9;
+constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9, kSortFewBits = 11;
 constexpr uint32_t kSortNarrowMaxRows = 1u << 24;  // beyond this many rows in use the wide shape saves a pass
 constexpr uint64_t kSortItems512 = 400000, kSortItems1024 = 1u << 20;  // largest batches of those block sizes
+constexpr uint64_t kSortFewMost = 1u << 17;
+constexpr uint32_t kSortFewRowsAbove = 1u << 16, kSortFewMaxRows = 1u << 22;
 constexpr uint64_t kSortSmall = 8192;
 inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
+  if (n <= kSortFewMost && hwm_bound > kSortFewRowsAbove && hwm_bound <= kSortFewMaxRows) return {kSortFewBits, 512u};
   if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, n <= kSortItems1024 ? 1024u : 4096u};
   return {kSortNarrowBits, n <= kSortItems512 ? 512u : (n <= kSortItems1024 ? 1024u : 2048u)};
 }
@@ -65,9 +71,10 @@ inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // 
 // unit, then the bin totals
 inline uint64_t sort_hist_words(uint64_t n) {
   uint64_t most = 0;
-  const uint64_t sizes[] = {n, n < kSortItems512 ? n : kSortItems512, n < kSortItems1024 ? n : kSortItems1024};
+  const uint64_t sizes[] = {n, n < kSortFewMost ? n : kSortFewMost, n < kSortItems512 ? n : kSortItems512,
+                            n < kSortItems1024 ? n : kSortItems1024};
   for (const uint64_t m : sizes)
-    for (const uint32_t rows : {kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
+    for (const uint32_t rows : {kSortFewMaxRows, kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
       const SortShape s = sort_shape_for(rows, m);
       const uint64_t words = (1ull << s.max_bits) * (sort_stride(sort_units(m, s.items)) + 1);
       most = words > most ? words : most;
@@ -155,10 +162,10 @@ struct ExportWorkspace {
   uint32_t* seen;            // [n]
   int64_t* slot;             // [n]
   uint32_t* hist;            // [256 * (export_sort_units(n) + 1)]
-  unsigned long long* bits;  // OR and AND of all keys
 };
 uint64_t export_sort_units(uint64_t n);
-hipError_t launch_export_bits(const ExportWorkspace& ws, uint64_t n, hipStream_t stream);
+// leaves OR and AND of the keys found in the control block's scratch
+hipError_t launch_export_bits(const TableView& t, const ExportWorkspace& ws, uint64_t max_n, hipStream_t stream);
 // varying: the bits in which the keys differ
 hipError_t launch_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t varying, int64_t* d_keys, int32_t* d_row,
                               uint32_t* d_last_seen, int64_t* d_slot, hipStream_t stream);

@@ -237,7 +237,10 @@ hipError_t launch_expire_sweep(const TableView& t, uint32_t now, uint64_t* d_n_e
 // ---- dump --------------------------------------------------------------------------------------
 
 __global__ void export_begin_kernel(TableView t) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) t.ctl->scratch[kExportCount] = 0;
+  if (blockIdx.x != 0 || threadIdx.x != 0) return;
+  t.ctl->scratch[kExportCount] = 0;
+  t.ctl->scratch[kExportBits] = 0;
+  t.ctl->scratch[kExportBits + 1] = ~0ull;
 }
 
 constexpr int kExportBlock = 1024;
@@ -258,7 +261,8 @@ __global__ __launch_bounds__(kExportBlock) void export_kernel(TableView t, int64
     const unsigned long long m = b->meta[l];
     row = meta_row(m);
     live = row != kNoRow;
-    key = b->key[l];
+    if (live && touched_only) live = t.state[row].touch == t.sync_epoch;
+    if (live) key = b->key[l];  // (a delta export skips most of the keys' half of the table)
     seen = meta_seen(m);
     where = (int64_t)g;
   } else if (g < total) {
@@ -269,9 +273,9 @@ __global__ __launch_bounds__(kExportBlock) void export_kernel(TableView t, int64
       key = t.stash[s].key;
       row = t.stash[s].row;
       seen = t.stash[s].seen;
+      if (touched_only) live = t.state[row].touch == t.sync_epoch;
     }
   }
-  if (live && touched_only) live = t.state[row].touch == t.sync_epoch;
   // one append per block: the waves' counts meet in LDS (a counter hit once per wave would serialise)
   __shared__ uint32_t wave_cnt[kExportBlock / 64];
   __shared__ unsigned long long block_base;

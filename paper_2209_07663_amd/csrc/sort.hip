@@ -37,10 +37,12 @@ template <uint32_t kBits, int kBlock, uint32_t kItems>
 struct Shape {
   static constexpr uint32_t kBins = 1u << kBits;
   static constexpr int kWaves = kBlock / 64;
-  static constexpr int kScanWaves = (int)kBins / 64;  // the first kBins threads of a block own one bin each
+  static constexpr uint32_t kBinsPerThread = kBins > (uint32_t)kBlock ? kBins / kBlock : 1;  // consecutive bins a thread owns
+  static constexpr uint32_t kBinThreads = kBins / kBinsPerThread;                            // threads that own bins
+  static constexpr int kScanWaves = (int)kBinThreads / 64;
   static constexpr uint32_t kPerWave = kItems / kWaves;
   static constexpr uint32_t kRounds = kPerWave / 64;
-  static_assert(kBlock >= (int)kBins && kBlock % 64 == 0 && kItems % (uint32_t)kBlock == 0, "one thread per bin");
+  static_assert(kBlock % 64 == 0 && kItems % (uint32_t)kBlock == 0 && kBinThreads % 64 == 0, "whole waves");
 };
 
 // Lanes of the wave that hold the same digit (of `bits` <= kBits bits) as this lane, among the lanes with valid == true.
@@ -199,6 +201,38 @@ __global__ __launch_bounds__(256) void sort_scan_kernel(const Control* __restric
   if (threadIdx.x == 0) totals[blockIdx.x] = carry;
 }
 
+// The same with one wave per bin, for at most 64 * kScanFew units.
+constexpr uint32_t kScanFew = 8;  // units per lane
+template <uint32_t kBits>
+__global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __restrict__ ctl, uint32_t pass,
+                                                            uint32_t* __restrict__ hist, uint32_t units, uint64_t stride,
+                                                            uint32_t* __restrict__ totals) {
+  const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
+  const uint32_t bin = blockIdx.x * 4 + (threadIdx.x >> 6), lane = lane_id();
+  if (pass >= plan.passes || bin >= (1u << plan.width(pass))) return;  // wave-uniform (no barriers below)
+  uint32_t* row = hist + (uint64_t)bin * stride;
+  const uint32_t per = (units + 63) / 64, first = lane * per;
+  uint32_t v[kScanFew], sum = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < kScanFew; ++j) {
+    v[j] = j < per && first + j < units ? row[first + j] : 0;
+    sum += v[j];
+  }
+  uint32_t x = sum;  // inclusive wave scan of the lane sums
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(x, d);
+    if ((int)lane >= d) x += y;
+  }
+  uint32_t run = x - sum;
+#pragma unroll
+  for (uint32_t j = 0; j < kScanFew; ++j) {
+    if (j < per && first + j < units) row[first + j] = run;
+    run += v[j];
+  }
+  if (lane == 63) totals[bin] = x;
+}
+
 template <uint32_t kBits, int kBlock, uint32_t kItems>
 __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restrict__ ctl, uint32_t pass,
                                                                   const int32_t* __restrict__ rows,
@@ -222,12 +256,16 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   const uint32_t shift = plan.shift(pass), bits = plan.width(pass), nbins = 1u << bits, mask = nbins - 1;
 
   // 0. what step 3 needs from memory is asked for first: it arrives while the elements are loaded
-  const bool bin_thread = threadIdx.x < S::kBins;
-  const uint32_t bin = threadIdx.x;
-  uint32_t tot = 0, before_me = 0;  // the bin in the whole batch / in the units before this one
-  if (bin_thread && bin < nbins) {
-    tot = totals[bin];
-    before_me = hist[(uint64_t)bin * stride + unit];
+  const bool bin_thread = threadIdx.x < S::kBinThreads;
+  const uint32_t bin0 = threadIdx.x * S::kBinsPerThread;  // the thread's bins
+  uint32_t tot[S::kBinsPerThread], before_me[S::kBinsPerThread];  // a bin in the whole batch / in the units before this one
+#pragma unroll
+  for (uint32_t q = 0; q < S::kBinsPerThread; ++q) {
+    tot[q] = before_me[q] = 0;
+    if (bin_thread && bin0 + q < nbins) {
+      tot[q] = totals[bin0 + q];
+      before_me[q] = hist[(uint64_t)(bin0 + q) * stride + unit];
+    }
   }
   // 1. this wave's elements -> registers (independent, coalesced loads)
   if (pass > 0) n = ctl->scratch[kValidPairs];
@@ -292,16 +330,20 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   }
   static_assert(kItems <= 0x10000, "rank and digit share a word");
   __syncthreads();
-  // 3. thread b < S::kBins owns bin b: exclusive scans of the bin totals, once within the block
+  // 3. a bin thread owns kBinsPerThread bins: exclusive scans of the bins' counts, once within the block
   //    (positions in `stage`) and once over all bins of the pass (start of the bin in dst)
   __shared__ uint32_t scan_sum[S::kScanWaves], scan_tot[S::kScanWaves];
   {
-    uint32_t mine = 0;
-    if (bin_thread && bin < nbins) {
+    uint32_t mine = 0, tots = 0;
+    if (bin_thread) {
 #pragma unroll
-      for (int w = 0; w < S::kWaves; ++w) mine += lds[w][bin];
+      for (uint32_t q = 0; q < S::kBinsPerThread; ++q) {
+        tots += tot[q];
+#pragma unroll
+        for (int w = 0; w < S::kWaves; ++w) mine += lds[w][bin0 + q];
+      }
     }
-    uint32_t x = mine, y = tot;  // inclusive wave scans
+    uint32_t x = mine, y = tots;  // inclusive wave scans
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
       const uint32_t xs = __shfl_up(x, d), ys = __shfl_up(y, d);
@@ -316,24 +358,25 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
     }
     __syncthreads();
     if (bin_thread) {
-      uint32_t run = x - mine, run_tot = y - tot;  // first position of the bin in the block / in dst
+      uint32_t run = x - mine, run_tot = y - tots;  // first position of the thread's first bin in the block / in dst
       for (uint32_t w = 0; w < wave; ++w) {
         run += scan_sum[w];
         run_tot += scan_tot[w];
       }
-      if (bin < nbins) {
-        local_start[bin] = run;
-        global_start[bin] = run_tot + before_me;
-        uint32_t at = run;
+#pragma unroll
+      for (uint32_t q = 0; q < S::kBinsPerThread; ++q) {
+        local_start[bin0 + q] = run;
+        global_start[bin0 + q] = run_tot + before_me[q];
+        run_tot += tot[q];
 #pragma unroll
         for (int w = 0; w < S::kWaves; ++w) {
-          const uint32_t c = lds[w][bin];
-          lds[w][bin] = at;
-          at += c;
+          const uint32_t c = lds[w][bin0 + q];
+          lds[w][bin0 + q] = run;
+          run += c;
         }
       }
-      if (pass == 0 && blockIdx.x == 0 && threadIdx.x == S::kBins - 1)
-        ctl->scratch[kValidPairs] = run_tot + tot;  // pairs that remain
+      if (pass == 0 && blockIdx.x == 0 && threadIdx.x == S::kBinThreads - 1)
+        ctl->scratch[kValidPairs] = run_tot;  // pairs that remain
     }
   }
   __syncthreads();
@@ -471,8 +514,12 @@ static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, con
     else
       MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems, 1>), dim3((unsigned)units + search),
                   block, t.ctl, p, d_rows, src, n, stride, ws.hist, d_offsets, n_bags, ws.unit_bag, search);
-    MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3(1u << kBits), dim3(256), t.ctl, p, ws.hist, units,
-                stride, totals);
+    if (units <= 64 * kScanFew)
+      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_few_kernel<kBits>, dim3((1u << kBits) / 4), dim3(256), t.ctl, p, ws.hist,
+                  (uint32_t)units, stride, totals);
+    else
+      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3(1u << kBits), dim3(256), t.ctl, p, ws.hist, units,
+                  stride, totals);
     MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems>), grid, block, t.ctl, p, d_rows,
                 d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, totals, dst);
   }
@@ -496,7 +543,9 @@ hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, cons
   }
 #define MONO_SORT(bits, block, items) \
   queue_sort_passes<bits, block, items>(t, ws, d_rows, n, d_offsets, n_bags, worst.passes, stream, prof)
-  if (shape.max_bits == kSortWideBits) {
+  if (shape.max_bits == kSortFewBits) {
+    MONO_SORT(kSortFewBits, 256, 512);
+  } else if (shape.max_bits == kSortWideBits) {
     if (shape.items == 1024)
       MONO_SORT(kSortWideBits, 512, 1024);
     else

@@ -24,6 +24,8 @@ struct mono_table {
   // lookup_or_insert leaves (its call tag << 32 | mark) in a pinned host word when it ends, and the host
   // remembers how many keys each of its latest calls held (a call hands out at most one row per key).
   unsigned long long* h_mail = nullptr;       // pinned; null: no bound is kept (the capacity is used)
+  Control* h_control = nullptr;               // pinned, beside the word, for read_control; null: there is none
+  std::mutex control_mutex;
   static constexpr uint32_t kRecentCalls = 256;
   uint32_t recent_tag[kRecentCalls] = {0};    // call tags, by tag % kRecentCalls (0 = unused)
   uint64_t recent_n[kRecentCalls] = {0};      // keys of that call
@@ -37,11 +39,12 @@ struct mono_table {
 constexpr uint64_t kStaticMaxIds = MONO_NOALLOC_MAX_IDS;  // largest batch of the allocation-free entry point
 constexpr uint32_t kStaticMaxDim = 1024;
 constexpr size_t static_part(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+constexpr size_t kStaticHistWords = 2048 * (kSortFewMost / 512 + 4);  // at least sort_hist_words(kStaticMaxIds): checked below
 constexpr uint64_t kStaticTiles = 2 * kTilesWanted;  // tiles of the reduction: reduce_tiles(kStaticMaxIds), checked below
 constexpr size_t kStaticPartFloats = 2 * ((kStaticMaxIds + 255) / 256) * kStaticMaxDim;  // for wide rows: tiles of 256 pairs
 constexpr size_t kStaticScratchBytes =
     static_part(kStaticMaxIds * 4) + 2 * static_part(kStaticMaxIds * sizeof(uint2)) +
-    static_part((size_t)256 * ((kStaticMaxIds + 511) / 512 + 4) * 4) +  // (at least sort_hist_words: checked below)
+    static_part(kStaticHistWords * 4) +
     static_part(kStaticPartFloats * sizeof(float)) + static_part(2 * kStaticTiles * sizeof(uint32_t));
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
@@ -161,7 +164,7 @@ void* g_scratch_ptr[kMaxDevices] = {nullptr};
 std::mutex g_scratch_mutex;
 
 hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
-  if (sort_hist_words(kStaticMaxIds) > (size_t)256 * ((kStaticMaxIds + 511) / 512 + 4)) return hipErrorInvalidValue;
+  if (sort_hist_words(kStaticMaxIds) > kStaticHistWords) return hipErrorInvalidValue;
   if (reduce_tiles(kStaticMaxIds) > kStaticTiles) return hipErrorInvalidValue;
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
   void* base = nullptr;
@@ -189,7 +192,7 @@ hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
   ws->unit_bag = (uint32_t*)take(kStaticMaxIds * 4);
   ws->pair_a = (uint2*)take(kStaticMaxIds * sizeof(uint2));
   ws->pair_b = (uint2*)take(kStaticMaxIds * sizeof(uint2));
-  ws->hist = (uint32_t*)take((size_t)256 * ((kStaticMaxIds + 511) / 512 + 4) * 4);
+  ws->hist = (uint32_t*)take(kStaticHistWords * 4);
   ws->part = (float*)take(kStaticPartFloats * sizeof(float));
   ws->part_row = (uint32_t*)take(2 * kStaticTiles * sizeof(uint32_t));
   ws->tiles = kStaticPartFloats / (2 * (uint64_t)dim) < kStaticTiles ? kStaticPartFloats / (2 * (uint64_t)dim) : kStaticTiles;
@@ -205,10 +208,10 @@ size_t export_workspace(ExportWorkspace* ws, char* base, uint64_t n) {
     return p;
   };
   char *k0 = take(n * 8), *k1 = take(n * 8), *i0 = take(n * 4), *i1 = take(n * 4), *row = take(n * 4), *seen = take(n * 4),
-       *slot = take(n * 8), *hist = take(256 * (export_sort_units(n) + 1) * 4), *bits = take(2 * 8);
+       *slot = take(n * 8), *hist = take(256 * (export_sort_units(n) + 1) * 4);
   if (ws)
     *ws = ExportWorkspace{{(uint64_t*)k0, (uint64_t*)k1}, {(uint32_t*)i0, (uint32_t*)i1}, (int32_t*)row,
-                          (uint32_t*)seen, (int64_t*)slot, (uint32_t*)hist, (unsigned long long*)bits};
+                          (uint32_t*)seen, (int64_t*)slot, (uint32_t*)hist};
   return off;
 }
 
@@ -233,6 +236,17 @@ uint32_t hwm_bound(const mono_table* t) {
     if (bound >= capacity) return (uint32_t)capacity;
   }
   return (uint32_t)(bound < capacity ? bound : capacity);
+}
+
+// The device's counters, once everything queued on `stream` so far has run.  They come through pinned memory where there
+// is some (a copy to ordinary memory took 27 us, most of it host work).
+hipError_t read_control(mono_table* t, Control* c, hipStream_t stream) {
+  std::lock_guard<std::mutex> lock(t->control_mutex);
+  void* to = t->h_control ? (void*)t->h_control : (void*)c;
+  hipError_t e = hipMemcpyAsync(to, t->view.ctl, sizeof(Control), hipMemcpyDeviceToHost, stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(stream);
+  if (e == hipSuccess && t->h_control) *c = *t->h_control;
+  return e;
 }
 
 void note_stream(mono_table* t, void* stream) {
@@ -329,9 +343,10 @@ int mono_table_create_ex(mono_table** out, uint64_t capacity, uint32_t dim, uint
   {  // (pinned host memory is allocated, never registered; without it the sort is simply sized for the capacity)
     void* mail = nullptr;
     void* mail_dev = nullptr;
-    if (hipHostMalloc(&mail, sizeof(unsigned long long), hipHostMallocMapped) == hipSuccess && mail &&
+    if (hipHostMalloc(&mail, 256 + sizeof(Control), hipHostMallocMapped) == hipSuccess && mail &&
         hipHostGetDevicePointer(&mail_dev, mail, 0) == hipSuccess && mail_dev) {
       t->h_mail = (unsigned long long*)mail;
+      t->h_control = (Control*)((char*)mail + 256);
       *t->h_mail = 0;  // call tag 0, mark 0: an empty table
       v.hwm_mail = (unsigned long long*)mail_dev;
     } else {
@@ -453,9 +468,7 @@ int mono_expire_sweep(mono_table* t, uint32_t now, uint64_t* d_n_expired, int64_
 int mono_table_stats(mono_table* t, mono_stats* h_out, void* stream) {
   if (!t || !h_out) return MONO_EINVAL;
   Control c;
-  if (hipMemcpyAsync(&c, t->view.ctl, sizeof(Control), hipMemcpyDeviceToHost, (hipStream_t)stream) != hipSuccess ||
-      hipStreamSynchronize((hipStream_t)stream) != hipSuccess)
-    return MONO_EHIP;
+  if (read_control(t, &c, (hipStream_t)stream) != hipSuccess) return MONO_EHIP;
   // (if that was the table's own stream, everything queued for the table has run: the mark just read is exact)
   if (t->h_mail && !t->tags_wrapped && t->used_stream && (hipStream_t)stream == t->last_stream)
     *t->h_mail = ((unsigned long long)t->epoch << 32) | (unsigned long long)c.hwm;
@@ -477,10 +490,9 @@ int mono_table_export(mono_table* t, int64_t* d_keys, int32_t* d_row, uint32_t* 
   if ((d_values || d_acc) && !d_row) return MONO_EINVAL;  // values are gathered through the row indices
   hipStream_t s = (hipStream_t)stream;
   if (launch_export(t->view, d_keys, d_row, d_last_seen, d_slot, max_n, false, s) != hipSuccess) return MONO_EHIP;
-  unsigned long long n = 0;
-  if (hipMemcpyAsync(&n, &t->view.ctl->scratch[kExportCount], sizeof(n), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return MONO_EHIP;
+  Control c;
+  if (read_control(t, &c, s) != hipSuccess) return MONO_EHIP;
+  const unsigned long long n = c.scratch[kExportCount];
   *h_n = n;
   const uint64_t wrote = n < max_n ? n : max_n;
   if ((d_values || d_acc) && wrote) {
@@ -505,18 +517,14 @@ int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t
   if (launch_export(t->view, (int64_t*)ws.key[0], ws.row, d_last_seen ? ws.seen : nullptr, d_slot ? ws.slot : nullptr,
                     max_n, touched_only != 0, s) != hipSuccess)
     return MONO_EHIP;
-  unsigned long long n = 0, bits[2] = {0, 0};
-  if (hipMemcpyAsync(&n, &t->view.ctl->scratch[kExportCount], sizeof(n), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return MONO_EHIP;
+  Control c;
+  if (launch_export_bits(t->view, ws, max_n, s) != hipSuccess || read_control(t, &c, s) != hipSuccess) return MONO_EHIP;
+  const unsigned long long n = c.scratch[kExportCount];
   *h_n = n;
   if (n > max_n) return MONO_OK;  // the caller's buffers are too small: nothing is written, a window stays open
   if (n) {
-    if (launch_export_bits(ws, n, s) != hipSuccess ||
-        hipMemcpyAsync(bits, ws.bits, sizeof(bits), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return MONO_EHIP;
-    if (launch_export_sort(ws, n, bits[0] & ~bits[1], d_keys, d_row, d_last_seen, d_slot, s) != hipSuccess) return MONO_EHIP;
+    const uint64_t varying = c.scratch[kExportBits] & ~c.scratch[kExportBits + 1];
+    if (launch_export_sort(ws, n, varying, d_keys, d_row, d_last_seen, d_slot, s) != hipSuccess) return MONO_EHIP;
     if ((d_values || d_acc) && launch_export_values(t->view, d_row, n, d_values, d_acc, s) != hipSuccess) return MONO_EHIP;
   }
   if (touched_only) t->view.sync_epoch += 1;  // a new window, as mono_export_touched starts one
@@ -529,10 +537,9 @@ int mono_export_touched(mono_table* t, int64_t* d_keys, int32_t* d_row, float* d
   if ((d_values || d_acc) && !d_row) return MONO_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   if (launch_export(t->view, d_keys, d_row, nullptr, nullptr, max_n, true, s) != hipSuccess) return MONO_EHIP;
-  unsigned long long n = 0;
-  if (hipMemcpyAsync(&n, &t->view.ctl->scratch[kExportCount], sizeof(n), hipMemcpyDeviceToHost, s) != hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return MONO_EHIP;
+  Control c;
+  if (read_control(t, &c, s) != hipSuccess) return MONO_EHIP;
+  const unsigned long long n = c.scratch[kExportCount];
   *h_n = n;
   if (n > max_n) return MONO_OK;  // the caller's buffers are too small: the window stays open
   if ((d_values || d_acc) && n) {
