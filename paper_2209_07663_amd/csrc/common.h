@@ -190,6 +190,20 @@ __device__ inline void st_agent(T* p, T v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Accesses whose data should not displace others from the 256 MB cache behind the L2s: a pair that nobody
+// reads again, results far larger than that cache.
+__device__ inline uint2 load_once(const uint2* p) {
+  const unsigned long long x = __builtin_nontemporal_load(reinterpret_cast<const unsigned long long*>(p));
+  return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
+}
+__device__ inline void store_float4(float* p, float4 v, bool past_caches) {
+  typedef float Vec __attribute__((ext_vector_type(4)));
+  if (past_caches)  // the same for the whole launch
+    __builtin_nontemporal_store(Vec{v.x, v.y, v.z, v.w}, reinterpret_cast<Vec*>(p));
+  else
+    *reinterpret_cast<float4*>(p) = v;
+}
+
 __device__ inline unsigned lane_id() { return __lane_id(); }
 __device__ inline uint64_t lanes_below() { return (1ull << lane_id()) - 1ull; }
 
