@@ -12,7 +12,7 @@ struct UpdateWorkspace {
                         // (a restore call borrows the whole array for its per-record results)
   uint2* pair_a;        // [max_ids] (row, bag) pairs, ping
   uint2* pair_b;        // [max_ids] pong
-  uint32_t* hist;       // [sort_hist_words(max_ids)]: per-unit digit histograms (bin-major), then the bin totals
+  uint32_t* hist;       // [sort_hist_words(max_ids)]: digit histograms (per unit, per group), then the bin totals
   float* part;          // [2 * tiles * dim] partial gradient sums of runs that cross tile borders
   uint32_t* part_row;   // [2 * tiles] row (+ head flag) of each partial, kNoRow if unused
   uint64_t tiles;       // what part and part_row are for
@@ -65,10 +65,11 @@ inline uint32_t reduce_tile(uint64_t n, uint32_t gpb) {
 #define MONO_NOALLOC_MAX_IDS (1ull << 18)
 #endif
 
-inline uint64_t sort_units(uint64_t n, uint32_t items) { return (n + items - 1) / items; }
-inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // of a bin's counts: whole 16-byte pieces
-// words of the histogram workspace for batches of at most n elements, whatever the shape: one histogram per
-// unit, then the bin totals
+constexpr uint64_t sort_units(uint64_t n, uint32_t items) { return (n + items - 1) / items; }
+constexpr uint32_t kSortGroupedAbove = 1024, kSortGroupUnits = 4;  // units of more elements come in groups (see sort_hist_kernel)
+inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // units in whole groups, or in whole 16-byte pieces
+// words of the histogram workspace for batches of at most n elements, whatever the shape: a histogram per unit, one
+// per group, the bin totals
 inline uint64_t sort_hist_words(uint64_t n) {
   uint64_t most = 0;
   const uint64_t sizes[] = {n, n < kSortFewMost ? n : kSortFewMost, n < kSortItems512 ? n : kSortItems512,
@@ -76,7 +77,8 @@ inline uint64_t sort_hist_words(uint64_t n) {
   for (const uint64_t m : sizes)
     for (const uint32_t rows : {kSortFewMaxRows, kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
       const SortShape s = sort_shape_for(rows, m);
-      const uint64_t words = (1ull << s.max_bits) * (sort_stride(sort_units(m, s.items)) + 1);
+      const uint64_t stride = sort_stride(sort_units(m, s.items)), groups = s.items > kSortGroupedAbove ? stride / kSortGroupUnits : 0;
+      const uint64_t words = (stride + groups + 1) << s.max_bits;
       most = words > most ? words : most;
     }
   return most;

@@ -12,8 +12,8 @@
 // (kValidPairs slot of the control block's scratch).
 //
 // Unit of work: one block owns kItems consecutive elements, an equal share per wave.  Per pass:
-//   hist     per-unit digit histogram (LDS atomics), written bin-major: hist[bin * stride + unit]
-//   scan     one block per bin: exclusive scan along the units; bin totals to `totals`
+//   hist     per-unit digit histograms (LDS atomics)
+//   scan     exclusive scan of every bin along the units (or groups of four); bin totals to `totals`
 //   scatter  the block loads its elements into registers (all loads independent); every wave ranks its elements
 //            64 at a time by digit matching with ballots (stable: rank = the wave's earlier elements of the digit
 //            + lower lanes with it; what the ranking leaves behind are the wave's digit counts, which a loop
@@ -23,9 +23,6 @@
 //            straight from the registers sends one 8-byte write per element to the L2: measured, that
 //            request rate was what bounded the pass.)
 // No kernel spins or waits for another block.
-// Measured at 5.8 M pairs of 24-bit rows, per pass: hist 20-24 us (neither its LDS atomics nor its scattered words
-// bound it alone: ballots instead of atomics, or four units per block and 16-byte pieces, change it by a
-// microsecond), scan 5.4 (9.1 with single-word loads), scatter 33-35, the first one 51 with its walk of the bags.
 #include "common.h"
 #include "kernels.h"
 
@@ -90,23 +87,41 @@ __device__ inline uint32_t bag_holding(const int64_t* offsets, uint64_t n_bags, 
   return (uint32_t)lo;
 }
 
-// A block counts kUnits consecutive units.  Pass 0 has more blocks than that, in front: for the scatter kernel of
-// the same pass, their waves find the bag that holds a unit's first occurrence, a unit each (four dependent
-// memory round trips, beside the counting instead of after it).
+// Units whose histograms a block of sort_hist_kernel makes, and that block's threads.
+template <uint32_t kItems>
+constexpr uint32_t kSortGroup = kItems > kSortGroupedAbove ? kSortGroupUnits : 1;
+constexpr int kGroupBlock = 512;
+
+// Digit histograms of kUnits consecutive units.
+//   kUnits == 1  (small batches) bin-major, to hist[bin * stride + unit]
+//   kUnits > 1   (large ones) a unit's words are what the units before it in the group hold, to hist[unit * bins + bin];
+//                the group's, to sums[group * bins + bin].  Whole lines are written here and read by the scatter kernel,
+//                and the scan has kUnits times less to read
+// Pass 0 has more blocks than that, in front: for the scatter kernel of the same pass, their waves find the bag that
+// holds a unit's first occurrence, a unit each (four dependent memory round trips, beside the counting instead of
+// after it).
+// LDS atomics to one word cost two cycles each where spread ones take a fifth of a cycle, and a batch has hot rows
+// and slots of few IDs: every counter is kept four times, for a quarter of the lanes each.
+// Both together: 22.8 -> 12.5 us a pass at 6.8 M pairs in 8-bit digits (reading the pairs takes 10), 75 -> 43 at 26 M
+// in 9-bit ones, and 39.6 -> 36.8 and 153 -> 146 in the scatter kernel.  A unit per block instead of four takes 5 us
+// less here at 26 M but 11 more in the scan; small batches have too few units for groups.
 template <uint32_t kBits, int kBlock, uint32_t kItems, uint32_t kUnits>
 __global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __restrict__ ctl, uint32_t pass,
                                                                const int32_t* __restrict__ rows,
                                                                const uint2* __restrict__ src, uint64_t n,
                                                                uint64_t stride, uint32_t* __restrict__ hist,
+                                                               uint32_t* __restrict__ sums,
                                                                const int64_t* __restrict__ offsets, uint64_t n_bags,
                                                                uint32_t* __restrict__ unit_bag,
                                                                uint32_t search_blocks) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   if (pass >= plan.passes) return;
-  using S = Shape<kBits, kBlock, kItems>;
-  __shared__ uint32_t cnt[kUnits][S::kBins];
+  constexpr uint32_t kBins = 1u << kBits;
+  constexpr uint32_t kCopies = kBits == kSortFewBits ? 1 : 4;  // (512 elements in 2048 bins hardly meet)
+  __shared__ uint4 words[kUnits * kBins * kCopies / 4];
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(words);  // [unit][bin][copy]
   if (blockIdx.x < search_blocks) {
-    const uint64_t unit = (uint64_t)blockIdx.x * S::kWaves + (threadIdx.x >> 6);
+    const uint64_t unit = (uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
     if (unit * kItems < n) {  // wave-uniform
       const uint32_t b0 = bag_holding(offsets, n_bags, n, unit * kItems);
       if (lane_id() == 0) unit_bag[unit] = b0;
@@ -115,94 +130,114 @@ __global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __rest
   }
   const uint64_t block = blockIdx.x - search_blocks;
   const uint32_t shift = plan.shift(pass), nbins = 1u << plan.width(pass), mask = nbins - 1;
-  for (uint32_t b = threadIdx.x; b < S::kBins * kUnits; b += kBlock) cnt[0][b] = 0;
-  __syncthreads();
-  const uint64_t base = block * kUnits * kItems;
   if (pass > 0) n = ctl->scratch[kValidPairs];
   // every key of the thread is requested before the first one is counted (left to itself the compiler
   // keeps each load behind the LDS atomic before it: a memory round trip for each)
-  constexpr uint32_t kPerThread = kItems / kBlock;
-  uint32_t key[kPerThread * kUnits];
+  constexpr uint32_t kPerThread = kItems * kUnits / kBlock;
+  static_assert(kItems % kBlock == 0, "a round of the block is in one unit");
+  uint32_t key[kPerThread];
 #pragma unroll
-  for (uint32_t r = 0; r < kPerThread * kUnits; ++r) {
-    const uint64_t i = base + (uint64_t)r * kBlock + threadIdx.x;
+  for (uint32_t r = 0; r < kPerThread; ++r) {
+    const uint64_t i = block * kUnits * kItems + (uint64_t)r * kBlock + threadIdx.x;
     key[r] = plan.hwm;
     if (i < n) key[r] = pass == 0 ? first_key(rows, i, plan.hwm) : src[i].x;
   }
+  for (uint32_t b = threadIdx.x; b < kUnits * kBins * kCopies / 4; b += kBlock) words[b] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  const uint32_t copy = threadIdx.x % kCopies;
 #pragma unroll
-  for (uint32_t r = 0; r < kPerThread * kUnits; ++r)
-    if (key[r] < plan.hwm) atomicAdd(&cnt[r / kPerThread][(key[r] >> shift) & mask], 1u);
+  for (uint32_t r = 0; r < kPerThread; ++r) {
+    const uint32_t bin = r * kBlock / kItems * kBins + ((key[r] >> shift) & mask);
+    if (key[r] < plan.hwm) atomicAdd(&cnt[bin * kCopies + copy], 1u);
+  }
   __syncthreads();
   for (uint32_t b = threadIdx.x; b < nbins; b += kBlock) {
-    uint32_t* to = hist + (uint64_t)b * stride + block * kUnits;
-    if constexpr (kUnits == 4)
-      *reinterpret_cast<uint4*>(to) = make_uint4(cnt[0][b], cnt[1][b], cnt[2][b], cnt[3][b]);
-    else
-      *to = cnt[0][b];
+    uint32_t run = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kUnits; ++u) {
+      uint32_t count;
+      if constexpr (kCopies == 4) {
+        const uint4 c = words[u * kBins + b];
+        count = c.x + c.y + c.z + c.w;
+      } else {
+        count = cnt[u * kBins + b];
+      }
+      if constexpr (kUnits == 1)
+        hist[(uint64_t)b * stride + block] = count;
+      else
+        hist[(block * kUnits + u) * kBins + b] = run;
+      run += count;
+    }
+    if constexpr (kUnits > 1) sums[block * kBins + b] = run;
   }
 }
 
-// exclusive scan of hist[bin * stride + 0 .. units) in place; total of the bin to totals[bin].
-// One block per bin; thread t owns a run of consecutive units (loaded at once in 16-byte pieces, summed serially),
-// the thread sums are scanned across the block, and the run is written back.
-constexpr uint32_t kScanQuads = 4;  // pieces of four units per thread and round
+// Exclusive scan of sums[0 .. groups)[bin] in place; total of the bin to totals[bin].  A block owns four bins (16 bytes of
+// every group's words); a thread takes consecutive groups, all asked for at once, the threads' sums are scanned
+// across the block and the words written back.  Eight blocks share a line: they run on one XCD (blocks go
+// round the XCDs), whose L2 then reads and writes the line once.
+__device__ inline uint4 plus(uint4 a, uint4 b) { return make_uint4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+__device__ inline uint4 minus(uint4 a, uint4 b) { return make_uint4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w); }
+__device__ inline uint4 wave_scan(uint4 x) {  // inclusive
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint4 y = make_uint4(__shfl_up(x.x, d), __shfl_up(x.y, d), __shfl_up(x.z, d), __shfl_up(x.w, d));
+    if ((int)lane_id() >= d) x = plus(x, y);
+  }
+  return x;
+}
+constexpr int kScanBlock = 1024;
+constexpr uint32_t kScanPer = 8;  // groups per thread and round
 template <uint32_t kBits>
-__global__ __launch_bounds__(256) void sort_scan_kernel(const Control* __restrict__ ctl, uint32_t pass,
-                                                        uint32_t* __restrict__ hist, uint64_t units,
-                                                        uint64_t stride, uint32_t* __restrict__ totals) {
+__global__ __launch_bounds__(kScanBlock) void sort_scan_kernel(const Control* __restrict__ ctl, uint32_t pass,
+                                                               uint32_t* __restrict__ sums, uint64_t groups,
+                                                               uint32_t* __restrict__ totals) {
+  static_assert(kBits >= 8, "whole lines on every XCD");
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
-  if (pass >= plan.passes || blockIdx.x >= (1u << plan.width(pass))) return;
-  __shared__ uint32_t wave_sum[4];
-  uint4* row = reinterpret_cast<uint4*>(hist + (uint64_t)blockIdx.x * stride);
-  const uint64_t quads = stride / 4;
+  const uint32_t xcd = blockIdx.x % 8, turn = blockIdx.x / 8;                    // the 8 blocks of a line: turns 8 k to 8 k + 7
+  const uint32_t strip = (turn / 8 * 8 + xcd) * 8 + turn % 8;
+  if (pass >= plan.passes || strip * 4 >= (1u << plan.width(pass))) return;
+  constexpr uint32_t kWaves = kScanBlock / 64;
+  __shared__ uint4 wave_sum[kWaves];
   const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // (few units: as few pieces per thread as cover them, so that more threads load)
-  const uint32_t per = quads >= 256 * kScanQuads ? kScanQuads : (uint32_t)((quads + 255) / 256);
-  uint32_t carry = 0;
-  for (uint64_t t0 = 0; t0 < quads; t0 += 256ull * per) {
-    const uint64_t first = t0 + (uint64_t)threadIdx.x * per;
-    uint4 v[kScanQuads];
-    uint32_t sum = 0;
+  uint4* at = reinterpret_cast<uint4*>(sums) + strip;
+  constexpr uint64_t kPitch = (1u << kBits) / 4;
+  // (few groups: as few per thread as cover them)
+  const uint32_t per = groups >= kScanBlock * kScanPer ? kScanPer : (uint32_t)((groups + kScanBlock - 1) / kScanBlock);
+  uint4 carry = make_uint4(0u, 0u, 0u, 0u);
+  for (uint64_t u0 = 0; u0 < groups; u0 += (uint64_t)kScanBlock * per) {
+    const uint64_t first = u0 + (uint64_t)threadIdx.x * per;
+    uint4 v[kScanPer], sum = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (uint32_t j = 0; j < kScanQuads; ++j) {
-      v[j] = j < per && first + j < quads ? row[first + j] : make_uint4(0u, 0u, 0u, 0u);
-      if ((first + j) * 4 + 4 > units) {  // the words after the last unit hold nothing
-        const uint64_t left = (first + j) * 4 < units ? units - (first + j) * 4 : 0;
-        if (left < 1) v[j].x = 0;
-        if (left < 2) v[j].y = 0;
-        if (left < 3) v[j].z = 0;
-        v[j].w = 0;
-      }
-      sum += v[j].x + v[j].y + v[j].z + v[j].w;
+    for (uint32_t j = 0; j < kScanPer; ++j) {
+      v[j] = make_uint4(0u, 0u, 0u, 0u);
+      if (j < per && first + j < groups) v[j] = at[(first + j) * kPitch];
     }
-    uint32_t x = sum;  // inclusive wave scan of the thread sums
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d);
-      if ((int)lane >= d) x += y;
-    }
+    for (uint32_t j = 0; j < kScanPer; ++j) sum = plus(sum, v[j]);
+    const uint4 x = wave_scan(sum);
     if (lane == 63) wave_sum[wave] = x;
     __syncthreads();
-    uint32_t run = carry + x - sum;
+    uint4 run = plus(carry, minus(x, sum));
 #pragma unroll
-    for (uint32_t w = 0; w < 4; ++w) {
-      if (w < wave) run += wave_sum[w];
-      carry += wave_sum[w];
+    for (uint32_t w = 0; w < kWaves; ++w) {
+      const uint4 s = wave_sum[w];
+      if (w < wave) run = plus(run, s);
+      carry = plus(carry, s);
     }
 #pragma unroll
-    for (uint32_t j = 0; j < kScanQuads; ++j) {
-      const uint4 c = v[j];
-      const uint4 o = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
-      if (j < per && first + j < quads) row[first + j] = o;
-      run = o.w + c.w;
+    for (uint32_t j = 0; j < kScanPer; ++j) {
+      if (j < per && first + j < groups) at[(first + j) * kPitch] = run;
+      run = plus(run, v[j]);
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) totals[blockIdx.x] = carry;
+  if (threadIdx.x == 0) reinterpret_cast<uint4*>(totals)[strip] = carry;
 }
 
-// The same with one wave per bin, for at most 64 * kScanFew units.
-constexpr uint32_t kScanFew = 8;  // units per lane
+// Exclusive scan of hist[bin * stride + 0 .. units) in place; total of the bin to totals[bin].  One wave per bin, for at
+// most 64 * 4 * kScanFew units.
+constexpr uint32_t kScanFew = 4;  // pieces of four units per lane
 template <uint32_t kBits>
 __global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __restrict__ ctl, uint32_t pass,
                                                             uint32_t* __restrict__ hist, uint32_t units, uint64_t stride,
@@ -210,13 +245,23 @@ __global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __res
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   const uint32_t bin = blockIdx.x * 4 + (threadIdx.x >> 6), lane = lane_id();
   if (pass >= plan.passes || bin >= (1u << plan.width(pass))) return;  // wave-uniform (no barriers below)
-  uint32_t* row = hist + (uint64_t)bin * stride;
-  const uint32_t per = (units + 63) / 64, first = lane * per;
-  uint32_t v[kScanFew], sum = 0;
+  uint4* row = reinterpret_cast<uint4*>(hist + (uint64_t)bin * stride);
+  const uint32_t quads = (uint32_t)stride / 4, per = (quads + 63) / 64, first = lane * per;
+  uint4 v[kScanFew];
 #pragma unroll
   for (uint32_t j = 0; j < kScanFew; ++j) {
-    v[j] = j < per && first + j < units ? row[first + j] : 0;
-    sum += v[j];
+    v[j] = make_uint4(0u, 0u, 0u, 0u);
+    if (j < per && first + j < quads) v[j] = row[first + j];
+  }
+  uint32_t sum = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < kScanFew; ++j) {
+    const uint32_t u = (first + j) * 4;  // the words after the last unit hold nothing
+    if (u >= units) v[j].x = 0;
+    if (u + 1 >= units) v[j].y = 0;
+    if (u + 2 >= units) v[j].z = 0;
+    if (u + 3 >= units) v[j].w = 0;
+    sum += v[j].x + v[j].y + v[j].z + v[j].w;
   }
   uint32_t x = sum;  // inclusive wave scan of the lane sums
 #pragma unroll
@@ -227,8 +272,9 @@ __global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __res
   uint32_t run = x - sum;
 #pragma unroll
   for (uint32_t j = 0; j < kScanFew; ++j) {
-    if (j < per && first + j < units) row[first + j] = run;
-    run += v[j];
+    const uint4 c = v[j], o = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
+    if (j < per && first + j < quads) row[first + j] = o;
+    run = o.w + c.w;
   }
   if (lane == 63) totals[bin] = x;
 }
@@ -242,6 +288,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
                                                                   const uint2* __restrict__ src,
                                                                   uint64_t n, uint64_t stride,
                                                                   const uint32_t* __restrict__ hist,
+                                                                  const uint32_t* __restrict__ sums,
                                                                   const uint32_t* __restrict__ totals,
                                                                   uint2* __restrict__ dst) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
@@ -267,7 +314,9 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
     tot[q] = before_me[q] = 0;
     if (bin_thread && bin0 + q < nbins) {
       tot[q] = totals[bin0 + q];
-      before_me[q] = hist[(uint64_t)(bin0 + q) * stride + unit];
+      before_me[q] = kSortGroup<kItems> == 1 ? hist[(uint64_t)(bin0 + q) * stride + unit]
+                                             : hist[unit * S::kBins + bin0 + q] +
+                                                   sums[unit / kSortGroup<kItems> * S::kBins + bin0 + q];
     }
   }
   // 1. this wave's elements -> registers (independent, coalesced loads)
@@ -499,32 +548,33 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
   if (tid == 0) ctl->scratch[kValidPairs] = count;
 }
 
+static_assert(sort_units(kSortItems512, 512) <= 256 * kScanFew && sort_units(kSortItems1024, 1024) <= 256 * kScanFew,
+              "one wave scans the units of a batch without groups");
 template <uint32_t kBits, int kBlock, uint32_t kItems>
 static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                               const int64_t* d_offsets, uint64_t n_bags, uint32_t passes, hipStream_t stream,
                               Profiler* prof) {
-  const uint64_t units = sort_units(n, kItems), stride = sort_stride(units);
-  uint32_t* totals = ws.hist + (uint64_t)(1u << kBits) * stride;
+  constexpr uint32_t kUnits = kSortGroup<kItems>;
+  constexpr int kHistBlock = kUnits > 1 ? kGroupBlock : kBlock;
+  const uint64_t units = sort_units(n, kItems), groups = (units + kUnits - 1) / kUnits, stride = sort_stride(units);
+  uint32_t* sums = ws.hist + (stride << kBits);
+  uint32_t* totals = kUnits > 1 ? sums + (groups << kBits) : sums;
   const dim3 block(kBlock), grid((unsigned)units);
   for (uint32_t p = 0; p < passes; ++p) {
     const uint2* src = p % 2 == 0 ? ws.pair_a : ws.pair_b;
     uint2* dst = p % 2 == 0 ? ws.pair_b : ws.pair_a;
-    const uint32_t search = p == 0 ? (uint32_t)((units + kBlock / 64 - 1) / (kBlock / 64)) : 0u;
-    if (kItems == 2048 && units >= 1024)
-      MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems, 4>),
-                  dim3((unsigned)(stride / 4) + search), block, t.ctl, p, d_rows, src, n, stride, ws.hist, d_offsets, n_bags,
-                  ws.unit_bag, search);
+    const uint32_t search = p == 0 ? (uint32_t)((units + kHistBlock / 64 - 1) / (kHistBlock / 64)) : 0u;
+    MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kHistBlock, kItems, kUnits>),
+                dim3((unsigned)groups + search), dim3(kHistBlock), t.ctl, p, d_rows, src, n, stride, ws.hist, sums, d_offsets,
+                n_bags, ws.unit_bag, search);
+    if constexpr (kUnits > 1)
+      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3((1u << kBits) / 4), dim3(kScanBlock), t.ctl, p,
+                  sums, groups, totals);
     else
-      MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kBlock, kItems, 1>), dim3((unsigned)units + search),
-                  block, t.ctl, p, d_rows, src, n, stride, ws.hist, d_offsets, n_bags, ws.unit_bag, search);
-    if (units <= 64 * kScanFew)
-      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_few_kernel<kBits>, dim3((1u << kBits) / 4), dim3(256), t.ctl, p, ws.hist,
-                  (uint32_t)units, stride, totals);
-    else
-      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3(1u << kBits), dim3(256), t.ctl, p, ws.hist, units,
-                  stride, totals);
+      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_few_kernel<kBits>, dim3((1u << kBits) / 4), dim3(256), t.ctl, p,
+                  ws.hist, (uint32_t)units, stride, totals);
     MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems>), grid, block, t.ctl, p, d_rows,
-                d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, totals, dst);
+                d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, sums, totals, dst);
   }
 }
 

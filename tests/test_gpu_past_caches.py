@@ -29,7 +29,9 @@ def test_large_gathers_and_updates(dim, n, bf16):
     total = torch.zeros(known, dim, dtype=torch.float64, device=dev)
     for lo in range(0, n, 1 << 18):                             # (in parts: a batch of fp64 gradients is large)
         at = torch.arange(lo, min(lo + (1 << 18), n), device=dev)
-        total.index_add_(0, keys[at], grad[at // 3].double())
+        hot = keys[at] == 7                                     # (summed apart: index_add_ is slow where one row repeats)
+        total.index_add_(0, keys[at[~hot]], grad[at[~hot] // 3].double())
+        total[7] += grad[at[hot] // 3].double().sum(dim=0)
     acc = total.pow(2).mean(dim=1, keepdim=True)
     ref = before.double() - 0.05 * total / (acc.sqrt() + 1e-6)
     tol = 2.0 ** -8 * ref.abs() + 1e-5 if bf16 else 2e-5 * (ref.abs() + 0.05)
