@@ -44,6 +44,8 @@ constexpr int kSmallMisses = 4;             // Control::scratch slots of the one
 constexpr int kSmallDone = 5;               // missing occurrences so far, blocks that have finished their probes
 constexpr int kMissTag = 7;                 // Control::scratch slots: tag of the latest call in which an occurrence missed,
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
+constexpr int kKeptOut = 11;                // Control::scratch slots: occurrences of keys kept out by their counters, in the
+constexpr int kCountersFirst = 12;          // running call's sample; is the next call to look at counters first?
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
 
 struct StashEntry {
@@ -115,7 +117,7 @@ struct TableView {
   uint32_t bf16;
   uint32_t filter_hashes;    // counters per key (1..4); the key's count is their minimum
   uint32_t sync_epoch;       // current synchronisation window (>= 1); rows with touch == sync_epoch are "touched"
-  unsigned long long* hwm_mail;  // pinned HOST word (or null): every lookup_or_insert leaves (its call tag << 32 | hwm)
+  unsigned long long* hwm_mail;  // pinned HOST word (or null): lookup_or_insert leaves (its call tag << 32 | hwm)
                                  // there, so that the host can bound the sort's key width without waiting
 };
 

@@ -20,6 +20,7 @@
 
 namespace mono {
 
+constexpr uint32_t kSmallPostEvery = 16;  // (far fewer than the calls that the host keeps on record)
 constexpr int kSmallThreads = 1024, kSmallKeysPerBlock = 256;
 constexpr uint32_t kSmallSet = 2 * kSmallKeysPerBlock;  // slots of a block's set of missing keys
 static_assert(kSmallThreads == 4 * kSmallKeysPerBlock, "two keys per group of eight lanes");
@@ -151,7 +152,9 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
   __syncthreads();
   const uint32_t missed = s_count;
   if (missed == 0) {
-    if (tid == 0 && t.hwm_mail) post_hwm(t, epoch);
+    // (the mark has not moved; the host only wants to hear of a call now and then, and the store over the bus holds
+    // the kernel's end: 7.5 -> 6.9 us for 1700 known keys)
+    if (tid == 0 && t.hwm_mail && epoch % kSmallPostEvery == 0) post_hwm(t, epoch);
     return;
   }
   uint32_t slots = 64;
