@@ -87,52 +87,21 @@ __device__ inline uint32_t bag_holding(const int64_t* offsets, uint64_t n_bags, 
   return (uint32_t)lo;
 }
 
-// The bag of every occurrence (the pooled gradient of bag b is the gradient of each of its occurrences), for bags
-// [b0, b0 + count), by a block: their offsets go to LDS, neighbouring threads take neighbouring occurrences, and a
-// thread looks its bag up only when it has left the one before.  `off` holds count + 1 words.  Whatever the offsets hold,
-// every write is to an occurrence of the batch and the loop ends.
-template <int kBlock>
-__device__ inline void write_bags(const int64_t* offsets, uint64_t n, uint64_t b0, uint32_t count, uint32_t* off,
-                                  uint32_t* bag_of) {
-  for (uint32_t k = threadIdx.x; k <= count; k += kBlock) off[k] = (uint32_t)bounded_offset(offsets, b0 + k, n);
-  __syncthreads();
-  const uint32_t last = off[count];
-  uint32_t bag = 0, end = 0;
-  for (uint64_t p = off[0] + threadIdx.x; p < last; p += kBlock) {
-    if (p >= end) {
-      uint32_t lo = 0, hi = count;  // the last bag that starts at or before p (empty ones in front of it do not)
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) / 2;
-        if (off[mid] <= p)
-          lo = mid;
-        else
-          hi = mid;
-      }
-      bag = (uint32_t)b0 + lo;
-      end = off[lo + 1];
-    }
-    bag_of[p] = bag;
-  }
-}
-
 // Units whose histograms a block of sort_hist_kernel makes, and that block's threads.
 template <uint32_t kItems>
 constexpr uint32_t kSortGroup = kItems > kSortGroupedAbove ? kSortGroupUnits : 1;
 constexpr int kGroupBlock = 512;
-constexpr uint32_t kSortBagsPerThread = 2;  // most bags of a block that writes the occurrences' bags, per thread
+template <uint32_t kItems>
+constexpr uint32_t kSortChunk = kItems > kSortGroupedAbove ? 16 : 1;  // see sort_scatter_kernel
 
 // Digit histograms of kUnits consecutive units.
 //   kUnits == 1  (small batches) bin-major, to hist[bin * stride + unit]
 //   kUnits > 1   (large ones) a unit's words are what the units before it in the group hold, to hist[unit * bins + bin];
 //                the group's, to sums[group * bins + bin].  Whole lines are written here and read by the scatter kernel,
 //                and the scan has kUnits times less to read
-// Pass 0 has more blocks than that, in front, for the scatter kernel of the same pass, to `bags`:
-//   kUnits == 1  the bag of every occurrence, bags_per_block bags a block
-//   kUnits > 1   the bag that holds a unit's first occurrence, found by a wave for each unit (four dependent memory
-//                round trips, beside the counting instead of after it): writing and reading a word for every occurrence
-//                costs a large batch more (26 M IDs: 94 us here and 26 less there) than walking the bags in the
-//                scatter kernel, a small one less (its walk is a chain of round trips: history of 500 K IDs 14.8 ->
-//                8.2 us there, 1 us more here)
+// Pass 0 has more blocks than that, in front: for the scatter kernel of the same pass, their waves find the bag that
+// holds a unit's first occurrence, a unit each (four dependent memory round trips, beside the counting instead of
+// after it).
 // LDS atomics to one word cost two cycles each where spread ones take a fifth of a cycle, and a batch has hot rows
 // and slots of few IDs: every counter is kept four times, for a quarter of the lanes each.
 // Both together: 22.8 -> 12.5 us a pass at 6.8 M pairs in 8-bit digits (reading the pairs takes 10), 75 -> 43 at 26 M
@@ -145,30 +114,23 @@ __global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __rest
                                                                uint64_t stride, uint32_t* __restrict__ hist,
                                                                uint32_t* __restrict__ sums,
                                                                const int64_t* __restrict__ offsets, uint64_t n_bags,
-                                                               uint32_t* __restrict__ bags, uint32_t bag_blocks,
-                                                               uint32_t bags_per_block) {
+                                                               uint32_t* __restrict__ unit_bag,
+                                                               uint32_t search_blocks) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   if (pass >= plan.passes) return;
   constexpr uint32_t kBins = 1u << kBits;
   constexpr uint32_t kCopies = kBits == kSortFewBits ? 1 : 4;  // (512 elements in 2048 bins hardly meet)
   __shared__ uint4 words[kUnits * kBins * kCopies / 4];
   uint32_t* cnt = reinterpret_cast<uint32_t*>(words);  // [unit][bin][copy]
-  if (blockIdx.x < bag_blocks) {
-    if constexpr (kUnits == 1) {
-      __shared__ uint32_t off[kSortBagsPerThread * kBlock + 1];
-      const uint64_t b0 = (uint64_t)blockIdx.x * bags_per_block;
-      const uint32_t count = (uint32_t)(n_bags - b0 < bags_per_block ? n_bags - b0 : bags_per_block);
-      write_bags<kBlock>(offsets, n, b0, count, off, bags);
-    } else {
-      const uint64_t unit = (uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-      if (unit * kItems < n) {  // wave-uniform
-        const uint32_t b = bag_holding(offsets, n_bags, n, unit * kItems);
-        if (lane_id() == 0) bags[unit] = b;
-      }
+  if (blockIdx.x < search_blocks) {
+    const uint64_t unit = (uint64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (unit * kItems < n) {  // wave-uniform
+      const uint32_t b = bag_holding(offsets, n_bags, n, unit * kItems);
+      if (lane_id() == 0) unit_bag[unit] = b;
     }
     return;
   }
-  const uint64_t block = blockIdx.x - bag_blocks;
+  const uint64_t block = blockIdx.x - search_blocks;
   const uint32_t shift = plan.shift(pass), nbins = 1u << plan.width(pass), mask = nbins - 1;
   if (pass > 0) n = ctl->scratch[kValidPairs];
   // every key of the thread is requested before the first one is counted (left to itself the compiler
@@ -320,12 +282,12 @@ __global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __res
 }
 
 // kFirst: pass 0 (in a kernel of its own: the code that finds the bags, though skipped, held the loads of the other
-// passes together: 26 M pairs 133 -> 113 and 107 -> 92 us)
+// passes together: 26 M pairs 133 -> 113 and 107 -> 92 us a pass)
 template <uint32_t kBits, int kBlock, uint32_t kItems, bool kFirst>
 __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restrict__ ctl, uint32_t pass,
                                                                   const int32_t* __restrict__ rows,
                                                                   const int64_t* __restrict__ offsets,
-                                                                  uint64_t n_bags, const uint32_t* __restrict__ bags,
+                                                                  uint64_t n_bags, const uint32_t* __restrict__ unit_bag,
                                                                   const uint2* __restrict__ src,
                                                                   uint64_t n, uint64_t stride,
                                                                   const uint32_t* __restrict__ hist,
@@ -343,8 +305,16 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   __shared__ uint32_t local_start[S::kBins];       // first position of a bin in `stage`
   __shared__ uint32_t global_start[S::kBins];      // where this block's part of a bin goes in dst
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  constexpr bool kWalk = kFirst && kSortGroup<kItems> > 1;
-  const uint64_t unit = blockIdx.x;
+  uint32_t* bag_here = reinterpret_cast<uint32_t*>(stage);  // (pass 0, until step 4)
+  // Which unit: blocks go round the eight XCDs, and the elements that neighbouring units have of a bin share lines, so
+  // that an XCD takes kSortChunk neighbouring units of a large batch and its L2 writes whole lines (26 M pairs: 187 -> 161,
+  // 114 -> 103 and 92 -> 91 us; chunks of 4, 64 or an eighth of the batch are a few us behind; small batches have
+  // too few units).
+  const uint32_t turn = blockIdx.x / 8;
+  const uint64_t unit = kSortChunk<kItems> == 1 ? blockIdx.x
+                                                : ((uint64_t)(turn / kSortChunk<kItems>) * 8 + blockIdx.x % 8) * kSortChunk<kItems> +
+                                                      turn % kSortChunk<kItems>;
+  if (unit * kItems >= n) return;  // (the grid is a whole number of chunks)
   const uint32_t last_bag = (uint32_t)(n_bags - 1);
   const uint32_t shift = plan.shift(pass), bits = plan.width(pass), nbins = 1u << bits, mask = nbins - 1;
 
@@ -372,26 +342,30 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
     const uint64_t i = base + (uint64_t)r * 64 + lane;
     kv[r] = make_uint2(0xFFFFFFFFu, 0u);
     if (i < n) {
-      if constexpr (kFirst)  // (an occurrence outside every bag has whatever the array held)
-        kv[r] = make_uint2(first_key(rows, i, plan.hwm), kWalk ? 0u : min(bags[i], last_bag));
+      if constexpr (kFirst)
+        kv[r] = make_uint2(first_key(rows, i, plan.hwm), 0u);
       else
         kv[r] = kLoadOnce ? load_once(src + i) : src[i];
     }
     if (kv[r].x >= plan.hwm) kv[r].x = 0xFFFFFFFFu;  // dropped occurrence (or past the end): left out
   }
-  // the unit's bags are walked from the one that holds its first occurrence, each thread kBagsPerThread consecutive
-  // ones a round (a unit of 2048 holds ~500 bags of four IDs); the first round's offsets arrive during step 2
-  constexpr uint32_t kBagsPerThread = 4;
+  // (pass 0) the unit's bags from the one that holds its first occurrence on, neighbouring threads
+  // neighbouring bags; the first of them start to arrive during step 2
+  constexpr uint32_t kBagsAhead = 2;
   const uint64_t uend = ubase + kItems < n ? ubase + kItems : n;
   uint64_t bag = 0;
-  uint32_t o[kBagsPerThread + 1];
+  uint32_t start[kBagsAhead];
   const auto ask = [&]() {
 #pragma unroll
-    for (uint32_t q = 0; q <= kBagsPerThread; ++q) o[q] = (uint32_t)(bag + q <= n_bags ? bounded_offset(offsets, bag + q, n) : uend);
+    for (uint32_t q = 0; q < kBagsAhead; ++q) {
+      const uint64_t b = bag + q * kBlock;
+      start[q] = (uint32_t)(b < n_bags ? bounded_offset(offsets, b, n) : uend);
+    }
   };
-  if constexpr (kWalk) {
-    bag = (uint64_t)bags[unit] + (uint64_t)threadIdx.x * kBagsPerThread;
+  if constexpr (kFirst) {
+    bag = (uint64_t)unit_bag[unit] + threadIdx.x;
     ask();
+    for (uint32_t p = threadIdx.x; p < kItems; p += kBlock) bag_here[p] = 0;
   }
   for (uint32_t b = threadIdx.x; b < S::kBins; b += kBlock) {
 #pragma unroll
@@ -461,30 +435,47 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
           run += c;
         }
       }
-      if (kFirst && blockIdx.x == 0 && threadIdx.x == S::kBinThreads - 1)
+      if (kFirst && unit == 0 && threadIdx.x == S::kBinThreads - 1)
         ctl->scratch[kValidPairs] = run_tot;  // pairs that remain
     }
   }
-  if constexpr (kWalk) {
+  if constexpr (kFirst) {
     // The bag of every occurrence of the unit (the pooled gradient of bag b is the gradient of each of its
-    // occurrences): a bag writes its number over its occurrences in an LDS array (the memory of `stage`, which is
-    // not needed yet).  Whatever the offsets hold, every write stays inside the unit and every bag number that is
-    // read is bounded to the bags of the batch.
-    // A thread stops at the first of its bags that starts at or after the end of the unit: offsets are
-    // non-decreasing, so no later bag of its can reach into the unit (no barrier inside the loop)
-    uint32_t* bag_here = reinterpret_cast<uint32_t*>(stage);
-    while (bag < n_bags && o[0] < uend) {
+    // occurrences): every bag leaves its number at its first occurrence (of bags that start at one place the last is
+    // the one that is not empty), and an occurrence takes the number left at or before it.  Offsets are
+    // non-decreasing: a thread stops at its first bag that starts at or after the end of the unit.  Whatever they
+    // hold, every write stays inside the unit and every bag number that is used is bounded to the bags of the batch.
+    __shared__ uint32_t wave_last[S::kWaves];
+    for (bool more = true; more;) {
 #pragma unroll
-      for (uint32_t q = 0; q < kBagsPerThread; ++q) {
-        const uint64_t from = o[q] > ubase ? o[q] : ubase, to = o[q + 1] < uend ? o[q + 1] : uend;
-        for (uint64_t i = from; i < to; ++i) bag_here[i - ubase] = (uint32_t)(bag + q);
+      for (uint32_t q = 0; q < kBagsAhead; ++q) {
+        const uint64_t b = bag + q * kBlock;
+        const uint64_t at = start[q] > ubase ? start[q] - ubase : 0;
+        more = b < n_bags && start[q] < uend;
+        if (more) atomicMax(&bag_here[at], (uint32_t)b + 1u);
       }
-      bag += (uint64_t)kBlock * kBagsPerThread;
-      if (bag < n_bags) ask();
+      bag += (uint64_t)kBlock * kBagsAhead;
+      if (more) ask();
     }
     __syncthreads();
+    uint32_t carry = 0;  // the last number left in the wave's earlier elements
 #pragma unroll
-    for (uint32_t r = 0; r < S::kRounds; ++r) kv[r].y = min(bag_here[wave * S::kPerWave + r * 64 + lane], last_bag);
+    for (uint32_t r = 0; r < S::kRounds; ++r) {
+      const uint32_t mark = bag_here[wave * S::kPerWave + r * 64 + lane];
+      const uint64_t upto = __ballot(mark != 0) & (lanes_below() | (1ull << lane));
+      const uint32_t v = __shfl(mark, upto ? 63 - (int)__clzll((long long)upto) : 0);
+      kv[r].y = upto ? v : carry;
+      carry = __shfl(kv[r].y, 63);
+    }
+    if (lane == 0) wave_last[wave] = carry;
+    __syncthreads();
+    uint32_t before = 0;
+    for (uint32_t w = 0; w < wave; ++w) before = wave_last[w] ? wave_last[w] : before;
+#pragma unroll
+    for (uint32_t r = 0; r < S::kRounds; ++r) {
+      const uint32_t b = kv[r].y ? kv[r].y : before;
+      kv[r].y = min(b ? b - 1u : 0u, last_bag);
+    }
   }
   __syncthreads();
   // 4. into `stage`, in sorted order
@@ -614,19 +605,15 @@ static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, con
   const uint64_t units = sort_units(n, kItems), groups = (units + kUnits - 1) / kUnits, stride = sort_stride(units);
   uint32_t* sums = ws.hist + (stride << kBits);
   uint32_t* totals = kUnits > 1 ? sums + (groups << kBits) : sums;
-  // blocks in front of pass 0's histograms: small batches, about a unit's worth of bags each; large ones,
-  // a wave per unit
-  const uint64_t fit = (uint64_t)kItems * n_bags / n, most = kSortBagsPerThread * kHistBlock;
-  const uint32_t bags_per_block = (uint32_t)(fit < 1 ? 1 : fit > most ? most : fit);
-  const uint32_t bag_blocks = (uint32_t)(kUnits == 1 ? (n_bags + bags_per_block - 1) / bags_per_block
-                                                     : (units + kHistBlock / 64 - 1) / (kHistBlock / 64));
-  const dim3 block(kBlock), grid((unsigned)units);
+  const uint64_t chunks = 8 * kSortChunk<kItems>;  // whole chunks on every XCD
+  const dim3 block(kBlock), grid((unsigned)(chunks == 8 ? units : (units + chunks - 1) / chunks * chunks));
   for (uint32_t p = 0; p < passes; ++p) {
     const uint2* src = p % 2 == 0 ? ws.pair_a : ws.pair_b;
     uint2* dst = p % 2 == 0 ? ws.pair_b : ws.pair_a;
+    const uint32_t search = p == 0 ? (uint32_t)((units + kHistBlock / 64 - 1) / (kHistBlock / 64)) : 0u;
     MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kHistBlock, kItems, kUnits>),
-                dim3((unsigned)groups + (p == 0 ? bag_blocks : 0u)), dim3(kHistBlock), t.ctl, p, d_rows, src, n, stride, ws.hist,
-                sums, d_offsets, n_bags, ws.bags, p == 0 ? bag_blocks : 0u, bags_per_block);
+                dim3((unsigned)groups + search), dim3(kHistBlock), t.ctl, p, d_rows, src, n, stride, ws.hist, sums, d_offsets,
+                n_bags, ws.unit_bag, search);
     if constexpr (kUnits > 1)
       MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3((1u << kBits) / 4), dim3(kScanBlock), t.ctl, p,
                   sums, groups, totals);
@@ -635,10 +622,10 @@ static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, con
                   ws.hist, (uint32_t)units, stride, totals);
     if (p == 0)
       MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems, true>), grid, block, t.ctl, p,
-                  d_rows, d_offsets, n_bags, ws.bags, src, n, stride, ws.hist, sums, totals, dst);
+                  d_rows, d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, sums, totals, dst);
     else
       MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems, false>), grid, block, t.ctl, p,
-                  d_rows, d_offsets, n_bags, ws.bags, src, n, stride, ws.hist, sums, totals, dst);
+                  d_rows, d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, sums, totals, dst);
   }
 }
 

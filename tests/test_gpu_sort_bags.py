@@ -1,5 +1,5 @@
-"""The bag of every occurrence, as the sort of small batches writes it: one bag, few long bags, one occurrence per bag,
-and bags of one occurrence among many empty ones, in batches that end within a block's bags; exact sums of integers."""
+"""The bag of every occurrence, which the first pass of the sort finds: one bag, few long bags, one occurrence per bag,
+and bags of one occurrence among many empty ones, in batches whose last unit is cut; exact sums of integers."""
 import pytest
 import torch
 
@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bags", ["one", "three", "each", "sparse"])
-@pytest.mark.parametrize("n", [8193, 70001, (1 << 20) - 1])
+@pytest.mark.parametrize("n", [8193, 70001, (1 << 20) - 1, (1 << 20) + 5000])
 def test_each_occurrence_takes_its_bags_gradient(n, bags):
     from paper_2209_07663_amd.binding import Table
     dev, dim = torch.device("cuda:0"), 4
