@@ -94,6 +94,15 @@ struct RowVec {
       v[q].w += o.v[q].w;
     }
   }
+  __device__ inline void add_xor(uint32_t lanes) {  // the share of the lane whose number differs by `lanes` (xor)
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) {
+      v[q].x += __shfl_xor(v[q].x, (int)lanes);
+      v[q].y += __shfl_xor(v[q].y, (int)lanes);
+      v[q].z += __shfl_xor(v[q].z, (int)lanes);
+      v[q].w += __shfl_xor(v[q].w, (int)lanes);
+    }
+  }
   __device__ inline float sum_sq() const {
     float ss = 0.f;
 #pragma unroll
@@ -331,11 +340,18 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
 }
 
 // One block per tile; only the block whose tile holds the head of a border-crossing run works.
-template <typename E, int SEG>
-__global__ __launch_bounds__(256) void combine_kernel(TableView t, uint64_t n_tiles, const float* __restrict__ part,
-                                                      const uint32_t* __restrict__ part_row, float lr, float eps,
-                                                      uint32_t group_log2) {
-  extern __shared__ float4 s_mem[];  // [groups_per_block][dim / 4]
+// The hottest row's chain of pieces bounds it in small batches, the blocks' own latency in large ones.  All rounds of
+// pieces are asked for eight at a time, the last one too, and the groups of a wave are summed by shuffles: 6.8 M pairs
+// 11.1 -> 7.7 us, 690 K 9.6 -> 7.8.  Rows that take a whole wave have blocks of 512 threads (98 K pairs of dim 512: 18.6
+// us with 256, 12.7 with 512, 14.2 with 1024); others 256 (6.8 M pairs: 10.2 with 512, 18.4 with 1024).
+// (A lane group per tile, and a whole block only for runs over more than seven tiles, took 25-43 us there: small
+// tiles have many such runs, one after the other in a block.)
+constexpr int kCombineWide = 512;
+template <typename E, int SEG, int kBlock>
+__global__ __launch_bounds__(kBlock) void combine_kernel(TableView t, uint64_t n_tiles, const float* __restrict__ part,
+                                                         const uint32_t* __restrict__ part_row, float lr, float eps,
+                                                         uint32_t group_log2) {
+  extern __shared__ float4 s_mem[];  // [waves of the block][dim / 4]
   using Vec = RowVec<SEG>;
   const uint64_t c = blockIdx.x;
   const uint32_t head = part_row[2 * c + 1];
@@ -363,7 +379,7 @@ __global__ __launch_bounds__(256) void combine_kernel(TableView t, uint64_t n_ti
   const uint64_t tail = c + 1 + mid;
   const bool has_tail = tail < n_tiles && part_row[2 * tail] == row;
   const uint64_t pieces = 1 + mid + (has_tail ? 1 : 0);
-  const uint32_t group = 1u << group_log2, gpb = 256u >> group_log2;
+  const uint32_t group = 1u << group_log2, gpb = (uint32_t)kBlock >> group_log2;
   const uint32_t g = threadIdx.x >> group_log2, l = threadIdx.x & (group - 1u);
   const uint32_t dim4 = t.dim >> 2;
   const bool active = l < dim4;
@@ -373,21 +389,25 @@ __global__ __launch_bounds__(256) void combine_kernel(TableView t, uint64_t n_ti
   const auto slot_of = [&](uint64_t p) { return p <= mid ? 2 * (c + p) + 1 : 2 * tail; };
   // (a hot row leaves a piece per tile: eight of them in flight)
   constexpr int kPieces = 8 / SEG;
-  uint64_t p = g;
-  for (; p + (uint64_t)gpb * (kPieces - 1) < pieces; p += (uint64_t)gpb * kPieces) {
+  for (uint64_t p0 = g; p0 < pieces; p0 += (uint64_t)gpb * kPieces) {
     Vec v[kPieces];
 #pragma unroll
-    for (int u = 0; u < kPieces; ++u) v[u] = load_vec<SEG>(part4 + slot_of(p + (uint64_t)gpb * u) * dim4, l, active);
+    for (int u = 0; u < kPieces; ++u) {
+      const uint64_t p = p0 + (uint64_t)gpb * u;
+      v[u] = load_vec<SEG>(part4 + slot_of(p < pieces ? p : 0) * dim4, l, active && p < pieces);
+    }
 #pragma unroll
     for (int u = 0; u < kPieces; ++u) sum.add(v[u]);
   }
-  for (; p < pieces; p += gpb) sum.add(load_vec<SEG>(part4 + slot_of(p) * dim4, l, active));
-  store_vec<SEG>(s_mem + g * dim4, l, active, sum);
+  // the groups of a wave, then the waves
+  for (uint32_t d = group; d < 64; d <<= 1) sum.add_xor(d);
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63, groups_per_wave = 64u >> group_log2;
+  const uint32_t used = pieces < gpb ? ((uint32_t)pieces + groups_per_wave - 1) / groups_per_wave : kBlock / 64;
+  if (wave < used && lane < group) store_vec<SEG>(s_mem + wave * dim4, l, active, sum);
   __syncthreads();
   if (g == 0) {
     Vec total;
     total.zero();
-    const uint32_t used = pieces < gpb ? (uint32_t)pieces : gpb;
     for (uint32_t q = 0; q < used; ++q) total.add(load_vec<SEG>(s_mem + q * dim4, l, active));
     adagrad_row<E, SEG, false>(t, row, total, active, l, group, lr, eps);
   }
@@ -410,7 +430,7 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
   if (n_tiles > ws.tiles) return hipErrorInvalidValue;  // (cannot happen: the workspace is made for this rule)
   const dim3 block(256), grid((unsigned)n_tiles);
   const size_t lds_reduce = 2 * gpb * (t.dim / 4) * sizeof(float4) + 2 * gpb * sizeof(uint32_t) + tile * sizeof(uint2);
-  const size_t lds_combine = gpb * (t.dim / 4) * sizeof(float4);
+  const size_t lds_combine = kCombineWide / 64 * (t.dim / 4) * sizeof(float4);  // (enough for either block)
 #define MONO_SEG_REDUCE_AS(E, GLOG, SEG, PAST)                                                                        \
   MONO_LAUNCH_SMEM(prof, K_SEG_REDUCE, stream, (seg_reduce_kernel<E, GLOG, SEG, PAST>), grid, block, lds_reduce, t,     \
                    ws.pair_a, ws.pair_b, n, d_grad, lr, eps, ws.part, ws.part_row, tile, launched, max_bits)
@@ -420,14 +440,14 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
   } else {                                                                  \
     MONO_SEG_REDUCE_AS(E, GLOG, SEG, false);                                \
   }
-#define MONO_COMBINE(E, SEG)                                                                                     \
-  MONO_LAUNCH_SMEM(prof, K_COMBINE, stream, (combine_kernel<E, SEG>), grid, block, lds_combine, t, n_tiles, ws.part, \
-                   ws.part_row, lr, eps, group_log2)
+#define MONO_COMBINE(E, SEG, BLOCK)                                                                                     \
+  MONO_LAUNCH_SMEM(prof, K_COMBINE, stream, (combine_kernel<E, SEG, BLOCK>), grid, dim3(BLOCK), lds_combine, t, n_tiles, \
+                   ws.part, ws.part_row, lr, eps, group_log2)
 #define MONO_SEG_REDUCE_ALL(E)                                          \
   switch (seg) {                                                        \
-    case 2: MONO_SEG_REDUCE(E, 6, 2); MONO_COMBINE(E, 2); break;        \
-    case 3: MONO_SEG_REDUCE(E, 6, 3); MONO_COMBINE(E, 3); break;        \
-    case 4: MONO_SEG_REDUCE(E, 6, 4); MONO_COMBINE(E, 4); break;        \
+    case 2: MONO_SEG_REDUCE(E, 6, 2); MONO_COMBINE(E, 2, kCombineWide); break; \
+    case 3: MONO_SEG_REDUCE(E, 6, 3); MONO_COMBINE(E, 3, kCombineWide); break; \
+    case 4: MONO_SEG_REDUCE(E, 6, 4); MONO_COMBINE(E, 4, kCombineWide); break; \
     default:                                                            \
       switch (group_log2) {                                             \
         case 0: MONO_SEG_REDUCE(E, 0, 1); break;                        \
@@ -438,7 +458,11 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
         case 5: MONO_SEG_REDUCE(E, 5, 1); break;                        \
         default: MONO_SEG_REDUCE(E, 6, 1); break;                       \
       }                                                                 \
-      MONO_COMBINE(E, 1);                                               \
+      if (group_log2 == 6) {                                            \
+        MONO_COMBINE(E, 1, kCombineWide);                               \
+      } else {                                                          \
+        MONO_COMBINE(E, 1, 256);                                        \
+      }                                                                 \
   }
   if (t.bf16) {
     MONO_SEG_REDUCE_ALL(uint16_t)
