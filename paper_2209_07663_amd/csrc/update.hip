@@ -180,8 +180,9 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   using Vec = RowVec<SEG>;
   constexpr uint32_t group = 1u << GLOG, gpb = 256u >> GLOG;  // groups (= chunks) per block
   const uint32_t chunk = tile >> (8 - GLOG);
-  constexpr int kWide = (int)group < 8 ? (int)group : 8;
-  constexpr int kBatch = kWide / SEG > 0 ? kWide / SEG : 1;   // gradient rows in flight per lane
+  // gradient rows in flight per lane (rows in pieces: two; four of dim 512, with four embedding rows, left the
+  // compute unit too few waves: 98 K bf16 pairs 55 -> 45 us)
+  constexpr int kBatch = SEG > 1 ? 2 : ((int)group < 8 ? (int)group : 8);
   const SortPlan plan = make_sort_plan(t.ctl->hwm, max_bits);
   if (plan.passes > launched) {  // the host's bound on the high-water mark was too low: nothing is sorted, nothing is touched
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&t.ctl->n_lost, 1ull);
