@@ -148,8 +148,9 @@ hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, cons
                              const int64_t* d_offsets, uint64_t n_bags, uint32_t hwm_bound, uint32_t* launched,
                              uint32_t* max_bits, hipStream_t stream, Profiler* prof);
 
-hipError_t launch_expire_sweep(const TableView& t, uint32_t now, uint64_t* d_n_expired, int64_t* d_expired_keys,
-                               uint64_t max_expired, hipStream_t stream, Profiler* prof);
+// look_all: the noted bounds cannot be relied on, every bucket that holds something is looked at
+hipError_t launch_expire_sweep(const TableView& t, uint32_t now, bool look_all, uint64_t* d_n_expired,
+                               int64_t* d_expired_keys, uint64_t max_expired, hipStream_t stream, Profiler* prof);
 
 hipError_t launch_export(const TableView& t, int64_t* d_keys, int32_t* d_row, uint32_t* d_last_seen, int64_t* d_slot,
                          uint64_t max_n, bool touched_only, hipStream_t stream);

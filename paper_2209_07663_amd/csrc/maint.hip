@@ -49,8 +49,8 @@ __device__ inline void sweep_stash(const TableView& t, uint32_t now, int64_t* ex
 // tables, which would have too few waves.
 // keep_slots: the lists take slots and the slots stay as they are (see sweep_remove).
 template <int kWords>
-__global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t now, int keep_slots, int64_t* expired_keys,
-                                                         uint64_t max_expired) {
+__global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t now, bool look_all, int keep_slots,
+                                                         int64_t* expired_keys, uint64_t max_expired) {
   constexpr uint32_t kBuckets = 256u * kWords;
   __shared__ uint16_t s_list[4][kBuckets];
   if (blockIdx.x == 0 && threadIdx.x == 0) sweep_stash(t, now, expired_keys, max_expired);
@@ -58,10 +58,11 @@ __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t n
   const uint64_t wave_id = (uint64_t)blockIdx.x * 4 + wave, bucket0 = wave_id * kBuckets, n = 2 * t.n_buckets;
   if (bucket0 >= n) return;  // wave-uniform (no barriers below)
   // Bounds are unambiguous while every key's last-seen step lies in the last kAgeModulus units: all keys that the
-  // latest sweep left were seen less than expire_steps before it.  Beyond that every bucket is looked at.
+  // latest sweep left were seen less than expire_steps before it.  Beyond that every bucket is looked at, as it is
+  // where the caller's steps went back behind the latest sweep (`now` did, or a lookup in between: look_all).
   const uint32_t unit_now = now >> t.sweep_q, swept = t.ctl->swept;
   const uint32_t unit_least = (swept > t.expire_steps ? swept - t.expire_steps : 0u) >> t.sweep_q;
-  const bool look_all = unit_now - unit_least >= kAgeModulus - 1 || now < swept;
+  look_all = look_all || unit_now - unit_least >= kAgeModulus - 1 || now < swept;
   const uint64_t first = bucket0 + (uint64_t)lane * (4 * kWords);  // the lane's buckets
   uint32_t word[kWords];
 #pragma unroll
@@ -216,8 +217,8 @@ __global__ void sweep_nothing_kernel(uint64_t* n_expired) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *n_expired = 0;
 }
 
-hipError_t launch_expire_sweep(const TableView& t, uint32_t now, uint64_t* d_n_expired, int64_t* d_expired_keys,
-                               uint64_t max_expired, hipStream_t stream, Profiler* prof) {
+hipError_t launch_expire_sweep(const TableView& t, uint32_t now, bool look_all, uint64_t* d_n_expired,
+                               int64_t* d_expired_keys, uint64_t max_expired, hipStream_t stream, Profiler* prof) {
   if (t.expire_steps == 0) {  // nothing ever expires: only the count is reported
     if (d_n_expired) MONO_LAUNCH(prof, K_SWEEP_END, stream, sweep_nothing_kernel, dim3(1), dim3(64), d_n_expired);
     return hipGetLastError();
@@ -226,9 +227,11 @@ hipError_t launch_expire_sweep(const TableView& t, uint32_t now, uint64_t* d_n_e
   const dim3 block(256), grid((unsigned)((waves + 3) / 4));
   const int keep_slots = d_expired_keys != nullptr;
   if (t.capacity >= kSweepLargeTable)
-    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<4>, grid, block, t, now, keep_slots, d_expired_keys, max_expired);
+    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<4>, grid, block, t, now, look_all, keep_slots, d_expired_keys,
+                max_expired);
   else
-    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<1>, grid, block, t, now, keep_slots, d_expired_keys, max_expired);
+    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<1>, grid, block, t, now, look_all, keep_slots, d_expired_keys,
+                max_expired);
   MONO_LAUNCH(prof, K_SWEEP_REMOVE, stream, sweep_remove_kernel, dim3(grid.x < 1024u ? grid.x : 1024u), block, t, now,
               d_expired_keys, max_expired, d_n_expired);
   return hipGetLastError();

@@ -15,6 +15,9 @@ struct mono_table {
   uint64_t max_ids = 0, max_bags = 0, dset_size = 0;
   uint32_t epoch = 0;       // per-call tag of the dedup set
   uint32_t last_step = 0;
+  uint32_t last_sweep = 0;  // `now` of the latest sweep, and
+  bool sweep_all = false;   // was there a lookup behind it since?  The bounds of the buckets then say nothing: the
+                            // lookup has stamped keys, or added some, with steps that are older than the bounds allow
   uint64_t seed = 0;
   uint32_t generation = 0;  // rehash generation of the placement hashes h0 / h1
   int device = 0;
@@ -394,6 +397,7 @@ int mono_lookup_or_insert(mono_table* t, const int64_t* d_keys, uint64_t n, uint
     epoch = 1;
     t->tags_wrapped = true;
   }
+  if (step < t->last_sweep) t->sweep_all = true;
   const RestoreSource none = {nullptr, nullptr, nullptr};
   if (launch_lookup_or_insert(t->view, d_keys, n, step, epoch, d_rows_out, none, (hipStream_t)stream, &t->prof) != hipSuccess)
     return MONO_EHIP;  // (the table's step and call tag move on only when the call was queued)
@@ -459,10 +463,12 @@ int mono_expire_sweep(mono_table* t, uint32_t now, uint64_t* d_n_expired, int64_
                       uint64_t max_expired, void* stream) {
   if (!t || now >= (1u << 24)) return MONO_EINVAL;
   note_stream(t, stream);
-  return launch_expire_sweep(t->view, now, d_n_expired, d_expired_keys, d_expired_keys ? max_expired : 0,
-                             (hipStream_t)stream, &t->prof) == hipSuccess
-             ? MONO_OK
-             : MONO_EHIP;
+  if (launch_expire_sweep(t->view, now, t->sweep_all, d_n_expired, d_expired_keys, d_expired_keys ? max_expired : 0,
+                          (hipStream_t)stream, &t->prof) != hipSuccess)
+    return MONO_EHIP;
+  t->last_sweep = now;
+  t->sweep_all = false;  // (it has written every bound anew)
+  return MONO_OK;
 }
 
 int mono_table_stats(mono_table* t, mono_stats* h_out, void* stream) {
