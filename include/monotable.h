@@ -133,7 +133,8 @@ int mono_gather_pool(mono_table* t, const int32_t* d_rows, uint64_t n, const int
  *   d_table_r, d_table_q  [2^log2_rows * dim] each, fp32 or bf16 (flags), row-major, device, caller-owned
  *   log2_rows             m, 1..30;  dim as in mono_table_create
  *   d_ids[n]              int64; an ID outside [0, 2^(2m)) (e.g. the padding key -1) contributes zero
- * d_out[n_bags * dim] is fp32.  Errors: MONO_EINVAL on a bad argument. */
+ * d_out[n_bags * dim] is fp32.  Of a bag of more than 2^31 - 1 IDs the first 2^31 - 1 count.
+ * Errors: MONO_EINVAL on a bad argument. */
 int mono_qr_gather_pool(const void* d_table_r, const void* d_table_q, uint32_t log2_rows, uint32_t dim, uint32_t flags,
                         const int64_t* d_ids, uint64_t n, const int64_t* d_offsets, uint64_t n_bags, float* d_out,
                         void* stream);

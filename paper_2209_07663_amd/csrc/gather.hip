@@ -31,6 +31,12 @@
 namespace mono {
 
 constexpr int kIdsInRegs = 8;
+// Positions in a bag, and the IDs of a bag that count.  The walk of a bag steps up to kIdsInRegs past its last ID, and
+// a signed step that wrapped there read in front of the caller's IDs (only the two dense tables take calls of so many).
+// 64-bit positions would hold more, but their registers cost the two-table kernel a wave in four (329 -> 399 us).
+using BagPos = uint32_t;
+constexpr BagPos kMostInBag = 0x7FFFFFFFu;
+static_assert(kMostInBag + (BagPos)kIdsInRegs > kMostInBag, "the step after the last ID must not wrap");
 constexpr uint64_t kWavesWanted = 4096;  // half of what the chip can hold: enough loads in flight to hide their latency
 
 // N consecutive elements of a row as they are stored (one load), and their sum in fp32.
@@ -156,7 +162,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   int64_t e = mine ? offsets[bag_base + lane + 1] : 0;
   s = s < 0 ? 0 : s;
   e = e > (int64_t)n ? (int64_t)n : e;
-  const int len = e > s ? (int)(e - s > 0x7FFFFFFF ? 0x7FFFFFFF : e - s) : 0;
+  const int len = e > s ? (int)(e - s > (int64_t)kMostInBag ? (int64_t)kMostInBag : e - s) : 0;
   Id id[kIdsInRegs];
 #pragma unroll
   for (int j = 0; j < kIdsInRegs; ++j) id[j] = j < len ? src.at(s + j) : src.none();
@@ -196,7 +202,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   }
   for (uint32_t q = 0; q < rounds; ++q) {
     const int from = (int)(q * bags_per_round + g);
-    const int blen = __shfl(len, from);
+    const BagPos blen = (BagPos)__shfl(len, from);
     const int64_t bs = __shfl(s, from);
     const uint64_t bag = bag_base + (uint32_t)from;
     for (uint32_t col0 = 0; col0 < dim; col0 += 64 * N) {  // one trip unless the row is wider than the wave
@@ -206,7 +212,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
       Id rid[kIdsInRegs];
 #pragma unroll
       for (int j = 0; j < kIdsInRegs; ++j) rid[j] = __shfl(id[j], from);
-      for (int c = 0;;) {
+      for (BagPos c = 0;;) {
         Row v[kIdsInRegs];
 #pragma unroll
         for (int j = 0; j < kIdsInRegs; ++j) {
