@@ -499,6 +499,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
 // memory would have left it.
 constexpr int kSmallBlock = 1024;
 constexpr uint32_t kSmallWaves = kSmallBlock / 64, kSmallRounds = (uint32_t)kSortSmall / kSmallBlock;
+constexpr uint32_t kSmallBag = 32, kSmallLong = (uint32_t)kSortSmall / kSmallBag;  // a longer bag is a long one; room for all of them
 __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __restrict__ ctl, uint32_t max_bits,
                                                                  const int32_t* __restrict__ rows, uint32_t n,
                                                                  const int64_t* __restrict__ offsets, uint64_t n_bags,
@@ -508,6 +509,8 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
   __shared__ uint2 pairs[kSortSmall];
   __shared__ uint32_t cnt[kSmallWaves][kBins];
   __shared__ uint32_t wave_sum[kBins / 64];
+  __shared__ uint4 long_bag[kSmallLong];  // bag, first and last of the occurrences that it has not written yet
+  __shared__ uint32_t n_long;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
   const uint32_t rounds = (n + kSmallBlock - 1) / kSmallBlock;  // a wave owns 64 * rounds consecutive pairs
   const uint32_t i0 = wave * 64 * rounds + lane;
@@ -519,13 +522,29 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
     if (r < rounds && i < n) kv[r].x = first_key(rows, i, plan.hwm);
     if (kv[r].x >= plan.hwm) kv[r].x = 0xFFFFFFFFu;  // dropped occurrence (or past the end): left out
   }
-  {  // every bag writes its number over its occurrences (all bags: a small batch has few)
+  {  // every bag writes its number over its occurrences (all bags: a small batch has few), a long one by a whole wave
+    // (by its thread alone, the only bag of 8192 pairs made the update take 294 us, 35 so)
     uint32_t* bag_here = reinterpret_cast<uint32_t*>(pairs);
+    if (tid == 0) n_long = 0;
+    __syncthreads();
     for (uint64_t b = tid; b < n_bags; b += kSmallBlock) {
-      const uint64_t from = bounded_offset(offsets, b, n), to = bounded_offset(offsets, b + 1, n);
-      for (uint64_t i = from; i < to; ++i) bag_here[i] = (uint32_t)b;
+      const uint32_t from = (uint32_t)bounded_offset(offsets, b, n), to = (uint32_t)bounded_offset(offsets, b + 1, n);
+      const uint32_t end = to > from && to - from > kSmallBag ? from + kSmallBag : to;
+      for (uint32_t i = from; i < end; ++i) bag_here[i] = (uint32_t)b;
+      if (end < to) {
+        const uint32_t at = atomicAdd(&n_long, 1u);
+        if (at < kSmallLong) long_bag[at] = make_uint4((uint32_t)b, end, to, 0u);  // (else the offsets decrease somewhere)
+      }
     }
     __syncthreads();
+    const uint32_t longs = n_long < kSmallLong ? n_long : kSmallLong;
+    if (longs) {  // block-uniform
+      for (uint32_t q = wave; q < longs; q += kSmallWaves) {
+        const uint4 x = long_bag[q];
+        for (uint32_t i = x.y + lane; i < x.z; i += 64) bag_here[i] = x.x;
+      }
+      __syncthreads();
+    }
     const uint32_t last_bag = (uint32_t)(n_bags - 1);  // (an occurrence outside every bag reads whatever the LDS held)
 #pragma unroll
     for (uint32_t r = 0; r < kSmallRounds; ++r)
