@@ -520,6 +520,7 @@ int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t
   ExportWorkspace ws;
   if (export_workspace(&ws, (char*)d_work, max_n ? max_n : 1) > work_bytes) return MONO_EINVAL;
   hipStream_t s = (hipStream_t)stream;
+  note_stream(t, stream);  // (the rows are still being read when this call returns)
   if (launch_export(t->view, (int64_t*)ws.key[0], ws.row, d_last_seen ? ws.seen : nullptr, d_slot ? ws.slot : nullptr,
                     max_n, touched_only != 0, s) != hipSuccess)
     return MONO_EHIP;
@@ -604,6 +605,7 @@ int mono_table_migrate(mono_table* dst, mono_table* src, uint32_t generation, vo
     return MONO_EINVAL;  // dst must be a fresh table with the same parameters
   hipStream_t s = (hipStream_t)stream;
   note_stream(dst, stream);
+  note_stream(src, stream);  // (src is still being read when this call returns)
   Control c;
   if (hipMemcpyAsync(&c, a.ctl, sizeof(Control), hipMemcpyDeviceToHost, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
