@@ -44,8 +44,8 @@ constexpr int kSmallMisses = 4;             // Control::scratch slots of the one
 constexpr int kSmallDone = 5;               // missing occurrences so far, blocks that have finished their probes
 constexpr int kMissTag = 7;                 // Control::scratch slots: tag of the latest call in which an occurrence missed,
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
-constexpr int kKeptOut = 11;                // Control::scratch slots: occurrences of keys kept out by their counters, in the
-constexpr int kCountersFirst = 12;          // running call's sample; is the next call to look at counters first?
+constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
+constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
 
 struct StashEntry {

@@ -118,6 +118,29 @@ struct RestoreSource {
 hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, uint64_t n, uint32_t step, uint32_t epoch,
                                    int32_t* d_rows_out, const RestoreSource& src, hipStream_t stream, Profiler* prof);
 
+// Tables without expiry: is a key's counter looked at before its buckets?  A counter below the threshold proves the key
+// absent and saves it both bucket lines, but the look costs every stored key a random access.  So it is taken after a call
+// in which enough occurrences missed, as about kSampledBlocks blocks of the election saw them:
+//   batches of at most kElectSmall  those of keys that their counters kept out, from a 16th of the batch on.  lookup_or_insert
+//             of 100 K uniform keys, threshold 3: 18.1 us without the look and 18.9 with it when all are known, 32.1 and
+//             30.7 at a tenth absent, 41.4 and 36.3 when all are; 200 K 20.7 / 23.9, 38.7 / 36.3, 53.6 / 48.3.  Keys that
+//             are new and admitted at once (threshold 0 or 1) do not count: their insertion reads the buckets anyway, and
+//             finds them in the L2 where the probe has just been (200 K new keys 91.7 us without the look, 96.3 with it)
+//   larger ones  all that missed, from 5 in 16 on.  4 M keys, threshold 3: 112 / 184 us when all are known, 196 / 218 at
+//             0.2 absent, 243 / 234 at 0.3, 384 / 325 at 0.6, 541 / 450 at 1; threshold 1: 425 / 422, 743 / 684, 1155 /
+//             1053; 700 K keys cross between 0.3 and 0.4 (70 / 73 and 76 / 75 us)
+constexpr uint64_t kElectSmall = 1u << 19;  // largest batch whose election takes one occurrence per thread, others four
+constexpr uint64_t kSampledBlocks = 16;     // (their atomics meet at one word, and hold up the end of a small election)
+struct MissSample {
+  uint32_t every;   // each `every`th block of the election is looked at; 0: none
+  uint64_t enough;  // missing occurrences in those blocks from which on the next call looks at counters first
+};
+inline MissSample miss_sample(uint64_t n, uint64_t blocks, uint64_t per_block) {
+  const uint64_t every = (blocks + kSampledBlocks - 1) / kSampledBlocks, looked_at = (blocks + every - 1) / every;
+  const uint64_t sampled = looked_at * per_block < n ? looked_at * per_block : n;
+  return {(uint32_t)every, sampled * (n <= kElectSmall ? 1 : 5) / 16 + 1};
+}
+
 // The same in one kernel, for batches of at most kSmallLookup keys that are not a restore call.
 constexpr uint64_t kSmallLookup = 4096;
 hipError_t launch_lookup_small(const TableView& t, const int64_t* d_keys, uint64_t n, uint32_t step, uint32_t epoch,

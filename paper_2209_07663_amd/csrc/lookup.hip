@@ -78,13 +78,6 @@ constexpr int kProbeBlock = 256;
 constexpr uint64_t kProbeBlocksWanted = 1024, kProbeMaxTurns = 8;
 constexpr int kProbeTries = 8;  // slots of the set that a missing key looks at
 
-// On tables without expiry a look at the counters first costs every stored key a random access and saves two for an
-// absent one: 26 M IDs that are all known took 588 us with it and 457 without, 100 K 11.4 and 8.9, four million of
-// which half are absent the same with both, four million absent ones 539 and 568.  So it is taken after a call in
-// which more than kCountersFirstShare eighths of the occurrences were those of keys that their counters keep out,
-// as about kSampledBlocks of the election's blocks saw them.
-constexpr uint64_t kCountersFirstShare = 5, kSampledBlocks = 64;
-
 // restore != 0: the keys are snapshot records; a stored key is marked absent (its record is refused)
 // and nothing is stamped or counted.
 // A block owns kProbeBlock * turns consecutive keys and takes them in turns of one key per thread.
@@ -98,6 +91,8 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   __shared__ unsigned long long miss_key[kMissSlots];
   __shared__ uint32_t miss_cnt[kMissSlots];
   __shared__ int any_miss;
+  // Are counters worth a look before the buckets?  (Counters that age prove nothing; see MissSample.)
+  const bool counters_first = t.expire_steps == 0 && !restore && t.ctl->scratch[kCountersFirst] != 0;
   if (threadIdx.x == 0) any_miss = 0;
   for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock) {
     miss_key[s] = kEmptyKey;
@@ -105,8 +100,6 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   }
   __syncthreads();  // the LDS set is cleared
   const uint32_t lane = lane_id(), gi = lane & 7u, gbase = lane & ~7u;
-  // Are counters worth a look before the buckets?  (Counters that age prove nothing; see kCountersFirstShare.)
-  const bool counters_first = t.expire_steps == 0 && !restore && t.ctl->scratch[kCountersFirst] != 0;
   bool sparse = false;  // (tables with expiry) less than a quarter full: the occupancy bitmap is worth a look
   if (t.expire_steps != 0) {
     const int32_t free_n = t.ctl->free_n;
@@ -203,7 +196,6 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
 // key -> dedup set -> exchange), and four of them side by side keep the memory busier than more blocks
 // with one would; and an ID that turns hot before it is admitted is led by one occurrence per block, and all those
 // leaders meet at one position of the dedup set.  One for batches of at most kElectSmall, which are short of blocks.
-constexpr uint64_t kElectSmall = 1u << 19;
 constexpr int kElectBlock = 256;
 template <int kPer>
 __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, const int64_t* __restrict__ keys,
@@ -218,7 +210,9 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   // re-reading the counter and competing for the same position of the dedup set serialised.
   __shared__ unsigned long long s_key[kElectSlots];
   __shared__ int32_t s_res[kElectSlots];  // what the leader found: kRowAbsent, or the elected occurrence as -occ - 3
-  if (t.ctl->scratch[kMissTag] != epoch) return;  // block-uniform: no occurrence of the call missed
+  // A large batch without a miss ends here.  (A small one reads its occurrences at once: the tag before them is one more
+  // round trip of a kernel that is hardly more than three.)
+  if (kPer > 1 && t.ctl->scratch[kMissTag] != epoch) return;  // block-uniform
   const uint64_t i0 = (uint64_t)blockIdx.x * (kElectBlock * kPer) + threadIdx.x;
   bool miss[kPer];
   uint64_t k[kPer];
@@ -230,7 +224,11 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   for (int s = threadIdx.x; s < kElectSlots; s += kElectBlock) s_key[s] = kEmptyKey;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) k[j] = miss[j] ? (uint64_t)keys[i0 + (uint64_t)j * kElectBlock] : kEmptyKey;
-  __syncthreads();
+  if (kPer > 1) {
+    __syncthreads();
+  } else if (!__syncthreads_or(miss[0])) {
+    return;
+  }
   bool leader[kPer];
   uint32_t ls[kPer];
 #pragma unroll
@@ -311,19 +309,16 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   }
   __syncthreads();
   bool duplicate = false;
-  uint32_t kept_out = 0;
+  uint32_t missed = 0;  // of the wave's occurrences, as MissSample counts them
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    if (!miss[j] || winner[j]) continue;
-    const int32_t found = s_res[ls[j]];
-    if (!leader[j]) rows_out[i0 + (uint64_t)j * kElectBlock] = found;
-    duplicate = duplicate || found <= -3;
-    kept_out += found == kRowAbsent;
-  }
-  if (sample_every && blockIdx.x % sample_every == 0) {  // block-uniform
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) kept_out += __shfl_xor(kept_out, d);
-    if (kept_out && lane_id() == 0) atomicAdd(&t.ctl->scratch[kKeptOut], (unsigned long long)kept_out);
+    int32_t found = kRowMiss;
+    if (miss[j] && !winner[j]) {
+      found = s_res[ls[j]];
+      if (!leader[j]) rows_out[i0 + (uint64_t)j * kElectBlock] = found;
+      duplicate = duplicate || found <= -3;
+    }
+    missed += (uint32_t)__popcll(__ballot(kPer > 1 ? miss[j] : found == kRowAbsent));
   }
   if (__ballot(duplicate) && lane_id() == 0) t.ctl->scratch[kDuplicateTag] = epoch;
   // block-aggregated append to sub-list (blockIdx mod kWinLists)
@@ -331,17 +326,19 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   uint32_t mine = 0;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) mine += (uint32_t)__popcll(__ballot(winner[j]));
-  if (lane_id() == 0) wave_cnt[wave] = mine;
+  if (lane_id() == 0) wave_cnt[wave] = missed << 16 | mine;
   __syncthreads();
   const uint32_t list = blockIdx.x & (kWinLists - 1);
   if (threadIdx.x == 0) {
-    uint32_t total = 0;
+    uint32_t total = 0;  // (both halves: at most kElectBlock * kPer each)
     for (int w = 0; w < kElectWaves; ++w) total += wave_cnt[w];
-    block_base = total ? atomicAdd(&t.win_cnt[list * kWinStride], total) : 0u;
+    block_base = total & 0xFFFFu ? atomicAdd(&t.win_cnt[list * kWinStride], total & 0xFFFFu) : 0u;
+    if (sample_every && blockIdx.x % sample_every == 0 && total >> 16)
+      atomicAdd(&t.ctl->scratch[kSampledMisses], (unsigned long long)(total >> 16));
   }
   __syncthreads();
   uint32_t p = block_base;
-  for (uint32_t w = 0; w < wave; ++w) p += wave_cnt[w];
+  for (uint32_t w = 0; w < wave; ++w) p += wave_cnt[w] & 0xFFFFu;
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const uint64_t m = __ballot(winner[j]);
@@ -433,7 +430,7 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint32_t st
 }
 
 __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, int32_t* rows_out, uint32_t epoch,
-                                                      uint64_t sampled) {
+                                                      uint64_t enough) {
   if (t.ctl->scratch[kDuplicateTag] == epoch) {  // (else every missing key of the call occurred once, or was not admitted)
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
@@ -448,9 +445,9 @@ __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, i
     for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
     if (threadIdx.x == 0) {
       settle_call(t, total, t.ctl->free_n, epoch);
-      if (sampled) {  // (occurrences)
-        t.ctl->scratch[kCountersFirst] = t.ctl->scratch[kKeptOut] * 8 > sampled * kCountersFirstShare;
-        t.ctl->scratch[kKeptOut] = 0;
+      if (enough) {
+        t.ctl->scratch[kCountersFirst] = t.ctl->scratch[kSampledMisses] >= enough;
+        t.ctl->scratch[kSampledMisses] = 0;
       }
     }
   }
@@ -484,24 +481,19 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
   }
   const uint64_t elect_per_block = n <= kElectSmall ? kElectBlock : 4 * kElectBlock;
   const dim3 egrid((unsigned)((n + elect_per_block - 1) / elect_per_block));
-  uint32_t sample_every = 0;
-  uint64_t sampled = 0;
-  if (t.expire_steps == 0 && !restore) {
-    sample_every = (uint32_t)((egrid.x + kSampledBlocks - 1) / kSampledBlocks);
-    sampled = (egrid.x + sample_every - 1) / sample_every * elect_per_block;
-    sampled = sampled < n ? sampled : n;
-  }
+  MissSample sample = {0, 0};
+  if (t.expire_steps == 0 && !restore) sample = miss_sample(n, egrid.x, elect_per_block);
   if (n <= kElectSmall)
     MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<1>, egrid, block, t, d_keys, n, epoch, d_rows_out, restore,
-                sample_every);
+                sample.every);
   else
     MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<4>, egrid, block, t, d_keys, n, epoch, d_rows_out, restore,
-                sample_every);
+                sample.every);
   if (t.bf16)
     MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<uint16_t>, igrid, block, t, step, d_rows_out, src);
   else
     MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<float>, igrid, block, t, step, d_rows_out, src);
-  MONO_LAUNCH(prof, K_RESOLVE, stream, resolve_kernel, igrid, block, t, n, d_rows_out, epoch, sampled);
+  MONO_LAUNCH(prof, K_RESOLVE, stream, resolve_kernel, igrid, block, t, n, d_rows_out, epoch, sample.enough);
   if (restore) hipLaunchKernelGGL(count_refused_kernel, grid, block, 0, stream, t, n, d_rows_out);
   return hipGetLastError();
 }
