@@ -234,17 +234,21 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   }
 }
 
-// Lanes per row, bags per wave, the grid of a launch, and whether the pooled rows go past the caches.  They do
-// where they are more than kPooledCached bytes: they would then push out of the 256 MB cache behind the L2s what
-// the step reads next, the gradients first (reduction of 690 K bf16 pairs of dim 64: 115 -> 89 us, of 5.8 M of
-// dim 32 against 128 MB of gradients 204 -> 195; nothing changed for the gather itself).  Smaller results stay in
-// the caches for the layer that takes them.
-constexpr uint64_t kPooledCached = 64ull << 20;
+// Lanes per row, bags per wave, the grid of a launch, and whether the pooled rows go past the caches.  The layer that
+// takes them reads them next, so what counts is the gather and that layer together, with caches that the rest of a step
+// has filled with something else.  Rows of four elements per lane go past them beyond kPooledCached bytes, three
+// quarters of the cache behind the L2s; the layer would then find little of them there (gather and a layer that reads
+// all of it, through the caches and past them: 100 MB of dim 32 117 and 126 us, 128 MB 142 and 150, 192 MB 204 and 198,
+// 400 MB 367 and 363; dim 256 192 MB 200 and 207, 256 MB 257 and 259; bf16 of dim 64 100 MB 96 and 110, 192 MB 177 and
+// 179, 240 MB 214 and 210, 400 MB 341 and 321).  Rows of eight elements per lane never do: a lane stores them in two
+// pieces, which past the caches reach the memory as half lines (bf16 of dim 512, 66 MB 71 and 91 us, 400 MB 350 and 429).
+constexpr uint64_t kPooledCached = 192ull << 20;
 struct GatherShape {
   uint32_t group_log2 = 0, bags_log2 = 6;
   bool past_caches;
   dim3 grid;
-  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags) : past_caches(n_bags * dim * sizeof(float) > kPooledCached) {
+  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags)
+      : past_caches(n_per_lane == 4 && n_bags * dim * sizeof(float) > kPooledCached) {
     while (group_log2 < 6 && (n_per_lane << group_log2) < dim) ++group_log2;
     while (bags_log2 > 6 - group_log2 && (n_bags >> bags_log2) < kWavesWanted) --bags_log2;
     const uint64_t waves = (n_bags + (1ull << bags_log2) - 1) >> bags_log2;

@@ -38,3 +38,23 @@ int main() {
   return 0;
 }
 """)
+
+
+def test_pooled_rows_stay_in_the_caches_unless_they_are_large(tmp_path):
+    """Pooled rows go past the caches beyond three quarters of the 256 MB cache, and never where a lane holds eight
+    elements of a row."""
+    _run(tmp_path, r"""
+#include "gather.hip"
+using namespace mono;
+int main() {
+  int wrong = 0;
+  const unsigned long long most = 192ull << 20;
+  for (unsigned dim : {4u, 32u, 36u, 64u, 256u, 512u, 1024u})
+    for (unsigned long long bytes : {1ull << 20, 64ull << 20, 65ull << 20, 128ull << 20, most, most + 4 * dim, 1ull << 32}) {
+      const unsigned long long bags = bytes / (4 * dim);
+      if (GatherShape(dim, 4, bags).past_caches != (bags * dim * 4 > most)) printf("dim %u, %llu bags\n", dim, bags), ++wrong;
+      if (GatherShape(dim, 8, bags).past_caches) printf("eight elements per lane, dim %u, %llu bags\n", dim, bags), ++wrong;
+    }
+  return wrong;
+}
+""")

@@ -1,4 +1,4 @@
-"""Large batches: pooled results of more than 64 MB are stored, and rows of updates of more than 256 MB read and
+"""Large batches: pooled results of more than 192 MB are stored, and rows of updates of more than 256 MB read and
 written, past the caches.  Both sides of each line, against small calls (gather) and a fp64 reduction (update)."""
 import pytest
 import torch
@@ -7,7 +7,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("dim,n", [(64, (1 << 18) + 1), (1024, 65536), (1024, 65537), (1024, 131073), (36, 3728271)])
+@pytest.mark.parametrize("dim,n", [(64, (1 << 18) + 1), (64, 786432), (64, 786433), (1024, 65536), (1024, 65537), (1024, 131073), (36, 3728271)])
 def test_large_gathers_and_updates(dim, n, bf16):
     from paper_2209_07663_amd.binding import Table
     dev, known = torch.device("cuda:0"), 30000
