@@ -180,9 +180,11 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   using Vec = RowVec<SEG>;
   constexpr uint32_t group = 1u << GLOG, gpb = 256u >> GLOG;  // groups (= chunks) per block
   const uint32_t chunk = tile >> (8 - GLOG);
-  // gradient rows in flight per lane (rows in pieces: two; four of dim 512, with four embedding rows, left the
-  // compute unit too few waves: 98 K bf16 pairs 55 -> 45 us)
-  constexpr int kBatch = SEG > 1 ? 2 : ((int)group < 8 ? (int)group : 8);
+  // gradient rows in flight per lane, each with the embedding row it may end in.  Rows in pieces: four, bf16 two (update of
+  // 400 K pairs with two and with four, of dim 512, 768, 1024: fp32 309 / 307, 474 / 466, 628 / 610 us, with hot rows
+  // 267 / 260, 382 / 365, 498 / 476; bf16 255 / 314, 387 / 473, 535 / 738.  Batches of up to 98 K pairs the same way or
+  // within 2 us)
+  constexpr int kBatch = SEG > 1 ? (sizeof(E) == 2 ? 2 : 4) : ((int)group < 8 ? (int)group : 8);
   const SortPlan plan = make_sort_plan(t.ctl->hwm, max_bits);
   if (plan.passes > launched) {  // the host's bound on the high-water mark was too low: nothing is sorted, nothing is touched
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&t.ctl->n_lost, 1ull);
@@ -344,7 +346,9 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
 // The hottest row's chain of pieces bounds it in small batches, the blocks' own latency in large ones.  All rounds of
 // pieces are asked for eight at a time, the last one too, and the groups of a wave are summed by shuffles: 6.8 M pairs
 // 11.1 -> 7.7 us, 690 K 9.6 -> 7.8.  Rows that take a whole wave have blocks of 512 threads (98 K pairs of dim 512: 18.6
-// us with 256, 12.7 with 512, 14.2 with 1024); others 256 (6.8 M pairs: 10.2 with 512, 18.4 with 1024).
+// us with 256, 12.7 with 512, 14.2 with 1024; the update of 98 K to 1 M pairs with hot rows, dims 512 to 1024, 1 to 6 %
+// longer with 256, of evenly spread ones and of dims 132 to 256 the same within 2 %); others 256 (6.8 M pairs: 10.2 with
+// 512, 18.4 with 1024).
 // (A lane group per tile, and a whole block only for runs over more than seven tiles, took 25-43 us there: small
 // tiles have many such runs, one after the other in a block.)
 constexpr int kCombineWide = 512;
