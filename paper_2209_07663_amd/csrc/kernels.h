@@ -30,9 +30,13 @@ struct UpdateWorkspace {
 // 26 K pairs takes 11.1 / 8.2 / 6.4 us with 2048 / 1024 / 512 elements per block, one of 204 K 10.8 / 8.0 / 7.0,
 // one of 690 K 12.0 / 9.9 / 10.5 (there the histograms, one word per bin and block, begin to cost more), one
 // of 1 M 12.9 / 12.5 / 12.8.
-// Where the batch is small and two digits of up to 11 bits save a pass of narrow ones (2^16 to 2^22 rows in use),
-// they are taken: all sort kernels of 100 K pairs 42 -> 36 us and three launches fewer, but 44 -> 45 at 204 K, 57 ->
-// 68 at 690 K (2048 histogram words per block).
+// Where the batch is small and two digits of up to 11 bits save a pass of narrow ones (2^16 to 2^22 rows in use), they
+// are taken, three launches fewer; but their histograms are 2^digit words per block, so that how small depends on the
+// digit.  Update of dim 16, two digits / three narrow ones, from 512 words (300 K rows in use) to 2048 (3.9 M):
+//                     32 K pairs    64 K          100 K         128 K         156 K
+//   300 K, 1 M rows   45 / 49 us    50 / 54       54 / 56       56 / 57       58 / 63, 66 / 65
+//   1.3 M             49 / 51       57 / 58       61 / 59       66 / 60
+//   3.9 M             52 / 53       61 / 59       66 / 60       72 / 62
 // And batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch instead of nine.
 struct SortShape {
   uint32_t max_bits, items;
@@ -40,11 +44,14 @@ struct SortShape {
 constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9, kSortFewBits = 11;
 constexpr uint32_t kSortNarrowMaxRows = 1u << 24;  // beyond this many rows in use the wide shape saves a pass
 constexpr uint64_t kSortItems512 = 400000, kSortItems1024 = 1u << 20;  // largest batches of those block sizes
-constexpr uint64_t kSortFewMost = 1u << 17;
-constexpr uint32_t kSortFewRowsAbove = 1u << 16, kSortFewMaxRows = 1u << 22;
+constexpr uint64_t kSortFewMost = 1u << 17;  // largest batch with two digits of at most 10 bits, halved for each bit more
+constexpr uint32_t kSortFewRowsAbove = 1u << 16, kSortFewRows10 = 1u << 20, kSortFewMaxRows = 1u << 22;
+inline uint64_t sort_few_most(uint32_t rows) {
+  return rows <= kSortFewRows10 ? kSortFewMost : (rows <= 2 * kSortFewRows10 ? kSortFewMost / 2 : kSortFewMost / 4);
+}
 constexpr uint64_t kSortSmall = 8192;
 inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
-  if (n <= kSortFewMost && hwm_bound > kSortFewRowsAbove && hwm_bound <= kSortFewMaxRows) return {kSortFewBits, 512u};
+  if (hwm_bound > kSortFewRowsAbove && hwm_bound <= kSortFewMaxRows && n <= sort_few_most(hwm_bound)) return {kSortFewBits, 512u};
   if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, n <= kSortItems1024 ? 1024u : 4096u};
   return {kSortNarrowBits, n <= kSortItems512 ? 512u : (n <= kSortItems1024 ? 1024u : 2048u)};
 }
@@ -75,7 +82,7 @@ inline uint64_t sort_hist_words(uint64_t n) {
   const uint64_t sizes[] = {n, n < kSortFewMost ? n : kSortFewMost, n < kSortItems512 ? n : kSortItems512,
                             n < kSortItems1024 ? n : kSortItems1024};
   for (const uint64_t m : sizes)
-    for (const uint32_t rows : {kSortFewMaxRows, kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
+    for (const uint32_t rows : {kSortFewRows10, kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
       const SortShape s = sort_shape_for(rows, m);
       const uint64_t stride = sort_stride(sort_units(m, s.items)), groups = s.items > kSortGroupedAbove ? stride / kSortGroupUnits : 0;
       const uint64_t words = (stride + groups + 1) << s.max_bits;
