@@ -5,6 +5,8 @@ memory and for the current stream.  There is no fallback: if the library is miss
 """
 import ctypes
 import os
+import threading
+import weakref
 
 import torch
 
@@ -103,20 +105,74 @@ def _dev(t, dtype):
         raise TypeError("need a contiguous CUDA tensor of %s" % dtype)
 
 
-PINNED_MOST = 64 << 20   # bytes of one answer that are copied through pinned memory
+PINNED_MOST = 64 << 20    # bytes of one answer that are copied through pinned memory
+PINNED_HELD = 256 << 20   # bytes of pinned memory that the answers a program still holds may take together
+
+
+class _PinnedAnswers:
+    """How much pinned memory the answers take that are still held, so that a program which keeps its answers does not
+    pin the host's memory without bound.  Shared by all tables and threads."""
+
+    def __init__(self):
+        self.lock, self.held = threading.RLock(), 0   # (a collection inside `take` may run a release)
+
+    def take(self, nbytes):
+        """True if nbytes more may be pinned; they are given back with `release`."""
+        with self.lock:
+            if self.held + nbytes > PINNED_HELD:
+                return False
+            self.held += nbytes
+            return True
+
+    def release(self, nbytes):
+        with self.lock:
+            self.held -= nbytes
+
+
+_pinned = _PinnedAnswers()
+
+
+def _pinned_bytes(t):
+    """What torch's pool of pinned memory takes for a tensor: whole powers of two."""
+    n = t.numel() * t.element_size()
+    return 1 << (n - 1).bit_length() if n else 0
+
+
+def _pinned_like(tensors):
+    """A pinned host tensor for each device tensor (the caller owes _pinned.release for each); None if that would be too
+    much, or if the host has none to give."""
+    if sum(t.numel() * t.element_size() for t in tensors.values()) > PINNED_MOST:
+        return None
+    nbytes = sum(map(_pinned_bytes, tensors.values()))
+    if not _pinned.take(nbytes):
+        return None
+    try:
+        return {name: torch.empty(t.shape, dtype=t.dtype, pin_memory=True) for name, t in tensors.items()}
+    except RuntimeError:
+        _pinned.release(nbytes)
+        return None
 
 
 def _to_numpy(tensors):
     """Device tensors as host numpy arrays.  An answer of moderate size lands in pinned memory (torch's pool, which
     takes it back with the arrays) by asynchronous copies: 0.2 ms for 11 MB where pageable copies took 1.3 ms.  A large
-    one takes the pageable way: it is no business of a dump to pin gigabytes of the host."""
-    if sum(t.numel() * t.element_size() for t in tensors.values()) > PINNED_MOST:
+    one takes the pageable way, and so does every one while the program holds PINNED_HELD bytes of earlier ones: it is no
+    business of a dump to pin gigabytes of the host."""
+    host = _pinned_like(tensors)
+    if host is None:
         return {name: t.cpu().numpy() for name, t in tensors.items()}
-    host = {name: torch.empty(t.shape, dtype=t.dtype, pin_memory=True).copy_(t, non_blocking=True)
-            for name, t in tensors.items()}
-    for device in {t.device for t in tensors.values()}:
-        torch.cuda.current_stream(device).synchronize()
-    return {name: t.numpy() for name, t in host.items()}
+    try:
+        for name, t in tensors.items():
+            host[name].copy_(t, non_blocking=True)
+        for device in {t.device for t in tensors.values()}:
+            torch.cuda.current_stream(device).synchronize()
+        out = {name: t.numpy() for name, t in host.items()}
+    except BaseException:
+        _pinned.release(sum(map(_pinned_bytes, host.values())))
+        raise
+    for name, a in out.items():   # (whatever is made of the array, a view or a tensor, keeps the array's base)
+        weakref.finalize(a.base, _pinned.release, _pinned_bytes(host[name])).atexit = False
+    return out
 
 
 def mono_qr_gather_pool(table_r, table_q, ids, offsets, out=None):
