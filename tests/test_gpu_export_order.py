@@ -1,5 +1,5 @@
 """Exports come sorted by key as unsigned numbers, by a radix sort on the device over the bits in which the keys
-differ: the numbers of elements at the edges of its units, keys that differ everywhere, in the low bits only, in the
+differ: numbers of elements at the edges of its units (512 elements, or 2048), keys that differ everywhere, in the low bits only, in the
 top bits only, and a single key; attributes and rows stay with their key."""
 import numpy as np
 import pytest
@@ -48,4 +48,22 @@ def test_exports_are_in_key_order(kind, n):
     for name in ("keys", "row", "rows", "acc"):
         assert (touched[name] == dump[name]).all()
     assert tab.mono_export_touched(with_values=False)["n"] == 0
+    tab.close()
+
+
+@pytest.mark.parametrize("kind", ["all", "low"])
+@pytest.mark.parametrize("n", [511, 512, 513, 400000, 400001, 524289])
+def test_exports_around_the_edges_of_both_unit_sizes(kind, n):
+    """Units of 512 elements up to 400 000 exported keys, of 2048 beyond."""
+    from paper_2209_07663_amd.binding import Table
+    dev = torch.device("cuda:0")
+    tab = Table(1 << 20, 4, 5, max_ids=1 << 20, device=dev)
+    keys = _keys(kind, n, np.random.default_rng(n)).astype(np.int64)
+    keys = np.random.default_rng(n + 1).permutation(keys)
+    rows = tab.mono_lookup_or_insert(torch.from_numpy(keys).to(dev), 3).cpu().numpy()
+    d = tab.mono_table_export()
+    order = np.argsort(keys.view(np.uint64))
+    assert (d["keys"] == keys[order]).all() and (d["row"] == rows[order]).all()
+    assert (d["rows"] == tc.init_rows(d["keys"], 4, 5).astype(np.float32)).all() and (d["last_seen"] == 3).all()
+    tc.check_placement(d, tab.capacity, 8, 5)
     tab.close()

@@ -175,7 +175,8 @@ def test_config4_full_size_as_specified_through_the_fill_limit_and_the_first_exp
 
 @pytest.mark.timeout(600)
 def test_update_with_more_than_16M_rows_in_use(say):
-    """Beyond 2^24 rows in use the backward's sort needs a fourth pass (25 bits in passes of seven).
+    """Beyond 2^24 rows in use the backward sorts by digits of nine bits (three passes for 25 bits, where digits of
+    eight would need four).
     17 M keys are admitted on both sides (threshold 1, dim 4 keeps the oracle small), then one batch
     whose occurrences reach rows over the whole range — every 64th key once, the lowest and highest
     rows many times, absent and padding keys — is trained and the whole table compared."""

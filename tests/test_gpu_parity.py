@@ -284,7 +284,7 @@ def test_long_stretches_of_empty_bags(dev):
 
 
 def test_sweeps_of_a_sparse_table_find_keys_that_come_back_to_emptied_buckets(dev):
-    """A sweep only looks at buckets that a bitmap does not prove empty.  Keys are admitted into a large,
+    """A sweep only looks at buckets that may hold a key that is too old.  Keys are admitted into a large,
     almost empty table, expire (their buckets empty out), a later sweep notes those buckets as empty, the
     same keys come back into the same buckets, and expire again: every sweep must report exactly what
     the oracle reports, and a capacity below one bitmap word (16 slots) works like any other."""
@@ -367,11 +367,13 @@ def test_hot_key_gradient_reduction_is_pairwise(dev):
 
 @pytest.mark.parametrize("stored", [255, 256, 257, 65535, 65536, 65537, 65538])
 def test_update_at_the_sort_width_boundaries(dev, stored):
-    """The backward sorts bit_length(highest row in use) bits, in passes of at most eight: with 256 /
-    257 and 65536 / 65537 rows in use the digit plan changes (one pass -> two -> three).  Exactly
+    """The backward sorts bit_length(highest row in use) bits, in as few passes as the digits of its shape
+    allow: with 256 / 257 rows in use one pass becomes two, with 65536 / 65537 two narrow digits become two
+    wide ones (three narrow ones in batches of more than 2^17 pairs: tests/test_gpu_sort_few.py).  Exactly
     `stored` keys are admitted, then a batch over all of them (every key once, the first and the
-    last rows many times, some absent keys) is trained and compared with the oracle."""
-    # stored = highest row + 1: 256 -> 8 bits, 257 -> 9 bits (two passes), 65536 -> 16, 65537 -> 17 (three)
+    last rows many times, some absent keys) is trained and compared with the oracle.  The batches of the first
+    three are small enough for the kernel that makes all passes in LDS."""
+    # stored = highest row + 1: 256 -> 8 bits, 257 -> 9 bits (two passes), 65536 -> 16, 65537 -> 17
     from paper_2209_07663_amd.binding import Table
     seed, dim, cap = 71, 4, 1 << 18
     tab = Table(cap, dim, seed, freq_threshold=2, max_ids=1 << 17, max_bags=1 << 17, device=dev)

@@ -259,13 +259,14 @@ def test_many_calls_queued_without_a_wait_then_updates(dev):
 
 
 @pytest.mark.parametrize("expire_steps", [0, 5])
-@pytest.mark.parametrize("n", [1000, 65 * 1024, 65 * 1024 + 1, 4 * 65 * 256 + 7])
+@pytest.mark.parametrize("n", [1000, 4097, 65 * 1024, 65 * 1024 + 1, 4 * 65 * 256 + 7, 1 << 19, 513 * 1024, 577 * 1024 + 1])
 def test_every_occurrence_a_new_key_fills_the_winner_lists_to_the_brim(dev, n, expire_steps):
     """Batches made of distinct new keys only, admitted on first sight: every occurrence is elected, so the
     sub-lists of elected occurrences hold as much as they ever can, at batch sizes where the blocks of the
-    election kernel (256 occurrences without expiry, 1024 with) are dealt to the 64 sub-lists unevenly."""
+    election kernel (256 occurrences in batches of up to 2^19, 1024 in larger ones) are dealt to the 64 sub-lists
+    unevenly.  (At most 4096 keys never come to those lists: they have a kernel of their own.)"""
     from paper_2209_07663_amd.binding import Table
-    seed, dim, cap = 59, 4, 1 << 18
+    seed, dim, cap = 59, 4, 1 << 18 if n < 1 << 17 else 1 << 20
     tab = Table(cap, dim, seed, freq_threshold=1, expire_steps=expire_steps, max_ids=n, max_bags=n, device=dev)
     orc = Oracle(cap, dim, seed, 1, expire_steps, False, kind="cuckoo")
     keys_h = (np.random.default_rng(n).permutation(1 << 22)[:n].astype(np.int64) + 1) * 1000003
