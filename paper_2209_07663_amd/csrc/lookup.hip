@@ -246,17 +246,14 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     }
   }
   // A snapshot record is admitted whatever its counter says, and with a threshold of 0 or 1 every
-  // missing key is admissible (its count is at least 1 by now): the counter is read for another reason only then, and
-  // only where it never ages: an unsaturated count (read as min(count, 255)) must never wrap.
+  // missing key is admissible (its count is at least 1 by now): no counter is read for either.
   bool admissible[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     uint32_t cnt = leader[j] ? 255u : 0u;
-    if (!restore && leader[j] && (t.freq_threshold > 1u || t.expire_steps == 0)) {
+    if (!restore && leader[j] && t.freq_threshold > 1u) {
       for (uint32_t h = 0; h < t.filter_hashes; ++h) {  // smallest of the key's counters
-        uint32_t* w = reinterpret_cast<uint32_t*>(&t.filter[filter_index(t, k[j], h)]);
-        const uint32_t c = *w;
-        if (t.expire_steps == 0 && c > kCountGuard) atomicMin(w, 255u);
+        const uint32_t c = reinterpret_cast<const uint32_t*>(&t.filter[filter_index(t, k[j], h)])[0];
         cnt = c < cnt ? c : cnt;
       }
     }

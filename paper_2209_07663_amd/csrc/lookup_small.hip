@@ -121,15 +121,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
   const uint32_t mine = s_count;
   if (mine) {  // block-uniform
     if (tid == 0) s_base = (uint32_t)atomicAdd(&t.ctl->scratch[kSmallMisses], (unsigned long long)mine);
-    if (tid < kSmallSet && s.p.miss_cnt[tid]) {
-      const uint64_t key = s.p.miss_key[tid];
-      if (t.expire_steps == 0)
-        for (uint32_t j = 0; j < t.filter_hashes; ++j) {  // an unsaturated count must never wrap
-          uint32_t* w = reinterpret_cast<uint32_t*>(&t.filter[filter_index(t, key, j)]);
-          if (*w > kCountGuard) atomicMin(w, 255u);
-        }
-      touch_counter(t, key, step, s.p.miss_cnt[tid]);
-    }
+    if (tid < kSmallSet && s.p.miss_cnt[tid]) touch_counter(t, s.p.miss_key[tid], step, s.p.miss_cnt[tid]);
     __syncthreads();
     if (tid < mine) {
       unsigned long long* to = reinterpret_cast<unsigned long long*>(&t.win_list[s_base + tid]);

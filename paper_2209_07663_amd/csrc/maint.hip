@@ -368,6 +368,20 @@ hipError_t launch_filter_export(const TableView& t, uint32_t* d_words, uint64_t 
   return hipGetLastError();
 }
 
+// See launch_filter_cut.  Two counters per lane, 16 bytes; the few that are too large are written.
+__global__ __launch_bounds__(256) void filter_cut_kernel(TableView t) {
+  const uint64_t g = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * 2;
+  if (g >= t.n_filter) return;
+  const uint4 w = *reinterpret_cast<const uint4*>(t.filter + g);
+  if (w.x > 255u) reinterpret_cast<uint32_t*>(t.filter + g)[0] = 255u;
+  if (w.z > 255u) reinterpret_cast<uint32_t*>(t.filter + g)[2] = 255u;
+}
+
+hipError_t launch_filter_cut(const TableView& t, hipStream_t stream) {
+  hipLaunchKernelGGL(filter_cut_kernel, dim3((unsigned)((t.n_filter + 511) / 512)), dim3(256), 0, stream, t);
+  return hipGetLastError();
+}
+
 // canonical word -> the table's own form (step << 32 | count)
 __global__ __launch_bounds__(256) void filter_import_kernel(TableView t, const uint32_t* words, uint64_t first,
                                                             uint64_t count) {

@@ -18,6 +18,7 @@ struct mono_table {
   uint32_t last_sweep = 0;  // `now` of the latest sweep, and
   bool sweep_all = false;   // was there a lookup behind it since?  The bounds of the buckets then say nothing: the
                             // lookup has stamped keys, or added some, with steps that are older than the bounds allow
+  uint64_t counted = 0;     // (tables without expiry) occurrences that a counter may have taken since the counts were cut
   uint64_t seed = 0;
   uint32_t generation = 0;  // rehash generation of the placement hashes h0 / h1
   int device = 0;
@@ -398,6 +399,14 @@ int mono_lookup_or_insert(mono_table* t, const int64_t* d_keys, uint64_t n, uint
     t->tags_wrapped = true;
   }
   if (step < t->last_sweep) t->sweep_all = true;
+  if (t->view.expire_steps == 0) {
+    const uint64_t most = n * t->view.filter_hashes;  // (two hashes of a key that fall on one counter touch it twice)
+    if (t->counted + most > kCountMost) {
+      if (launch_filter_cut(t->view, (hipStream_t)stream) != hipSuccess) return MONO_EHIP;
+      t->counted = 0;
+    }
+    t->counted += most;
+  }
   const RestoreSource none = {nullptr, nullptr, nullptr};
   if (launch_lookup_or_insert(t->view, d_keys, n, step, epoch, d_rows_out, none, (hipStream_t)stream, &t->prof) != hipSuccess)
     return MONO_EHIP;  // (the table's step and call tag move on only when the call was queued)
@@ -615,6 +624,7 @@ int mono_table_migrate(mono_table* dst, mono_table* src, uint32_t generation, vo
   b.sync_epoch = a.sync_epoch;
   dst->generation = generation;
   dst->last_step = src->last_step;
+  dst->counted = src->counted;
   dst->epoch = 1;  // dst counts as used from here on (a second migration into it is refused)
   if (dst->h_mail) *dst->h_mail = (1ull << 32) | (unsigned long long)c.hwm;  // rows keep their indices: so does the mark
   // rows and their state keep their indices: copied position for position up to the high-water mark

@@ -18,10 +18,8 @@
 namespace mono {
 
 // Counts are kept unsaturated in the low half of a counter word and read as min(count, 255).  Where
-// counters age, the first touch of a batch cuts the count back to 255; where they do not, a reader
-// does so once the count has passed kCountGuard (a batch adds less than 2^28).
-constexpr uint32_t kCountGuard = 1u << 30;
-
+// counters age, the first touch of a batch cuts the count back to 255; where they do not, the host has all counts cut
+// back (launch_filter_cut) before they could have taken more than kCountMost occurrences since the last time.
 // one counter word: `times` occurrences at `step`
 __device__ inline void touch_word(const TableView& t, unsigned long long* w, uint32_t step, uint32_t times) {
   if (t.expire_steps == 0) {
