@@ -133,9 +133,12 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
 //             30.7 at a tenth absent, 41.4 and 36.3 when all are; 200 K 20.7 / 23.9, 38.7 / 36.3, 53.6 / 48.3.  Keys that
 //             are new and admitted at once (threshold 0 or 1) do not count: their insertion reads the buckets anyway, and
 //             finds them in the L2 where the probe has just been (200 K new keys 91.7 us without the look, 96.3 with it)
-//   larger ones  all that missed, from 5 in 16 on.  4 M keys, threshold 3: 112 / 184 us when all are known, 196 / 218 at
-//             0.2 absent, 243 / 234 at 0.3, 384 / 325 at 0.6, 541 / 450 at 1; threshold 1: 425 / 422, 743 / 684, 1155 /
-//             1053; 700 K keys cross between 0.3 and 0.4 (70 / 73 and 76 / 75 us)
+//   larger ones  all that missed, from an eighth on.  What counts is how many distinct keys miss for each distinct one that
+//             is found (they break even at about one), and hot IDs are found many times: streams of Zipf IDs, where an
+//             eighth to a fifth of the occurrences miss, take 660 us of probes with the look and 730 without (26 M IDs a
+//             step, threshold 1) and 200 and 207 (6.8 M, threshold 3).  Evenly spread IDs want the line at a quarter: 4 M
+//             keys, threshold 3, 112 us without and 184 with it when all are known, 178 / 215 at a tenth absent, 196 / 218
+//             at a fifth, 243 / 234 at 0.3, 384 / 325 at 0.6, 541 / 450 at 1; threshold 1 743 / 684 and 1155 / 1053
 constexpr uint64_t kElectSmall = 1u << 19;  // largest batch whose election takes one occurrence per thread, others four
 constexpr uint64_t kSampledBlocks = 16;     // (their atomics meet at one word, and hold up the end of a small election)
 struct MissSample {
@@ -145,7 +148,7 @@ struct MissSample {
 inline MissSample miss_sample(uint64_t n, uint64_t blocks, uint64_t per_block) {
   const uint64_t every = (blocks + kSampledBlocks - 1) / kSampledBlocks, looked_at = (blocks + every - 1) / every;
   const uint64_t sampled = looked_at * per_block < n ? looked_at * per_block : n;
-  return {(uint32_t)every, sampled * (n <= kElectSmall ? 1 : 5) / 16 + 1};
+  return {(uint32_t)every, sampled * (n <= kElectSmall ? 1 : 2) / 16 + 1};
 }
 
 // The same in one kernel, for batches of at most kSmallLookup keys that are not a restore call.

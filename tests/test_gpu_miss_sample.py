@@ -24,7 +24,7 @@ def _counters_first(tab):
 @pytest.mark.parametrize("n,threshold,share,want", [
     (70000, 3, 0.02, 0), (70000, 3, 0.2, 1), (70000, 1, 1.0, 0), (70000, 0, 0.5, 0),
     (1 << 19, 3, 0.2, 1), (1 << 19, 1, 1.0, 0),
-    ((1 << 19) + 1, 3, 0.2, 0), ((1 << 19) + 1, 3, 0.5, 1), ((1 << 19) + 1, 1, 0.2, 0), ((1 << 19) + 1, 1, 0.5, 1),
+    ((1 << 19) + 1, 3, 0.1, 0), ((1 << 19) + 1, 3, 0.15, 1), ((1 << 19) + 1, 1, 0.1, 0), ((1 << 19) + 1, 1, 0.15, 1),
     ((1 << 19) + 1, 0, 1.0, 1)])
 def test_order_of_the_next_call_follows_the_misses_of_this_one(n, threshold, share, want):
     from paper_2209_07663_amd.binding import Table
