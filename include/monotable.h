@@ -165,7 +165,8 @@ int mono_apply_grad_adagrad_noalloc(mono_table* t, const int32_t* d_rows, uint64
 uint64_t mono_noalloc_max_ids(void);
 
 /* Expiry (section 2.1, second heuristic): removes every key with now - last_seen >= expire_steps
- * (nothing if expire_steps == 0) and frees its row.
+ * (nothing if expire_steps == 0) and frees its row.  Lookups are held to non-decreasing steps among themselves; one whose
+ * step lies behind the latest sweep is served, and costs the next sweep a look at every bucket that holds something.
  *   d_n_expired     nullable; receives the number of keys removed by this call
  *   d_expired_keys  nullable; receives up to max_expired of the removed keys, in no particular order */
 int mono_expire_sweep(mono_table* t, uint32_t now, uint64_t* d_n_expired, int64_t* d_expired_keys,

@@ -15,8 +15,8 @@
 // thousand of them: 64 where that still leaves kWavesWanted waves (the index loads are then as coalesced
 // as they can be), else as few as one round needs (33 K bags of dim 512: one wave per 64 bags was 512
 // waves on 256 compute units).
-// Large batches are bound by the rows and pooled rows that move behind the L2 (4.1-4.2 TB/s at 6.8 M and
-// 26 M IDs, of the 4.9 TB/s a plain copy reaches).
+// Large batches are bound by the rows and pooled rows that move behind the L2 (4.7 TB/s at 6.8 M IDs, 5.5 at 26 M, of
+// the 6.2 that a plain copy reaches to consecutive addresses).
 // Summation is in occurrence order, in fp32.
 //
 // Where the rows come from is a policy of the kernel:
