@@ -12,9 +12,12 @@
 // together instead (81 -> 69 us on the workload with one ID per bag).
 //
 // How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
-// thousand of them: 64 where that still leaves kWavesWanted waves (the index loads are then as coalesced
-// as they can be), else as few as one round needs (33 K bags of dim 512: one wave per 64 bags was 512
-// waves on 256 compute units).
+// thousand of them: 64, where that still leaves kWavesWanted waves (the index loads are then as coalesced as they can be),
+// else as few as one round needs (33 K bags of dim 512: one wave per 64 bags was 512 waves on 256 compute units).
+// Never more than 4 (8 with eight elements per lane) where a row takes a whole wave: a wave of many rounds lasts long, and
+// the chip is idle beside the last ones (249 K bags of one ID, fp32 dim 512, gather and update 491 -> 441 us; 293 K bags of
+// four, dim 256, 215 -> 205).  Two tables, for the same reason, 32 bags where 8 lanes share a row, 16 where 16 or 32 do
+// (500 K bags of four, dim 32 67 -> 56 us, dim 64 159 -> 135, dim 128 272 -> 227; smaller dims the same with 64 and 32).
 // Large batches are bound by the rows and pooled rows that move behind the L2 (4.7 TB/s at 6.8 M IDs, 5.5 at 26 M, of
 // the 6.2 that a plain copy reaches to consecutive addresses).
 // Summation is in occurrence order, in fp32.
@@ -30,7 +33,7 @@
 
 namespace mono {
 
-constexpr int kIdsInRegs = 8;
+constexpr int kIdsInRegs = 8;  // (four where two tables' rows are read: see QuotRemRows)
 // Positions in a bag, and the IDs of a bag that count.  The walk of a bag steps up to kIdsInRegs past its last ID, and
 // a signed step that wrapped there read in front of the caller's IDs (only the two dense tables take calls of so many).
 // 64-bit positions would hold more, but their registers cost the two-table kernel a wave in four (329 -> 399 us).
@@ -85,7 +88,7 @@ __device__ inline void load_piece(Piece<E, N>& p, const E* rows, uint64_t row, u
 
 template <typename E, int N_>
 struct TableRows {
-  static constexpr int N = N_;
+  static constexpr int N = N_, kIds = kIdsInRegs;
   using Id = int32_t;
   const E* rows;
   const int32_t* idx;
@@ -101,9 +104,12 @@ struct TableRows {
   __device__ void fetch(Row& x, Id r, uint32_t dim, uint32_t col) const { load_piece(x.p, rows, (uint32_t)r, dim, col); }
 };
 
-template <typename E, int N_>
+// kIds_: IDs of a bag whose rows, two each, are in flight together.  Four: with eight their registers leave four waves to
+// a SIMD instead of six (bf16: five and eight).  Eight where bags are long, on average, since each step of the walk waits
+// for the one before (see kQrBag).
+template <typename E, int N_, int kIds_>
 struct QuotRemRows {
-  static constexpr int N = N_;
+  static constexpr int N = N_, kIds = kIds_;
   using Id = int64_t;
   const E* rem;    // E_r: 2^m rows
   const E* quot;   // E_q: 2^m rows
@@ -149,7 +155,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
                                                           bool past_caches, float* __restrict__ out) {
   using Id = typename Src::Id;
   using Row = typename Src::Row;
-  constexpr int N = Src::N;
+  constexpr int N = Src::N, kIds = Src::kIds;
   const uint64_t wave = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const uint64_t bag_base = wave << bags_log2;
   if (bag_base >= n_bags) return;  // wave-uniform
@@ -163,15 +169,15 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   s = s < 0 ? 0 : s;
   e = e > (int64_t)n ? (int64_t)n : e;
   const int len = e > s ? (int)(e - s > (int64_t)kMostInBag ? (int64_t)kMostInBag : e - s) : 0;
-  Id id[kIdsInRegs];
+  Id id[kIds];
 #pragma unroll
-  for (int j = 0; j < kIdsInRegs; ++j) id[j] = j < len ? src.at(s + j) : src.none();
+  for (int j = 0; j < kIds; ++j) id[j] = j < len ? src.at(s + j) : src.none();
   // phase 2: group <-> bag, one bag per group and round
   const uint32_t group = 1u << group_log2, l = lane & (group - 1u), g = lane >> group_log2;
   const uint32_t bags_per_round = 64u >> group_log2, rounds = (1u << bags_log2) >> (6u - group_log2);
   // Short bags (one or two IDs each, as in one-hot slots): a round keeps only one or two rows per
   // lane in flight, so four rounds are issued together instead.
-  constexpr int kShort = 2, kRoundsTogether = kIdsInRegs / kShort;
+  constexpr int kShort = 2, kRoundsTogether = kIds / kShort;
   int longest = len;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) longest = max(longest, __shfl_xor(longest, d));
@@ -209,24 +215,24 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
       const uint32_t col = col0 + l * N;
       const bool active = col < dim;
       float acc[N] = {0.f};
-      Id rid[kIdsInRegs];
+      Id rid[kIds];
 #pragma unroll
-      for (int j = 0; j < kIdsInRegs; ++j) rid[j] = __shfl(id[j], from);
+      for (int j = 0; j < kIds; ++j) rid[j] = __shfl(id[j], from);
       for (BagPos c = 0;;) {
-        Row v[kIdsInRegs];
+        Row v[kIds];
 #pragma unroll
-        for (int j = 0; j < kIdsInRegs; ++j) {
+        for (int j = 0; j < kIds; ++j) {
           v[j].clear();
           if (src.present(rid[j]) && active) src.fetch(v[j], rid[j], dim, col);
         }
-        c += kIdsInRegs;
+        c += kIds;
         const bool more = c < blen;
         if (more) {  // a long bag: its next indices, straight from memory (the group's lanes ask for the same words)
 #pragma unroll
-          for (int j = 0; j < kIdsInRegs; ++j) rid[j] = c + j < blen ? src.at(bs + c + j) : src.none();
+          for (int j = 0; j < kIds; ++j) rid[j] = c + j < blen ? src.at(bs + c + j) : src.none();
         }
 #pragma unroll
-        for (int j = 0; j < kIdsInRegs; ++j) v[j].add_to(acc);
+        for (int j = 0; j < kIds; ++j) v[j].add_to(acc);
         if (!more) break;
       }
       if (bag < n_bags && active) store_pooled<N>(out + bag * dim + col, acc, past_caches);
@@ -246,22 +252,25 @@ constexpr uint64_t kPooledCached = 192ull << 20;
 struct GatherShape {
   uint32_t group_log2 = 0, bags_log2 = 6;
   bool past_caches;
-  dim3 grid;
-  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags)
+  uint64_t waves;
+  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags, uint32_t ids = kIdsInRegs)
       : past_caches(n_per_lane == 4 && n_bags * dim * sizeof(float) > kPooledCached) {
     while (group_log2 < 6 && (n_per_lane << group_log2) < dim) ++group_log2;
+    if (group_log2 == 6)
+      bags_log2 = n_per_lane == 4 ? 2 : 3;
+    else if (group_log2 >= 3 && ids < (uint32_t)kIdsInRegs)
+      bags_log2 = group_log2 == 3 ? 5 : 4;
     while (bags_log2 > 6 - group_log2 && (n_bags >> bags_log2) < kWavesWanted) --bags_log2;
-    const uint64_t waves = (n_bags + (1ull << bags_log2) - 1) >> bags_log2;
-    grid = dim3((unsigned)((waves + 3) / 4));
+    waves = (n_bags + (1ull << bags_log2) - 1) >> bags_log2;
   }
 };
 
 template <typename Src>
 static hipError_t queue_gather(const Src& src, const int64_t* d_offsets, uint64_t n_bags, uint64_t n, uint32_t dim,
                                float* d_out, hipStream_t stream, Profiler* prof) {
-  const GatherShape sh(dim, Src::N, n_bags);
-  MONO_LAUNCH(prof, K_GATHER_POOL, stream, gather_pool_kernel<Src>, sh.grid, dim3(256), src, d_offsets, n_bags, n, dim,
-              sh.group_log2, sh.bags_log2, sh.past_caches, d_out);
+  const GatherShape sh(dim, Src::N, n_bags, Src::kIds);
+  MONO_LAUNCH(prof, K_GATHER_POOL, stream, gather_pool_kernel<Src>, dim3((unsigned)((sh.waves + 3) / 4)), dim3(256), src,
+              d_offsets, n_bags, n, dim, sh.group_log2, sh.bags_log2, sh.past_caches, d_out);
   return hipGetLastError();
 }
 
@@ -281,16 +290,26 @@ hipError_t launch_gather_pool(const TableView& t, const int32_t* d_rows, uint64_
   return queue_gather(TableRows<uint16_t, 4>{rows, d_rows, cap}, d_offsets, n_bags, n, t.dim, d_out, stream, prof);
 }
 
+// Average bags from which on eight IDs' rows are in flight.  With eight and with four: 6.8 M Zipf IDs in bags of four,
+// dim 32, 327 and 278 us; 0.4 to 8 M IDs in bags of two to five, dims 64 to 512, 15 to 50 % longer with eight; bags of 16
+// and 30, uniform IDs, dims 16 and 64, 150 and 159, 62 and 63, 141 and 145; 3037 bags of 28, dim 128, 19.6 and 20.5.  bf16
+// rows of up to 32 elements are short of neither registers nor waves: bags of five, dim 16 376 and 390, of two, dim 32, 45 and 38.
+constexpr uint64_t kQrBag = 12, kQrBagNarrow = 3;
+
 hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t log2_rows, uint32_t dim, bool bf16,
                                  const int64_t* d_ids, uint64_t n, const int64_t* d_offsets, uint64_t n_bags,
                                  float* d_out, hipStream_t stream) {
   if (n_bags == 0) return hipSuccess;
-  if (!bf16)
-    return queue_gather(QuotRemRows<float, 4>{(const float*)d_rem, (const float*)d_quot, d_ids, log2_rows}, d_offsets,
-                        n_bags, n, dim, d_out, stream, nullptr);
+  const bool eight = n / n_bags >= (bf16 && dim <= 32 ? kQrBagNarrow : kQrBag);
+  const auto queue = [&](const auto& src) { return queue_gather(src, d_offsets, n_bags, n, dim, d_out, stream, nullptr); };
+  if (!bf16) {
+    const float *rem = (const float*)d_rem, *quot = (const float*)d_quot;
+    return eight ? queue(QuotRemRows<float, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows})
+               : queue(QuotRemRows<float, 4, 4>{rem, quot, d_ids, log2_rows});
+  }
   const uint16_t *rem = (const uint16_t*)d_rem, *quot = (const uint16_t*)d_quot;
-  return queue_gather(QuotRemRows<uint16_t, 4>{rem, quot, d_ids, log2_rows}, d_offsets, n_bags, n, dim, d_out, stream,
-                      nullptr);
+  return eight ? queue(QuotRemRows<uint16_t, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows})
+               : queue(QuotRemRows<uint16_t, 4, 4>{rem, quot, d_ids, log2_rows});
 }
 
 }  // namespace mono

@@ -1,0 +1,57 @@
+"""Pooling where the bags of a wave and the IDs in flight change: rows that share 4 to 64 lanes, bags whose average length
+lies on either side of the rules, numbers of bags that end inside a wave; against a plain fp64 sum."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(bags, average, space, dev):
+    """Bags of `average` IDs on average, some empty, one long; IDs outside the space count as absent."""
+    g = torch.Generator(device=dev).manual_seed(bags + average)
+    lens = torch.randint(0, 2 * average + 1, (bags,), device=dev, generator=g)
+    lens[bags // 2] += 100
+    offs = torch.zeros(bags + 1, dtype=torch.int64, device=dev)
+    torch.cumsum(lens, 0, out=offs[1:])
+    return lens, offs, torch.randint(-1, space + 1, (int(offs[-1]),), device=dev, generator=g)
+
+
+def _check(got, picked, lens):
+    bag = torch.repeat_interleave(torch.arange(lens.shape[0], device=lens.device), lens)
+    want = torch.zeros((lens.shape[0], picked.shape[1]), dtype=torch.float64, device=lens.device).index_add_(0, bag, picked)
+    size = torch.zeros_like(want).index_add_(0, bag, picked.abs())
+    # every fp32 addition rounds by at most 2^-24 of a partial sum, which the sum of the sizes bounds
+    assert ((got.double() - want).abs() <= 2.0 ** -24 * (lens[:, None] + 2) * size).all()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("dim", [16, 32, 64, 128, 256, 512])
+def test_two_tables(dim, bf16):
+    from paper_2209_07663_amd.binding import mono_qr_gather_pool
+    dev, m = torch.device("cuda:0"), 9
+    g = torch.Generator(device=dev).manual_seed(dim)
+    tabs = [torch.randn((1 << m, dim), device=dev, generator=g).to(torch.bfloat16 if bf16 else torch.float32) for _ in range(2)]
+    for bags, average in ((4099, 2), (4099, 4), (4099, 11), (4099, 13), (70001, 1)):
+        lens, offs, ids = _batch(bags, average, 1 << 2 * m, dev)
+        got = mono_qr_gather_pool(tabs[0], tabs[1], ids, offs)
+        inside = ((ids >= 0) & (ids < 1 << 2 * m))[:, None]
+        at = ids.clamp(0, (1 << 2 * m) - 1)
+        _check(got, (tabs[0].double()[at % (1 << m)] + tabs[1].double()[at >> m]) * inside, lens)
+
+
+@pytest.mark.parametrize("dim,bf16", [(64, False), (64, True), (128, False), (256, False), (256, True), (512, False), (512, True)])
+def test_one_table(dim, bf16):
+    from paper_2209_07663_amd.binding import Table
+    dev = torch.device("cuda:0")
+    tab = Table(1 << 12, dim, 3, bf16=bf16, max_ids=1 << 18, max_bags=1 << 17, device=dev)
+    tab.mono_lookup_or_insert(torch.arange(3000, dtype=torch.int64, device=dev), 0)
+    d = tab.mono_table_export()
+    rows = torch.zeros((1 << 12, dim), dtype=torch.float64, device=dev)
+    rows[torch.from_numpy(d["row"].astype("int64")).to(dev)] = torch.from_numpy(d["rows"]).to(dev).double()
+    for bags, average in ((1000, 4), (16387, 3), (66003, 1)):
+        lens, offs, at = _batch(bags, average, 1 << 12, dev)
+        at = torch.where((at >= 3000) & (at < 1 << 12), -1, at)        # (rows that were never handed out hold anything)
+        got = tab.mono_gather_pool(at.int(), offs)
+        inside = ((at >= 0) & (at < 1 << 12))[:, None]
+        _check(got, rows[at.clamp(0, (1 << 12) - 1)] * inside, lens)
+    tab.close()
