@@ -8,7 +8,7 @@
 //                group of the block (dim/4 lanes, four elements each); the group loads its chunk's pairs at once, then walks
 //                them with eight gradient rows in flight, summing grad[bag] along each run.  A run that lies
 //                inside the chunk is complete: Adagrad is applied at once.  A run that crosses a
-//                chunk border leaves a partial sum in LDS; the groups of a block then join the
+//                chunk border leaves a partial sum; a segmented scan over the block's chunks then joins the
 //                partials of runs that stay inside the block's tile (Adagrad again) and only runs
 //                that cross a BLOCK border leave partials in global memory (at most two per block)
 //   combine      one block per run that crosses block borders: adds its partials (lane groups in
@@ -18,15 +18,15 @@
 // The store that writes a row's new accumulator also carries the number of the current
 // synchronisation window: that is the row's "touched" mark (paper section 2.2.3), at no extra cost.
 //
-// Partial-slot convention (same at chunk level in LDS and at tile level in global memory): unit u
-// has slot A = 2u ("run that started before this unit and ends inside it") and slot B = 2u + 1
-// ("run that continues past the end of this unit"; flag kHeadFlag if it also starts inside it).
+// Partial slots of tile u in global memory: slot A = 2u ("run that started before this tile and ends inside it") and slot
+// B = 2u + 1 ("run that continues past the end of this tile"; flag kHeadFlag if it also starts inside it).
 #include "common.h"
 #include "kernels.h"
 
 namespace mono {
 
 constexpr uint32_t kHeadFlag = 0x80000000u;
+constexpr uint32_t kReduceWaves = 4;  // waves of a block of seg_reduce
 
 // seg_reduce reads and writes embedding rows past the caches where the batch's occurrences come to more bytes of
 // rows than the 256 MB cache behind the L2s holds: each row is used once and would not be there for the next
@@ -104,6 +104,13 @@ struct RowVec {
       v[q].w += __shfl_xor(v[q].w, (int)lanes);
     }
   }
+  __device__ inline RowVec from_up(uint32_t lanes) const {  // the share of the lane `lanes` before this one
+    RowVec o;
+#pragma unroll
+    for (int q = 0; q < SEG; ++q)
+      o.v[q] = make_float4(__shfl_up(v[q].x, lanes), __shfl_up(v[q].y, lanes), __shfl_up(v[q].z, lanes), __shfl_up(v[q].w, lanes));
+    return o;
+  }
   __device__ inline float sum_sq() const {
     float ss = 0.f;
 #pragma unroll
@@ -151,19 +158,14 @@ __device__ inline void update_row(E* rows, uint32_t row, uint32_t dim, uint32_t 
 }
 
 // Row-wise Adagrad on one row by one lane group; g = this lane's share of the gradient (zero in
-// lanes beyond dim).  acc += mean_j g_j^2; w_j -= lr * g_j / (sqrt(acc) + eps).
+// lanes beyond dim), w and acc what the row and its accumulator hold.  acc += mean_j g_j^2; w_j -= lr * g_j / (sqrt(acc) + eps).
 template <typename E, int SEG, bool PAST>
-__device__ inline void adagrad_row(const TableView& t, uint32_t row, const RowVec<SEG>& g, bool active, uint32_t l,
-                                   uint32_t group, float lr, float eps) {
+__device__ inline void adagrad_row(const TableView& t, uint32_t row, const RowVec<SEG>& w, float acc, const RowVec<SEG>& g,
+                                   bool active, uint32_t l, uint32_t group, float lr, float eps) {
   float ss = g.sum_sq();
   for (uint32_t d = 1; d < group; d <<= 1) ss += __shfl_xor(ss, (int)d);
-  const float acc = t.state[row].acc + ss / (float)t.dim;
-  const float scale = step_scale(acc, lr, eps);
-  if (active) {
-    E* rows = reinterpret_cast<E*>(t.rows);
-    const RowVec<SEG> w = load_row<E, SEG, PAST>(rows, row, t.dim, l, true);
-    update_row<E, SEG, PAST>(rows, row, t.dim, l, w, g, scale);
-  }
+  acc += ss / (float)t.dim;
+  if (active) update_row<E, SEG, PAST>(reinterpret_cast<E*>(t.rows), row, t.dim, l, w, g, step_scale(acc, lr, eps));
   if (l == 0) t.state[row] = RowState{acc, t.sync_epoch};  // trained in this window
 }
 
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
                                                          float* __restrict__ part, uint32_t* __restrict__ part_row,
                                                          uint32_t tile, uint32_t launched, uint32_t max_bits) {
   static_assert(SEG == 1 || GLOG == 6, "rows wider than 256 elements are held by a whole wave");
-  extern __shared__ float4 s_mem[];  // [2 * groups_per_block][dim / 4] vectors, the slot rows, the tile's pairs
+  extern __shared__ float4 s_mem[];  // [groups_per_block + waves][dim / 4] vectors, the tile's pairs
   using Vec = RowVec<SEG>;
   constexpr uint32_t group = 1u << GLOG, gpb = 256u >> GLOG;  // groups (= chunks) per block
   const uint32_t chunk = tile >> (8 - GLOG);
@@ -200,8 +202,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   n = t.ctl->scratch[kValidPairs];  // the sort left the dropped occurrences out
   const uint32_t g = threadIdx.x >> GLOG, l = threadIdx.x & (group - 1u);
   const uint32_t dim4 = t.dim >> 2;
-  float4* s_vec = s_mem;
-  uint32_t* s_row = reinterpret_cast<uint32_t*>(s_mem + 2 * gpb * dim4);
+  float4* s_vec = s_mem;                   // a group's partial of the run that ends in its chunk
+  float4* s_carry = s_mem + gpb * dim4;    // a wave's sum over the run that continues past its last chunk
   const uint64_t n_chunks = (n + chunk - 1) / chunk;
   const uint64_t c0 = (uint64_t)blockIdx.x * gpb;  // first chunk of this block's tile
   const uint64_t c = c0 + g;
@@ -210,7 +212,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   const float4* g4 = reinterpret_cast<const float4*>(grad);
 
   // ---- phase 0: the tile's sorted pairs -> LDS (coalesced) ---------------------------------------
-  uint2* s_pairs = reinterpret_cast<uint2*>(s_row + 2 * gpb);
+  uint2* s_pairs = reinterpret_cast<uint2*>(s_carry + kReduceWaves * dim4);
   __shared__ uint32_t s_edge[2];  // rows of the pairs before and after the tile (asked for with the pairs, not after them)
   {
     const uint64_t t0 = (uint64_t)blockIdx.x * tile;
@@ -227,7 +229,11 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   __syncthreads();
 
   // ---- phase 1: every group reduces the runs of its chunk -------------------------------------
-  uint32_t a_row = kNoRow, b_row = kNoRow;
+  uint32_t a_row = kNoRow;      // the run that started before this chunk and ends in it
+  uint32_t b_row = kNoRow;      // the run that continues past the end of this chunk,
+  bool b_head = false;          // and does it start in this chunk?
+  Vec sum;
+  sum.zero();
   if (c < n_chunks) {
     const uint64_t cs = c * chunk;
     const uint32_t count = (uint32_t)(n - cs < chunk ? n - cs : chunk);
@@ -238,8 +244,6 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     const bool first_head_in = cs == 0 || before != first;
     uint32_t run = first;
     bool head_in = first_head_in;
-    Vec sum;
-    sum.zero();
     E* rows = reinterpret_cast<E*>(t.rows);
     const float inv_dim = 1.0f / (float)t.dim;
     for (uint32_t p0 = 0; p0 < count; p0 += kBatch) {  // position of the batch in the chunk
@@ -287,59 +291,85 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
               if (l == 0) t.state[run] = RowState{acc, t.sync_epoch};
             } else if (run < hwm) {  // started in an earlier chunk, ends here
               a_row = run;
-              store_vec<SEG>(s_vec + (2 * g) * dim4, l, active, sum);
+              store_vec<SEG>(s_vec + g * dim4, l, active, sum);
             }
           }
         }
       }
     }
-    if (after == run && run < hwm) {  // the last run continues in the next chunk
-      b_row = run | (head_in ? kHeadFlag : 0u);
-      store_vec<SEG>(s_vec + (2 * g + 1) * dim4, l, active, sum);
+    if (after == run && run < hwm) {
+      b_row = run;
+      b_head = head_in;
     }
-  }
-  if (l == 0) {
-    s_row[2 * g] = a_row;
-    s_row[2 * g + 1] = b_row;
   }
   if (threadIdx.x == 0) {
     part_row[2 * (uint64_t)blockIdx.x] = kNoRow;
     part_row[2 * (uint64_t)blockIdx.x + 1] = kNoRow;
   }
-  __syncthreads();
 
   // ---- phase 2: join the chunk partials of runs inside this tile -------------------------------
-  // The group holding the first piece of a run within the tile walks the following chunks.
-  float4* part4 = reinterpret_cast<float4*>(part);
-  const bool walker = c < n_chunks && b_row != kNoRow && ((b_row & kHeadFlag) || g == 0);
-  if (walker) {
-    const uint32_t row = b_row & ~kHeadFlag;
-    const bool head_in_tile = (b_row & kHeadFlag) != 0;
-    Vec sum = load_vec<SEG>(s_vec + (2 * g + 1) * dim4, l, active);
-    uint32_t cc = g + 1;
-    bool tail = false;
-    while (cc < chunks_here) {
-      if (s_row[2 * cc] == row) {  // the run ends in chunk cc
-        sum.add(load_vec<SEG>(s_vec + (2 * cc) * dim4, l, active));
-        tail = true;
-        break;
+  // A segmented inclusive scan over the chunks: afterwards `sum` of a chunk whose last run continues is that run's sum
+  // from its start in the tile on.  The chunks of a wave by shuffles, then the waves through LDS.  (The group with the
+  // first piece of a run walked the chunks that follow, one after the other, before: with a hot row in the tile 256 steps
+  // for rows of dim 4, 64 for dim 16.  Whole training steps: 58 K IDs of dim 4 99 -> 58 us, 64 K of dim 8 76 -> 56, 264 K
+  // of dim 8 103 -> 79, 2 M of dim 4 240 -> 184, 204 K of dim 16 86 -> 77; from dim 36 on the same.)
+  if (b_row == kNoRow) sum.zero();
+  __shared__ uint32_t s_flags[kReduceWaves];
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+  const bool joins = a_row != kNoRow && g > 0;  // what it joins is asked for beside the scan
+  const E* rows = reinterpret_cast<const E*>(t.rows);
+  const Vec w = load_row<E, SEG, PAST>(rows, a_row, t.dim, l, joins && active);
+  const float acc = joins ? t.state[a_row].acc : 0.f;
+  // bit 0: the run comes from the chunk before those summed so far; bit 1: its head is in the tile
+  uint32_t flags = (b_row != kNoRow && !b_head && g > 0 ? 1u : 0u) | (b_head ? 2u : 0u);
+  if (__ballot(flags & 1u)) {  // wave-uniform
+#pragma unroll
+    for (uint32_t d = group; d < 64; d <<= 1) {
+      const Vec before = sum.from_up(d);
+      const uint32_t flags_before = __shfl_up(flags, d);
+      if (lane >= d && (flags & 1u)) {
+        sum.add(before);
+        flags = flags_before;
       }
-      if (s_row[2 * cc + 1] != row) break;  // (cannot happen for consistent slots)
-      sum.add(load_vec<SEG>(s_vec + (2 * cc + 1) * dim4, l, active));
-      ++cc;
-    }
-    if (tail && head_in_tile) {
-      adagrad_row<E, SEG, PAST>(t, row, sum, active, l, group, lr, eps);
-    } else {
-      const uint64_t slot = 2 * (uint64_t)blockIdx.x + (tail ? 0 : 1);
-      store_vec<SEG>(part4 + slot * dim4, l, active, sum);
-      if (l == 0) part_row[slot] = tail ? row : (row | (head_in_tile ? kHeadFlag : 0u));
     }
   }
-  // a run that entered the tile from before and ends in chunk 0 is the tile's A partial as it stands
-  if (g == 0 && c < n_chunks && a_row != kNoRow) {
-    store_vec<SEG>(part4 + (2 * (uint64_t)blockIdx.x) * dim4, l, active, load_vec<SEG>(s_vec, l, active));
-    if (l == 0) part_row[2 * (uint64_t)blockIdx.x] = a_row;
+  if (lane >= 64 - group) store_vec<SEG>(s_carry + wave * dim4, l, active, sum);
+  if (lane == 63) s_flags[wave] = flags;
+  __syncthreads();
+  if (!__ballot(a_row != kNoRow || b_row != kNoRow)) return;  // no run of this wave crosses a border of its chunks
+  Vec prev;  // the same sum of the chunk before this one
+  prev.zero();
+  uint32_t flags_prev = 0;
+  for (uint32_t v = wave; v > 0; --v) {  // (wave-uniform)
+    prev.add(load_vec<SEG>(s_carry + (v - 1) * dim4, l, active));
+    flags_prev = s_flags[v - 1];
+    if (!(flags_prev & 1u)) break;
+  }
+  if (flags & 1u) {
+    sum.add(prev);
+    flags = flags_prev;
+  }
+  if (group < 64) {
+    const Vec up = sum.from_up(group);
+    const uint32_t flags_up = __shfl_up(flags, group);
+    if (lane >= group) {
+      prev = up;
+      flags_prev = flags_up;
+    }
+  }
+  float4* part4 = reinterpret_cast<float4*>(part);
+  if (a_row != kNoRow) {
+    prev.add(load_vec<SEG>(s_vec + g * dim4, l, active));  // (nothing comes before the first chunk)
+    if (g > 0 && (flags_prev & 2u)) {
+      adagrad_row<E, SEG, PAST>(t, a_row, w, acc, prev, active, l, group, lr, eps);
+    } else {  // it entered the tile from before
+      store_vec<SEG>(part4 + (2 * (uint64_t)blockIdx.x) * dim4, l, active, prev);
+      if (l == 0) part_row[2 * (uint64_t)blockIdx.x] = a_row;
+    }
+  }
+  if (g == chunks_here - 1 && b_row != kNoRow) {
+    store_vec<SEG>(part4 + (2 * (uint64_t)blockIdx.x + 1) * dim4, l, active, sum);
+    if (l == 0) part_row[2 * (uint64_t)blockIdx.x + 1] = b_row | (flags & 2u ? kHeadFlag : 0u);
   }
 }
 
@@ -390,6 +420,8 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(TableView t, uint64_t n
   const uint32_t dim4 = t.dim >> 2;
   const bool active = l < dim4;
   const float4* part4 = reinterpret_cast<const float4*>(part);
+  const Vec w = load_row<E, SEG, false>(reinterpret_cast<const E*>(t.rows), row, t.dim, l, g == 0 && active);
+  const float acc = t.state[row].acc;
   Vec sum;
   sum.zero();
   const auto slot_of = [&](uint64_t p) { return p <= mid ? 2 * (c + p) + 1 : 2 * tail; };
@@ -415,7 +447,7 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(TableView t, uint64_t n
     Vec total;
     total.zero();
     for (uint32_t q = 0; q < used; ++q) total.add(load_vec<SEG>(s_mem + q * dim4, l, active));
-    adagrad_row<E, SEG, false>(t, row, total, active, l, group, lr, eps);
+    adagrad_row<E, SEG, false>(t, row, w, acc, total, active, l, group, lr, eps);
   }
 }
 
@@ -435,7 +467,7 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
   const uint64_t n_tiles = (n + tile - 1) / tile;
   if (n_tiles > ws.tiles) return hipErrorInvalidValue;  // (cannot happen: the workspace is made for this rule)
   const dim3 block(256), grid((unsigned)n_tiles);
-  const size_t lds_reduce = 2 * gpb * (t.dim / 4) * sizeof(float4) + 2 * gpb * sizeof(uint32_t) + tile * sizeof(uint2);
+  const size_t lds_reduce = (gpb + kReduceWaves) * (t.dim / 4) * sizeof(float4) + tile * sizeof(uint2);
   const size_t lds_combine = kCombineWide / 64 * (t.dim / 4) * sizeof(float4);  // (enough for either block)
 #define MONO_SEG_REDUCE_AS(E, GLOG, SEG, PAST)                                                                        \
   MONO_LAUNCH_SMEM(prof, K_SEG_REDUCE, stream, (seg_reduce_kernel<E, GLOG, SEG, PAST>), grid, block, lds_reduce, t,     \
