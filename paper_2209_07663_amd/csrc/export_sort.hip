@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kThreads) void export_scatter_kernel(const uint64_t
     at += c;
   }
   __syncthreads();
-  volatile uint32_t* off = cnt[wave];
+  uint32_t* off = cnt[wave];
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) {
     const bool valid = base + (uint64_t)r * 64 + lane < n;
@@ -181,14 +181,15 @@ __global__ __launch_bounds__(kThreads) void export_scatter_kernel(const uint64_t
       const uint64_t vote = __ballot(bit);
       peers &= bit ? vote : ~vote;
     }
+    const uint32_t at = wave_load(off + digit);
     if (valid) {
-      const uint32_t p = off[digit] + (uint32_t)__popcll(peers & lanes_below());
+      const uint32_t p = at + (uint32_t)__popcll(peers & lanes_below());
       s_key[p] = key[r];
       s_idx[p] = idx[r];
     }
-    __builtin_amdgcn_wave_barrier();
-    if (valid && (peers & lanes_below()) == 0) off[digit] += (uint32_t)__popcll(peers);
-    __builtin_amdgcn_wave_barrier();
+    wave_order();
+    if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
+    wave_order();
   }
   __syncthreads();
   const uint64_t ubase = (uint64_t)blockIdx.x * kUnit;

@@ -100,12 +100,12 @@ __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t n
   }
   const uint32_t total = __shfl(inc, 63);
   if (total == 0) return;  // wave-uniform
-  volatile uint16_t* list = s_list[wave];  // the buckets to look at, of the wave's
+  uint16_t* list = s_list[wave];  // the buckets to look at, of the wave's
   {
     uint32_t at = inc - (uint32_t)__popc(look);
-    for (uint32_t m = look; m; m &= m - 1) list[at++] = (uint16_t)(lane * (4 * kWords) + (uint32_t)__ffs((int)m) - 1u);
+    for (uint32_t m = look; m; m &= m - 1) wave_store(list + at++, (uint16_t)(lane * (4 * kWords) + (uint32_t)__ffs((int)m) - 1u));
   }
-  __builtin_amdgcn_wave_barrier();
+  wave_order();
   const uint32_t out = (uint32_t)wave_id & (kWinLists - 1);  // sub-list of this wave
   constexpr int kTurns = 8;  // buckets per group of eight lanes with their meta words (64 bytes) in flight
   for (uint32_t e0 = 0; e0 < total; e0 += 8 * kTurns) {
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t n
     for (int r = 0; r < kTurns; ++r) {
       const uint32_t e = e0 + 8u * (uint32_t)r + grp;
       m[r] = kNoMeta;
-      if (e < total) m[r] = t.buckets[bucket0 + list[e]].meta[l8];
+      if (e < total) m[r] = t.buckets[bucket0 + wave_load(list + e)].meta[l8];
     }
     uint64_t gone[kTurns];
     uint32_t found = 0;
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t n
 #pragma unroll
       for (int d = 1; d < 8; d <<= 1) least = min(least, __shfl_xor(least, d));
       if (e < total && l8 == 0) {
-        const uint64_t b = bucket0 + list[e];
+        const uint64_t b = bucket0 + wave_load(list + e);
         // (a key from the future, seen after `now`: nothing is known)
         const uint32_t age = least == 0xFFFFFFFFu ? kAgeEmpty : (least > now ? kAgeLook : sweep_unit(least, t.sweep_q));
         reinterpret_cast<uint8_t*>(t.oldest)[b] = (uint8_t)age;
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t n
 #pragma unroll
     for (int r = 0; r < kTurns; ++r) {
       if ((gone[r] >> lane) & 1ull) {
-        const uint64_t b = bucket0 + list[e0 + 8u * (uint32_t)r + grp];
+        const uint64_t b = bucket0 + wave_load(list + e0 + 8u * (uint32_t)r + grp);
         t.sweep_list[(uint64_t)out * t.sweep_cap + p + (uint32_t)__popcll(gone[r] & lanes_below())] =
             keep_slots ? (uint32_t)(b * kBucket + l8) : meta_row(m[r]);
         if (!keep_slots) {

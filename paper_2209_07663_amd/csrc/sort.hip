@@ -376,16 +376,16 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   //    `lds` is the wave's digit counts
   uint32_t rank[S::kRounds];  // digit << 16 | rank
   {
-    volatile uint32_t* off = lds[wave];
+    uint32_t* off = lds[wave];
 #pragma unroll
     for (uint32_t r = 0; r < S::kRounds; ++r) {
       const bool valid = kv[r].x != 0xFFFFFFFFu;
       const uint32_t digit = (kv[r].x >> shift) & mask;
       const uint64_t peers = same_digit_lanes<kBits>(digit, bits, valid);
-      rank[r] = (digit << 16) | (off[digit] + (uint32_t)__popcll(peers & lanes_below()));
-      __builtin_amdgcn_wave_barrier();
-      if (valid && (peers & lanes_below()) == 0) off[digit] += (uint32_t)__popcll(peers);
-      __builtin_amdgcn_wave_barrier();
+      rank[r] = (digit << 16) | (wave_load(off + digit) + (uint32_t)__popcll(peers & lanes_below()));
+      wave_order();
+      if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, (rank[r] & 0xFFFFu) + (uint32_t)__popcll(peers));
+      wave_order();
     }
   }
   static_assert(kItems <= 0x10000, "rank and digit share a word");
@@ -559,10 +559,10 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
       for (uint32_t r = 0; r < kSmallRounds; ++r)
         kv[r] = r < rounds && i0 + r * 64 < count ? pairs[i0 + r * 64] : make_uint2(0xFFFFFFFFu, 0u);
     }
-    volatile uint32_t* off = cnt[wave];
+    uint32_t* off = cnt[wave];
 #pragma unroll
-    for (uint32_t b = 0; b < kBins; b += 64) off[b + lane] = 0;
-    __builtin_amdgcn_wave_barrier();
+    for (uint32_t b = 0; b < kBins; b += 64) wave_store(off + b + lane, 0u);
+    wave_order();
     uint32_t rank[kSmallRounds];  // digit << 16 | rank among the wave's elements of the digit
 #pragma unroll
     for (uint32_t r = 0; r < kSmallRounds; ++r) {
@@ -571,10 +571,10 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
         const bool valid = kv[r].x != 0xFFFFFFFFu;
         const uint32_t digit = (kv[r].x >> shift) & mask;
         const uint64_t peers = same_digit_lanes<kSortNarrowBits>(digit, bits, valid);
-        rank[r] = (digit << 16) | (off[digit] + (uint32_t)__popcll(peers & lanes_below()));
-        __builtin_amdgcn_wave_barrier();
-        if (valid && (peers & lanes_below()) == 0) off[digit] += (uint32_t)__popcll(peers);
-        __builtin_amdgcn_wave_barrier();
+        rank[r] = (digit << 16) | (wave_load(off + digit) + (uint32_t)__popcll(peers & lanes_below()));
+        wave_order();
+        if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, (rank[r] & 0xFFFFu) + (uint32_t)__popcll(peers));
+        wave_order();
       }
     }
     __syncthreads();  // every wave has counted, and has its pairs in registers
