@@ -46,6 +46,7 @@ constexpr int kMissTag = 7;                 // Control::scratch slots: tag of th
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
 constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
+constexpr int kHotBins = 13;                // Control::scratch slot: rows with a bin of their own (see sort_split.hip)
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
 
 struct StashEntry {
@@ -226,5 +227,17 @@ __device__ inline void wave_order() {
 
 __device__ inline unsigned lane_id() { return __lane_id(); }
 __device__ inline uint64_t lanes_below() { return (1ull << lane_id()) - 1ull; }
+
+// Inclusive sum over the lanes of a wave, by moves between registers (a shuffle goes through LDS: 130 cycles a step).
+// Called by whole waves.
+__device__ inline uint32_t wave_sums(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);  // the lane before, of the row of 16
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);  // two before
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // last lane of the row before, rows 1 and 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // last lane of row 1, rows 2 and 3
+  return x;
+}
 
 }  // namespace mono

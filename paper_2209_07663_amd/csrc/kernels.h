@@ -27,9 +27,7 @@ struct UpdateWorkspace {
 // From the size of the batch: how many elements a block owns.  Large batches want long shares of a bin (8
 // elements on average: 2048 per narrow block, 4096 per wide one).  Small ones are bound by the chain of
 // latencies of one block, which its elements lengthen, and have too few blocks to fill the chip: a scatter of
-// 26 K pairs takes 11.1 / 8.2 / 6.4 us with 2048 / 1024 / 512 elements per block, one of 204 K 10.8 / 8.0 / 7.0,
-// one of 690 K 12.0 / 9.9 / 10.5 (there the histograms, one word per bin and block, begin to cost more), one
-// of 1 M 12.9 / 12.5 / 12.8.
+// 26 K pairs takes 11.1 / 8.2 / 6.4 us with 2048 / 1024 / 512 elements per block, one of 204 K 10.8 / 8.0 / 7.0.
 // Where the batch is small and two digits of up to 11 bits save a pass of narrow ones (2^16 to 2^22 rows in use), they
 // are taken, three launches fewer; but their histograms are 2^digit words per block, so that how small depends on the
 // digit.  Update of dim 16, two digits / three narrow ones, from 512 words (300 K rows in use) to 2048 (3.9 M):
@@ -37,23 +35,25 @@ struct UpdateWorkspace {
 //   300 K, 1 M rows   45 / 49 us    50 / 54       54 / 56       56 / 57       58 / 63, 66 / 65
 //   1.3 M             49 / 51       57 / 58       61 / 59       66 / 60
 //   3.9 M             52 / 53       61 / 59       66 / 60       72 / 62
-// And batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch instead of nine.
+// Batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch, and those of up to kSplitMost in two
+// (below): of such batches only those of at most kSortSmall pairs in more than twice as many bags come here.  (One block or
+// split: steps of 2.3 and 3 K pairs 42.5 and 43.6, 37.5 and 40.3 us, of 4.3 K 52 and 49, of 7.1 K 51 and 45.)
 struct SortShape {
   uint32_t max_bits, items;
 };
 constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9, kSortFewBits = 11;
 constexpr uint32_t kSortNarrowMaxRows = 1u << 24;  // beyond this many rows in use the wide shape saves a pass
-constexpr uint64_t kSortItems512 = 400000, kSortItems1024 = 1u << 20;  // largest batches of those block sizes
+constexpr uint64_t kSortItems512 = 400000;  // largest batch of that block size
 constexpr uint64_t kSortFewMost = 1u << 17;  // largest batch with two digits of at most 10 bits, halved for each bit more
 constexpr uint32_t kSortFewRowsAbove = 1u << 16, kSortFewRows10 = 1u << 20, kSortFewMaxRows = 1u << 22;
 inline uint64_t sort_few_most(uint32_t rows) {
   return rows <= kSortFewRows10 ? kSortFewMost : (rows <= 2 * kSortFewRows10 ? kSortFewMost / 2 : kSortFewMost / 4);
 }
-constexpr uint64_t kSortSmall = 8192;
+constexpr uint64_t kSortSmall = 4096;
 inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
   if (hwm_bound > kSortFewRowsAbove && hwm_bound <= kSortFewMaxRows && n <= sort_few_most(hwm_bound)) return {kSortFewBits, 512u};
-  if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, n <= kSortItems1024 ? 1024u : 4096u};
-  return {kSortNarrowBits, n <= kSortItems512 ? 512u : (n <= kSortItems1024 ? 1024u : 2048u)};
+  if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, 4096u};
+  return {kSortNarrowBits, n <= kSortItems512 ? 512u : 2048u};
 }
 // Pairs of a tile of the reduction: kReduceTile, halved while that leaves fewer than kTilesWanted tiles, as long as a
 // lane group (gpb of them in a block) keeps eight pairs to have in flight together.
@@ -75,12 +75,43 @@ inline uint32_t reduce_tile(uint64_t n, uint32_t gpb) {
 constexpr uint64_t sort_units(uint64_t n, uint32_t items) { return (n + items - 1) / items; }
 constexpr uint32_t kSortGroupedAbove = 1024, kSortGroupUnits = 4;  // units of more elements come in groups (see sort_hist_kernel)
 inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // units in whole groups, or in whole 16-byte pieces
-// words of the histogram workspace for batches of at most n elements, whatever the shape: a histogram per unit, one
-// per group, the bin totals
-inline uint64_t sort_hist_words(uint64_t n) {
+// Batches of more than kSortSmall and at most kSplitMost pairs are split and sorted by bucket (sort_split.hip), in one of
+// four sizes: pairs of a unit, occurrences drawn (a row drawn kSplitHits times has a bin of its own), most buckets (of
+// about 512 pairs, where that is not too many), threads of a block that splits.  The sample has to find what would not
+// fit into a bin (4096 pairs, with the bin's other rows): rows of 1.6 % of 128 K pairs, 0.4 % of a million; a row of twice
+// that is missed once in a thousand times.  600 K to a million pairs with units of 1024 instead of 2048 (twice the units
+// to collect from) take 20 us longer, with blocks of 256 threads instead of 512 5 to 8; 200 K with samples of 512 25 us
+// of `bucket` instead of 12 (too large bins).  Four neighbouring rows in a bucket: 60 to 600 K pairs 0 to 3 % of the
+// step faster than with one; a million pairs (rows that were handed out together are hot together) 330 and 294 us.
+constexpr uint64_t kSplitMost = 1u << 20;
+constexpr uint32_t kSplitSizes = 4, kSplitHits = 4, kSplitTurn = 4096;
+constexpr uint64_t kSplitUpTo[kSplitSizes] = {1u << 16, 1u << 17, 1u << 19, kSplitMost};
+constexpr uint32_t kSplitItems[kSplitSizes] = {512, 512, 1024, 2048}, kSplitSamples[kSplitSizes] = {512, 1024, 1024, 2048};
+constexpr uint32_t kSplitBuckets[kSplitSizes] = {256, 256, 512, 1024};
+constexpr int kSplitThreads[kSplitSizes] = {256, 256, 256, 512};
+struct SplitShape {
+  uint32_t size, buckets_log2, group_log2;
+};
+inline SplitShape split_shape_for(uint64_t n) {
+  uint32_t size = 0, lg = 3;
+  while (n > kSplitUpTo[size]) ++size;
+  while ((512ull << lg) < n && (1u << lg) < kSplitBuckets[size]) ++lg;
+  return {size, lg, size < 3 ? 2u : 0u};
+}
+inline uint64_t split_words(uint64_t n) {  // shares of all bins in all units and the list of turns, for batches of at most n elements
   uint64_t most = 0;
-  const uint64_t sizes[] = {n, n < kSortFewMost ? n : kSortFewMost, n < kSortItems512 ? n : kSortItems512,
-                            n < kSortItems1024 ? n : kSortItems1024};
+  for (uint32_t i = 0; i < kSplitSizes && (i == 0 || n > kSplitUpTo[i - 1]); ++i) {
+    const uint64_t m = n < kSplitUpTo[i] ? n : kSplitUpTo[i], hot = kSplitSamples[i] / kSplitHits;
+    const uint64_t words = sort_units(m, kSplitItems[i]) * (kSplitBuckets[i] + hot) + 2 + 2 * (hot + m / kSplitTurn);
+    most = words > most ? words : most;
+  }
+  return most;
+}
+// words of the histogram workspace for batches of at most n elements, whatever the shape: a histogram per unit, one
+// per group, the bin totals; or the shares of a split
+inline uint64_t sort_hist_words(uint64_t n) {
+  uint64_t most = split_words(n);
+  const uint64_t sizes[] = {n, n < kSortFewMost ? n : kSortFewMost, n < kSortItems512 ? n : kSortItems512};
   for (const uint64_t m : sizes)
     for (const uint32_t rows : {kSortFewRows10, kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
       const SortShape s = sort_shape_for(rows, m);
@@ -173,6 +204,11 @@ hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t
 hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                                      const int64_t* d_offsets, uint64_t n_bags, const float* d_grad, float lr, float eps,
                                      uint32_t hwm_bound, hipStream_t stream, Profiler* prof);
+
+// Groups the (row, bag) pairs of a batch of more than kSortSmall and at most kSplitMost pairs by row; the result is in
+// pair_b, the number of pairs in the control block's scratch.
+hipError_t launch_split_pairs(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
+                              const int64_t* d_offsets, uint64_t n_bags, hipStream_t stream, Profiler* prof);
 
 // Stable LSD radix sort of the (row, bag) pairs of a batch; the result is in pair_b if the plan for
 // the device's high-water mark (digits of at most *max_bits bits) has an odd number of passes, else in pair_a.

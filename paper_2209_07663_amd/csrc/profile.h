@@ -14,6 +14,8 @@ enum KernelId {
   K_RESOLVE,
   K_LOOKUP_SMALL,
   K_GATHER_POOL,
+  K_SORT_SPLIT,
+  K_SORT_BUCKET,
   K_SORT_HIST,
   K_SORT_SCAN,
   K_SORT_SCATTER,
@@ -27,8 +29,8 @@ enum KernelId {
 
 inline const char* kernel_name(int id) {
   static const char* names[K_COUNT] = {"probe_count", "admit_elect", "insert", "resolve",   "lookup_small",
-                                       "gather_pool", "sort_hist",   "sort_scan",    "sort_scatter", "seg_reduce",
-                                       "combine",     "sweep_find",  "sweep_remove", "sweep_end"};
+                                       "gather_pool", "sort_split",  "sort_bucket",  "sort_hist",   "sort_scan",    "sort_scatter",
+                                       "seg_reduce",  "combine",     "sweep_find",   "sweep_remove", "sweep_end"};
   return id >= 0 && id < K_COUNT ? names[id] : "?";
 }
 

@@ -25,6 +25,7 @@
 // No kernel spins or waits for another block.
 #include "common.h"
 #include "kernels.h"
+#include "sort_ops.h"
 
 namespace mono {
 
@@ -41,33 +42,6 @@ struct Shape {
   static constexpr uint32_t kRounds = kPerWave / 64;
   static_assert(kBlock % 64 == 0 && kItems % (uint32_t)kBlock == 0 && kBinThreads % 64 == 0, "whole waves");
 };
-
-// Lanes of the wave that hold the same digit (of `bits` <= kBits bits) as this lane, among the lanes with valid == true.
-template <uint32_t kBits>
-__device__ inline uint64_t same_digit_lanes(uint32_t digit, uint32_t bits, bool valid) {
-  uint64_t peers = __ballot(valid);
-#pragma unroll
-  for (uint32_t b = 0; b < kBits; ++b) {
-    if (b < bits) {  // wave-uniform
-      const bool bit = (digit >> b) & 1u;
-      const uint64_t vote = __ballot(bit);
-      peers &= bit ? vote : ~vote;
-    }
-  }
-  return peers;
-}
-
-// key of occurrence i in pass 0: its row, or hwm if the occurrence was dropped
-__device__ inline uint32_t first_key(const int32_t* rows, uint64_t i, uint32_t hwm) {
-  const uint32_t r = (uint32_t)rows[i];
-  return r < hwm ? r : hwm;
-}
-
-// An offset of the caller's, bounded to the n occurrences of the batch.
-__device__ inline uint64_t bounded_offset(const int64_t* offsets, uint64_t b, uint64_t n) {
-  const int64_t o = offsets[b];
-  return o < 0 ? 0ull : ((uint64_t)o > n ? n : (uint64_t)o);
-}
 
 // The bag that holds occurrence `pos`: the last bag b with offsets[b] <= pos (offsets are non-decreasing
 // and start at 0).  Run by a whole wave: 64 probes per step, four dependent steps for two million bags.
@@ -494,9 +468,8 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   }
 }
 
-// The whole sort of a batch of at most kSortSmall pairs by one block, all passes in LDS: 9 us for 8192 pairs where the
-// three kernels of three passes and the gaps between them take 55.  The result goes where the passes over
-// memory would have left it.
+// The whole sort of a batch of at most kSortSmall pairs by one block, all passes in LDS, in one launch.  The result goes
+// where the passes over memory would have left it.
 constexpr int kSmallBlock = 1024;
 constexpr uint32_t kSmallWaves = kSmallBlock / 64, kSmallRounds = (uint32_t)kSortSmall / kSmallBlock;
 constexpr uint32_t kSmallBag = 32, kSmallLong = (uint32_t)kSortSmall / kSmallBag;  // a longer bag is a long one; room for all of them
@@ -613,7 +586,7 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
   if (tid == 0) ctl->scratch[kValidPairs] = count;
 }
 
-static_assert(sort_units(kSortItems512, 512) <= 256 * kScanFew && sort_units(kSortItems1024, 1024) <= 256 * kScanFew,
+static_assert(sort_units(kSortItems512, 512) <= 256 * kScanFew,
               "one wave scans the units of a batch without groups");
 template <uint32_t kBits, int kBlock, uint32_t kItems>
 static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
@@ -669,15 +642,10 @@ hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, cons
   if (shape.max_bits == kSortFewBits) {
     MONO_SORT(kSortFewBits, 256, 512);
   } else if (shape.max_bits == kSortWideBits) {
-    if (shape.items == 1024)
-      MONO_SORT(kSortWideBits, 512, 1024);
-    else
-      MONO_SORT(kSortWideBits, 512, 4096);
+    MONO_SORT(kSortWideBits, 512, 4096);
   } else {
     if (shape.items == 512)
       MONO_SORT(kSortNarrowBits, 256, 512);
-    else if (shape.items == 1024)
-      MONO_SORT(kSortNarrowBits, 256, 1024);
     else
       MONO_SORT(kSortNarrowBits, 256, 2048);
   }

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   // 267 / 260, 382 / 365, 498 / 476; bf16 255 / 314, 387 / 473, 535 / 738.  Batches of up to 98 K pairs the same way or
   // within 2 us)
   constexpr int kBatch = SEG > 1 ? (sizeof(E) == 2 ? 2 : 4) : ((int)group < 8 ? (int)group : 8);
-  const SortPlan plan = make_sort_plan(t.ctl->hwm, max_bits);
+  const SortPlan plan = make_sort_plan(t.ctl->hwm, max_bits ? max_bits : 32);  // (max_bits == 0: no radix passes)
   if (plan.passes > launched) {  // the host's bound on the high-water mark was too low: nothing is sorted, nothing is touched
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&t.ctl->n_lost, 1ull);
     if (threadIdx.x == 0) {
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     }
     return;
   }
-  const uint2* __restrict__ sp = plan.passes % 2 ? pair_b : pair_a;  // where the sort left its result
+  const uint2* __restrict__ sp = max_bits == 0 || plan.passes % 2 ? pair_b : pair_a;  // where the sort left its result
   const uint32_t hwm = plan.hwm;
   n = t.ctl->scratch[kValidPairs];  // the sort left the dropped occurrences out
   const uint32_t g = threadIdx.x >> GLOG, l = threadIdx.x & (group - 1u);
@@ -455,8 +455,10 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
                                      const int64_t* d_offsets, uint64_t n_bags, const float* d_grad, float lr, float eps,
                                      uint32_t hwm_bound, hipStream_t stream, Profiler* prof) {
   if (n == 0 || n_bags == 0) return hipSuccess;
-  uint32_t launched = 0, max_bits = 0;
-  hipError_t e = launch_sort_pairs(t, ws, d_rows, n, d_offsets, n_bags, hwm_bound, &launched, &max_bits, stream, prof);
+  uint32_t launched = 1, max_bits = 0;
+  hipError_t e = n > kSortSmall && n <= kSplitMost
+                     ? launch_split_pairs(t, ws, d_rows, n, d_offsets, n_bags, stream, prof)
+                     : launch_sort_pairs(t, ws, d_rows, n, d_offsets, n_bags, hwm_bound, &launched, &max_bits, stream, prof);
   if (e != hipSuccess) return e;
   uint32_t group_log2 = 0;
   while (group_log2 < 6 && (4u << group_log2) < t.dim) ++group_log2;
