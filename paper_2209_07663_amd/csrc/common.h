@@ -15,7 +15,8 @@ constexpr uint32_t kStashCap = 4096;        // homeless elements kept aside afte
 constexpr int32_t kRowAbsent = -1;          // rows_out: key not in the table
 constexpr int32_t kRowMiss = -2;            // rows_out, between the kernels of one call: missed, undecided
 // rows_out values <= -3 between the kernels of one call: duplicate of an admitted key, -occ - 3 of the occurrence
-// that was elected for it
+// that was elected for it; (batches of at most kElectSmall) of that occurrence, kRowElected - its place in its sub-list
+constexpr int32_t kRowElected = -(1 << 29);  // (a batch has at most 2^28 occurrences)
 
 // One bucket = one 128-byte line (the unit the memory system fetches): eight keys, then eight
 // `meta` words = last-seen step << 32 | row index.  A probe costs one line per bucket; the row and
@@ -46,6 +47,7 @@ constexpr int kMissTag = 7;                 // Control::scratch slots: tag of th
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
 constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
+constexpr int kInsertDone = 14;             // Control::scratch slot: sub-lists whose blocks of the insertion are done (zero between calls)
 constexpr int kHotBins = 13;                // Control::scratch slot: rows with a bin of their own (see sort_split.hip)
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
 
@@ -91,7 +93,8 @@ struct TableView {
   StashEntry* stash;         // [kStashCap]
   unsigned long long* dset;  // [dset_size] per-call dedup set: epoch << 32 | occurrence index
   Winner* win_list;          // [kWinLists * win_cap] elected occurrences
-  uint32_t* win_cnt;         // [kWinLists * kWinStride] fill of each sub-list (zero between calls)
+  uint32_t* win_cnt;         // [kWinLists * kWinStride] fill of each sub-list, and in the word beside it the blocks that are
+                             // done with the insertion (all zero between calls)
   uint64_t win_cap;
   // (tables with expiry) per bucket, for the sweep: a lower bound of the last-seen steps of its keys, in units of
   // 1 << sweep_q steps (see sweep_unit); kAgeEmpty: the bucket holds nothing; kAgeLook: nothing is known.

@@ -1,7 +1,7 @@
 // lookup_or_insert: cuckoo probe, count-before-admit, insertion with bounded eviction chain,
 // resolve (paper section 2.1; batch semantics of the build's contract).
 //
-// Four kernels per call (small batches have one kernel of their own: lookup_small.hip):
+// Three kernels per call, four where it is large (small batches have one kernel of their own: lookup_small.hip):
 //   probe_count   (thread per occurrence) hit -> row index + last-seen stamp; miss -> touch the
 //                 key's occurrence counter
 //   admit_elect   (thread per occurrence, after ALL counts) miss with counter >= threshold -> one
@@ -12,10 +12,10 @@
 //                 table's fill limit (else none is placed): take a row from the free stack by rank
 //                 (no atomics), insert the key (CAS on 64-bit key slots, eviction chain), note it
 //                 in its bucket's bound for the sweep, initialise the row with the whole wave
-//   resolve       duplicates of an admitted key pick up the row of the elected occurrence; one
-//                 thread settles the counters and reports the high-water mark of rows to the host
+//   resolve       (in batches of at most kElectSmall at the end of insert) duplicates of an admitted key pick up its
+//                 row, the counters are settled and the high-water mark of rows is reported to the host
 //
-// The same four kernels restore snapshot records (RestoreSource): every record is a forced
+// The same kernels restore snapshot records (RestoreSource): every record is a forced
 // admission whose row, accumulator and last-seen step come from the caller instead of from
 // init(seed, key) / the current step; a record whose key is already stored is refused.  The
 // migrate kernel re-inserts every stored element of one table into another (rehash / grow).
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
       found = restore ? kRowAbsent : -(int32_t)owner - 3;
     }
     s_res[ls[j]] = found;
-    if (!winner[j]) rows_out[i] = found;  // the winner keeps kRowMiss until the insertion gives it its row
+    if (!winner[j]) rows_out[i] = found;  // (the winner's word is written with its place in the list, or by the insertion)
   }
   __syncthreads();
   bool duplicate = false;
@@ -339,42 +339,62 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const uint64_t m = __ballot(winner[j]);
-    if (winner[j])
-      t.win_list[(uint64_t)list * t.win_cap + p + (uint32_t)__popcll(m & lanes_below())] =
-          Winner{k[j], (uint32_t)(i0 + (uint64_t)j * kElectBlock), 0u};
+    if (winner[j]) {
+      const uint32_t at = p + (uint32_t)__popcll(m & lanes_below());
+      const uint64_t i = i0 + (uint64_t)j * kElectBlock;
+      t.win_list[(uint64_t)list * t.win_cap + at] = Winner{k[j], (uint32_t)i, 0u};
+      if (kPer == 1) rows_out[i] = kRowElected - (int32_t)at;  // (see insert_kernel)
+    }
     p += (uint32_t)__popcll(m);
   }
 }
 
 // ---- insertion ---------------------------------------------------------------------------------
 
+// Whether the next call is to look at counters first (see MissSample).
+__device__ inline void note_sample(const TableView& t, uint64_t enough) {
+  if (enough == 0) return;
+  t.ctl->scratch[kCountersFirst] = t.ctl->scratch[kSampledMisses] >= enough;
+  t.ctl->scratch[kSampledMisses] = 0;
+}
+
 // Dense over the elected occurrences: winner number w of the call takes free_rows[free_n - 1 - w].
-template <typename E>
-__global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint32_t step, int32_t* rows_out,
-                                                     RestoreSource src) {
+// kAll (batches of at most kElectSmall): the duplicates of admitted keys take their rows here too.  The elected
+// occurrence's word in rows_out tells its place in its sub-list until it holds the row, and the number of a winner follows
+// from its place, so that nobody waits for anybody; the block that finishes last settles the counters.  A kernel of its
+// own for that is a launch more, 3 us of a call that has no miss (steps of 5 to 200 K known IDs 23 -> 19, 30 -> 28, 64 -> 60
+// us).  Large batches have it: the winners' places are a write more per new key (6.8 M IDs, a million new: election and
+// insertion 276 us, with resolve_kernel 267).
+template <typename E, bool kAll>
+__global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n, uint32_t step, uint32_t epoch,
+                                                        int32_t* rows_out, RestoreSource src, uint64_t enough) {
   // Keys that find both of their buckets full wait here until the block has placed the others: an eviction is a
   // dozen dependent accesses, and one lane in twenty that needs it (load 0.7) would hold up every wave.
-  constexpr uint32_t kWaiting = 256;
-  __shared__ unsigned long long s_key[kWaiting], s_meta[kWaiting];
-  __shared__ uint32_t s_waiting;
+  // (The list has room for all the keys of four rounds, after which it is worked off.)
+  constexpr uint32_t kListRounds = 4;
+  __shared__ unsigned long long s_key[256 * kListRounds], s_meta[256 * kListRounds];
+  __shared__ uint32_t s_waiting, s_last;
   if (threadIdx.x == 0) s_waiting = 0;
   __syncthreads();
   const uint32_t lane = lane_id();
   const uint32_t unit = src.seen ? kAgeLook : sweep_unit(step, t.sweep_q);
   // inclusive prefix of the sub-list fills, one list per lane
-  uint32_t inc = t.win_cnt[lane * kWinStride];
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(inc, d);
-    if ((int)lane >= d) inc += y;
+  const uint32_t inc = wave_sums(t.win_cnt[lane * kWinStride]), total = __shfl(inc, 63);
+  if (total == 0) {  // nothing to place or to settle (a duplicate needs an elected occurrence)
+    if (kAll && blockIdx.x == 0 && threadIdx.x == 0) {
+      if (t.hwm_mail && epoch % kPostEvery == 0) post_hwm(t, epoch, t.ctl->hwm);
+      note_sample(t, enough);
+    }
+    return;
   }
-  const uint32_t total = __shfl(inc, 63);
-  const int32_t free0 = t.ctl->free_n;  // settled by the resolve kernel, constant here
+  const int32_t free0 = t.ctl->free_n;  // settled when all blocks are done, constant until then
+  const uint32_t hwm0 = t.ctl->hwm;
   // all of the call's new keys fit under the fill limit, or none of them is placed
   const bool room = (int64_t)total <= rows_on_offer(t.capacity, free0);
   const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t w0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); w0 < total; w0 += stride) {
-    const uint32_t w = w0 + lane;
+  uint32_t round = 0;
+  for (uint32_t b0 = blockIdx.x * blockDim.x; b0 < total; b0 += stride) {  // block-uniform
+    const uint32_t w = b0 + threadIdx.x;
     const bool valid = w < total;
     // sub-list of w: the first list whose inclusive prefix exceeds w
     uint32_t lo = 0, hi = 64;
@@ -400,12 +420,8 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint32_t st
         const unsigned long long meta = make_meta(row, src.seen ? src.seen[e.occ] : step);
         if (!claim_free(t, k, meta, unit)) {
           const uint32_t at = atomicAdd(&s_waiting, 1u);
-          if (at < kWaiting) {
-            s_key[at] = k;
-            s_meta[at] = meta;
-          } else {
-            cuckoo_insert(t, k, meta, unit);
-          }
+          s_key[at] = k;
+          s_meta[at] = meta;
         }
         if (src.values && t.expire_steps == 0) {
           // a restored key counts as seen freq_threshold times: its counters are raised to that
@@ -420,32 +436,72 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint32_t st
       }
     }
     init_new_rows<E>(t, valid && row != kNoRow, k, row, occ, src);
+    if (++round == kListRounds || b0 + stride >= total) {
+      __syncthreads();
+      for (uint32_t q = threadIdx.x; q < s_waiting; q += blockDim.x) cuckoo_insert(t, s_key[q], s_meta[q], unit);
+      __syncthreads();
+      if (threadIdx.x == 0) s_waiting = 0;
+      __syncthreads();
+      round = 0;
+    }
+  }
+  if constexpr (!kAll) return;
+  if (t.ctl->scratch[kDuplicateTag] == epoch) {  // (else every missing key of the call occurred once, or was not admitted)
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ((n + 63) & ~63ull); i += stride) {  // wave-uniform
+      const int32_t v = i < n ? rows_out[i] : kRowAbsent;
+      const bool duplicate = v <= -3 && v > kRowElected;
+      if (!__ballot(duplicate)) continue;
+      const uint64_t owner = duplicate ? (uint64_t)(-(int64_t)v - 3) : 0;
+      const int32_t o = duplicate ? rows_out[owner] : kRowAbsent;
+      const uint32_t list = (uint32_t)(owner / kElectBlock) & (kWinLists - 1);  // (a block of the election appends to one)
+      const uint32_t before = __shfl(inc, (int)(list > 0 ? list - 1 : 0));
+      if (duplicate) {
+        int32_t row = o;  // the row, or kRowAbsent, if the elected occurrence has it by now
+        if (o <= kRowElected) {
+          const uint32_t w = (list > 0 ? before : 0u) + (uint32_t)(kRowElected - o);
+          row = room ? (int32_t)t.free_rows[free0 - 1 - (int32_t)w] : kRowAbsent;
+        }
+        rows_out[i] = row;
+      }
+    }
+  }
+  // (Many blocks count themselves on the lists' 64 lines first, and the last of each line on one word: one word alone would
+  // serialise thousands of them at ~12 ns each.)
+  constexpr uint32_t kCountedAtOnce = 128;
+  __syncthreads();  // every wave has read the counters
+  if (threadIdx.x == 0) {
+    const uint32_t lines = gridDim.x <= kCountedAtOnce ? 1u : kWinLists, line = blockIdx.x & (lines - 1);
+    const uint32_t blocks = (gridDim.x - line + lines - 1) / lines;  // that count themselves here
+    s_last = atomicAdd(&t.win_cnt[line * kWinStride + 1], 1u) == blocks - 1 &&
+             (lines == 1 || atomicAdd(&t.ctl->scratch[kInsertDone], 1ull) == (unsigned long long)lines - 1);
   }
   __syncthreads();
-  const uint32_t waiting = s_waiting < kWaiting ? s_waiting : kWaiting;
-  for (uint32_t w = threadIdx.x; w < waiting; w += blockDim.x) cuckoo_insert(t, s_key[w], s_meta[w], unit);
+  if (!s_last || threadIdx.x >= kWinLists) return;
+  t.win_cnt[lane * kWinStride] = 0;
+  t.win_cnt[lane * kWinStride + 1] = 0;
+  if (threadIdx.x == 0) {
+    t.ctl->scratch[kInsertDone] = 0;
+    settle_call(t, total, free0, hwm0, epoch);
+    note_sample(t, enough);
+  }
 }
 
+// (large batches) Duplicates of admitted keys, and what insert_kernel settles for the others.
 __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, int32_t* rows_out, uint32_t epoch,
                                                       uint64_t enough) {
-  if (t.ctl->scratch[kDuplicateTag] == epoch) {  // (else every missing key of the call occurred once, or was not admitted)
+  if (t.ctl->scratch[kDuplicateTag] == epoch) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
       const int32_t v = rows_out[i];
       if (v <= -3) rows_out[i] = rows_out[-(int64_t)(v + 3)];  // (the elected occurrence has its row, or kRowAbsent, by now)
     }
   }
-  if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // settle the counters of this call (the insert kernel has finished)
-    uint32_t total = t.win_cnt[threadIdx.x * kWinStride];
+  if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // (the insert kernel has finished)
+    const uint32_t total = __shfl(wave_sums(t.win_cnt[threadIdx.x * kWinStride]), 63);
     t.win_cnt[threadIdx.x * kWinStride] = 0;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) total += __shfl_xor(total, d);
     if (threadIdx.x == 0) {
-      settle_call(t, total, t.ctl->free_n, epoch);
-      if (enough) {
-        t.ctl->scratch[kCountersFirst] = t.ctl->scratch[kSampledMisses] >= enough;
-        t.ctl->scratch[kSampledMisses] = 0;
-      }
+      settle_call(t, total, t.ctl->free_n, t.ctl->hwm, epoch);
+      note_sample(t, enough);
     }
   }
 }
@@ -486,11 +542,21 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
   else
     MONO_LAUNCH(prof, K_ADMIT_ELECT, stream, admit_elect_kernel<4>, egrid, block, t, d_keys, n, epoch, d_rows_out, restore,
                 sample.every);
-  if (t.bf16)
-    MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<uint16_t>, igrid, block, t, step, d_rows_out, src);
-  else
-    MONO_LAUNCH(prof, K_INSERT, stream, insert_kernel<float>, igrid, block, t, step, d_rows_out, src);
-  MONO_LAUNCH(prof, K_RESOLVE, stream, resolve_kernel, igrid, block, t, n, d_rows_out, epoch, sample.enough);
+#define MONO_INSERT(E, all) \
+  MONO_LAUNCH(prof, K_INSERT, stream, (insert_kernel<E, all>), igrid, block, t, n, step, epoch, d_rows_out, src, sample.enough)
+  if (n <= kElectSmall) {
+    if (t.bf16)
+      MONO_INSERT(uint16_t, true);
+    else
+      MONO_INSERT(float, true);
+  } else {
+    if (t.bf16)
+      MONO_INSERT(uint16_t, false);
+    else
+      MONO_INSERT(float, false);
+    MONO_LAUNCH(prof, K_RESOLVE, stream, resolve_kernel, igrid, block, t, n, d_rows_out, epoch, sample.enough);
+  }
+#undef MONO_INSERT
   if (restore) hipLaunchKernelGGL(count_refused_kernel, grid, block, 0, stream, t, n, d_rows_out);
   return hipGetLastError();
 }

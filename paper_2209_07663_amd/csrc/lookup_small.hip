@@ -20,7 +20,6 @@
 
 namespace mono {
 
-constexpr uint32_t kSmallPostEvery = 16;  // (far fewer than the calls that the host keeps on record)
 constexpr int kSmallThreads = 1024, kSmallKeysPerBlock = 256;
 constexpr uint32_t kSmallSet = 2 * kSmallKeysPerBlock;  // slots of a block's set of missing keys
 static_assert(kSmallThreads == 4 * kSmallKeysPerBlock, "two keys per group of eight lanes");
@@ -146,7 +145,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
   if (missed == 0) {
     // (the mark has not moved; the host only wants to hear of a call now and then, and the store over the bus holds
     // the kernel's end: 7.5 -> 6.9 us for 1700 known keys)
-    if (tid == 0 && t.hwm_mail && epoch % kSmallPostEvery == 0) post_hwm(t, epoch);
+    if (tid == 0 && t.hwm_mail && epoch % kPostEvery == 0) post_hwm(t, epoch, t.ctl->hwm);
     return;
   }
   uint32_t slots = 64;
@@ -211,6 +210,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
     total += s_wave[w];
   }
   const int32_t free0 = t.ctl->free_n;
+  const uint32_t hwm0 = t.ctl->hwm;
   // all of the call's new keys fit under the fill limit, or none of them is placed
   const bool room = (int64_t)total <= rows_on_offer(t.capacity, free0);
 #pragma unroll
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
       }
       init_new_rows<E>(t, w < total, key, row, 0u, none);
     }
-  if (tid == 0) settle_call(t, total, free0, epoch);
+  if (tid == 0) settle_call(t, total, free0, hwm0, epoch);
 }
 
 hipError_t launch_lookup_small(const TableView& t, const int64_t* d_keys, uint64_t n, uint32_t step, uint32_t epoch,

@@ -222,24 +222,27 @@ __device__ inline void init_new_rows(const TableView& t, bool ok_lane, uint64_t 
   }
 }
 
+// A small call that has not moved the mark tells the host only now and then: the store over the bus holds the kernel's end.
+constexpr uint32_t kPostEvery = 16;  // (far fewer than the calls that the host keeps on record)
+
 // Tells the host the high-water mark of rows after call `epoch` (it reads the word when it pleases; the mark
 // only ever grows, so a stale value is a safe one).
-__device__ inline void post_hwm(const TableView& t, uint32_t epoch) {
-  __hip_atomic_store(t.hwm_mail, ((unsigned long long)epoch << 32) | (unsigned long long)t.ctl->hwm, __ATOMIC_RELAXED,
+__device__ inline void post_hwm(const TableView& t, uint32_t epoch, uint32_t hwm) {
+  __hip_atomic_store(t.hwm_mail, ((unsigned long long)epoch << 32) | (unsigned long long)hwm, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Settles the counters of a call that elected `total` new keys when free0 rows were free (one thread, after
-// everybody has read free_n).
-__device__ inline void settle_call(const TableView& t, uint32_t total, int32_t free0, uint32_t epoch) {
+// Settles the counters of a call that elected `total` new keys when free0 rows were free and the mark was hwm0 (one
+// thread, after everybody has read free_n; it reads nothing itself, which would be one more trip to memory at the end).
+__device__ inline void settle_call(const TableView& t, uint32_t total, int32_t free0, uint32_t hwm0, uint32_t epoch) {
   const uint32_t offer = (uint32_t)rows_on_offer(t.capacity, free0);
   const uint32_t got = total <= offer ? total : 0u;  // all of the call's new keys or none
   t.ctl->free_n = free0 - (int32_t)got;
   const uint32_t in_use = (uint32_t)t.capacity - (uint32_t)(free0 - (int32_t)got);
-  if (in_use > t.ctl->hwm) t.ctl->hwm = in_use;  // rows are handed out in ascending order
-  if (t.hwm_mail) post_hwm(t, epoch);
-  t.ctl->n_admitted += got;
-  t.ctl->n_full += total - got;
+  if (in_use > hwm0) t.ctl->hwm = in_use;  // rows are handed out in ascending order
+  if (t.hwm_mail) post_hwm(t, epoch, in_use > hwm0 ? in_use : hwm0);
+  if (got) atomicAdd(&t.ctl->n_admitted, (unsigned long long)got);
+  if (total - got) atomicAdd(&t.ctl->n_full, (unsigned long long)(total - got));
 }
 
 }  // namespace mono
