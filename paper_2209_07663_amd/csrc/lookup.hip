@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   // Keys that find both of their buckets full wait here until the block has placed the others: an eviction is a
   // dozen dependent accesses, and one lane in twenty that needs it (load 0.7) would hold up every wave.
   // (The list has room for all the keys of four rounds, after which it is worked off.)
-  constexpr uint32_t kListRounds = 4;
+  constexpr uint32_t kListRounds = 4, kLeastSpan = 8;
   __shared__ unsigned long long s_key[256 * kListRounds], s_meta[256 * kListRounds];
   __shared__ uint32_t s_waiting, s_last;
   if (threadIdx.x == 0) s_waiting = 0;
@@ -392,10 +392,16 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   // all of the call's new keys fit under the fill limit, or none of them is placed
   const bool room = (int64_t)total <= rows_on_offer(t.capacity, free0);
   const uint32_t stride = gridDim.x * blockDim.x;
+  // How many winners a wave takes at a time: fewer than 64 where that would leave waves without any.  A new row's values
+  // are hashes, 130 cycles of a wave for 64 of them, so that 64 rows of dim 128 hold one wave for 10 us while others have
+  // none.  Training steps with 64 throughout and with this: 4.3 K IDs, most new, dim 128 79 -> 62 us; 26 K of dim 64
+  // 69 -> 65; 690 K of dim 32 161 -> 152; 78 K of dim 16 in bf16 292 -> 283.  Less than eight is not faster.
+  uint32_t span = 64;
+  while (span > kLeastSpan && total <= gridDim.x * 2 * span) span >>= 1;
   uint32_t round = 0;
-  for (uint32_t b0 = blockIdx.x * blockDim.x; b0 < total; b0 += stride) {  // block-uniform
-    const uint32_t w = b0 + threadIdx.x;
-    const bool valid = w < total;
+  for (uint32_t b0 = blockIdx.x * 4 * span; b0 < total; b0 += gridDim.x * 4 * span) {  // block-uniform
+    const uint32_t w = b0 + (threadIdx.x >> 6) * span + lane;
+    const bool valid = lane < span && w < total;
     // sub-list of w: the first list whose inclusive prefix exceeds w
     uint32_t lo = 0, hi = 64;
 #pragma unroll
@@ -435,8 +441,8 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
         }
       }
     }
-    init_new_rows<E>(t, valid && row != kNoRow, k, row, occ, src);
-    if (++round == kListRounds || b0 + stride >= total) {
+    init_new_rows<E>(t, valid && row != kNoRow, span, k, row, occ, src);
+    if (++round == kListRounds || b0 + gridDim.x * 4 * span >= total) {
       __syncthreads();
       for (uint32_t q = threadIdx.x; q < s_waiting; q += blockDim.x) cuckoo_insert(t, s_key[q], s_meta[q], unit);
       __syncthreads();
@@ -519,7 +525,8 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
   const int restore = src.values != nullptr;
   if (!restore && n <= kSmallLookup) return launch_lookup_small(t, d_keys, n, step, epoch, d_rows_out, stream, prof);
   const dim3 block(256), grid((unsigned)((n + 255) / 256));
-  const dim3 igrid(grid.x < 2048u ? grid.x : 2048u);
+  const uint64_t iblocks = (n + 63) / 64;
+  const dim3 igrid((unsigned)(iblocks < 2048 ? iblocks : 2048));
   {
     uint64_t turns = t.expire_steps == 0 ? 1 : n / ((uint64_t)kProbeBlock * kProbeBlocksWanted);
     turns = turns < 1 ? 1 : (turns > kProbeMaxTurns ? kProbeMaxTurns : turns);

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
         row = (uint32_t)s.f.row[x];
         cuckoo_insert(t, key, make_meta(row, step), sweep_unit(step, t.sweep_q));
       }
-      init_new_rows<E>(t, w < total, key, row, 0u, none);
+      init_new_rows<E>(t, w < total, 64u, key, row, 0u, none);
     }
   if (tid == 0) settle_call(t, total, free0, hwm0, epoch);
 }

@@ -189,10 +189,10 @@ __device__ inline void store_init4<uint16_t>(uint16_t* rows, uint64_t idx, float
 
 // The wave initialises its new rows together: a group of dim/4 lanes per row (at most the whole wave, which
 // then walks the row in pieces of 256 elements), four elements per lane, 64/group rows at a time, stored as
-// whole 16-byte (fp32) or 8-byte (bf16) pieces.  Called by a whole wave; ok: this lane has a new row `row`
-// for key k, `occ` is the record it comes from (src.values != nullptr) or unused.
+// whole 16-byte (fp32) or 8-byte (bf16) pieces.  Called by a whole wave; ok: this lane, one of the first `lanes`, has a new
+// row `row` for key k, `occ` is the record it comes from (src.values != nullptr) or unused.
 template <typename E>
-__device__ inline void init_new_rows(const TableView& t, bool ok_lane, uint64_t k, uint32_t row, uint32_t occ,
+__device__ inline void init_new_rows(const TableView& t, bool ok_lane, uint32_t lanes, uint64_t k, uint32_t row, uint32_t occ,
                                      const RestoreSource& src) {
   const uint32_t lane = lane_id();
   E* rows = reinterpret_cast<E*>(t.rows);
@@ -202,7 +202,7 @@ __device__ inline void init_new_rows(const TableView& t, bool ok_lane, uint64_t 
   if (__ballot(ok_lane) == 0) return;  // wave-uniform
   const uint64_t mine = mix64(k ^ t.s_init);
   const uint32_t row_or_none = ok_lane ? row : kNoRow;
-  for (uint32_t q = 0; q < group; ++q) {
+  for (uint32_t q = 0; q * per_round < lanes; ++q) {
     const int from = (int)(q * per_round + gi);
     const uint64_t base_h = __shfl(mine, from);
     const uint32_t rr = __shfl(row_or_none, from);
