@@ -41,8 +41,10 @@ constexpr int kExportBits = 9;              // Control::scratch slots (two): OR 
 constexpr int kValidPairs = 2;              // Control::scratch slot: (row, bag) pairs kept by the sort
 constexpr int kRefusedRecords = 3;          // Control::scratch slot: records refused by the running restore call
 
-constexpr int kSmallMisses = 4;             // Control::scratch slots of the one-kernel lookup (zero between calls):
-constexpr int kSmallDone = 5;               // missing occurrences so far, blocks that have finished their probes
+constexpr int kSmallMisses = 4;             // Control::scratch slots of the one-kernel lookup: missing occurrences so far, blocks
+constexpr int kSmallDone = 5;               // that have finished their probes and their misses (zero between calls);
+constexpr int kSmallGo = 15;                // tag << 32 | number of new rows, of the latest such call with misses; the next
+constexpr int kSmallNext = 16;              // chunk of them that nobody has taken yet
 constexpr int kMissTag = 7;                 // Control::scratch slots: tag of the latest call in which an occurrence missed,
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
@@ -79,7 +81,7 @@ struct Control {
   uint32_t hwm;              // every row index ever handed out is below this high-water mark
   uint32_t swept;            // step of the latest sweep
   unsigned long long n_admitted, n_expired, n_insert_failed, n_lost, n_full, max_chain;
-  unsigned long long scratch[16];  // per-call scalars, indexed by the constants above
+  unsigned long long scratch[20];  // per-call scalars, indexed by the constants above
 };
 
 // Everything a kernel needs to know about a table; passed by value.

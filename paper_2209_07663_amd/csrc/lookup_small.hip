@@ -3,24 +3,31 @@
 // The general path is four kernels, because counting, election, placement and resolution each need the one
 // before finished on the whole chip.  A batch of a few thousand keys is nothing but their latency: 1700 keys
 // that the table knows took 5.4 + 1.8 + 2.1 + 2.8 us in four kernels and about as much again between them.
-// Here every block probes 256 keys with 1024 threads (eight lanes per key, both of its buckets requested at
+// Here every block probes 128 keys with 512 threads (eight lanes per key, both of its buckets requested at
 // once: a small batch has no bandwidth to save), stamps the hits, counts the misses, and hands the missing
 // occurrences to the block that finishes last, which elects, places and resolves them alone, with the set of
 // distinct missing keys in LDS.  A batch without misses, the usual one when serving, ends with the probe.
+// (Known keys, GPU time of a call of 200, 1088 and 4096 with 256 keys and 1024 threads: 4.7, 5.2, 5.3 us; with 128 and 512:
+// 4.3, 4.6, 4.7; with 64 and 256: 4.5, 4.6, 5.0.)
 // 4096 is where one block's work on a batch that misses throughout still costs no more than the launches
 // it saves.
 //
 // Blocks run on different XCDs, whose L2s are not coherent for ordinary accesses.  What a block leaves for
 // the last one in this same kernel (missing occurrences, counters, last-seen stamps that an eviction may
 // move) goes through agent-scope atomics, and a block reports itself done only after its waves have waited
-// for theirs.  Nobody waits for another block.
+// for theirs.  Only the first values of new rows are not left to that block: they are hashes, 20 us of one block for a
+// thousand rows of dim 128.  Blocks that know of a miss when they finish stay, look for the list of new rows and share it
+// (1088 IDs of dim 128, half of them new: 70 -> 60 us for a training step).  They wait a bounded time, and nothing depends
+// on them: every block has counted itself done before it waits, and a list that nobody helps with the last block does.
 #include "common.h"
 #include "kernels.h"
 #include "table_ops.h"
 
 namespace mono {
 
-constexpr int kSmallThreads = 1024, kSmallKeysPerBlock = 256;
+constexpr int kSmallThreads = 512, kSmallKeysPerBlock = 128;
+constexpr uint32_t kSmallChunk = 16;   // new rows that a wave initialises at a time
+constexpr int kSmallPolls = 4096;      // looks of a waiting block at the last block's word: some milliseconds
 constexpr uint32_t kSmallSet = 2 * kSmallKeysPerBlock;  // slots of a block's set of missing keys
 static_assert(kSmallThreads == 4 * kSmallKeysPerBlock, "two keys per group of eight lanes");
 constexpr int kSmallPerThread = (int)(kSmallLookup / kSmallThreads);
@@ -36,6 +43,28 @@ struct SmallFinish {
   uint32_t slot[2 * kSmallLookup];       // set of distinct missing keys (number of the first occurrence); later: the winners
   int32_t row[kSmallLookup];             // what a leader found for its key
 };
+
+// Initialises new rows from the list that the last block has left, in chunks that the waves of all blocks take in turn.
+template <typename E>
+__device__ inline void init_listed_rows(const TableView& t, uint32_t total) {
+  const uint32_t lane = lane_id();
+  const RestoreSource none = {nullptr, nullptr, nullptr};
+  for (;;) {  // (every turn takes a chunk: at most total / kSmallChunk turns and one)
+    unsigned long long chunk = 0;
+    if (lane == 0) chunk = atomicAdd(&t.ctl->scratch[kSmallNext], 1ull);
+    const uint32_t w0 = (uint32_t)__shfl(chunk, 0) * kSmallChunk;
+    if (w0 >= total) return;
+    const bool mine = lane < kSmallChunk && w0 + lane < total;
+    uint64_t key = kEmptyKey;
+    uint32_t row = kNoRow;
+    if (mine) {
+      const unsigned long long* from = reinterpret_cast<const unsigned long long*>(&t.win_list[w0 + lane]);
+      key = ld_agent(from);
+      row = (uint32_t)ld_agent(from + 1);
+    }
+    init_new_rows<E>(t, mine, kSmallChunk, key, row, 0u, none);
+  }
+}
 
 template <typename E>
 __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t, const int64_t* __restrict__ keys,
@@ -130,9 +159,27 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
   }
   wait_all_memory_ops();  // stamps, counters and list entries of this wave are performed
   __syncthreads();
-  if (tid == 0) s_last = atomicAdd(&t.ctl->scratch[kSmallDone], 1ull) == (unsigned long long)gridDim.x - 1;
+  if (tid == 0) {  // low half: blocks done; high half: their missing occurrences
+    const unsigned long long before = atomicAdd(&t.ctl->scratch[kSmallDone], (unsigned long long)mine << 32 | 1ull);
+    s_last = (uint32_t)before == gridDim.x - 1;
+    s_count = 0;
+    if (!s_last && ((before >> 32) != 0 || mine)) {
+      // Someone misses: stay for the list of new rows that the last block makes of it, but not for ever.
+      for (int poll = 0; poll < kSmallPolls; ++poll) {
+        const unsigned long long go = ld_agent(&t.ctl->scratch[kSmallGo]);
+        if ((uint32_t)(go >> 32) == epoch) {
+          s_count = (uint32_t)go;
+          break;
+        }
+        __builtin_amdgcn_s_sleep(8);
+      }
+    }
+  }
   __syncthreads();
-  if (!s_last) return;
+  if (!s_last) {
+    if (s_count) init_listed_rows<E>(t, s_count);
+    return;
+  }
 
   // ---- the block that finished last: everything about the missing occurrences -----------------------
   if (tid == 0) {
@@ -230,20 +277,23 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
     const uint32_t x = (uint32_t)j * kSmallThreads + tid;
     if (x < missed) rows_out[mo[j]] = s.f.row[lead[j]];
   }
-  const RestoreSource none = {nullptr, nullptr, nullptr};
-  if (room)
-    for (uint32_t w0 = tid & ~63u; w0 < total; w0 += kSmallThreads) {  // wave-uniform
-      const uint32_t w = w0 + lane;
-      uint64_t key = kEmptyKey;
-      uint32_t row = kNoRow;
-      if (w < total) {
-        const uint32_t x = s.f.slot[w];
-        key = s.f.key[x];
-        row = (uint32_t)s.f.row[x];
-        cuckoo_insert(t, key, make_meta(row, step), sweep_unit(step, t.sweep_q));
-      }
-      init_new_rows<E>(t, w < total, 64u, key, row, 0u, none);
-    }
+  // The list of new rows goes to the blocks that wait for it, and this one joins them when it has placed the keys.
+  const uint32_t placed = room ? total : 0u;
+  for (uint32_t w = tid; w < placed; w += kSmallThreads) {
+    const uint32_t x = s.f.slot[w];
+    unsigned long long* to = reinterpret_cast<unsigned long long*>(&t.win_list[w]);
+    st_agent(to, s.f.key[x]);
+    st_agent(to + 1, (unsigned long long)(uint32_t)s.f.row[x]);
+  }
+  if (tid == 0) st_agent(&t.ctl->scratch[kSmallNext], 0ull);
+  wait_all_memory_ops();
+  __syncthreads();
+  if (tid == 0) st_agent(&t.ctl->scratch[kSmallGo], (unsigned long long)epoch << 32 | placed);
+  for (uint32_t w = tid; w < placed; w += kSmallThreads) {
+    const uint32_t x = s.f.slot[w];
+    cuckoo_insert(t, s.f.key[x], make_meta((uint32_t)s.f.row[x], step), sweep_unit(step, t.sweep_q));
+  }
+  if (placed) init_listed_rows<E>(t, placed);
   if (tid == 0) settle_call(t, total, free0, hwm0, epoch);
 }
 

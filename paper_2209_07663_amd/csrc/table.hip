@@ -385,6 +385,11 @@ int mono_table_destroy(mono_table* t) {
   return rc;
 }
 
+static hipError_t forget_tags(const mono_table* t, hipStream_t stream) {
+  const hipError_t e = hipMemsetAsync(t->view.dset, 0, t->dset_size * sizeof(unsigned long long), stream);
+  return e != hipSuccess ? e : hipMemsetAsync(&t->view.ctl->scratch[kSmallGo], 0, sizeof(unsigned long long), stream);
+}
+
 int mono_lookup_or_insert(mono_table* t, const int64_t* d_keys, uint64_t n, uint32_t step, int32_t* d_rows_out,
                           void* stream) {
   if (!t || n > t->max_ids || step >= (1u << 24) || step < t->last_step) return MONO_EINVAL;
@@ -393,8 +398,7 @@ int mono_lookup_or_insert(mono_table* t, const int64_t* d_keys, uint64_t n, uint
   note_stream(t, stream);
   uint32_t epoch = t->epoch + 1;
   if (epoch == 0) {  // the 32-bit call tag wrapped: forget every old tag
-    if (hipMemsetAsync(t->view.dset, 0, t->dset_size * sizeof(unsigned long long), (hipStream_t)stream) != hipSuccess)
-      return MONO_EHIP;
+    if (forget_tags(t, (hipStream_t)stream) != hipSuccess) return MONO_EHIP;
     epoch = 1;
     t->tags_wrapped = true;
   }
@@ -575,7 +579,7 @@ int mono_table_import(mono_table* t, const int64_t* d_keys, const float* d_value
   if (!d_keys || !d_values || !d_acc || !d_last_seen) return MONO_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   if (++t->epoch == 0) {
-    if (hipMemsetAsync(t->view.dset, 0, t->dset_size * sizeof(unsigned long long), s) != hipSuccess) return MONO_EHIP;
+    if (forget_tags(t, s) != hipSuccess) return MONO_EHIP;
     t->epoch = 1;
     t->tags_wrapped = true;
   }
