@@ -44,113 +44,150 @@ __device__ inline void sweep_stash(const TableView& t, uint32_t now, int64_t* ex
   c->scratch[kSweepRemoved] = removed;
 }
 
-// kWords: words of four bounds per lane, so that a wave owns 256 * kWords buckets.  Four of them (16-byte loads) on
-// large tables, whose bounds are then a plain stream and whose waves are not too many to launch; one on small
-// tables, which would have too few waves.
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+// Which bounds (bytes of `oldest`) mean that a bucket may hold a key that is too old: a byte in [0, low) or in
+// [from, from + many).  Bounds go round, so that the young ones, from now's back to the oldest that is still young, are one
+// interval or the two ends of 1..254; 0 (kAgeLook) is looked at and 255 (kAgeEmpty) never.  Two bytes an instruction: with
+// the age of every byte worked out alone, 2^28 slots were bound by instructions (32 waves of 400 each to a SIMD, 20 us).
+struct OldBounds {
+  uint32_t low, from, many;
+  __device__ OldBounds(const TableView& t, uint32_t now, bool all) {
+    const uint32_t unit_now = now >> t.sweep_q, rest = now - (unit_now << t.sweep_q), here = sweep_unit(now, t.sweep_q);
+    // the greatest age in units of which even the first step is less than expire_steps ago
+    const uint32_t units = min((t.expire_steps - 1u - rest) >> t.sweep_q, unit_now);
+    low = all ? 255u : (here > units ? here - units : 1u);
+    from = here + 1u;
+    many = all ? 0u : (here > units ? 254u - here : 253u - units);
+  }
+  // two bytes in the halves of x: 1 in the halves of those
+  __device__ uint32_t operator()(uint32_t x) const {
+    const u16x2 v = __builtin_bit_cast(u16x2, x), one = (uint16_t)1;
+    const u16x2 found = __builtin_elementwise_sub_sat((u16x2)(uint16_t)low, v) |
+                        __builtin_elementwise_sub_sat((u16x2)(uint16_t)many, (u16x2)(v - (u16x2)(uint16_t)from));
+    return __builtin_bit_cast(uint32_t, (u16x2)__builtin_elementwise_min(found, one));
+  }
+};
+
+// smallest value of the group of eight lanes (called by whole waves)
+__device__ inline uint32_t least_of_eight(uint32_t x) {
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, false));   // lane ^ 1
+  x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, false));   // lane ^ 2
+  return min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false));  // 7 - lane
+}
+
+// kWords: words of four bounds per lane, so that a wave takes 256 * kWords buckets at a time.  Four of them (16-byte loads)
+// on large tables, whose bounds are then a plain stream; one on small tables, which would have too few waves.
 // keep_slots: the lists take slots and the slots stay as they are (see sweep_remove).
 template <int kWords>
 __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t now, bool look_all, int keep_slots,
-                                                         int64_t* expired_keys, uint64_t max_expired) {
+                                                            int64_t* expired_keys, uint64_t max_expired) {
   constexpr uint32_t kBuckets = 256u * kWords;
   __shared__ uint16_t s_list[4][kBuckets];
   if (blockIdx.x == 0 && threadIdx.x == 0) sweep_stash(t, now, expired_keys, max_expired);
   const uint32_t lane = lane_id(), grp = lane >> 3, l8 = lane & 7, wave = threadIdx.x >> 6;
-  const uint64_t wave_id = (uint64_t)blockIdx.x * 4 + wave, bucket0 = wave_id * kBuckets, n = 2 * t.n_buckets;
-  if (bucket0 >= n) return;  // wave-uniform (no barriers below)
+  const uint64_t n = 2 * t.n_buckets;
+  const uint32_t shares = (uint32_t)((n + kBuckets - 1) / kBuckets), step = gridDim.x * 4;
+  uint32_t share = blockIdx.x * 4 + wave;
+  if (share >= shares) return;  // wave-uniform (no barriers below)
+  uint32_t word[kWords];
+  const auto ask = [&]() {
+#pragma unroll
+    for (int w = 0; w < kWords; ++w) word[w] = 0xFFFFFFFFu;
+    const uint64_t first = (uint64_t)share * kBuckets + (uint64_t)lane * (4 * kWords);  // the lane's buckets
+    if (share >= shares) return;
+    if (first + 4 * kWords <= n) {
+      if constexpr (kWords == 4) {
+        const uint4 q = *reinterpret_cast<const uint4*>(t.oldest + (first >> 2));
+        word[0] = q.x;
+        word[1] = q.y;
+        word[2] = q.z;
+        word[3] = q.w;
+      } else {
+        word[0] = t.oldest[first >> 2];
+      }
+    } else {
+      for (uint32_t j = 0; j < 4 * kWords && first + j < n; ++j) {  // (tables of fewer than 2048 slots)
+        const uint32_t byte = reinterpret_cast<const uint8_t*>(t.oldest)[first + j];
+        word[j >> 2] = (word[j >> 2] & ~(0xFFu << (8 * (j & 3)))) | (byte << (8 * (j & 3)));
+      }
+    }
+  };
+  ask();
   // Bounds are unambiguous while every key's last-seen step lies in the last kAgeModulus units: all keys that the
   // latest sweep left were seen less than expire_steps before it.  Beyond that every bucket is looked at, as it is
   // where the caller's steps went back behind the latest sweep (`now` did, or a lookup in between: look_all).
   const uint32_t unit_now = now >> t.sweep_q, swept = t.ctl->swept;
   const uint32_t unit_least = (swept > t.expire_steps ? swept - t.expire_steps : 0u) >> t.sweep_q;
   look_all = look_all || unit_now - unit_least >= kAgeModulus - 1 || now < swept;
-  const uint64_t first = bucket0 + (uint64_t)lane * (4 * kWords);  // the lane's buckets
-  uint32_t word[kWords];
-#pragma unroll
-  for (int w = 0; w < kWords; ++w) word[w] = 0xFFFFFFFFu;
-  if (first + 4 * kWords <= n) {
-    if constexpr (kWords == 4) {
-      const uint4 q = *reinterpret_cast<const uint4*>(t.oldest + (first >> 2));
-      word[0] = q.x;
-      word[1] = q.y;
-      word[2] = q.z;
-      word[3] = q.w;
-    } else {
-      word[0] = t.oldest[first >> 2];
-    }
-  } else {
-    for (uint32_t j = 0; j < 4 * kWords && first + j < n; ++j) {  // (tables of fewer than 2048 slots)
-      const uint32_t byte = reinterpret_cast<const uint8_t*>(t.oldest)[first + j];
-      word[j >> 2] = (word[j >> 2] & ~(0xFFu << (8 * (j & 3)))) | (byte << (8 * (j & 3)));
-    }
-  }
-  uint32_t look = 0;  // bit j: bucket first + j may hold a key that is too old
-#pragma unroll
-  for (uint32_t j = 0; j < 4u * kWords; ++j) {
-    const uint32_t b = (word[j >> 2] >> (8 * (j & 3))) & 0xFFu;
-    const uint32_t age = (unit_now + kAgeModulus - (b - 1u)) % kAgeModulus;  // of the bound, in units (b >= 1)
-    const uint32_t bound = (unit_now - age) << t.sweep_q;                   // no key was last seen before this step
-    const bool young = b != kAgeLook && age <= unit_now && !look_all && now - bound < t.expire_steps;
-    if (b != kAgeEmpty && !young) look |= 1u << j;
-  }
-  uint32_t inc = (uint32_t)__popc(look);
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(inc, d);
-    if ((int)lane >= d) inc += y;
-  }
-  const uint32_t total = __shfl(inc, 63);
-  if (total == 0) return;  // wave-uniform
+  const OldBounds is_old(t, now, look_all);
   uint16_t* list = s_list[wave];  // the buckets to look at, of the wave's
-  {
-    uint32_t at = inc - (uint32_t)__popc(look);
-    for (uint32_t m = look; m; m &= m - 1) wave_store(list + at++, (uint16_t)(lane * (4 * kWords) + (uint32_t)__ffs((int)m) - 1u));
-  }
-  wave_order();
-  const uint32_t out = (uint32_t)wave_id & (kWinLists - 1);  // sub-list of this wave
-  constexpr int kTurns = 8;  // buckets per group of eight lanes with their meta words (64 bytes) in flight
-  for (uint32_t e0 = 0; e0 < total; e0 += 8 * kTurns) {
-    unsigned long long m[kTurns];
+  while (share < shares) {
+    const uint64_t bucket0 = (uint64_t)share * kBuckets;
+    const uint32_t out = share & (kWinLists - 1);  // the sub-list
+    uint32_t look = 0;  // one bit per bucket of the lane's; bit 16 h + 2 w + o: byte 2 h + o of word w
 #pragma unroll
-    for (int r = 0; r < kTurns; ++r) {
-      const uint32_t e = e0 + 8u * (uint32_t)r + grp;
-      m[r] = kNoMeta;
-      if (e < total) m[r] = t.buckets[bucket0 + wave_load(list + e)].meta[l8];
-    }
-    uint64_t gone[kTurns];
-    uint32_t found = 0;
-#pragma unroll
-    for (int r = 0; r < kTurns; ++r) {
-      const uint32_t e = e0 + 8u * (uint32_t)r + grp;
-      const bool live = meta_row(m[r]) != kNoRow, old = live && is_expired(t, now, meta_seen(m[r]));
-      gone[r] = __ballot(old);
-      found += (uint32_t)__popcll(gone[r]);
-      uint32_t least = live && !old ? meta_seen(m[r]) : 0xFFFFFFFFu;  // over the keys that stay
-#pragma unroll
-      for (int d = 1; d < 8; d <<= 1) least = min(least, __shfl_xor(least, d));
-      if (e < total && l8 == 0) {
-        const uint64_t b = bucket0 + wave_load(list + e);
-        // (a key from the future, seen after `now`: nothing is known)
-        const uint32_t age = least == 0xFFFFFFFFu ? kAgeEmpty : (least > now ? kAgeLook : sweep_unit(least, t.sweep_q));
-        reinterpret_cast<uint8_t*>(t.oldest)[b] = (uint8_t)age;
-        if (age == kAgeEmpty) atomicAnd(&t.occupied[b >> 6], ~(1ull << (b & 63)));
+    for (int w = 0; w < kWords; ++w)
+      look |= is_old(word[w] & 0x00FF00FFu) << (2 * w) | is_old((word[w] >> 8) & 0x00FF00FFu) << (2 * w + 1);
+    share += step;
+    ask();
+    if (__ballot(look != 0) == 0) continue;  // wave-uniform
+    const uint32_t inc = wave_sums((uint32_t)__popc(look)), total = __shfl(inc, 63);
+    wave_order();
+    {
+      uint32_t at = inc - (uint32_t)__popc(look);
+      for (uint32_t m = look; m; m &= m - 1) {
+        const uint32_t i = (uint32_t)__ffs((int)m) - 1u;
+        wave_store(list + at++, (uint16_t)(lane * (4 * kWords) + ((i >> 1) & 7u) * 4u + (i >> 4) * 2u + (i & 1u)));
       }
     }
-    if (found == 0) continue;  // wave-uniform
-    uint32_t p = 0;
-    if (lane == 0) p = atomicAdd(&t.sweep_cnt[out * kWinStride], found);
-    p = __shfl(p, 0);
+    wave_order();
+    constexpr int kTurns = 8;  // buckets per group of eight lanes with their meta words (64 bytes) in flight
+    for (uint32_t e0 = 0; e0 < total; e0 += 8 * kTurns) {
+      unsigned long long m[kTurns];
 #pragma unroll
-    for (int r = 0; r < kTurns; ++r) {
-      if ((gone[r] >> lane) & 1ull) {
-        const uint64_t b = bucket0 + wave_load(list + e0 + 8u * (uint32_t)r + grp);
-        t.sweep_list[(uint64_t)out * t.sweep_cap + p + (uint32_t)__popcll(gone[r] & lanes_below())] =
-            keep_slots ? (uint32_t)(b * kBucket + l8) : meta_row(m[r]);
-        if (!keep_slots) {
-          t.buckets[b].meta[l8] = kNoMeta;
-          t.buckets[b].key[l8] = kEmptyKey;
+      for (int r = 0; r < kTurns; ++r) {
+        const uint32_t e = e0 + 8u * (uint32_t)r + grp;
+        m[r] = kNoMeta;
+        if (e < total) m[r] = t.buckets[bucket0 + wave_load(list + e)].meta[l8];
+      }
+      uint64_t gone[kTurns];
+      uint32_t found = 0;
+#pragma unroll
+      for (int r = 0; r < kTurns; ++r) {
+        gone[r] = 0;
+        if (e0 + 8u * (uint32_t)r >= total) continue;  // wave-uniform
+        const uint32_t e = e0 + 8u * (uint32_t)r + grp;
+        const bool live = meta_row(m[r]) != kNoRow, old = live && is_expired(t, now, meta_seen(m[r]));
+        gone[r] = __ballot(old);
+        found += (uint32_t)__popcll(gone[r]);
+        const uint32_t least = least_of_eight(live && !old ? meta_seen(m[r]) : 0xFFFFFFFFu);  // over the keys that stay
+        if (e < total && l8 == 0) {
+          const uint64_t b = bucket0 + wave_load(list + e);
+          // (a key from the future, seen after `now`: nothing is known)
+          const uint32_t age = least == 0xFFFFFFFFu ? kAgeEmpty : (least > now ? kAgeLook : sweep_unit(least, t.sweep_q));
+          reinterpret_cast<uint8_t*>(t.oldest)[b] = (uint8_t)age;
+          if (age == kAgeEmpty) atomicAnd(&t.occupied[b >> 6], ~(1ull << (b & 63)));
         }
       }
-      p += (uint32_t)__popcll(gone[r]);
+      if (found == 0) continue;  // wave-uniform
+      uint32_t p = 0;
+      if (lane == 0) p = atomicAdd(&t.sweep_cnt[out * kWinStride], found);
+      p = __shfl(p, 0);
+#pragma unroll
+      for (int r = 0; r < kTurns; ++r) {
+        if (gone[r] == 0) continue;  // wave-uniform
+        if ((gone[r] >> lane) & 1ull) {
+          const uint64_t b = bucket0 + wave_load(list + e0 + 8u * (uint32_t)r + grp);
+          t.sweep_list[(uint64_t)out * t.sweep_cap + p + (uint32_t)__popcll(gone[r] & lanes_below())] =
+              keep_slots ? (uint32_t)(b * kBucket + l8) : meta_row(m[r]);
+          if (!keep_slots) {
+            t.buckets[b].meta[l8] = kNoMeta;
+            t.buckets[b].key[l8] = kEmptyKey;
+          }
+        }
+        p += (uint32_t)__popcll(gone[r]);
+      }
     }
   }
 }
@@ -217,6 +254,8 @@ __global__ void sweep_nothing_kernel(uint64_t* n_expired) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *n_expired = 0;
 }
 
+constexpr uint64_t kSweepBlocks = 4096;
+
 hipError_t launch_expire_sweep(const TableView& t, uint32_t now, bool look_all, uint64_t* d_n_expired,
                                int64_t* d_expired_keys, uint64_t max_expired, hipStream_t stream, Profiler* prof) {
   if (t.expire_steps == 0) {  // nothing ever expires: only the count is reported
@@ -224,7 +263,7 @@ hipError_t launch_expire_sweep(const TableView& t, uint32_t now, bool look_all, 
     return hipGetLastError();
   }
   const uint64_t waves = (2 * t.n_buckets + sweep_wave_buckets(t.capacity) - 1) / sweep_wave_buckets(t.capacity);
-  const dim3 block(256), grid((unsigned)((waves + 3) / 4));
+  const dim3 block(256), grid((unsigned)(waves < 4 * kSweepBlocks ? (waves + 3) / 4 : kSweepBlocks));
   const int keep_slots = d_expired_keys != nullptr;
   if (t.capacity >= kSweepLargeTable)
     MONO_LAUNCH(prof, K_SWEEP, stream, sweep_find_kernel<4>, grid, block, t, now, look_all, keep_slots, d_expired_keys,
