@@ -45,6 +45,8 @@ constexpr int kSmallMisses = 4;             // Control::scratch slots of the one
 constexpr int kSmallDone = 5;               // that have finished their probes and their misses (zero between calls);
 constexpr int kSmallGo = 15;                // tag << 32 | number of new rows, of the latest such call with misses; the next
 constexpr int kSmallNext = 16;              // chunk of them that nobody has taken yet
+constexpr int kOrderDone = 17;              // Control::scratch slots: blocks of order_tiles that are done, and their tiles of one
+constexpr int kOrdered = 18;                // row (zero between calls); 1 + tiles of several rows if seg_reduce is to take that order
 constexpr int kMissTag = 7;                 // Control::scratch slots: tag of the latest call in which an occurrence missed,
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see

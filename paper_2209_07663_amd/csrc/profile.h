@@ -19,6 +19,7 @@ enum KernelId {
   K_SORT_HIST,
   K_SORT_SCAN,
   K_SORT_SCATTER,
+  K_ORDER_TILES,
   K_SEG_REDUCE,
   K_COMBINE,
   K_SWEEP,
@@ -30,7 +31,7 @@ enum KernelId {
 inline const char* kernel_name(int id) {
   static const char* names[K_COUNT] = {"probe_count", "admit_elect", "insert", "resolve",   "lookup_small",
                                        "gather_pool", "sort_split",  "sort_bucket",  "sort_hist",   "sort_scan",    "sort_scatter",
-                                       "seg_reduce",  "combine",     "sweep_find",   "sweep_remove", "sweep_end"};
+                                       "order_tiles", "seg_reduce",  "combine",     "sweep_find",   "sweep_remove", "sweep_end"};
   return id >= 0 && id < K_COUNT ? names[id] : "?";
 }
 

@@ -22,6 +22,7 @@
 // B = 2u + 1 ("run that continues past the end of this tile"; flag kHeadFlag if it also starts inside it).
 #include "common.h"
 #include "kernels.h"
+#include "table_ops.h"
 
 namespace mono {
 
@@ -169,6 +170,104 @@ __device__ inline void adagrad_row(const TableView& t, uint32_t row, const RowVe
   if (l == 0) t.state[row] = RowState{acc, t.sync_epoch};  // trained in this window
 }
 
+// Order in which seg_reduce takes its tiles where the gradients are more than the caches hold and each is the gradient of
+// several occurrences: first the tiles that hold several rows, which read gradients from anywhere, then those of one hot row,
+// by the bag that they begin with.  (A row's pairs are in the order of the bags, so that tiles of different hot rows that run
+// together read the same part of the gradients.)  Of the latter an XCD takes an eighth of the bags, in order: neighbouring
+// blocks run on different XCDs, which do not share an L2.  26 M pairs of dim 64, Zipf 1.1, half of them in such tiles, 1.3 GB
+// of gradients: seg_reduce 1690 us without, 1540 without the eighths, 1530 so; with the tiles of several rows last 1550; tiles
+// of 512 pairs 1520, but 30 us more to combine.
+// All blocks look for the tiles' bins (bags, in equal parts), and the one that finishes last counts and orders them: the
+// looking is what takes memory's time, and 26 K tiles are 25 for each of a block's threads (19 us in all).  Where fewer than
+// one tile in 16 is of one row the order stays as it is.
+constexpr uint32_t kOrderThreads = 1024, kOrderBins = 2 * kOrderThreads;  // (bin 0: several rows, or not full)
+
+__global__ __launch_bounds__(kOrderThreads) void order_tiles_kernel(Control* __restrict__ ctl, const uint2* __restrict__ pair_a,
+                                                                    const uint2* __restrict__ pair_b, uint32_t tiles,
+                                                                    uint32_t tile, uint64_t n_bags, uint32_t launched,
+                                                                    uint32_t max_bits, uint32_t* bins, uint32_t* __restrict__ order) {
+  __shared__ uint32_t s_at[kOrderBins], s_wave[kOrderThreads / 64], s_several[kOrderThreads / 64], s_hot, s_last;
+  const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
+  const SortPlan plan = make_sort_plan(ctl->hwm, max_bits ? max_bits : 32);
+  if (plan.passes > launched) return;  // (nothing is sorted; see seg_reduce_kernel)
+  const uint2* __restrict__ sp = max_bits == 0 || plan.passes % 2 ? pair_b : pair_a;
+  const uint64_t n = ctl->scratch[kValidPairs], t0 = ((uint64_t)blockIdx.x * kOrderThreads + tid) * tile;
+  const uint32_t mine = blockIdx.x * kOrderThreads + tid;
+  if (tid == 0) s_hot = 0;
+  for (uint32_t b = tid; b < kOrderBins; b += kOrderThreads) s_at[b] = 0;
+  uint32_t bin = 0;
+  if (mine < tiles && t0 + tile <= n) {
+    const uint2 first = sp[t0];
+    if (first.x == sp[t0 + tile - 1].x) bin = 1u + (uint32_t)((uint64_t)first.y * (kOrderBins - 1) / n_bags);
+  }
+  if (mine < tiles) st_agent(&bins[mine], bin);
+  wait_all_memory_ops();
+  __syncthreads();
+  const uint64_t of_wave = __ballot(bin != 0);
+  if (lane == 0 && of_wave) atomicAdd(&s_hot, (uint32_t)__popcll(of_wave));
+  __syncthreads();
+  if (tid == 0) {  // low half: blocks; high half: tiles of one row
+    const unsigned long long one = (unsigned long long)s_hot << 32 | 1ull, sum = atomicAdd(&ctl->scratch[kOrderDone], one) + one;
+    s_last = (uint32_t)sum == gridDim.x;
+    s_hot = (uint32_t)(sum >> 32);
+  }
+  __syncthreads();
+  if (!s_last) return;
+  const bool ordered = s_hot > tiles / 16;
+  if (tid == 0) {
+    ctl->scratch[kOrderDone] = 0;
+    if (!ordered) ctl->scratch[kOrdered] = 0;
+  }
+  if (!ordered) return;
+  constexpr uint32_t kAhead = 32;  // tiles of a thread whose bins it holds: all of a batch of 32 M pairs
+  uint32_t held[kAhead], several = 0;  // tiles of bin 0, of this wave: they are many, and need no word that all add to
+  for (uint32_t pass = 0; pass < 2; ++pass) {
+    for (uint32_t u0 = 0; u0 < tiles; u0 += kAhead * kOrderThreads) {
+      if (pass == 0 || tiles > kAhead * kOrderThreads) {
+#pragma unroll
+        for (uint32_t q = 0; q < kAhead; ++q) {
+          const uint32_t u = u0 + q * kOrderThreads + tid;
+          held[q] = u < tiles ? ld_agent(&bins[u]) : kOrderBins;
+        }
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < kAhead; ++q) {
+        if (u0 + q * kOrderThreads >= tiles) break;  // block-uniform
+        const uint64_t none = __ballot(held[q] == 0);
+        uint32_t at = several + (uint32_t)__popcll(none & lanes_below());
+        several += (uint32_t)__popcll(none);
+        if (held[q] - 1u < kOrderBins - 1u) at = atomicAdd(&s_at[held[q]], 1u);
+        if (pass == 1 && held[q] < kOrderBins) order[at] = u0 + q * kOrderThreads + tid;
+      }
+    }
+    if (pass == 1) break;
+    if (lane == 0) s_several[wave] = several;
+    __syncthreads();
+    uint32_t first = 0, all = 0;
+    for (uint32_t w = 0; w < kOrderThreads / 64; ++w) {
+      if (w == wave) first = all;
+      all += s_several[w];
+    }
+    several = first;
+    const uint32_t c0 = s_at[2 * tid], c1 = s_at[2 * tid + 1], x = wave_sums(c0 + c1);
+    if (lane == 63) s_wave[wave] = x;
+    __syncthreads();
+    uint32_t at = all + x - c0 - c1;
+    for (uint32_t w = 0; w < wave; ++w) at += s_wave[w];
+    s_at[2 * tid] = at;
+    s_at[2 * tid + 1] = at + c0;
+    if (tid == 0) ctl->scratch[kOrdered] = all + 1ull;
+    __syncthreads();
+  }
+}
+
+// The tile of a block: an XCD's blocks take an eighth of the tiles of one row.
+__device__ inline uint32_t tile_of_block(const uint32_t* __restrict__ order, uint64_t ordered, uint32_t block, uint32_t tiles) {
+  if (!order || ordered == 0) return block;
+  const uint32_t several = (uint32_t)(ordered - 1), share = (tiles - several) / 8, x = block - several;
+  return order[block >= several && x < 8 * share ? several + x % 8 * share + x / 8 : block];
+}
+
 // GLOG = log2(lanes per row), SEG = pieces of four elements per lane (1 unless GLOG == 6).  A block of 256
 // threads owns a tile of `tile` consecutive sorted pairs, a group an equal chunk of it; the host picks the size
 // of the tile so that small batches still fill the machine.
@@ -177,7 +276,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
                                                          const uint2* __restrict__ pair_b, uint64_t n,
                                                          const float* __restrict__ grad, float lr, float eps,
                                                          float* __restrict__ part, uint32_t* __restrict__ part_row,
-                                                         uint32_t tile, uint32_t launched, uint32_t max_bits) {
+                                                         uint32_t tile, uint32_t launched, uint32_t max_bits,
+                                                         const uint32_t* __restrict__ order) {
   static_assert(SEG == 1 || GLOG == 6, "rows wider than 256 elements are held by a whole wave");
   extern __shared__ float4 s_mem[];  // [groups_per_block + waves][dim / 4] vectors, the tile's pairs
   using Vec = RowVec<SEG>;
@@ -197,6 +297,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     }
     return;
   }
+  const uint32_t at_tile = tile_of_block(order, t.ctl->scratch[kOrdered], blockIdx.x, gridDim.x);
   const uint2* __restrict__ sp = max_bits == 0 || plan.passes % 2 ? pair_b : pair_a;  // where the sort left its result
   const uint32_t hwm = plan.hwm;
   n = t.ctl->scratch[kValidPairs];  // the sort left the dropped occurrences out
@@ -205,7 +306,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   float4* s_vec = s_mem;                   // a group's partial of the run that ends in its chunk
   float4* s_carry = s_mem + gpb * dim4;    // a wave's sum over the run that continues past its last chunk
   const uint64_t n_chunks = (n + chunk - 1) / chunk;
-  const uint64_t c0 = (uint64_t)blockIdx.x * gpb;  // first chunk of this block's tile
+  const uint64_t c0 = (uint64_t)at_tile * gpb;  // first chunk of this block's tile
   const uint64_t c = c0 + g;
   const uint32_t chunks_here = (uint32_t)(n_chunks - c0 < gpb ? n_chunks - c0 : gpb);
   const bool active = l < dim4;
@@ -215,7 +316,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   uint2* s_pairs = reinterpret_cast<uint2*>(s_carry + kReduceWaves * dim4);
   __shared__ uint32_t s_edge[2];  // rows of the pairs before and after the tile (asked for with the pairs, not after them)
   {
-    const uint64_t t0 = (uint64_t)blockIdx.x * tile;
+    const uint64_t t0 = (uint64_t)at_tile * tile;
     if (threadIdx.x < 2) {
       const uint64_t at = threadIdx.x == 0 ? t0 - 1 : t0 + tile;  // (t0 - 1 of the first tile is beyond every n)
       s_edge[threadIdx.x] = at < n ? sp[at].x : kNoRow;
@@ -303,8 +404,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     }
   }
   if (threadIdx.x == 0) {
-    part_row[2 * (uint64_t)blockIdx.x] = kNoRow;
-    part_row[2 * (uint64_t)blockIdx.x + 1] = kNoRow;
+    part_row[2 * (uint64_t)at_tile] = kNoRow;
+    part_row[2 * (uint64_t)at_tile + 1] = kNoRow;
   }
 
   // ---- phase 2: join the chunk partials of runs inside this tile -------------------------------
@@ -363,13 +464,13 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     if (g > 0 && (flags_prev & 2u)) {
       adagrad_row<E, SEG, PAST>(t, a_row, w, acc, prev, active, l, group, lr, eps);
     } else {  // it entered the tile from before
-      store_vec<SEG>(part4 + (2 * (uint64_t)blockIdx.x) * dim4, l, active, prev);
-      if (l == 0) part_row[2 * (uint64_t)blockIdx.x] = a_row;
+      store_vec<SEG>(part4 + (2 * (uint64_t)at_tile) * dim4, l, active, prev);
+      if (l == 0) part_row[2 * (uint64_t)at_tile] = a_row;
     }
   }
   if (g == chunks_here - 1 && b_row != kNoRow) {
-    store_vec<SEG>(part4 + (2 * (uint64_t)blockIdx.x + 1) * dim4, l, active, sum);
-    if (l == 0) part_row[2 * (uint64_t)blockIdx.x + 1] = b_row | (flags & 2u ? kHeadFlag : 0u);
+    store_vec<SEG>(part4 + (2 * (uint64_t)at_tile + 1) * dim4, l, active, sum);
+    if (l == 0) part_row[2 * (uint64_t)at_tile + 1] = b_row | (flags & 2u ? kHeadFlag : 0u);
   }
 }
 
@@ -451,6 +552,16 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(TableView t, uint64_t n
   }
 }
 
+// The order is worth its launch, 6 to 19 us, where the gradients are more than the caches hold, several occurrences share
+// one, and there are a gigabyte or more of them to be read.  Updates without and with it, us: 26 M pairs of 5.2 M bags of dim
+// 64 2000 / 1865, 4.2 M of 1 M bags of dim 64 372 / 361 and of dim 128 636 / 596, 1.2 M of 131 K bags of dim 1024 1100 / 1025,
+// 25 M of 8.4 M bags of dim 16 965 / 890 (all Zipf 1.1 to 1.2); with half a gigabyte to be read, 0.5 M of 262 K bags of dim
+// 256 218 / 228, 2.1 M of 1 M bags of dim 64 241 / 238; where no row is hot 8.4 M of 2.1 M bags of dim 64 925 / 930.
+inline bool orders_tiles(uint64_t n, uint64_t n_bags, uint32_t dim) {
+  const uint64_t row = dim * sizeof(float);
+  return n_bags * row >= kRowsCached && n >= 2 * n_bags && n * row >= 4 * kRowsCached;
+}
+
 hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                                      const int64_t* d_offsets, uint64_t n_bags, const float* d_grad, float lr, float eps,
                                      uint32_t hwm_bound, hipStream_t stream, Profiler* prof) {
@@ -471,9 +582,17 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
   const dim3 block(256), grid((unsigned)n_tiles);
   const size_t lds_reduce = (gpb + kReduceWaves) * (t.dim / 4) * sizeof(float4) + tile * sizeof(uint2);
   const size_t lds_combine = kCombineWide / 64 * (t.dim / 4) * sizeof(float4);  // (enough for either block)
+  // (see order_tiles_kernel; the sort's counters are free by now, and many more than two words a tile)
+  uint32_t* order = nullptr;
+  if (orders_tiles(n, n_bags, t.dim)) {
+    order = ws.hist + n_tiles;
+    MONO_LAUNCH(prof, K_ORDER_TILES, stream, order_tiles_kernel, dim3((unsigned)((n_tiles + kOrderThreads - 1) / kOrderThreads)),
+                dim3(kOrderThreads), t.ctl, ws.pair_a, ws.pair_b, (uint32_t)n_tiles, tile, n_bags, launched, max_bits, ws.hist,
+                order);
+  }
 #define MONO_SEG_REDUCE_AS(E, GLOG, SEG, PAST)                                                                        \
   MONO_LAUNCH_SMEM(prof, K_SEG_REDUCE, stream, (seg_reduce_kernel<E, GLOG, SEG, PAST>), grid, block, lds_reduce, t,     \
-                   ws.pair_a, ws.pair_b, n, d_grad, lr, eps, ws.part, ws.part_row, tile, launched, max_bits)
+                   ws.pair_a, ws.pair_b, n, d_grad, lr, eps, ws.part, ws.part_row, tile, launched, max_bits, order)
 #define MONO_SEG_REDUCE(E, GLOG, SEG)                                       \
   if (n * t.dim * sizeof(E) > kRowsCached) {                                \
     MONO_SEG_REDUCE_AS(E, GLOG, SEG, true);                                 \
