@@ -100,6 +100,9 @@ def _p(t):
 check, device_pointer, current_stream = _check, _p, _stream
 
 
+_INT32, _INT64, _FLOAT32 = torch.int32, torch.int64, torch.float32
+
+
 def _dev(t, dtype):
     if not (t.is_cuda and t.dtype == dtype and t.is_contiguous()):
         raise TypeError("need a contiguous CUDA tensor of %s" % dtype)
@@ -223,6 +226,9 @@ class Table:
                                                  self.filter_hashes, self.filter_log2, self.arena.data_ptr(), nbytes,
                                                  _stream(self.device)), "mono_table_create_ex")
         self.h = h
+        # what the calls of a serving request need, looked up once: those are bound by the host, 3 us of them the launch
+        self._lookup, self._gather = self.lib.mono_lookup_or_insert, self.lib.mono_gather_pool
+        self._index, self._raw_stream = self.device.index, torch._C._cuda_getCurrentRawStream
 
     def _s(self):
         return _stream(self.device)
@@ -236,24 +242,33 @@ class Table:
     def __del__(self):
         self.close()
 
+    # (checks and conversions stand in the two methods themselves: as calls of helpers 1.0 and 0.6 us of 4.1 and 4.6)
     def mono_lookup_or_insert(self, keys, step, rows_out=None):
-        _dev(keys, torch.int64)
+        if not (keys.is_cuda and keys.dtype == _INT64 and keys.is_contiguous()):
+            _dev(keys, _INT64)  # raises
         if rows_out is None:
-            rows_out = torch.empty(keys.shape[0], dtype=torch.int32, device=keys.device)
-        _dev(rows_out, torch.int32)
-        _check(self.lib.mono_lookup_or_insert(self.h, _p(keys), keys.shape[0], step, _p(rows_out), self._s()),
-               "mono_lookup_or_insert")
+            rows_out = torch.empty(keys.shape[0], dtype=_INT32, device=keys.device)
+        elif not (rows_out.is_cuda and rows_out.dtype == _INT32 and rows_out.is_contiguous()):
+            _dev(rows_out, _INT32)
+        rc = self._lookup(self.h, keys.data_ptr(), keys.shape[0], step, rows_out.data_ptr(), self._raw_stream(self._index))
+        if rc:
+            _check(rc, "mono_lookup_or_insert")
         return rows_out
 
     def mono_gather_pool(self, rows, offsets, out=None):
-        _dev(rows, torch.int32)
-        _dev(offsets, torch.int64)
+        if not (rows.is_cuda and rows.dtype == _INT32 and rows.is_contiguous()):
+            _dev(rows, _INT32)  # raises
+        if not (offsets.is_cuda and offsets.dtype == _INT64 and offsets.is_contiguous()):
+            _dev(offsets, _INT64)
         n_bags = offsets.shape[0] - 1
         if out is None:
-            out = torch.empty((n_bags, self.dim), dtype=torch.float32, device=rows.device)
-        _dev(out, torch.float32)
-        _check(self.lib.mono_gather_pool(self.h, _p(rows), rows.shape[0], _p(offsets), n_bags, _p(out), self._s()),
-               "mono_gather_pool")
+            out = torch.empty((n_bags, self.dim), dtype=_FLOAT32, device=rows.device)
+        elif not (out.is_cuda and out.dtype == _FLOAT32 and out.is_contiguous()):
+            _dev(out, _FLOAT32)
+        rc = self._gather(self.h, rows.data_ptr(), rows.shape[0], offsets.data_ptr(), n_bags, out.data_ptr(),
+                          self._raw_stream(self._index))
+        if rc:
+            _check(rc, "mono_gather_pool")
         return out
 
     def mono_apply_grad_adagrad(self, rows, offsets, grad, lr, eps):
