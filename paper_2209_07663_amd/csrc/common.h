@@ -53,7 +53,8 @@ constexpr int kSampledMisses = 11;          // Control::scratch slots: missing o
 constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
 constexpr int kInsertDone = 14;             // Control::scratch slot: sub-lists whose blocks of the insertion are done (zero between calls)
 constexpr int kHotBins = 13;                // Control::scratch slot: rows with a bin of their own (see sort_split.hip)
-constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists whose blocks are done (zero between calls)
+constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists, or blocks, that are done; of sweep_small also the keys
+                                            // removed so far << 32 (zero between calls)
 
 struct StashEntry {
   uint64_t key;

@@ -10,7 +10,7 @@ __device__ inline bool is_expired(const TableView& t, uint32_t now, uint32_t see
   return t.expire_steps > 0 && now >= seen && now - seen >= t.expire_steps;
 }
 
-// Sweep in two kernels:
+// Sweep in two kernels, or where the table is small and nobody asks for the keys in one that does both (sweep_small):
 //   sweep_find    reads the bound of every bucket (a byte each, kept by insertions and by the sweep itself) and looks
 //                 only at buckets that may hold a key that is too old; takes such keys out of their slots,
 //                 appends their rows to one of kWinLists lists (one atomic per wave and 64 buckets, spread
@@ -76,120 +76,216 @@ __device__ inline uint32_t least_of_eight(uint32_t x) {
   return min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, false));  // 7 - lane
 }
 
+constexpr int kSweepTurns = 8;  // buckets per group of eight lanes with their meta words (64 bytes) in flight
+
+// The wave's list of buckets to look at, from the bounds of kWords * 256 of them, and how many they are.
+template <int kWords>
+__device__ inline uint32_t list_old_buckets(const uint32_t (&word)[kWords], const OldBounds& is_old, uint16_t* list) {
+  uint32_t look = 0;  // one bit per bucket of the lane's; bit 16 h + 2 w + o: byte 2 h + o of word w
+#pragma unroll
+  for (int w = 0; w < kWords; ++w)
+    look |= is_old(word[w] & 0x00FF00FFu) << (2 * w) | is_old((word[w] >> 8) & 0x00FF00FFu) << (2 * w + 1);
+  if (__ballot(look != 0) == 0) return 0;  // wave-uniform
+  const uint32_t inc = wave_sums((uint32_t)__popc(look));
+  wave_order();
+  uint32_t at = inc - (uint32_t)__popc(look);
+  for (uint32_t m = look; m; m &= m - 1) {
+    const uint32_t i = (uint32_t)__ffs((int)m) - 1u;
+    wave_store(list + at++, (uint16_t)(lane_id() * (4 * kWords) + ((i >> 1) & 7u) * 4u + (i >> 4) * 2u + (i & 1u)));
+  }
+  wave_order();
+  return __shfl(inc, 63);
+}
+
+// Looks at 8 * kSweepTurns buckets of the list, from e0 on, and writes their new bounds.  m: meta words; gone: the lanes whose
+// keys are too old; returns how many.
+__device__ inline uint32_t look_at_buckets(const TableView& t, uint32_t now, uint64_t bucket0, const uint16_t* list, uint32_t e0,
+                                           uint32_t total, unsigned long long (&m)[kSweepTurns], uint64_t (&gone)[kSweepTurns]) {
+  const uint32_t grp = lane_id() >> 3, l8 = lane_id() & 7;
+#pragma unroll
+  for (int r = 0; r < kSweepTurns; ++r) {
+    const uint32_t e = e0 + 8u * (uint32_t)r + grp;
+    m[r] = kNoMeta;
+    if (e < total) m[r] = t.buckets[bucket0 + wave_load(list + e)].meta[l8];
+  }
+  uint32_t found = 0;
+#pragma unroll
+  for (int r = 0; r < kSweepTurns; ++r) {
+    gone[r] = 0;
+    if (e0 + 8u * (uint32_t)r >= total) continue;  // wave-uniform
+    const uint32_t e = e0 + 8u * (uint32_t)r + grp;
+    const bool live = meta_row(m[r]) != kNoRow, old = live && is_expired(t, now, meta_seen(m[r]));
+    gone[r] = __ballot(old);
+    found += (uint32_t)__popcll(gone[r]);
+    const uint32_t least = least_of_eight(live && !old ? meta_seen(m[r]) : 0xFFFFFFFFu);  // over the keys that stay
+    if (e < total && l8 == 0) {
+      const uint64_t b = bucket0 + wave_load(list + e);
+      // (a key from the future, seen after `now`: nothing is known)
+      const uint32_t age = least == 0xFFFFFFFFu ? kAgeEmpty : (least > now ? kAgeLook : sweep_unit(least, t.sweep_q));
+      reinterpret_cast<uint8_t*>(t.oldest)[b] = (uint8_t)age;
+      if (age == kAgeEmpty) atomicAnd(&t.occupied[b >> 6], ~(1ull << (b & 63)));
+    }
+  }
+  return found;
+}
+
+// Hands out the keys that are gone: calls `each` with their numbers from p on, buckets, slots and meta words.
+template <typename F>
+__device__ inline void each_gone(uint64_t bucket0, const uint16_t* list, uint32_t e0, const unsigned long long (&m)[kSweepTurns],
+                                 const uint64_t (&gone)[kSweepTurns], uint32_t p, const F& each) {
+  const uint32_t lane = lane_id();
+#pragma unroll
+  for (int r = 0; r < kSweepTurns; ++r) {
+    if (gone[r] == 0) continue;  // wave-uniform
+    if ((gone[r] >> lane) & 1ull)
+      each(p + (uint32_t)__popcll(gone[r] & lanes_below()), bucket0 + wave_load(list + e0 + 8u * (uint32_t)r + (lane >> 3)), m[r]);
+    p += (uint32_t)__popcll(gone[r]);
+  }
+}
+
+// Bounds are unambiguous while every key's last-seen step lies in the last kAgeModulus units: all keys that the
+// latest sweep left were seen less than expire_steps before it.  Beyond that every bucket is looked at, as it is
+// where the caller's steps went back behind the latest sweep (`now` did, or a lookup in between: look_all).
+__device__ inline bool looks_at_all(const TableView& t, uint32_t now, bool look_all) {
+  const uint32_t unit_now = now >> t.sweep_q, swept = t.ctl->swept;
+  const uint32_t unit_least = (swept > t.expire_steps ? swept - t.expire_steps : 0u) >> t.sweep_q;
+  return look_all || unit_now - unit_least >= kAgeModulus - 1 || now < swept;
+}
+
+// The bounds of the lane's buckets of a share of 256 * kWords; kAgeEmpty beyond the table's n.
+template <int kWords>
+__device__ inline void load_bounds(const TableView& t, uint64_t share, uint64_t n, uint32_t (&word)[kWords]) {
+#pragma unroll
+  for (int w = 0; w < kWords; ++w) word[w] = 0xFFFFFFFFu;
+  const uint64_t first = share * (256u * kWords) + (uint64_t)lane_id() * (4 * kWords);  // the lane's buckets
+  if (first + 4 * kWords <= n) {
+    if constexpr (kWords == 4) {
+      const uint4 q = *reinterpret_cast<const uint4*>(t.oldest + (first >> 2));
+      word[0] = q.x;
+      word[1] = q.y;
+      word[2] = q.z;
+      word[3] = q.w;
+    } else {
+      word[0] = t.oldest[first >> 2];
+    }
+  } else {
+    for (uint32_t j = 0; j < 4 * kWords && first + j < n; ++j) {  // (tables of fewer than 2048 slots)
+      const uint32_t byte = reinterpret_cast<const uint8_t*>(t.oldest)[first + j];
+      word[j >> 2] = (word[j >> 2] & ~(0xFFu << (8 * (j & 3)))) | (byte << (8 * (j & 3)));
+    }
+  }
+}
+
 // kWords: words of four bounds per lane, so that a wave takes 256 * kWords buckets at a time.  Four of them (16-byte loads)
 // on large tables, whose bounds are then a plain stream; one on small tables, which would have too few waves.
 // keep_slots: the lists take slots and the slots stay as they are (see sweep_remove).
 template <int kWords>
 __global__ __launch_bounds__(256) void sweep_find_kernel(TableView t, uint32_t now, bool look_all, int keep_slots,
-                                                            int64_t* expired_keys, uint64_t max_expired) {
+                                                         int64_t* expired_keys, uint64_t max_expired) {
   constexpr uint32_t kBuckets = 256u * kWords;
   __shared__ uint16_t s_list[4][kBuckets];
   if (blockIdx.x == 0 && threadIdx.x == 0) sweep_stash(t, now, expired_keys, max_expired);
-  const uint32_t lane = lane_id(), grp = lane >> 3, l8 = lane & 7, wave = threadIdx.x >> 6;
+  const uint32_t lane = lane_id(), wave = threadIdx.x >> 6;
   const uint64_t n = 2 * t.n_buckets;
   const uint32_t shares = (uint32_t)((n + kBuckets - 1) / kBuckets), step = gridDim.x * 4;
   uint32_t share = blockIdx.x * 4 + wave;
   if (share >= shares) return;  // wave-uniform (no barriers below)
   uint32_t word[kWords];
-  const auto ask = [&]() {
-#pragma unroll
-    for (int w = 0; w < kWords; ++w) word[w] = 0xFFFFFFFFu;
-    const uint64_t first = (uint64_t)share * kBuckets + (uint64_t)lane * (4 * kWords);  // the lane's buckets
-    if (share >= shares) return;
-    if (first + 4 * kWords <= n) {
-      if constexpr (kWords == 4) {
-        const uint4 q = *reinterpret_cast<const uint4*>(t.oldest + (first >> 2));
-        word[0] = q.x;
-        word[1] = q.y;
-        word[2] = q.z;
-        word[3] = q.w;
-      } else {
-        word[0] = t.oldest[first >> 2];
-      }
-    } else {
-      for (uint32_t j = 0; j < 4 * kWords && first + j < n; ++j) {  // (tables of fewer than 2048 slots)
-        const uint32_t byte = reinterpret_cast<const uint8_t*>(t.oldest)[first + j];
-        word[j >> 2] = (word[j >> 2] & ~(0xFFu << (8 * (j & 3)))) | (byte << (8 * (j & 3)));
-      }
-    }
-  };
-  ask();
-  // Bounds are unambiguous while every key's last-seen step lies in the last kAgeModulus units: all keys that the
-  // latest sweep left were seen less than expire_steps before it.  Beyond that every bucket is looked at, as it is
-  // where the caller's steps went back behind the latest sweep (`now` did, or a lookup in between: look_all).
-  const uint32_t unit_now = now >> t.sweep_q, swept = t.ctl->swept;
-  const uint32_t unit_least = (swept > t.expire_steps ? swept - t.expire_steps : 0u) >> t.sweep_q;
-  look_all = look_all || unit_now - unit_least >= kAgeModulus - 1 || now < swept;
-  const OldBounds is_old(t, now, look_all);
+  load_bounds<kWords>(t, share, n, word);
+  const OldBounds is_old(t, now, looks_at_all(t, now, look_all));
   uint16_t* list = s_list[wave];  // the buckets to look at, of the wave's
   while (share < shares) {
     const uint64_t bucket0 = (uint64_t)share * kBuckets;
     const uint32_t out = share & (kWinLists - 1);  // the sub-list
-    uint32_t look = 0;  // one bit per bucket of the lane's; bit 16 h + 2 w + o: byte 2 h + o of word w
-#pragma unroll
-    for (int w = 0; w < kWords; ++w)
-      look |= is_old(word[w] & 0x00FF00FFu) << (2 * w) | is_old((word[w] >> 8) & 0x00FF00FFu) << (2 * w + 1);
+    const uint32_t total = list_old_buckets<kWords>(word, is_old, list);
     share += step;
-    ask();
-    if (__ballot(look != 0) == 0) continue;  // wave-uniform
-    const uint32_t inc = wave_sums((uint32_t)__popc(look)), total = __shfl(inc, 63);
-    wave_order();
-    {
-      uint32_t at = inc - (uint32_t)__popc(look);
-      for (uint32_t m = look; m; m &= m - 1) {
-        const uint32_t i = (uint32_t)__ffs((int)m) - 1u;
-        wave_store(list + at++, (uint16_t)(lane * (4 * kWords) + ((i >> 1) & 7u) * 4u + (i >> 4) * 2u + (i & 1u)));
-      }
-    }
-    wave_order();
-    constexpr int kTurns = 8;  // buckets per group of eight lanes with their meta words (64 bytes) in flight
-    for (uint32_t e0 = 0; e0 < total; e0 += 8 * kTurns) {
-      unsigned long long m[kTurns];
-#pragma unroll
-      for (int r = 0; r < kTurns; ++r) {
-        const uint32_t e = e0 + 8u * (uint32_t)r + grp;
-        m[r] = kNoMeta;
-        if (e < total) m[r] = t.buckets[bucket0 + wave_load(list + e)].meta[l8];
-      }
-      uint64_t gone[kTurns];
-      uint32_t found = 0;
-#pragma unroll
-      for (int r = 0; r < kTurns; ++r) {
-        gone[r] = 0;
-        if (e0 + 8u * (uint32_t)r >= total) continue;  // wave-uniform
-        const uint32_t e = e0 + 8u * (uint32_t)r + grp;
-        const bool live = meta_row(m[r]) != kNoRow, old = live && is_expired(t, now, meta_seen(m[r]));
-        gone[r] = __ballot(old);
-        found += (uint32_t)__popcll(gone[r]);
-        const uint32_t least = least_of_eight(live && !old ? meta_seen(m[r]) : 0xFFFFFFFFu);  // over the keys that stay
-        if (e < total && l8 == 0) {
-          const uint64_t b = bucket0 + wave_load(list + e);
-          // (a key from the future, seen after `now`: nothing is known)
-          const uint32_t age = least == 0xFFFFFFFFu ? kAgeEmpty : (least > now ? kAgeLook : sweep_unit(least, t.sweep_q));
-          reinterpret_cast<uint8_t*>(t.oldest)[b] = (uint8_t)age;
-          if (age == kAgeEmpty) atomicAnd(&t.occupied[b >> 6], ~(1ull << (b & 63)));
-        }
-      }
+    load_bounds<kWords>(t, share, n, word);  // (nothing beyond the last share)
+    for (uint32_t e0 = 0; e0 < total; e0 += 8 * kSweepTurns) {
+      unsigned long long m[kSweepTurns];
+      uint64_t gone[kSweepTurns];
+      const uint32_t found = look_at_buckets(t, now, bucket0, list, e0, total, m, gone);
       if (found == 0) continue;  // wave-uniform
       uint32_t p = 0;
       if (lane == 0) p = atomicAdd(&t.sweep_cnt[out * kWinStride], found);
       p = __shfl(p, 0);
-#pragma unroll
-      for (int r = 0; r < kTurns; ++r) {
-        if (gone[r] == 0) continue;  // wave-uniform
-        if ((gone[r] >> lane) & 1ull) {
-          const uint64_t b = bucket0 + wave_load(list + e0 + 8u * (uint32_t)r + grp);
-          t.sweep_list[(uint64_t)out * t.sweep_cap + p + (uint32_t)__popcll(gone[r] & lanes_below())] =
-              keep_slots ? (uint32_t)(b * kBucket + l8) : meta_row(m[r]);
-          if (!keep_slots) {
-            t.buckets[b].meta[l8] = kNoMeta;
-            t.buckets[b].key[l8] = kEmptyKey;
-          }
+      each_gone(bucket0, list, e0, m, gone, p, [&](uint32_t at, uint64_t b, unsigned long long meta) {
+        const uint32_t l8 = lane_id() & 7;
+        t.sweep_list[(uint64_t)out * t.sweep_cap + at] = keep_slots ? (uint32_t)(b * kBucket + l8) : meta_row(meta);
+        if (!keep_slots) {
+          t.buckets[b].meta[l8] = kNoMeta;
+          t.buckets[b].key[l8] = kEmptyKey;
         }
-        p += (uint32_t)__popcll(gone[r]);
-      }
+      });
     }
   }
+}
+
+// Both in one, for tables of few blocks whose caller does not ask for the removed keys: a block adds what it has found to one
+// word, at most four times, which gives it its place on the free stack; the block that comes last settles the counters.
+// One word takes an addition every 12 ns, so that with more blocks they wait for it as long as a launch takes (both kernels and
+// this one: 2^13 slots 11.9 and 8.7 us, 2^22 slots 9.4 and 5.8; training steps of 2^20 slots 64.6 and 60.8, 2^23 slots 112 and
+// 108; with 512 blocks for 2^24 slots 248.6 and 249.6, with 1024 for 2^25, a million keys removed, 1122 and 1128).
+constexpr int kSweepSmallThreads = 1024, kSweepSmallWaves = kSweepSmallThreads / 64;
+constexpr uint64_t kSweepSmallBlocks = 256;  // 2^23 slots
+
+__global__ __launch_bounds__(kSweepSmallThreads) void sweep_small_kernel(TableView t, uint32_t now, bool look_all,
+                                                                         uint64_t* n_expired) {
+  __shared__ uint16_t s_list[kSweepSmallWaves][256];
+  __shared__ uint32_t s_found[kSweepSmallWaves], s_rounds;
+  __shared__ unsigned long long s_before;
+  const uint32_t wave = threadIdx.x >> 6, share = blockIdx.x * kSweepSmallWaves + wave;
+  uint32_t word[1];
+  load_bounds<1>(t, share, 2 * t.n_buckets, word);
+  // settled by the last block, constant until then
+  const int32_t free0 = t.ctl->free_n;
+  const uint32_t in_stash = t.ctl->stash_n;
+  const unsigned long long expired0 = t.ctl->n_expired;
+  const OldBounds is_old(t, now, looks_at_all(t, now, look_all));
+  if (threadIdx.x == 0) s_rounds = 1;
+  __syncthreads();
+  uint16_t* list = s_list[wave];
+  const uint64_t bucket0 = (uint64_t)share * 256u;
+  const uint32_t total = list_old_buckets<1>(word, is_old, list);
+  if (total > 8 * kSweepTurns && lane_id() == 0) atomicMax(&s_rounds, (total + 8 * kSweepTurns - 1) / (8 * kSweepTurns));
+  __syncthreads();
+  const uint32_t rounds = s_rounds;
+  unsigned long long removed = 0;  // by this block and those before it
+  for (uint32_t round = 0; round < rounds; ++round) {  // block-uniform
+    const uint32_t e0 = round * 8 * kSweepTurns;
+    unsigned long long m[kSweepTurns];
+    uint64_t gone[kSweepTurns];
+    uint32_t found = 0;
+    if (e0 < total) found = look_at_buckets(t, now, bucket0, list, e0, total, m, gone);  // wave-uniform
+    if (lane_id() == 0) s_found[wave] = found;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    for (uint32_t w = 0; w < (uint32_t)kSweepSmallWaves; ++w) {
+      if (w == wave) before = all;
+      all += s_found[w];
+    }
+    // high half: keys removed; low half: blocks done
+    if (threadIdx.x == 0)
+      s_before = atomicAdd(&t.ctl->scratch[kSweepDone], (unsigned long long)all << 32 | (round == rounds - 1 ? 1ull : 0ull));
+    __syncthreads();
+    const uint32_t first = (uint32_t)(s_before >> 32);
+    removed = (unsigned long long)first + all;
+    if (found)
+      each_gone(bucket0, list, e0, m, gone, first + before, [&](uint32_t at, uint64_t b, unsigned long long meta) {
+        t.free_rows[free0 + (int32_t)at] = meta_row(meta);
+        t.buckets[b].meta[lane_id() & 7] = kNoMeta;
+        t.buckets[b].key[lane_id() & 7] = kEmptyKey;
+      });
+  }
+  if (threadIdx.x != 0 || (uint32_t)s_before != gridDim.x - 1) return;
+  t.ctl->scratch[kSweepDone] = 0;
+  t.ctl->free_n = free0 + (int32_t)removed;
+  t.ctl->swept = now;
+  if (in_stash) {
+    sweep_stash(t, now, nullptr, 0);  // (counts on from there)
+    removed += t.ctl->scratch[kSweepRemoved];
+  }
+  t.ctl->n_expired = expired0 + removed;
+  if (n_expired) *n_expired = removed;
 }
 
 // expired_keys != nullptr: the lists hold slots, which are cleared here.
@@ -260,6 +356,12 @@ hipError_t launch_expire_sweep(const TableView& t, uint32_t now, bool look_all, 
                                int64_t* d_expired_keys, uint64_t max_expired, hipStream_t stream, Profiler* prof) {
   if (t.expire_steps == 0) {  // nothing ever expires: only the count is reported
     if (d_n_expired) MONO_LAUNCH(prof, K_SWEEP_END, stream, sweep_nothing_kernel, dim3(1), dim3(64), d_n_expired);
+    return hipGetLastError();
+  }
+  const uint64_t small = (2 * t.n_buckets + 256 * kSweepSmallWaves - 1) / (256 * kSweepSmallWaves);
+  if (!d_expired_keys && small <= kSweepSmallBlocks) {
+    MONO_LAUNCH(prof, K_SWEEP, stream, sweep_small_kernel, dim3((unsigned)small), dim3(kSweepSmallThreads), t, now, look_all,
+                d_n_expired);
     return hipGetLastError();
   }
   const uint64_t waves = (2 * t.n_buckets + sweep_wave_buckets(t.capacity) - 1) / sweep_wave_buckets(t.capacity);

@@ -1,5 +1,5 @@
-"""Tables so large that a wave of the sweep takes several shares of the buckets: keys all over the table, few to a share,
-expire, stay or come back; every sweep removes the oracle's keys."""
+"""Tables on either side of the sizes from which a sweep takes two kernels and from which its waves take several shares of the
+buckets: keys all over the table, expire, stay or come back; every sweep removes the oracle's keys."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +10,7 @@ from tests import table_checks as tc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("log2,expire", [(27, 3), (28, 3), (28, 205)])       # (one share a wave; two; two, bounds in units of four)
+@pytest.mark.parametrize("log2,expire", [(23, 3), (23, 205), (24, 3), (27, 3), (28, 3), (28, 205)])
 def test_sweeps_remove_what_the_oracle_removes(log2, expire):
     from paper_2209_07663_amd.binding import Table
     dev, seed = torch.device("cuda:0"), 41
