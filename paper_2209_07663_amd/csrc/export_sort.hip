@@ -85,12 +85,7 @@ __global__ __launch_bounds__(kThreads) void export_scan_kernel(uint32_t* __restr
   for (uint64_t u0 = 0; u0 < units; u0 += kThreads) {
     const uint64_t u = u0 + threadIdx.x;
     const uint32_t v = u < units ? row[u] : 0u;
-    uint32_t x = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d);
-      if ((int)lane >= d) x += y;
-    }
+    const uint32_t x = wave_sums(v);
     if (lane == 63) wave_sum[wave] = x;
     __syncthreads();
     uint32_t before = carry, all = 0;
@@ -141,15 +136,7 @@ __global__ __launch_bounds__(kThreads) void export_scatter_kernel(const uint64_t
   uint32_t mine = 0;
 #pragma unroll
   for (int w = 0; w < kWaves; ++w) mine += cnt[w][tid];
-  uint32_t x = mine, y = tot;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t xs = __shfl_up(x, d), ys = __shfl_up(y, d);
-    if ((int)lane >= d) {
-      x += xs;
-      y += ys;
-    }
-  }
+  const uint32_t x = wave_sums(mine), y = wave_sums(tot);
   if (lane == 63) {
     sum_w[wave] = x;
     tot_w[wave] = y;

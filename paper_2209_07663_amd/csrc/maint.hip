@@ -292,12 +292,7 @@ __global__ __launch_bounds__(kSweepSmallThreads) void sweep_small_kernel(TableVi
 __global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, uint32_t now, int64_t* expired_keys,
                                                            uint64_t max_expired, uint64_t* n_expired) {
   const uint32_t lane = lane_id();
-  uint32_t inc = t.sweep_cnt[lane * kWinStride];
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(inc, d);
-    if ((int)lane >= d) inc += y;
-  }
+  const uint32_t inc = wave_sums(t.sweep_cnt[lane * kWinStride]);
   const uint32_t total = __shfl(inc, 63);
   const int32_t free0 = t.ctl->free_n;                     // settled by the last block, constant until then
   const unsigned long long out0 = t.ctl->scratch[kSweepRemoved];       // keys already reported from the stash

@@ -155,12 +155,7 @@ __global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __rest
 __device__ inline uint4 plus(uint4 a, uint4 b) { return make_uint4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 __device__ inline uint4 minus(uint4 a, uint4 b) { return make_uint4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w); }
 __device__ inline uint4 wave_scan(uint4 x) {  // inclusive
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint4 y = make_uint4(__shfl_up(x.x, d), __shfl_up(x.y, d), __shfl_up(x.z, d), __shfl_up(x.w, d));
-    if ((int)lane_id() >= d) x = plus(x, y);
-  }
-  return x;
+  return make_uint4(wave_sums(x.x), wave_sums(x.y), wave_sums(x.z), wave_sums(x.w));
 }
 constexpr int kScanBlock = 1024;
 constexpr uint32_t kScanPer = 8;  // groups per thread and round
@@ -239,12 +234,7 @@ __global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __res
     if (u + 3 >= units) v[j].w = 0;
     sum += v[j].x + v[j].y + v[j].z + v[j].w;
   }
-  uint32_t x = sum;  // inclusive wave scan of the lane sums
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const uint32_t y = __shfl_up(x, d);
-    if ((int)lane >= d) x += y;
-  }
+  const uint32_t x = wave_sums(sum);
   uint32_t run = x - sum;
 #pragma unroll
   for (uint32_t j = 0; j < kScanFew; ++j) {
@@ -377,15 +367,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
         for (int w = 0; w < S::kWaves; ++w) mine += lds[w][bin0 + q];
       }
     }
-    uint32_t x = mine, y = tots;  // inclusive wave scans
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t xs = __shfl_up(x, d), ys = __shfl_up(y, d);
-      if ((int)lane >= d) {
-        x += xs;
-        y += ys;
-      }
-    }
+    const uint32_t x = wave_sums(mine), y = wave_sums(tots);
     if (bin_thread && lane == 63) {
       scan_sum[wave] = x;
       scan_tot[wave] = y;
@@ -556,12 +538,7 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
 #pragma unroll
       for (uint32_t w = 0; w < kSmallWaves; ++w) mine += cnt[w][tid];
     }
-    uint32_t x = mine;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t y = __shfl_up(x, d);
-      if ((int)lane >= d) x += y;
-    }
+    const uint32_t x = wave_sums(mine);
     if (tid < kBins && lane == 63) wave_sum[wave] = x;
     __syncthreads();
     if (tid < kBins) {
