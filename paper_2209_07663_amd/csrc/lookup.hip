@@ -525,6 +525,7 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
   const int restore = src.values != nullptr;
   if (!restore && n <= kSmallLookup) return launch_lookup_small(t, d_keys, n, step, epoch, d_rows_out, stream, prof);
   const dim3 block(256), grid((unsigned)((n + 255) / 256));
+  // (insertion: a wave for 16 IDs, all of which may be new; see insert_kernel's span)
   const uint64_t iblocks = (n + 63) / 64;
   const dim3 igrid((unsigned)(iblocks < 2048 ? iblocks : 2048));
   {

@@ -1,9 +1,10 @@
 // apply_grad_adagrad: duplicate-ID gradient scatter-reduce + row-wise Adagrad.
 //
-//   sort         stable radix sort of (row, bag) by row: the occurrences of a row become one run (the
+//   sort         grouping of (row, bag) by row, stable: the occurrences of a row become one run (the
 //                pooled gradient of bag b is the gradient of each of its occurrences; the first pass
 //                finds the bag of every occurrence from the offsets); dropped occurrences (row -1) are
 //                left out
+//   order_tiles  (many gradients, each of several occurrences) the order in which seg_reduce takes its tiles
 //   seg_reduce   the sorted sequence is cut into tiles, a block each, and a tile into chunks, one for each lane
 //                group of the block (dim/4 lanes, four elements each); the group loads its chunk's pairs at once, then walks
 //                them with eight gradient rows in flight, summing grad[bag] along each run.  A run that lies
