@@ -211,6 +211,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
       s.f.key[x] = mk[j];
     }
   }
+  wait_all_memory_ops();  // (the list is written over below, and nothing else waits for the last occurrence number)
   __syncthreads();
   uint32_t cnt[kSmallPerThread];
 #pragma unroll
