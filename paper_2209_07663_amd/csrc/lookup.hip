@@ -360,10 +360,11 @@ __device__ inline void note_sample(const TableView& t, uint64_t enough) {
 
 // Dense over the elected occurrences: winner number w of the call takes free_rows[free_n - 1 - w].
 // kAll (batches of at most kElectSmall): the duplicates of admitted keys take their rows here too.  The elected
-// occurrence's word in rows_out tells its place in its sub-list until it holds the row, and the number of a winner follows
-// from its place, so that nobody waits for anybody; the block that finishes last settles the counters.  A kernel of its
-// own for that is a launch more, 3 us of a call that has no miss (steps of 5 to 200 K known IDs 23 -> 19, 30 -> 28, 64 -> 60
-// us).  Large batches have it: the winners' places are a write more per new key (6.8 M IDs, a million new: election and
+// occurrence's word in rows_out tells its place in its sub-list until it holds the row (stored and read at agent scope: its
+// block and the duplicates' run together), and the number of a winner follows from its place, so that nobody waits for
+// anybody; the block that finishes last settles the counters.  A kernel of its own for that is a launch more, 3 us of a
+// call that has no miss (steps of 5 to 200 K known IDs 23 -> 19, 30 -> 28, 64 -> 60 us).  Large batches have it: the
+// winners' places are a write more per new key (6.8 M IDs, a million new: election and
 // insertion 276 us, with resolve_kernel 267).
 template <typename E, bool kAll>
 __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n, uint32_t step, uint32_t epoch,
@@ -421,7 +422,11 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
       occ = e.occ;
       k = e.key;
       if (room) row = t.free_rows[free0 - 1 - (int32_t)w];
-      rows_out[e.occ] = row == kNoRow ? kRowAbsent : (int32_t)row;
+      const int32_t found = row == kNoRow ? kRowAbsent : (int32_t)row;
+      if (kAll)  // (other blocks look for it below)
+        st_agent(&rows_out[e.occ], found);
+      else
+        rows_out[e.occ] = found;
       if (row != kNoRow) {
         const unsigned long long meta = make_meta(row, src.seen ? src.seen[e.occ] : step);
         if (!claim_free(t, k, meta, unit)) {
@@ -454,11 +459,11 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   if constexpr (!kAll) return;
   if (t.ctl->scratch[kDuplicateTag] == epoch) {  // (else every missing key of the call occurred once, or was not admitted)
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ((n + 63) & ~63ull); i += stride) {  // wave-uniform
-      const int32_t v = i < n ? rows_out[i] : kRowAbsent;
+      const int32_t v = i < n ? ld_agent(&rows_out[i]) : kRowAbsent;
       const bool duplicate = v <= -3 && v > kRowElected;
       if (!__ballot(duplicate)) continue;
       const uint64_t owner = duplicate ? (uint64_t)(-(int64_t)v - 3) : 0;
-      const int32_t o = duplicate ? rows_out[owner] : kRowAbsent;
+      const int32_t o = duplicate ? ld_agent(&rows_out[owner]) : kRowAbsent;
       const uint32_t list = (uint32_t)(owner / kElectBlock) & (kWinLists - 1);  // (a block of the election appends to one)
       const uint32_t before = __shfl(inc, (int)(list > 0 ? list - 1 : 0));
       if (duplicate) {
