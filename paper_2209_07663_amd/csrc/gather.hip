@@ -249,6 +249,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
 // 179, 240 MB 214 and 210, 400 MB 341 and 321).  Rows of eight elements per lane never do: a lane stores them in two
 // pieces, which past the caches reach the memory as half lines (bf16 of dim 512, 66 MB 71 and 91 us, 400 MB 350 and 429).
 constexpr uint64_t kPooledCached = 192ull << 20;
+constexpr uint64_t kMostWaves = (1ull << 26) - 4;  // a launch has fewer than 2^32 threads, in whole blocks of four waves
 struct GatherShape {
   uint32_t group_log2 = 0, bags_log2 = 6;
   bool past_caches;
@@ -261,7 +262,9 @@ struct GatherShape {
     else if (group_log2 >= 3 && ids < (uint32_t)kIdsInRegs)
       bags_log2 = group_log2 == 3 ? 5 : 4;
     while (bags_log2 > 6 - group_log2 && (n_bags >> bags_log2) < kWavesWanted) --bags_log2;
-    waves = (n_bags + (1ull << bags_log2) - 1) >> bags_log2;
+    const auto waves_of = [&](uint32_t lg) { return (n_bags + (1ull << lg) - 1) >> lg; };
+    while (bags_log2 < 6 && waves_of(bags_log2) > kMostWaves) ++bags_log2;
+    waves = waves_of(bags_log2);
   }
 };
 

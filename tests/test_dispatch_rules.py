@@ -60,6 +60,32 @@ int main() {
 """)
 
 
+def test_pooling_launches_less_than_2_to_32_threads(tmp_path):
+    """However many bags there are, and however few of them a wave takes for the dimension: a launch of 2^32 threads or
+    more is refused.  (Of 2^32 bags and more there is no launch, with 64 of them in a wave.)"""
+    _run(tmp_path, r"""
+#include "gather.hip"
+using namespace mono;
+int main() {
+  int wrong = 0;
+  const unsigned long long most = (1ull << 32) - 256;
+  for (unsigned dim : {4u, 16u, 32u, 36u, 64u, 128u, 132u, 256u, 512u, 768u, 1024u})
+    for (unsigned per_lane : {4u, 8u})
+      for (unsigned ids : {4u, 8u})
+        for (unsigned lg = 0; lg <= 32; ++lg)
+          for (long long d : {-70ll, -16ll, -15ll, -1ll, 0ll, 1ll, 17ll}) {
+            const long long bags = (1ll << lg) + d;
+            if (bags < 1 || bags > (long long)most) continue;
+            const GatherShape s(dim, per_lane, bags, ids);
+            const unsigned long long threads = (s.waves + 3) / 4 * 256;
+            if (threads >= 1ull << 32 || s.waves << s.bags_log2 < (unsigned long long)bags || s.bags_log2 > 6 || s.bags_log2 + s.group_log2 < 6)
+              printf("dim %u, %lld bags: %llu threads\n", dim, bags, threads), ++wrong;
+          }
+  return wrong ? 1 : 0;
+}
+""")
+
+
 def test_two_wide_digits_only_where_they_are_faster_and_the_workspace_holds_every_shape(tmp_path):
     """Two digits of up to 11 bits: batches of 2^17 pairs up to 2^20 rows in use (digits of 10 bits), 2^16 up to 2^21,
     2^15 up to 2^22.  The histogram workspace for batches of n pairs holds what any shape of any smaller batch needs."""
