@@ -35,9 +35,11 @@ struct UpdateWorkspace {
 //   300 K, 1 M rows   45 / 49 us    50 / 54       54 / 56       56 / 57       58 / 63, 66 / 65
 //   1.3 M             49 / 51       57 / 58       61 / 59       66 / 60
 //   3.9 M             52 / 53       61 / 59       66 / 60       72 / 62
-// Batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch, and those of up to kSplitMost in two
-// (below): of such batches only those of at most kSortSmall pairs in more than twice as many bags come here.  (One block or
-// split: steps of 2.3 and 3 K pairs 42.5 and 43.6, 37.5 and 40.3 us, of 4.3 K 52 and 49, of 7.1 K 51 and 45.)
+// Batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch, unless they have more than
+// kSortSmallBags bags, which that block would have to walk all by itself; those of up to kSplitMost are sorted in two
+// launches (below).  (One block or split: steps of 2.3 and 3 K pairs 42.5 and 43.6, 37.5 and 40.3 us, of 4.3 K 52 and 49, of
+// 7.1 K 51 and 45.  Updates of 4 K pairs in 12 K bags, dims 4, 32, 512, in one block or with two wide digits: 28 / 35 us,
+// 32 / 37, 36 / 42.)
 struct SortShape {
   uint32_t max_bits, items;
 };
@@ -49,7 +51,8 @@ constexpr uint32_t kSortFewRowsAbove = 1u << 16, kSortFewRows10 = 1u << 20, kSor
 inline uint64_t sort_few_most(uint32_t rows) {
   return rows <= kSortFewRows10 ? kSortFewMost : (rows <= 2 * kSortFewRows10 ? kSortFewMost / 2 : kSortFewMost / 4);
 }
-constexpr uint64_t kSortSmall = 4096;
+constexpr uint64_t kSortSmall = 4096, kSortSmallBags = 1u << 14;
+inline bool sorts_in_one_block(uint64_t n, uint64_t n_bags) { return n <= kSortSmall && n_bags <= kSortSmallBags; }
 inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
   if (hwm_bound > kSortFewRowsAbove && hwm_bound <= kSortFewMaxRows && n <= sort_few_most(hwm_bound)) return {kSortFewBits, 512u};
   if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, 4096u};

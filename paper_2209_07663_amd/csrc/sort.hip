@@ -609,7 +609,7 @@ hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, cons
   if (launched) *launched = worst.passes;
   if (max_bits) *max_bits = shape.max_bits;
   if (n == 0) return hipSuccess;
-  if (n <= kSortSmall && n_bags <= 2 * kSortSmall) {  // (one block walks all bags: not for a million empty ones)
+  if (sorts_in_one_block(n, n_bags)) {
     MONO_LAUNCH(prof, K_SORT_SCATTER, stream, sort_small_kernel, dim3(1), dim3(kSmallBlock), t.ctl, shape.max_bits, d_rows,
                 (uint32_t)n, d_offsets, n_bags, ws.pair_a, ws.pair_b);
     return hipGetLastError();

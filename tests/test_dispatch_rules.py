@@ -86,6 +86,21 @@ int main() {
 """)
 
 
+def test_small_batches_of_many_bags_are_sorted_by_one_block(tmp_path):
+    """Up to 4096 pairs in up to 16384 bags, most of them empty: one launch instead of six or nine."""
+    _run(tmp_path, r"""
+#include "kernels.h"
+using namespace mono;
+int main() {
+  int wrong = 0;
+  for (unsigned long long n : {1ull, 100ull, 4095ull, 4096ull, 4097ull, 8192ull, 1ull << 20, 1ull << 22})
+    for (unsigned long long bags : {1ull, 4096ull, 8192ull, 8193ull, 12288ull, 16384ull, 16385ull, 1ull << 20})
+      if (sorts_in_one_block(n, bags) != (n <= 4096 && bags <= 16384)) printf("%llu pairs, %llu bags\n", n, bags), ++wrong;
+  return wrong;
+}
+""")
+
+
 def test_two_wide_digits_only_where_they_are_faster_and_the_workspace_holds_every_shape(tmp_path):
     """Two digits of up to 11 bits: batches of 2^17 pairs up to 2^20 rows in use (digits of 10 bits), 2^16 up to 2^21,
     2^15 up to 2^22.  The histogram workspace for batches of n pairs holds what any shape of any smaller batch needs."""
