@@ -8,6 +8,7 @@ pytestmark = pytest.mark.gpu
 
 LR, EPS, DIM = 0.05, 1e-8, 4
 MOST_IN_LDS = 4096
+LOSES_NO_PAIR = 16 * 2.0 ** -24
 
 
 def _table(used, capacity):
@@ -21,13 +22,18 @@ def _table(used, capacity):
 
 
 def _step(tab, dev, used, rows, lengths, acc):
-    """One update of the table; `acc` (fp64, per row) goes along.  Compares every row in use."""
+    """One update of the table; `acc` (fp64, per row) goes along.  Compares every row in use and its accumulator.
+
+    Gradients are 7, 8 or 9 times 2^-10: the sum of up to 2^20 of them is exact in fp32, in whatever order.  The mean of
+    their four squares takes at most five roundings of 2^-24, and one more for every step before; a pair that is lost or
+    taken twice changes it by 2 * 7 / 9 * 2^-20 or more.  (A row's move says little of the length of its sum: from an
+    accumulator of zero it is the same for a sum and for half of it.)"""
     g = torch.Generator(device=dev).manual_seed(rows.shape[0])
     rows = torch.as_tensor(rows, dtype=torch.int32, device=dev)
     offs = torch.zeros(lengths.shape[0] + 1, dtype=torch.int64, device=dev)
     torch.cumsum(lengths, 0, out=offs[1:])
     assert int(offs[-1]) == rows.shape[0]
-    grad = torch.rand((lengths.shape[0], DIM), device=dev, generator=g) + 0.25     # (no sum cancels)
+    grad = torch.randint(7, 10, (lengths.shape[0], DIM), device=dev, generator=g).float() * 2.0 ** -10
     each, every = torch.arange(used + 1, device=dev), torch.arange(used, dtype=torch.int32, device=dev)
     before = tab.mono_gather_pool(every, each).double()
     tab.mono_apply_grad_adagrad(rows, offs, grad, LR, EPS)
@@ -42,9 +48,12 @@ def _step(tab, dev, used, rows, lengths, acc):
     total = sums[ends] - sums[ends - count[:, 0].long()]
     acc += (total ** 2).mean(1)
     move = LR * total / (acc.sqrt()[:, None] + EPS)
-    # see test_gpu_reduce_runs.py; the accumulator of an earlier step carries another such error
-    rel = 4 * (272 + count / 256) * 2.0 ** -24
-    assert ((after - (before - move)).abs() <= rel * move + before.abs() * 2.0 ** -23 + 2.0 ** -40).all()
+    dump = tab.mono_table_export()
+    stored = torch.zeros(used, dtype=torch.float64, device=dev)
+    stored[torch.from_numpy(dump["row"].astype(np.int64)).to(dev)] = torch.from_numpy(dump["acc"].astype(np.float64)).to(dev)
+    assert ((stored - acc).abs() <= LOSES_NO_PAIR * acc).all()
+    # half of the accumulator's error, a root and a reciprocal of one unit each, three roundings of products and the row's own
+    assert ((after - (before - move)).abs() <= 16 * 2.0 ** -24 * move + before.abs() * 2.0 ** -23 + 2.0 ** -40).all()
     assert tab.mono_table_stats()["n_lost"] == 0
 
 
