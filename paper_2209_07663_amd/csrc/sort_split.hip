@@ -13,8 +13,10 @@
 // Bins must fit into LDS whatever rows the batch holds.  A bin is the upper bits of a bijective hash of the row (four
 // neighbouring rows, whose states share a line, stay together), so that rows spread evenly; rows that make up a good part
 // of the batch are told from a sample of it and have a bin each, which needs no sort and may be of any size.  Every block
-// takes the same sample and comes to the same answer.  A bin that is too large all the same (by chance, or because
-// someone chose the rows so) is taken in pieces, by ranges of rows: 60 us for 4.2 K pairs of one bin.
+// takes the same sample and comes to the same answer.  A bin that is too large all the same, for a row that the sample has
+// missed, is sorted by words of half the size (kBucketWords).  What is larger than that takes rows that someone chose for
+// it; such a bin is taken in pieces, by ranges of rows, by its one block: the more pairs, the more ranges and the longer
+// each, 0.9 ms for 30 K pairs of one bin, 12 for 120 K, 117 for 500 K, 680 for a million.
 //
 // Both kernels are chains of dependent steps, ten thousand cycles in all: blocks of few waves (one to a SIMD: instructions
 // of several would queue for it; two where a block has 2048 pairs), loads as early as their addresses are known, little
@@ -322,6 +324,11 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
 // ---- buckets ---------------------------------------------------------------------------------------
 
 constexpr uint32_t kBucketMost = 4096;  // pairs that a block sorts in LDS
+// Twice as many, where a key within the bucket and a place in it fit a word together: the words are sorted then, which take
+// half the room, and the bags fetched in their order.  (Of 200 batches each of 524 K and of a million pairs, Zipf 0.9 to 1.5,
+// one in six has such a bin, and none a bin of more than 5.6 K; taken in pieces, such a bin held up the update of 400 K
+// pairs, dim 128 in bf16, 130 us instead of 102, and of a million, dim 32, 151 instead of 104.)
+constexpr uint32_t kPlaceBits = 13, kBucketWords = 1u << kPlaceBits;
 constexpr uint32_t kBucketDigit = 8, kBucketBins = 1u << kBucketDigit;
 constexpr uint32_t kTogether = 4;  // pairs that a thread asks for at a time
 
@@ -330,32 +337,47 @@ struct BucketLds {
   static constexpr int kWaves = kBlock / 64;
   uint32_t first[kBlock];  // pairs of the bin in the units before this one
   uint32_t from[kBlock];   // where the unit's share of the bin lies
-  uint2 pairs[2][kBucketMost];
+  union {
+    uint2 pairs[2][kBucketMost];
+    uint32_t words[2][kBucketWords];  // key within the bucket << kPlaceBits | place in the bin
+  };
   uint32_t cnt[kWaves][kBucketBins];
   uint32_t wave_sum[2 * kWaves];
   uint32_t range[3];
 };
 
-// kTogether pairs of the bin, in the order of the batch: q, q + step, ...; those from `end` on are left as they are
+// The pairs at kTogether places of the bin, which is in the order of the batch; those at places from `end` on are left as they are.
 template <int kBlock>
-__device__ inline void pairs_of_bin(const BucketLds<kBlock>& s, uint32_t units_pow2, const uint2* __restrict__ src,
-                                    uint32_t q, uint32_t step, uint32_t end, uint2 (&p)[kTogether]) {
+__device__ inline void pairs_at(const BucketLds<kBlock>& s, uint32_t units_pow2, const uint2* __restrict__ src,
+                                const uint32_t (&at)[kTogether], uint32_t end, uint2 (&p)[kTogether]) {
   uint32_t u[kTogether];
 #pragma unroll
   for (uint32_t j = 0; j < kTogether; ++j) u[j] = 0;
   for (uint32_t d = units_pow2 >> 1; d > 0; d >>= 1) {
 #pragma unroll
-    for (uint32_t j = 0; j < kTogether; ++j) u[j] += s.first[u[j] + d] <= q + j * step ? d : 0u;
+    for (uint32_t j = 0; j < kTogether; ++j) u[j] += s.first[u[j] + d] <= at[j] ? d : 0u;
   }
 #pragma unroll
   for (uint32_t j = 0; j < kTogether; ++j)
-    if (q + j * step < end) p[j] = src[s.from[u[j]] + (q + j * step - s.first[u[j]])];
+    if (at[j] < end) p[j] = src[s.from[u[j]] + (at[j] - s.first[u[j]])];
+}
+// q, q + step, ...
+template <int kBlock>
+__device__ inline void pairs_of_bin(const BucketLds<kBlock>& s, uint32_t units_pow2, const uint2* __restrict__ src,
+                                    uint32_t q, uint32_t step, uint32_t end, uint2 (&p)[kTogether]) {
+  uint32_t at[kTogether];
+#pragma unroll
+  for (uint32_t j = 0; j < kTogether; ++j) at[j] = q + j * step;
+  pairs_at(s, units_pow2, src, at, end, p);
 }
 
-// Stable sort of s.pairs[0][0 .. count) by the low `bits` bits of their keys; returns which half of s.pairs holds the result.
-// Per digit two walks over the pairs, 64 at a time: one counts, one ranks and places.
-template <int kBlock>
-__device__ inline uint32_t sort_bucket(BucketLds<kBlock>& s, uint32_t count, uint32_t bits) {
+__device__ inline uint32_t sort_key(uint2 pair) { return pair.x; }
+__device__ inline uint32_t sort_key(uint32_t word) { return word >> kPlaceBits; }
+
+// Stable sort of first[0 .. count) by the low `bits` bits of the keys, with room in `second`; returns which holds the result.
+// Per digit two walks over the elements, 64 at a time: one counts, one ranks and places.
+template <int kBlock, typename T>
+__device__ inline const T* sort_bucket(BucketLds<kBlock>& s, T* first, T* second, uint32_t count, uint32_t bits) {
   constexpr int kWaves = kBlock / 64;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
   const uint32_t passes = (bits + kBucketDigit - 1) / kBucketDigit, per = passes ? (bits + passes - 1) / passes : 0;
@@ -364,12 +386,12 @@ __device__ inline uint32_t sort_bucket(BucketLds<kBlock>& s, uint32_t count, uin
 #pragma unroll 1
   for (uint32_t pass = 0; pass < passes; ++pass) {
     const uint32_t shift = pass * per, width = min(bits - shift, per), mask = (1u << width) - 1;
-    const uint2* from = s.pairs[pass & 1];
-    uint2* to = s.pairs[1 - (pass & 1)];
+    const T* from = pass & 1 ? second : first;
+    T* to = pass & 1 ? first : second;
 #pragma unroll
     for (uint32_t b = 0; b < kBucketBins; b += 64) wave_store(off + b + lane, 0u);
     wave_order();
-    for (uint32_t i = wave * share + lane; i < end; i += 64) atomicAdd(&s.cnt[wave][(from[i].x >> shift) & mask], 1u);
+    for (uint32_t i = wave * share + lane; i < end; i += 64) atomicAdd(&s.cnt[wave][(sort_key(from[i]) >> shift) & mask], 1u);
     __syncthreads();
     uint32_t c[kWaves], mine = 0;  // a bin per thread
 #pragma unroll
@@ -392,18 +414,18 @@ __device__ inline uint32_t sort_bucket(BucketLds<kBlock>& s, uint32_t count, uin
     __syncthreads();
     for (uint32_t i0 = wave * share; i0 < end; i0 += 64) {  // wave-uniform
       const bool valid = i0 + lane < end;
-      const uint2 p = valid ? from[i0 + lane] : make_uint2(0u, 0u);
-      const uint32_t digit = (p.x >> shift) & mask;
+      const T e = valid ? from[i0 + lane] : T{};
+      const uint32_t digit = (sort_key(e) >> shift) & mask;
       const uint64_t peers = same_digit_lanes<kBucketDigit>(digit, width, valid);
       const uint32_t at = wave_load(off + digit);
-      if (valid) to[at + (uint32_t)__popcll(peers & lanes_below())] = p;
+      if (valid) to[at + (uint32_t)__popcll(peers & lanes_below())] = e;
       wave_order();
       if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
       wave_order();
     }
     __syncthreads();
   }
-  return passes & 1;
+  return passes & 1 ? second : first;
 }
 
 template <int kBlock>
@@ -468,10 +490,35 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
     }
     return;
   }
+  const uint32_t all = 1u << split.rest, keys = all - 1;
+  if (count > kBucketMost && count <= kBucketWords && split.rest <= 32 - kPlaceBits) {
+    for (uint32_t q = tid; q < count; q += kBlock * kTogether) {
+      uint2 p[kTogether];
+      pairs_of_bin(s, units_pow2, src, q, kBlock, count, p);
+#pragma unroll
+      for (uint32_t j = 0; j < kTogether; ++j) {
+        const uint32_t at = q + j * kBlock;
+        if (at < count) s.words[0][at] = (p[j].x & keys) << kPlaceBits | at;
+      }
+    }
+    __syncthreads();
+    const uint32_t* sorted = sort_bucket(s, s.words[0], s.words[1], count, split.rest);
+    for (uint32_t q = tid; q < count; q += kBlock * kTogether) {
+      uint32_t at[kTogether];
+      uint2 p[kTogether];
+#pragma unroll
+      for (uint32_t j = 0; j < kTogether; ++j)
+        at[j] = q + j * kBlock < count ? sorted[q + j * kBlock] & (kBucketWords - 1) : 0xFFFFFFFEu;
+      pairs_at(s, units_pow2, src, at, count, p);
+#pragma unroll
+      for (uint32_t j = 0; j < kTogether; ++j)
+        if (q + j * kBlock < count) dst[base + q + j * kBlock] = make_uint2(split.row(p[j].x, inv), p[j].y);
+    }
+    return;
+  }
   // Ranges [low, high) of the keys within the bucket, one after the other, each with no more pairs than fit into LDS: all
   // keys at once, nearly always.  A key with more pairs than that is copied.
   uint32_t done = 0, low = 0;
-  const uint32_t all = 1u << split.rest, keys = all - 1;
   while (low < all && done < count) {
     uint32_t high = all, here = count;
     bool copy = false;
@@ -554,7 +601,7 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
     }
     __syncthreads();
     if (!copy) {
-      const uint2* sorted = s.pairs[sort_bucket(s, here, split.rest)];
+      const uint2* sorted = sort_bucket(s, s.pairs[0], s.pairs[1], here, split.rest);
       for (uint32_t q = tid; q < here; q += kBlock)
         dst[base + done + q] = make_uint2(split.row(sorted[q].x, inv), sorted[q].y);
       __syncthreads();

@@ -1,5 +1,5 @@
 """Updates of 4 K to a million pairs, which are split and sorted by bucket: both sides of every size, few rows in use, hot
-rows, dropped occurrences and empty bags, and buckets that do not fit into a block's LDS; against fp64 sums and Adagrad."""
+rows, dropped occurrences and empty bags, and buckets that do not fit into a block's LDS at once; against fp64 sums and Adagrad."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ LOSES_NO_PAIR = 16 * 2.0 ** -24
 def _table(used, capacity):
     from paper_2209_07663_amd.binding import Table
     dev = torch.device("cuda:0")
-    tab = Table(capacity, DIM, 5, max_ids=1 << 21, max_bags=1 << 21, device=dev)
+    tab = Table(capacity, DIM, 5, max_ids=max(1 << 21, used), device=dev)
     for lo in range(0, used, 1 << 21):
         tab.mono_lookup_or_insert(torch.arange(lo, min(lo + (1 << 21), used), device=dev), 0)
     assert tab.mono_table_stats()["size"] == used           # rows 0 .. used - 1 are the ones in use
@@ -128,4 +128,27 @@ def test_buckets_too_large_for_a_block(n, buckets_log2, group_log2, samples):
     rows[free[12000:17000]] = heavier
     assert (rows == heavier).sum() > MOST_IN_LDS and (_bucket(rows, bits, buckets_log2, group_log2) == 5).sum() > 2 * MOST_IN_LDS
     _step(tab, dev, used, rows, _bags(n, dev, 2), acc)
+    tab.close()
+
+
+@pytest.mark.parametrize("bits,pairs", [(18, 4096), (18, 4097), (18, 8191), (18, 8192), (18, 8193), (24, 4097), (24, 7500)])
+def test_buckets_at_the_limits_of_a_block(bits, pairs):
+    """One bucket of 4096 pairs, which are sorted as they are, of up to 8192, of which a word each is sorted, and of more,
+    which are taken in pieces, as all of more than 4096 are where a word does not hold the key within the bucket (of 2^24
+    rows in 16 buckets)."""
+    n = 60000 if bits < 24 else 8192
+    buckets_log2, used = (7, 1 << 18) if bits < 24 else (4, (1 << 23) + 11)
+    rng = np.random.default_rng(pairs)
+    tab, dev = _table(used, 1 << 24 if bits == 24 else 1 << 20)
+    acc = torch.zeros(used, dtype=torch.float64, device=dev)
+    bucket = _bucket(np.arange(used), bits, buckets_log2, 2)
+    ours, others = np.flatnonzero(bucket == 3), np.flatnonzero(bucket != 3)
+    rows = rng.choice(others, n)
+    seen = _sampled(n, 512).astype(np.int64)
+    free = rng.permutation(np.setdiff1d(np.arange(n), seen))
+    some = np.concatenate([ours[rng.integers(0, ours.shape[0], 1500)], ours[rng.integers(0, 400, 6000)], np.full(1000, ours[7])])
+    rows[free[:pairs]] = np.resize(rng.permutation(some), pairs)     # (none that a sample looks at: no row has a bin of its own)
+    assert (bucket[rows] == 3).sum() == pairs
+    for lengths in (_bags(n, dev, 3), torch.ones(n, dtype=torch.int64, device=dev)):
+        _step(tab, dev, used, rows, lengths, acc)
     tab.close()
