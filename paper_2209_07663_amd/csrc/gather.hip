@@ -14,9 +14,14 @@
 // How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
 // thousand of them: 64, where that still leaves kWavesWanted waves (the index loads are then as coalesced as they can be),
 // else as few as one round needs (33 K bags of dim 512: one wave per 64 bags was 512 waves on 256 compute units).
-// Never more than 4 (8 with eight elements per lane) where a row takes a whole wave: a wave of many rounds lasts long, and
-// the chip is idle beside the last ones (249 K bags of one ID, fp32 dim 512, gather and update 491 -> 441 us; 293 K bags of
-// four, dim 256, 215 -> 205).  Two tables, for the same reason, 32 bags where 8 lanes share a row, 16 where 16 or 32 do
+// Never more than 4 where a row takes a whole wave, 2 where it takes two pieces of a wave's width, 1 where it takes more: a
+// wave of many rounds lasts long, and the chip is idle beside the last ones (249 K bags of one ID, fp32 dim 512, gather and
+// update 491 -> 441 us; 293 K bags of four, dim 256, 215 -> 205; 66 K bags of two with 4 and with 1 or 2, dims 512, 768, 1024:
+// fp32 78 / 75 us, 117 / 102, 153 / 142, bf16 with 8 / 4 elements a lane 56 / 52, - , 123 / 112).  But twice as many where the
+// launch would be a little more than the chip holds (8192 waves of these kernels, kHeld), up to half as much again: its last
+// waves then run alone (33 K bags with 4 and with 8, dim 256, bags of one and four: fp32 13.9 / 13.1, 27.5 / 27.1 us, bf16
+// 11.8 / 10.5, 19.7 / 17.7; 36 K of dim 132 10 % each; from 12 K waves on the same).
+// Two tables, for the same reason, 32 bags where 8 lanes share a row, 16 where 16 or 32 do
 // (500 K bags of four, dim 32 67 -> 56 us, dim 64 159 -> 135, dim 128 272 -> 227; smaller dims the same with 64 and 32).
 // Large batches are bound by the rows and pooled rows that move behind the L2 (4.7 TB/s at 6.8 M IDs, 5.5 at 26 M, of
 // the 6.2 that a plain copy reaches to consecutive addresses).
@@ -89,6 +94,7 @@ __device__ inline void load_piece(Piece<E, N>& p, const E* rows, uint64_t row, u
 template <typename E, int N_>
 struct TableRows {
   static constexpr int N = N_, kIds = kIdsInRegs;
+  static constexpr uint64_t kHeld = 8192;  // waves that run at a time; 0: does not matter
   using Id = int32_t;
   const E* rows;
   const int32_t* idx;
@@ -110,6 +116,7 @@ struct TableRows {
 template <typename E, int N_, int kIds_>
 struct QuotRemRows {
   static constexpr int N = N_, kIds = kIds_;
+  static constexpr uint64_t kHeld = 0;
   using Id = int64_t;
   const E* rem;    // E_r: 2^m rows
   const E* quot;   // E_q: 2^m rows
@@ -254,15 +261,17 @@ struct GatherShape {
   uint32_t group_log2 = 0, bags_log2 = 6;
   bool past_caches;
   uint64_t waves;
-  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags, uint32_t ids = kIdsInRegs)
+  GatherShape(uint32_t dim, uint32_t n_per_lane, uint64_t n_bags, uint32_t ids = kIdsInRegs, uint64_t held = 0)
       : past_caches(n_per_lane == 4 && n_bags * dim * sizeof(float) > kPooledCached) {
     while (group_log2 < 6 && (n_per_lane << group_log2) < dim) ++group_log2;
+    const uint32_t pieces = (dim + 64 * n_per_lane - 1) / (64 * n_per_lane);
     if (group_log2 == 6)
-      bags_log2 = n_per_lane == 4 ? 2 : 3;
+      bags_log2 = pieces == 1 ? 2 : (pieces == 2 ? 1 : 0);
     else if (group_log2 >= 3 && ids < (uint32_t)kIdsInRegs)
       bags_log2 = group_log2 == 3 ? 5 : 4;
     while (bags_log2 > 6 - group_log2 && (n_bags >> bags_log2) < kWavesWanted) --bags_log2;
     const auto waves_of = [&](uint32_t lg) { return (n_bags + (1ull << lg) - 1) >> lg; };
+    if (bags_log2 < 6 && held != 0 && waves_of(bags_log2) >= held && waves_of(bags_log2) <= held + held / 2) ++bags_log2;
     while (bags_log2 < 6 && waves_of(bags_log2) > kMostWaves) ++bags_log2;
     waves = waves_of(bags_log2);
   }
@@ -271,7 +280,7 @@ struct GatherShape {
 template <typename Src>
 static hipError_t queue_gather(const Src& src, const int64_t* d_offsets, uint64_t n_bags, uint64_t n, uint32_t dim,
                                float* d_out, hipStream_t stream, Profiler* prof) {
-  const GatherShape sh(dim, Src::N, n_bags, Src::kIds);
+  const GatherShape sh(dim, Src::N, n_bags, Src::kIds, Src::kHeld);
   MONO_LAUNCH(prof, K_GATHER_POOL, stream, gather_pool_kernel<Src>, dim3((unsigned)((sh.waves + 3) / 4)), dim3(256), src,
               d_offsets, n_bags, n, dim, sh.group_log2, sh.bags_log2, sh.past_caches, d_out);
   return hipGetLastError();

@@ -82,7 +82,7 @@ inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // 
 // four sizes: pairs of a unit, occurrences drawn (a row drawn kSplitHits times has a bin of its own), most buckets (of
 // about 512 pairs, where that is not too many), threads of a block that splits.  The sample has to find what would not
 // fit into a bin (8192 pairs, with the bin's other rows): rows of 1.4 % of 512 K pairs, 0.7 % of a million; such a row is
-// missed once in two thousand times, one of half that one in seven (a bin of 4096 to 8192 pairs costs little: see
+// missed once in 2800 times, one of half that once in fourteen (a bin of 4096 to 8192 pairs costs little: see
 // sort_split.hip).  600 K to a million pairs with units of 1024 instead of 2048 (twice the units
 // to collect from) take 20 us longer, with blocks of 256 threads instead of 512 5 to 8; 200 K with samples of 512 25 us
 // of `bucket` instead of 12 (too large bins).  Four neighbouring rows in a bucket: 60 to 600 K pairs 0 to 3 % of the

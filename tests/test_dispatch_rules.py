@@ -86,6 +86,36 @@ int main() {
 """)
 
 
+def test_waves_of_wide_rows_are_short_and_not_a_few_more_than_run_at_a_time(tmp_path):
+    """Rows that take a whole wave: at most four pieces of a wave's width to a wave, twice as many bags where the launch
+    would be up to half as many waves again as the chip holds."""
+    _run(tmp_path, r"""
+#include "gather.hip"
+using namespace mono;
+template <typename Src>
+int wrong(unsigned dim) {
+  int bad = 0;
+  const unsigned long long pieces = (dim + 64 * Src::N - 1) / (64 * Src::N);
+  for (unsigned long long bags = 1; bags < 3000000; bags += 1 + bags / 400) {
+    const GatherShape s(dim, Src::N, bags, Src::kIds, Src::kHeld);
+    const bool few = s.waves >= 4096 || s.bags_log2 == 0, ends_alone = s.waves >= 8192 && s.waves <= 12288;
+    const bool wide = (pieces << s.bags_log2) > 8 || ((pieces << s.bags_log2) > 4 && pieces != 3 && s.waves > 6145);
+    if (!few || ends_alone || wide) printf("dim %u, %llu bags: %llu waves of %u bags\n", dim, bags, (unsigned long long)s.waves, 1u << s.bags_log2), ++bad;
+  }
+  return bad;
+}
+int main() {
+  int bad = 0;
+  for (unsigned dim : {132u, 256u, 512u, 768u, 1024u}) {
+    bad += wrong<TableRows<float, 4>>(dim);
+    if (dim < 512) bad += wrong<TableRows<uint16_t, 4>>(dim);
+    else bad += wrong<TableRows<uint16_t, 8>>(dim);
+  }
+  return bad ? 1 : 0;
+}
+""")
+
+
 def test_small_batches_of_many_bags_are_sorted_by_one_block(tmp_path):
     """Up to 4096 pairs in up to 16384 bags, most of them empty: one launch instead of six or nine."""
     _run(tmp_path, r"""

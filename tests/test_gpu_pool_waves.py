@@ -39,7 +39,8 @@ def test_two_tables(dim, bf16):
         _check(got, (tabs[0].double()[at % (1 << m)] + tabs[1].double()[at >> m]) * inside, lens)
 
 
-@pytest.mark.parametrize("dim,bf16", [(64, False), (64, True), (128, False), (256, False), (256, True), (512, False), (512, True)])
+@pytest.mark.parametrize("dim,bf16", [(64, False), (64, True), (128, False), (256, False), (256, True), (512, False), (512, True),
+                                      (132, False), (768, False), (768, True), (1024, False), (1024, True)])
 def test_one_table(dim, bf16):
     from paper_2209_07663_amd.binding import Table
     dev = torch.device("cuda:0")
@@ -48,7 +49,7 @@ def test_one_table(dim, bf16):
     d = tab.mono_table_export()
     rows = torch.zeros((1 << 12, dim), dtype=torch.float64, device=dev)
     rows[torch.from_numpy(d["row"].astype("int64")).to(dev)] = torch.from_numpy(d["rows"]).to(dev).double()
-    for bags, average in ((1000, 4), (16387, 3), (66003, 1)):
+    for bags, average in ((1000, 4), (8195, 2), (16387, 3), (33001, 1), (66003, 1)):
         lens, offs, at = _batch(bags, average, 1 << 12, dev)
         at = torch.where((at >= 3000) & (at < 1 << 12), -1, at)        # (rows that were never handed out hold anything)
         got = tab.mono_gather_pool(at.int(), offs)
