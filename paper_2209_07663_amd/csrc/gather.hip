@@ -18,11 +18,13 @@
 // wave of many rounds lasts long, and the chip is idle beside the last ones (249 K bags of one ID, fp32 dim 512, gather and
 // update 491 -> 441 us; 293 K bags of four, dim 256, 215 -> 205; 66 K bags of two with 4 and with 1 or 2, dims 512, 768, 1024:
 // fp32 78 / 75 us, 117 / 102, 153 / 142, bf16 with 8 / 4 elements a lane 56 / 52, - , 123 / 112).  But twice as many where the
-// launch would be a little more than the chip holds (8192 waves of these kernels, kHeld), up to half as much again: its last
+// launch would be a little more than the chip holds (8192 waves, kHeld), up to half as much again: its last
 // waves then run alone (33 K bags with 4 and with 8, dim 256, bags of one and four: fp32 13.9 / 13.1, 27.5 / 27.1 us, bf16
 // 11.8 / 10.5, 19.7 / 17.7; 36 K of dim 132 10 % each; from 12 K waves on the same).
-// Two tables, for the same reason, 32 bags where 8 lanes share a row, 16 where 16 or 32 do
-// (500 K bags of four, dim 32 67 -> 56 us, dim 64 159 -> 135, dim 128 272 -> 227; smaller dims the same with 64 and 32).
+// Two tables, for the same reason, 32 bags where 8 lanes share a row, 16 where 16 or 32 do (500 K bags of four, dim 32 67 -> 56
+// us, dim 64 159 -> 135, dim 128 272 -> 227; smaller dims the same with 64 and 32), and again twice as many where that is a
+// little more than the chip holds, of fp32 rows 6144 waves here (130 K bags of eight of dim 64 94 and 82 us, of dim 128 210
+// and 193, 250 K of dim 32 94 and 85).
 // Large batches are bound by the rows and pooled rows that move behind the L2 (4.7 TB/s at 6.8 M IDs, 5.5 at 26 M, of
 // the 6.2 that a plain copy reaches to consecutive addresses).
 // Summation is in occurrence order, in fp32.
@@ -116,7 +118,7 @@ struct TableRows {
 template <typename E, int N_, int kIds_>
 struct QuotRemRows {
   static constexpr int N = N_, kIds = kIds_;
-  static constexpr uint64_t kHeld = 0;
+  static constexpr uint64_t kHeld = kIds_ == 4 && sizeof(E) == 4 ? 6144 : 0;
   using Id = int64_t;
   const E* rem;    // E_r: 2^m rows
   const E* quot;   // E_q: 2^m rows
@@ -306,13 +308,21 @@ hipError_t launch_gather_pool(const TableView& t, const int32_t* d_rows, uint64_
 // dim 32, 327 and 278 us; 0.4 to 8 M IDs in bags of two to five, dims 64 to 512, 15 to 50 % longer with eight; bags of 16
 // and 30, uniform IDs, dims 16 and 64, 150 and 159, 62 and 63, 141 and 145; 3037 bags of 28, dim 128, 19.6 and 20.5.  bf16
 // rows of up to 32 elements are short of neither registers nor waves: bags of five, dim 16 376 and 390, of two, dim 32, 45 and 38.
-constexpr uint64_t kQrBag = 12, kQrBagNarrow = 3;
+// Shorter bags of fp32 rows that share a wave with three others or more, where there are so many that the chip is full twice
+// over: bags of eight, uniform IDs, 500 K of dim 32 164 and 171, 250 K of dim 64 153 and 160 (90 K of dim 128 142 and 134, 66 K
+// of dim 64 57 and 45).
+constexpr uint64_t kQrBag = 12, kQrBagNarrow = 3, kQrBagMany = 6;
+inline bool qr_takes_eight(uint64_t n, uint64_t n_bags, uint32_t dim, bool bf16) {
+  if (bf16) return n / n_bags >= (dim <= 32 ? kQrBagNarrow : kQrBag);
+  const GatherShape four(dim, 4, n_bags, 4);
+  return n / n_bags >= (four.group_log2 <= 4 && four.waves >= 2 * QuotRemRows<float, 4, 4>::kHeld ? kQrBagMany : kQrBag);
+}
 
 hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t log2_rows, uint32_t dim, bool bf16,
                                  const int64_t* d_ids, uint64_t n, const int64_t* d_offsets, uint64_t n_bags,
                                  float* d_out, hipStream_t stream) {
   if (n_bags == 0) return hipSuccess;
-  const bool eight = n / n_bags >= (bf16 && dim <= 32 ? kQrBagNarrow : kQrBag);
+  const bool eight = qr_takes_eight(n, n_bags, dim, bf16);
   const auto queue = [&](const auto& src) { return queue_gather(src, d_offsets, n_bags, n, dim, d_out, stream, nullptr); };
   if (!bf16) {
     const float *rem = (const float*)d_rem, *quot = (const float*)d_quot;

@@ -116,6 +116,34 @@ int main() {
 """)
 
 
+def test_two_tables_eight_rows_in_flight_for_long_bags_and_for_many_of_six(tmp_path):
+    """Of fp32 rows, from 12 IDs a bag on, or from 6 where four rows or more share a wave and four IDs in flight would be more
+    than twice the 6144 waves that the chip holds; and the latter are never a little more than those."""
+    _run(tmp_path, r"""
+#include "gather.hip"
+using namespace mono;
+int main() {
+  int bad = 0;
+  for (unsigned dim : {4u, 16u, 32u, 36u, 64u, 100u, 128u, 256u, 512u})
+    for (unsigned long long bags = 1; bags < 3000000; bags += 1 + bags / 300) {
+      const unsigned lanes_log2 = dim <= 4 ? 0 : dim <= 16 ? 2 : dim <= 32 ? 3 : dim <= 64 ? 4 : dim <= 128 ? 5 : 6;
+      const unsigned long long usual = lanes_log2 < 3 ? 64 : lanes_log2 == 3 ? 32 : 16;
+      const bool many = lanes_log2 <= 4 && bags / usual >= 12288;
+      for (unsigned long long each : {1ull, 5ull, 6ull, 11ull, 12ull, 40ull}) {
+        if (qr_takes_eight(bags * each, bags, dim, true) != (each >= (dim <= 32 ? 3u : 12u))) printf("bf16 %u %llu %llu\n", dim, bags, each), ++bad;
+        if (many != (lanes_log2 <= 4 && (bags + usual - 1) / usual >= 12288)) continue;
+        if (qr_takes_eight(bags * each, bags, dim, false) != (each >= 12 || (each >= 6 && many))) printf("%u %llu %llu\n", dim, bags, each), ++bad;
+      }
+      using Four = QuotRemRows<float, 4, 4>;
+      const GatherShape s(dim, 4, bags, Four::kIds, Four::kHeld);
+      if (lanes_log2 >= 3 && s.bags_log2 < 6 && s.waves >= 6144 && s.waves <= 9216 && s.bags_log2 + 1 < (lanes_log2 == 6 ? 3u : 7u))
+        printf("dim %u, %llu bags: %llu waves\n", dim, bags, (unsigned long long)s.waves), ++bad;
+    }
+  return bad ? 1 : 0;
+}
+""")
+
+
 def test_small_batches_of_many_bags_are_sorted_by_one_block(tmp_path):
     """Up to 4096 pairs in up to 16384 bags, most of them empty: one launch instead of six or nine."""
     _run(tmp_path, r"""

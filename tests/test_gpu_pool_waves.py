@@ -31,7 +31,7 @@ def test_two_tables(dim, bf16):
     dev, m = torch.device("cuda:0"), 9
     g = torch.Generator(device=dev).manual_seed(dim)
     tabs = [torch.randn((1 << m, dim), device=dev, generator=g).to(torch.bfloat16 if bf16 else torch.float32) for _ in range(2)]
-    for bags, average in ((4099, 2), (4099, 4), (4099, 11), (4099, 13), (70001, 1)):
+    for bags, average in ((4099, 2), (4099, 4), (4099, 11), (4099, 13), (70001, 1), (110000, 2)):
         lens, offs, ids = _batch(bags, average, 1 << 2 * m, dev)
         got = mono_qr_gather_pool(tabs[0], tabs[1], ids, offs)
         inside = ((ids >= 0) & (ids < 1 << 2 * m))[:, None]
