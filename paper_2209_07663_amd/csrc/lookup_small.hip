@@ -1,6 +1,6 @@
 // lookup_or_insert for small batches (at most kSmallLookup keys): one launch.
 //
-// The general path is four kernels, because counting, election, placement and resolution each need the one
+// The general path is three kernels (four for large batches), because counting, election and placement each need the one
 // before finished on the whole chip.  A batch of a few thousand keys is nothing but their latency: 1700 keys
 // that the table knows took 5.4 + 1.8 + 2.1 + 2.8 us in four kernels and about as much again between them.
 // Here every block probes 128 keys with 512 threads (eight lanes per key, both of its buckets requested at
@@ -9,16 +9,20 @@
 // distinct missing keys in LDS.  A batch without misses, the usual one when serving, ends with the probe.
 // (Known keys, GPU time of a call of 200, 1088 and 4096 with 256 keys and 1024 threads: 4.7, 5.2, 5.3 us; with 128 and 512:
 // 4.3, 4.6, 4.7; with 64 and 256: 4.5, 4.6, 5.0.)
-// 4096 is where one block's work on a batch that misses throughout still costs no more than the launches
-// it saves.
+// 4096 keys that the table knows, or nearly all, take half the time of 5000 in three kernels (dim 32: 5 to 7 and 14 to 16 us;
+// with 1 % unknown 10 to 14 and 16 to 22, 5 % 12 to 16 and 18 to 24); from a third of them unknown on one block's work costs as
+// much as the launches it saves (30 % 16 to 30 and 21 to 26), and all of them, where they are admitted, twice as much (54 to 68
+// and 31; 27 and 24 where they are not).
 //
 // Blocks run on different XCDs, whose L2s are not coherent for ordinary accesses.  What a block leaves for
 // the last one in this same kernel (missing occurrences, counters, last-seen stamps that an eviction may
 // move) goes through agent-scope atomics, and a block reports itself done only after its waves have waited
 // for theirs.  Only the first values of new rows are not left to that block: they are hashes, 20 us of one block for a
 // thousand rows of dim 128.  Blocks that know of a miss when they finish stay, look for the list of new rows and share it
-// (1088 IDs of dim 128, half of them new: 70 -> 60 us for a training step).  They wait a bounded time, and nothing depends
-// on them: every block has counted itself done before it waits, and a list that nobody helps with the last block does.
+// (1088 IDs of dim 128, half of them new: 70 -> 60 us for a training step; lookups with that block alone and so, 200 and 4096
+// IDs of which 5 % are new, dim 16 10.5 / 10.6 and 14.4 / 14.4 us, dim 32 11.6 / 12.0 and 16.3 / 14.8, dim 128 14.0 / 12.1 and
+// 23.7 / 15.3; 30 % new, dim 16 12.4 / 11.7 and 24.3 / 24.1, dim 128 21.5 / 14.2 and 49 / 25).  They wait a bounded time, and
+// nothing depends on them: every block has counted itself done before it waits, and a list that nobody helps with the last block does.
 #include "common.h"
 #include "kernels.h"
 #include "table_ops.h"
@@ -40,7 +44,7 @@ struct SmallProbe {
 };
 struct SmallFinish {
   unsigned long long key[kSmallLookup];  // the batch's missing occurrences
-  uint32_t slot[2 * kSmallLookup];       // set of distinct missing keys (number of the first occurrence); later: the winners
+  alignas(16) uint32_t slot[4 * kSmallLookup];  // set of distinct missing keys (number of the first occurrence); later: the winners
   int32_t row[kSmallLookup];             // what a leader found for its key
 };
 
@@ -195,9 +199,12 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
     if (tid == 0 && t.hwm_mail && epoch % kPostEvery == 0) post_hwm(t, epoch, t.ctl->hwm);
     return;
   }
+  // Four slots for each: the slowest of a wave's 64 keys then finds its place in three or four steps, with two slots for each in
+  // seven or eight, and a thread has up to eight keys (4096 unknown keys below the threshold 32 -> 27 us, admitted 59 -> 54).
   uint32_t slots = 64;
-  while (slots < 2 * missed) slots <<= 1;
-  for (uint32_t q = tid; q < slots; q += kSmallThreads) s.f.slot[q] = 0xFFFFFFFFu;
+  while (slots < 4 * missed) slots <<= 1;
+  for (uint32_t q = 4 * tid; q < slots; q += 4 * kSmallThreads)
+    *reinterpret_cast<uint4*>(&s.f.slot[q]) = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
   uint64_t mk[kSmallPerThread];
   uint32_t mo[kSmallPerThread], lead[kSmallPerThread];
 #pragma unroll
@@ -221,7 +228,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
     cnt[j] = 0;
     if (x >= missed) continue;
     uint32_t pos = (uint32_t)(mix64(mk[j] ^ t.s_dedup) >> 32) & (slots - 1);
-    for (;;) {  // at most half of the slots are ever taken: a free slot always turns up
+    for (;;) {  // at most a quarter of the slots is ever taken: a free slot always turns up
       const uint32_t old = atomicCAS(&s.f.slot[pos], 0xFFFFFFFFu, x);
       if (old == 0xFFFFFFFFu) break;
       if (s.f.key[old] == mk[j]) {
