@@ -8,7 +8,7 @@ namespace mono {
 
 // Per-call scratch for the update path, carved out of the table's arena.
 struct UpdateWorkspace {
-  uint32_t* unit_bag;   // [max_ids]: first [sort_units] words: the bag that holds each sort unit's first occurrence
+  uint32_t* unit_bag;   // [max_ids]: (radix passes) first [sort_units] words: the bag that holds each unit's first occurrence
                         // (a restore call borrows the whole array for its per-record results)
   uint2* pair_a;        // [max_ids] (row, bag) pairs, ping
   uint2* pair_b;        // [max_ids] pong
@@ -18,45 +18,28 @@ struct UpdateWorkspace {
   uint64_t tiles;       // what part and part_row are for
 };
 
-// The sort comes in several shapes, chosen per call by the host.  From its bound on the rows in use:
+// How the pairs of a batch are grouped by row.  At most kSortSmall of them are sorted by one block in LDS, in one launch, unless
+// they have more than kSortSmallBags bags, which that block would have to walk all by itself; up to kSplitMost, and few pairs
+// of many bags, are split and sorted by bucket, in two launches (below); more are sorted by radix passes.  (One block or
+// split: steps of 2.3 and 3 K pairs 42.5 and 43.6, 37.5 and 40.3 us, of 4.3 K 52 and 49, of 7.1 K 51 and 45.  Updates of 4 K
+// pairs in 40 K and a million bags, 600 K rows in use, by radix passes over units of 512 pairs and split: 41 and 28 us, 134 and
+// 125; 17 M rows in use 82 and 28.)
+constexpr uint64_t kSortSmall = 4096, kSortSmallBags = 1u << 14;
+inline bool sorts_in_one_block(uint64_t n, uint64_t n_bags) { return n <= kSortSmall && n_bags <= kSortSmallBags; }
+// The radix passes come in two shapes, chosen per call by the host from its bound on the rows in use:
 //   narrow  digits of at most 8 bits, blocks of 256 threads: three passes up to 2^24 rows
 //   wide    digits of at most 9 bits, blocks of 512 threads: three passes up to 2^27 rows, where narrow needs four.
 //           A wide pass takes a quarter longer than a narrow one (measured on 6.8 M pairs), so wide is taken only
 //           where it saves a pass: 1.33 -> 1.30 ms per step on the streaming workload (25 M rows in use), 5.78 ->
 //           5.70 ms on the 26 M-ID workload.
-// From the size of the batch: how many elements a block owns.  Large batches want long shares of a bin (8
-// elements on average: 2048 per narrow block, 4096 per wide one).  Small ones are bound by the chain of
-// latencies of one block, which its elements lengthen, and have too few blocks to fill the chip: a scatter of
-// 26 K pairs takes 11.1 / 8.2 / 6.4 us with 2048 / 1024 / 512 elements per block, one of 204 K 10.8 / 8.0 / 7.0.
-// Where the batch is small and two digits of up to 11 bits save a pass of narrow ones (2^16 to 2^22 rows in use), they
-// are taken, three launches fewer; but their histograms are 2^digit words per block, so that how small depends on the
-// digit.  Update of dim 16, two digits / three narrow ones, from 512 words (300 K rows in use) to 2048 (3.9 M):
-//                     32 K pairs    64 K          100 K         128 K         156 K
-//   300 K, 1 M rows   45 / 49 us    50 / 54       54 / 56       56 / 57       58 / 63, 66 / 65
-//   1.3 M             49 / 51       57 / 58       61 / 59       66 / 60
-//   3.9 M             52 / 53       61 / 59       66 / 60       72 / 62
-// Batches of at most kSortSmall pairs are sorted by one block in LDS, in one launch, unless they have more than
-// kSortSmallBags bags, which that block would have to walk all by itself; those of up to kSplitMost are sorted in two
-// launches (below).  (One block or split: steps of 2.3 and 3 K pairs 42.5 and 43.6, 37.5 and 40.3 us, of 4.3 K 52 and 49, of
-// 7.1 K 51 and 45.  Updates of 4 K pairs in 12 K bags, dims 4, 32, 512, in one block or with two wide digits: 28 / 35 us,
-// 32 / 37, 36 / 42.)
+// A block owns as many pairs (a unit) as leave it 8 of a bin on average: 2048 and 4096.
 struct SortShape {
   uint32_t max_bits, items;
 };
-constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9, kSortFewBits = 11;
+constexpr uint32_t kSortNarrowBits = 8, kSortWideBits = 9, kSortNarrowItems = 2048, kSortWideItems = 4096;
 constexpr uint32_t kSortNarrowMaxRows = 1u << 24;  // beyond this many rows in use the wide shape saves a pass
-constexpr uint64_t kSortItems512 = 400000;  // largest batch of that block size
-constexpr uint64_t kSortFewMost = 1u << 17;  // largest batch with two digits of at most 10 bits, halved for each bit more
-constexpr uint32_t kSortFewRowsAbove = 1u << 16, kSortFewRows10 = 1u << 20, kSortFewMaxRows = 1u << 22;
-inline uint64_t sort_few_most(uint32_t rows) {
-  return rows <= kSortFewRows10 ? kSortFewMost : (rows <= 2 * kSortFewRows10 ? kSortFewMost / 2 : kSortFewMost / 4);
-}
-constexpr uint64_t kSortSmall = 4096, kSortSmallBags = 1u << 14;
-inline bool sorts_in_one_block(uint64_t n, uint64_t n_bags) { return n <= kSortSmall && n_bags <= kSortSmallBags; }
-inline SortShape sort_shape_for(uint32_t hwm_bound, uint64_t n) {
-  if (hwm_bound > kSortFewRowsAbove && hwm_bound <= kSortFewMaxRows && n <= sort_few_most(hwm_bound)) return {kSortFewBits, 512u};
-  if (hwm_bound > kSortNarrowMaxRows) return {kSortWideBits, 4096u};
-  return {kSortNarrowBits, n <= kSortItems512 ? 512u : 2048u};
+constexpr SortShape sort_shape_for(uint32_t hwm_bound) {
+  return hwm_bound > kSortNarrowMaxRows ? SortShape{kSortWideBits, kSortWideItems} : SortShape{kSortNarrowBits, kSortNarrowItems};
 }
 // Pairs of a tile of the reduction: kReduceTile, halved while that leaves fewer than kTilesWanted tiles, as long as a
 // lane group (gpb of them in a block) keeps eight pairs to have in flight together.
@@ -76,10 +59,9 @@ inline uint32_t reduce_tile(uint64_t n, uint32_t gpb) {
 #endif
 
 constexpr uint64_t sort_units(uint64_t n, uint32_t items) { return (n + items - 1) / items; }
-constexpr uint32_t kSortGroupedAbove = 1024, kSortGroupUnits = 4;  // units of more elements come in groups (see sort_hist_kernel)
-inline uint64_t sort_stride(uint64_t units) { return (units + 3) & ~3ull; }  // units in whole groups, or in whole 16-byte pieces
-// Batches of more than kSortSmall and at most kSplitMost pairs are split and sorted by bucket (sort_split.hip), in one of
-// four sizes: pairs of a unit, occurrences drawn (a row drawn kSplitHits times has a bin of its own), most buckets (of
+constexpr uint32_t kSortGroupUnits = 4;  // units come in groups (see sort_hist_kernel)
+constexpr uint64_t sort_groups(uint64_t n, uint32_t items) { return sort_units(sort_units(n, items), kSortGroupUnits); }
+// The split (sort_split.hip) comes in four sizes: pairs of a unit, occurrences drawn (a row drawn kSplitHits times has a bin of its own), most buckets (of
 // about 512 pairs, where that is not too many), threads of a block that splits.  The sample has to find what would not
 // fit into a bin (8192 pairs, with the bin's other rows): rows of 1.4 % of 512 K pairs, 0.7 % of a million; such a row is
 // missed once in 2800 times, one of half that once in fourteen (a bin of 4096 to 8192 pairs costs little: see
@@ -102,7 +84,7 @@ inline SplitShape split_shape_for(uint64_t n) {
   while ((512ull << lg) < n && (1u << lg) < kSplitBuckets[size]) ++lg;
   return {size, lg, size < 3 ? 2u : 0u};
 }
-inline uint64_t split_words(uint64_t n) {  // shares of all bins in all units and the list of turns, for batches of at most n elements
+constexpr uint64_t split_words(uint64_t n) {  // shares of all bins in all units and the list of turns, for batches of at most n elements
   uint64_t most = 0;
   for (uint32_t i = 0; i < kSplitSizes && (i == 0 || n > kSplitUpTo[i - 1]); ++i) {
     const uint64_t m = n < kSplitUpTo[i] ? n : kSplitUpTo[i], hot = kSplitSamples[i] / kSplitHits;
@@ -111,16 +93,13 @@ inline uint64_t split_words(uint64_t n) {  // shares of all bins in all units an
   }
   return most;
 }
-// words of the histogram workspace for batches of at most n elements, whatever the shape: a histogram per unit, one
-// per group, the bin totals; or the shares of a split
-inline uint64_t sort_hist_words(uint64_t n) {
+// words of the histogram workspace for batches of at most n elements: the shares of a split, or a histogram per unit (in whole
+// groups), one per group and the bin totals
+constexpr uint64_t sort_hist_words(uint64_t n) {
   uint64_t most = split_words(n);
-  const uint64_t sizes[] = {n, n < kSortFewMost ? n : kSortFewMost, n < kSortItems512 ? n : kSortItems512};
-  for (const uint64_t m : sizes)
-    for (const uint32_t rows : {kSortFewRows10, kSortNarrowMaxRows, kSortNarrowMaxRows + 1}) {
-      const SortShape s = sort_shape_for(rows, m);
-      const uint64_t stride = sort_stride(sort_units(m, s.items)), groups = s.items > kSortGroupedAbove ? stride / kSortGroupUnits : 0;
-      const uint64_t words = (stride + groups + 1) << s.max_bits;
+  if (n > kSplitMost)
+    for (const SortShape s : {sort_shape_for(kSortNarrowMaxRows), sort_shape_for(kSortNarrowMaxRows + 1)}) {
+      const uint64_t words = ((kSortGroupUnits + 1) * sort_groups(n, s.items) + 1) << s.max_bits;
       most = words > most ? words : most;
     }
   return most;
@@ -209,12 +188,14 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
                                      const int64_t* d_offsets, uint64_t n_bags, const float* d_grad, float lr, float eps,
                                      uint32_t hwm_bound, hipStream_t stream, Profiler* prof);
 
-// Groups the (row, bag) pairs of a batch of more than kSortSmall and at most kSplitMost pairs by row; the result is in
-// pair_b, the number of pairs in the control block's scratch.
+// Group the (row, bag) pairs of a batch by row; the result is in pair_b, the number of pairs in the control block's scratch.
+// Of a batch that sorts_in_one_block, and of at most kSplitMost pairs.
+hipError_t launch_sort_small(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
+                             const int64_t* d_offsets, uint64_t n_bags, hipStream_t stream, Profiler* prof);
 hipError_t launch_split_pairs(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                               const int64_t* d_offsets, uint64_t n_bags, hipStream_t stream, Profiler* prof);
 
-// Stable LSD radix sort of the (row, bag) pairs of a batch; the result is in pair_b if the plan for
+// Stable LSD radix sort of the (row, bag) pairs of a larger batch; the result is in pair_b if the plan for
 // the device's high-water mark (digits of at most *max_bits bits) has an odd number of passes, else in pair_a.
 // Returns how many passes were queued (those the plan for hwm_bound needs) and the widest digit of the shape used.
 hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,

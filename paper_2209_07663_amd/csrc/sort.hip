@@ -1,5 +1,6 @@
-// Stable LSD radix sort of (row index, bag) pairs, used to bring the occurrences of one embedding
-// row together before the gradient reduction.
+// Stable LSD radix sort of (row index, bag) pairs, which brings the occurrences of one embedding row together before the
+// gradient reduction: of more pairs than the split takes (sort_split.hip), and, at the end of the file, of so few that one
+// block sorts them in LDS.
 //
 // The key width is decided ON THE DEVICE: row indices are handed out in ascending order, so every
 // row in use is below the high-water mark `hwm` kept in the control block.  bit_length(hwm - 1)
@@ -13,7 +14,7 @@
 //
 // Unit of work: one block owns kItems consecutive elements, an equal share per wave.  Per pass:
 //   hist     per-unit digit histograms (LDS atomics)
-//   scan     exclusive scan of every bin along the units (or groups of four); bin totals to `totals`
+//   scan     exclusive scan of every bin along the units, in groups of four; bin totals to `totals`
 //   scatter  the block loads its elements into registers (all loads independent); every wave ranks its elements
 //            64 at a time by digit matching with ballots (stable: rank = the wave's earlier elements of the digit
 //            + lower lanes with it; what the ranking leaves behind are the wave's digit counts, which a loop
@@ -29,18 +30,16 @@
 
 namespace mono {
 
-// A kernel of the sort is compiled for one shape (see kernels.h): kBits = widest digit, kBlock = threads,
-// kItems = elements owned by a block.
-template <uint32_t kBits, int kBlock, uint32_t kItems>
+// A kernel of the sort is compiled for one shape (see kernels.h): kBits = widest digit, kItems = elements owned by a block,
+// which has a thread for every bin.
+template <uint32_t kBits, uint32_t kItems>
 struct Shape {
   static constexpr uint32_t kBins = 1u << kBits;
+  static constexpr int kBlock = (int)kBins;
   static constexpr int kWaves = kBlock / 64;
-  static constexpr uint32_t kBinsPerThread = kBins > (uint32_t)kBlock ? kBins / kBlock : 1;  // consecutive bins a thread owns
-  static constexpr uint32_t kBinThreads = kBins / kBinsPerThread;                            // threads that own bins
-  static constexpr int kScanWaves = (int)kBinThreads / 64;
   static constexpr uint32_t kPerWave = kItems / kWaves;
   static constexpr uint32_t kRounds = kPerWave / 64;
-  static_assert(kBlock % 64 == 0 && kItems % (uint32_t)kBlock == 0 && kBinThreads % 64 == 0, "whole waves");
+  static_assert(kItems % kBins == 0, "whole waves");
 };
 
 // The bag that holds occurrence `pos`: the last bag b with offsets[b] <= pos (offsets are non-decreasing
@@ -61,18 +60,12 @@ __device__ inline uint32_t bag_holding(const int64_t* offsets, uint64_t n_bags, 
   return (uint32_t)lo;
 }
 
-// Units whose histograms a block of sort_hist_kernel makes, and that block's threads.
-template <uint32_t kItems>
-constexpr uint32_t kSortGroup = kItems > kSortGroupedAbove ? kSortGroupUnits : 1;
-constexpr int kGroupBlock = 512;
-template <uint32_t kItems>
-constexpr uint32_t kSortChunk = kItems > kSortGroupedAbove ? 16 : 1;  // see sort_scatter_kernel
+constexpr int kGroupBlock = 512;     // threads of a block of sort_hist_kernel
+constexpr uint32_t kSortChunk = 16;  // see sort_scatter_kernel
 
-// Digit histograms of kUnits consecutive units.
-//   kUnits == 1  (small batches) bin-major, to hist[bin * stride + unit]
-//   kUnits > 1   (large ones) a unit's words are what the units before it in the group hold, to hist[unit * bins + bin];
-//                the group's, to sums[group * bins + bin].  Whole lines are written here and read by the scatter kernel,
-//                and the scan has kUnits times less to read
+// Digit histograms of a group of consecutive units: a unit's words are what the units before it in the group hold, to
+// hist[unit * bins + bin]; the group's, to sums[group * bins + bin].  Whole lines are written here and read by the scatter
+// kernel, and the scan has kSortGroupUnits times less to read.
 // Pass 0 has more blocks than that, in front: for the scatter kernel of the same pass, their waves find the bag that
 // holds a unit's first occurrence, a unit each (four dependent memory round trips, beside the counting instead of
 // after it).
@@ -80,20 +73,19 @@ constexpr uint32_t kSortChunk = kItems > kSortGroupedAbove ? 16 : 1;  // see sor
 // and slots of few IDs: every counter is kept four times, for a quarter of the lanes each.
 // Both together: 22.8 -> 12.5 us a pass at 6.8 M pairs in 8-bit digits (reading the pairs takes 10), 75 -> 43 at 26 M
 // in 9-bit ones, and 39.6 -> 36.8 and 153 -> 146 in the scatter kernel.  A unit per block instead of four takes 5 us
-// less here at 26 M but 11 more in the scan; small batches have too few units for groups.
-template <uint32_t kBits, int kBlock, uint32_t kItems, uint32_t kUnits>
-__global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __restrict__ ctl, uint32_t pass,
+// less here at 26 M but 11 more in the scan.
+template <uint32_t kBits, uint32_t kItems>
+__global__ __launch_bounds__(kGroupBlock) void sort_hist_kernel(const Control* __restrict__ ctl, uint32_t pass,
                                                                const int32_t* __restrict__ rows,
                                                                const uint2* __restrict__ src, uint64_t n,
-                                                               uint64_t stride, uint32_t* __restrict__ hist,
+                                                               uint32_t* __restrict__ hist,
                                                                uint32_t* __restrict__ sums,
                                                                const int64_t* __restrict__ offsets, uint64_t n_bags,
                                                                uint32_t* __restrict__ unit_bag,
                                                                uint32_t search_blocks) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   if (pass >= plan.passes) return;
-  constexpr uint32_t kBins = 1u << kBits;
-  constexpr uint32_t kCopies = kBits == kSortFewBits ? 1 : 4;  // (512 elements in 2048 bins hardly meet)
+  constexpr uint32_t kBins = 1u << kBits, kBlock = kGroupBlock, kUnits = kSortGroupUnits, kCopies = 4;
   __shared__ uint4 words[kUnits * kBins * kCopies / 4];
   uint32_t* cnt = reinterpret_cast<uint32_t*>(words);  // [unit][bin][copy]
   if (blockIdx.x < search_blocks) {
@@ -131,20 +123,11 @@ __global__ __launch_bounds__(kBlock) void sort_hist_kernel(const Control* __rest
     uint32_t run = 0;
 #pragma unroll
     for (uint32_t u = 0; u < kUnits; ++u) {
-      uint32_t count;
-      if constexpr (kCopies == 4) {
-        const uint4 c = words[u * kBins + b];
-        count = c.x + c.y + c.z + c.w;
-      } else {
-        count = cnt[u * kBins + b];
-      }
-      if constexpr (kUnits == 1)
-        hist[(uint64_t)b * stride + block] = count;
-      else
-        hist[(block * kUnits + u) * kBins + b] = run;
-      run += count;
+      const uint4 c = words[u * kBins + b];
+      hist[(block * kUnits + u) * kBins + b] = run;
+      run += c.x + c.y + c.z + c.w;
     }
-    if constexpr (kUnits > 1) sums[block * kBins + b] = run;
+    sums[block * kBins + b] = run;
   }
 }
 
@@ -206,55 +189,15 @@ __global__ __launch_bounds__(kScanBlock) void sort_scan_kernel(const Control* __
   if (threadIdx.x == 0) reinterpret_cast<uint4*>(totals)[strip] = carry;
 }
 
-// Exclusive scan of hist[bin * stride + 0 .. units) in place; total of the bin to totals[bin].  One wave per bin, for at
-// most 64 * 4 * kScanFew units.
-constexpr uint32_t kScanFew = 4;  // pieces of four units per lane
-template <uint32_t kBits>
-__global__ __launch_bounds__(256) void sort_scan_few_kernel(const Control* __restrict__ ctl, uint32_t pass,
-                                                            uint32_t* __restrict__ hist, uint32_t units, uint64_t stride,
-                                                            uint32_t* __restrict__ totals) {
-  const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
-  const uint32_t bin = blockIdx.x * 4 + (threadIdx.x >> 6), lane = lane_id();
-  if (pass >= plan.passes || bin >= (1u << plan.width(pass))) return;  // wave-uniform (no barriers below)
-  uint4* row = reinterpret_cast<uint4*>(hist + (uint64_t)bin * stride);
-  const uint32_t quads = (uint32_t)stride / 4, per = (quads + 63) / 64, first = lane * per;
-  uint4 v[kScanFew];
-#pragma unroll
-  for (uint32_t j = 0; j < kScanFew; ++j) {
-    v[j] = make_uint4(0u, 0u, 0u, 0u);
-    if (j < per && first + j < quads) v[j] = row[first + j];
-  }
-  uint32_t sum = 0;
-#pragma unroll
-  for (uint32_t j = 0; j < kScanFew; ++j) {
-    const uint32_t u = (first + j) * 4;  // the words after the last unit hold nothing
-    if (u >= units) v[j].x = 0;
-    if (u + 1 >= units) v[j].y = 0;
-    if (u + 2 >= units) v[j].z = 0;
-    if (u + 3 >= units) v[j].w = 0;
-    sum += v[j].x + v[j].y + v[j].z + v[j].w;
-  }
-  const uint32_t x = wave_sums(sum);
-  uint32_t run = x - sum;
-#pragma unroll
-  for (uint32_t j = 0; j < kScanFew; ++j) {
-    const uint4 c = v[j], o = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
-    if (j < per && first + j < quads) row[first + j] = o;
-    run = o.w + c.w;
-  }
-  if (lane == 63) totals[bin] = x;
-}
-
 // kFirst: pass 0 (in a kernel of its own: the code that finds the bags, though skipped, held the loads of the other
 // passes together: 26 M pairs 133 -> 113 and 107 -> 92 us a pass)
-template <uint32_t kBits, int kBlock, uint32_t kItems, bool kFirst>
-__global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restrict__ ctl, uint32_t pass,
+template <uint32_t kBits, uint32_t kItems, bool kFirst>
+__global__ __launch_bounds__(1 << kBits) void sort_scatter_kernel(Control* __restrict__ ctl, uint32_t pass,
                                                                   const int32_t* __restrict__ rows,
                                                                   const int64_t* __restrict__ offsets,
                                                                   uint64_t n_bags, const uint32_t* __restrict__ unit_bag,
                                                                   const uint2* __restrict__ src,
-                                                                  uint64_t n, uint64_t stride,
-                                                                  const uint32_t* __restrict__ hist,
+                                                                  uint64_t n, const uint32_t* __restrict__ hist,
                                                                   const uint32_t* __restrict__ sums,
                                                                   const uint32_t* __restrict__ totals,
                                                                   uint2* __restrict__ dst) {
@@ -263,7 +206,8 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   // The large blocks serve batches whose pairs do not stay in the 256 MB cache behind the L2s until the next pass: read
   // past it they leave room for the pairs being written (a pass over 26 M pairs 170 -> 153 us; over 6.8 M the same)
   constexpr bool kLoadOnce = kItems >= 4096;
-  using S = Shape<kBits, kBlock, kItems>;
+  using S = Shape<kBits, kItems>;
+  constexpr int kBlock = S::kBlock;
   __shared__ uint2 stage[kItems];          // the block's elements in sorted order
   __shared__ uint32_t lds[S::kWaves][S::kBins];   // per-wave digit counts, then local start offsets
   __shared__ uint32_t local_start[S::kBins];       // first position of a bin in `stage`
@@ -271,30 +215,20 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   uint32_t* bag_here = reinterpret_cast<uint32_t*>(stage);  // (pass 0, until step 4)
   // Which unit: blocks go round the eight XCDs, and the elements that neighbouring units have of a bin share lines, so
-  // that an XCD takes kSortChunk neighbouring units of a large batch and its L2 writes whole lines (26 M pairs: 187 -> 161,
-  // 114 -> 103 and 92 -> 91 us; chunks of 4, 64 or an eighth of the batch are a few us behind; small batches have
-  // too few units).
+  // that an XCD takes kSortChunk neighbouring units and its L2 writes whole lines (26 M pairs: 187 -> 161,
+  // 114 -> 103 and 92 -> 91 us; chunks of 4, 64 or an eighth of the batch are a few us behind).
   const uint32_t turn = blockIdx.x / 8;
-  const uint64_t unit = kSortChunk<kItems> == 1 ? blockIdx.x
-                                                : ((uint64_t)(turn / kSortChunk<kItems>) * 8 + blockIdx.x % 8) * kSortChunk<kItems> +
-                                                      turn % kSortChunk<kItems>;
+  const uint64_t unit = ((uint64_t)(turn / kSortChunk) * 8 + blockIdx.x % 8) * kSortChunk + turn % kSortChunk;
   if (unit * kItems >= n) return;  // (the grid is a whole number of chunks)
   const uint32_t last_bag = (uint32_t)(n_bags - 1);
   const uint32_t shift = plan.shift(pass), bits = plan.width(pass), nbins = 1u << bits, mask = nbins - 1;
 
   // 0. what step 3 needs from memory is asked for first: it arrives while the elements are loaded
-  const bool bin_thread = threadIdx.x < S::kBinThreads;
-  const uint32_t bin0 = threadIdx.x * S::kBinsPerThread;  // the thread's bins
-  uint32_t tot[S::kBinsPerThread], before_me[S::kBinsPerThread];  // a bin in the whole batch / in the units before this one
-#pragma unroll
-  for (uint32_t q = 0; q < S::kBinsPerThread; ++q) {
-    tot[q] = before_me[q] = 0;
-    if (bin_thread && bin0 + q < nbins) {
-      tot[q] = totals[bin0 + q];
-      before_me[q] = kSortGroup<kItems> == 1 ? hist[(uint64_t)(bin0 + q) * stride + unit]
-                                             : hist[unit * S::kBins + bin0 + q] +
-                                                   sums[unit / kSortGroup<kItems> * S::kBins + bin0 + q];
-    }
+  const uint32_t bin = threadIdx.x;  // the thread's bin
+  uint32_t tot = 0, before_me = 0;   // its pairs in the whole batch / in the units before this one
+  if (bin < nbins) {
+    tot = totals[bin];
+    before_me = hist[unit * S::kBins + bin] + sums[unit / kSortGroupUnits * S::kBins + bin];
   }
   // 1. this wave's elements -> registers (independent, coalesced loads)
   if constexpr (!kFirst) n = ctl->scratch[kValidPairs];
@@ -354,46 +288,34 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   }
   static_assert(kItems <= 0x10000, "rank and digit share a word");
   __syncthreads();
-  // 3. a bin thread owns kBinsPerThread bins: exclusive scans of the bins' counts, once within the block
-  //    (positions in `stage`) and once over all bins of the pass (start of the bin in dst)
-  __shared__ uint32_t scan_sum[S::kScanWaves], scan_tot[S::kScanWaves];
+  // 3. exclusive scans of the bins' counts, once within the block (positions in `stage`) and once over all bins of the
+  //    pass (start of the bin in dst)
+  __shared__ uint32_t scan_sum[S::kWaves], scan_tot[S::kWaves];
   {
-    uint32_t mine = 0, tots = 0;
-    if (bin_thread) {
+    uint32_t mine = 0;
 #pragma unroll
-      for (uint32_t q = 0; q < S::kBinsPerThread; ++q) {
-        tots += tot[q];
-#pragma unroll
-        for (int w = 0; w < S::kWaves; ++w) mine += lds[w][bin0 + q];
-      }
-    }
-    const uint32_t x = wave_sums(mine), y = wave_sums(tots);
-    if (bin_thread && lane == 63) {
+    for (int w = 0; w < S::kWaves; ++w) mine += lds[w][bin];
+    const uint32_t x = wave_sums(mine), y = wave_sums(tot);
+    if (lane == 63) {
       scan_sum[wave] = x;
       scan_tot[wave] = y;
     }
     __syncthreads();
-    if (bin_thread) {
-      uint32_t run = x - mine, run_tot = y - tots;  // first position of the thread's first bin in the block / in dst
-      for (uint32_t w = 0; w < wave; ++w) {
-        run += scan_sum[w];
-        run_tot += scan_tot[w];
-      }
-#pragma unroll
-      for (uint32_t q = 0; q < S::kBinsPerThread; ++q) {
-        local_start[bin0 + q] = run;
-        global_start[bin0 + q] = run_tot + before_me[q];
-        run_tot += tot[q];
-#pragma unroll
-        for (int w = 0; w < S::kWaves; ++w) {
-          const uint32_t c = lds[w][bin0 + q];
-          lds[w][bin0 + q] = run;
-          run += c;
-        }
-      }
-      if (kFirst && unit == 0 && threadIdx.x == S::kBinThreads - 1)
-        ctl->scratch[kValidPairs] = run_tot;  // pairs that remain
+    uint32_t run = x - mine, run_tot = y - tot;  // first position of the bin in the block / in dst
+#pragma unroll 1  // (unrolled it holds registers that cost the wide shape a wave in six)
+    for (uint32_t w = 0; w < wave; ++w) {
+      run += scan_sum[w];
+      run_tot += scan_tot[w];
     }
+    local_start[bin] = run;
+    global_start[bin] = run_tot + before_me;
+#pragma unroll
+    for (int w = 0; w < S::kWaves; ++w) {
+      const uint32_t c = lds[w][bin];
+      lds[w][bin] = run;
+      run += c;
+    }
+    if (kFirst && unit == 0 && bin == S::kBins - 1) ctl->scratch[kValidPairs] = run_tot + tot;  // pairs that remain
   }
   if constexpr (kFirst) {
     // The bag of every occurrence of the unit (the pooled gradient of bag b is the gradient of each of its
@@ -442,7 +364,7 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   // 5. out: neighbouring threads write neighbouring elements of a bin
   uint32_t total = 0;
 #pragma unroll
-  for (int w = 0; w < S::kScanWaves; ++w) total += scan_sum[w];
+  for (int w = 0; w < S::kWaves; ++w) total += scan_sum[w];
   for (uint32_t p = threadIdx.x; p < total; p += kBlock) {
     const uint2 e = stage[p];
     const uint32_t digit = (e.x >> shift) & mask;
@@ -450,17 +372,15 @@ __global__ __launch_bounds__(kBlock) void sort_scatter_kernel(Control* __restric
   }
 }
 
-// The whole sort of a batch of at most kSortSmall pairs by one block, all passes in LDS, in one launch.  The result goes
-// where the passes over memory would have left it.
+// The whole sort of a batch of at most kSortSmall pairs by one block, all passes in LDS, in one launch.
 constexpr int kSmallBlock = 1024;
 constexpr uint32_t kSmallWaves = kSmallBlock / 64, kSmallRounds = (uint32_t)kSortSmall / kSmallBlock;
 constexpr uint32_t kSmallBag = 32, kSmallLong = (uint32_t)kSortSmall / kSmallBag;  // a longer bag is a long one; room for all of them
-__global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __restrict__ ctl, uint32_t max_bits,
-                                                                 const int32_t* __restrict__ rows, uint32_t n,
-                                                                 const int64_t* __restrict__ offsets, uint64_t n_bags,
-                                                                 uint2* __restrict__ pair_a, uint2* __restrict__ pair_b) {
+__global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __restrict__ ctl, const int32_t* __restrict__ rows,
+                                                                 uint32_t n, const int64_t* __restrict__ offsets,
+                                                                 uint64_t n_bags, uint2* __restrict__ dst) {
   constexpr uint32_t kBins = 1u << kSortNarrowBits;
-  const SortPlan real = make_sort_plan(ctl->hwm, max_bits), plan = make_sort_plan(ctl->hwm, kSortNarrowBits);
+  const SortPlan plan = make_sort_plan(ctl->hwm, kSortNarrowBits);
   __shared__ uint2 pairs[kSortSmall];
   __shared__ uint32_t cnt[kSmallWaves][kBins];
   __shared__ uint32_t wave_sum[kBins / 64];
@@ -558,43 +478,40 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
       if (kv[r].x != 0xFFFFFFFFu) pairs[cnt[wave][rank[r] >> 16] + (rank[r] & 0xFFFFu)] = kv[r];
     __syncthreads();
   }
-  uint2* dst = real.passes % 2 ? pair_b : pair_a;
   for (uint32_t i = tid; i < count; i += kSmallBlock) dst[i] = pairs[i];
   if (tid == 0) ctl->scratch[kValidPairs] = count;
 }
 
-static_assert(sort_units(kSortItems512, 512) <= 256 * kScanFew,
-              "one wave scans the units of a batch without groups");
-template <uint32_t kBits, int kBlock, uint32_t kItems>
+hipError_t launch_sort_small(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
+                             const int64_t* d_offsets, uint64_t n_bags, hipStream_t stream, Profiler* prof) {
+  MONO_LAUNCH(prof, K_SORT_SCATTER, stream, sort_small_kernel, dim3(1), dim3(kSmallBlock), t.ctl, d_rows, (uint32_t)n, d_offsets,
+              n_bags, ws.pair_b);
+  return hipGetLastError();
+}
+
+template <uint32_t kBits, uint32_t kItems>
 static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                               const int64_t* d_offsets, uint64_t n_bags, uint32_t passes, hipStream_t stream,
                               Profiler* prof) {
-  constexpr uint32_t kUnits = kSortGroup<kItems>;
-  constexpr int kHistBlock = kUnits > 1 ? kGroupBlock : kBlock;
-  const uint64_t units = sort_units(n, kItems), groups = (units + kUnits - 1) / kUnits, stride = sort_stride(units);
-  uint32_t* sums = ws.hist + (stride << kBits);
-  uint32_t* totals = kUnits > 1 ? sums + (groups << kBits) : sums;
-  const uint64_t chunks = 8 * kSortChunk<kItems>;  // whole chunks on every XCD
-  const dim3 block(kBlock), grid((unsigned)(chunks == 8 ? units : (units + chunks - 1) / chunks * chunks));
+  const uint64_t units = sort_units(n, kItems), groups = sort_groups(n, kItems);
+  uint32_t* sums = ws.hist + ((groups * kSortGroupUnits) << kBits);
+  uint32_t* totals = sums + (groups << kBits);
+  const uint64_t chunks = 8 * kSortChunk;  // whole chunks on every XCD
+  const dim3 block(Shape<kBits, kItems>::kBlock), grid((unsigned)((units + chunks - 1) / chunks * chunks));
   for (uint32_t p = 0; p < passes; ++p) {
     const uint2* src = p % 2 == 0 ? ws.pair_a : ws.pair_b;
     uint2* dst = p % 2 == 0 ? ws.pair_b : ws.pair_a;
-    const uint32_t search = p == 0 ? (uint32_t)((units + kHistBlock / 64 - 1) / (kHistBlock / 64)) : 0u;
-    MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kHistBlock, kItems, kUnits>),
-                dim3((unsigned)groups + search), dim3(kHistBlock), t.ctl, p, d_rows, src, n, stride, ws.hist, sums, d_offsets,
-                n_bags, ws.unit_bag, search);
-    if constexpr (kUnits > 1)
-      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3((1u << kBits) / 4), dim3(kScanBlock), t.ctl, p,
-                  sums, groups, totals);
-    else
-      MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_few_kernel<kBits>, dim3((1u << kBits) / 4), dim3(256), t.ctl, p,
-                  ws.hist, (uint32_t)units, stride, totals);
+    const uint32_t search = p == 0 ? (uint32_t)((units + kGroupBlock / 64 - 1) / (kGroupBlock / 64)) : 0u;
+    MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kItems>), dim3((unsigned)groups + search), dim3(kGroupBlock),
+                t.ctl, p, d_rows, src, n, ws.hist, sums, d_offsets, n_bags, ws.unit_bag, search);
+    MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3((1u << kBits) / 4), dim3(kScanBlock), t.ctl, p, sums,
+                groups, totals);
     if (p == 0)
-      MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems, true>), grid, block, t.ctl, p,
-                  d_rows, d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, sums, totals, dst);
+      MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kItems, true>), grid, block, t.ctl, p, d_rows,
+                  d_offsets, n_bags, ws.unit_bag, src, n, ws.hist, sums, totals, dst);
     else
-      MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kBlock, kItems, false>), grid, block, t.ctl, p,
-                  d_rows, d_offsets, n_bags, ws.unit_bag, src, n, stride, ws.hist, sums, totals, dst);
+      MONO_LAUNCH(prof, K_SORT_SCATTER, stream, (sort_scatter_kernel<kBits, kItems, false>), grid, block, t.ctl, p, d_rows,
+                  d_offsets, n_bags, ws.unit_bag, src, n, ws.hist, sums, totals, dst);
   }
 }
 
@@ -604,29 +521,14 @@ hipError_t launch_sort_pairs(const TableView& t, const UpdateWorkspace& ws, cons
   // the shape and as many passes as the largest high-water mark the table can have by now needs (the device
   // knows the real mark: passes beyond its plan return at once)
   const uint32_t bound = hwm_bound < (uint32_t)t.capacity ? hwm_bound : (uint32_t)t.capacity;
-  const SortShape shape = sort_shape_for(bound, n);
+  const SortShape shape = sort_shape_for(bound);
   const SortPlan worst = make_sort_plan(bound, shape.max_bits);
-  if (launched) *launched = worst.passes;
-  if (max_bits) *max_bits = shape.max_bits;
-  if (n == 0) return hipSuccess;
-  if (sorts_in_one_block(n, n_bags)) {
-    MONO_LAUNCH(prof, K_SORT_SCATTER, stream, sort_small_kernel, dim3(1), dim3(kSmallBlock), t.ctl, shape.max_bits, d_rows,
-                (uint32_t)n, d_offsets, n_bags, ws.pair_a, ws.pair_b);
-    return hipGetLastError();
-  }
-#define MONO_SORT(bits, block, items) \
-  queue_sort_passes<bits, block, items>(t, ws, d_rows, n, d_offsets, n_bags, worst.passes, stream, prof)
-  if (shape.max_bits == kSortFewBits) {
-    MONO_SORT(kSortFewBits, 256, 512);
-  } else if (shape.max_bits == kSortWideBits) {
-    MONO_SORT(kSortWideBits, 512, 4096);
-  } else {
-    if (shape.items == 512)
-      MONO_SORT(kSortNarrowBits, 256, 512);
-    else
-      MONO_SORT(kSortNarrowBits, 256, 2048);
-  }
-#undef MONO_SORT
+  *launched = worst.passes;
+  *max_bits = shape.max_bits;
+  if (shape.max_bits == kSortWideBits)
+    queue_sort_passes<kSortWideBits, kSortWideItems>(t, ws, d_rows, n, d_offsets, n_bags, worst.passes, stream, prof);
+  else
+    queue_sort_passes<kSortNarrowBits, kSortNarrowItems>(t, ws, d_rows, n, d_offsets, n_bags, worst.passes, stream, prof);
   return hipGetLastError();
 }
 

@@ -43,7 +43,7 @@ struct mono_table {
 constexpr uint64_t kStaticMaxIds = MONO_NOALLOC_MAX_IDS;  // largest batch of the allocation-free entry point
 constexpr uint32_t kStaticMaxDim = 1024;
 constexpr size_t static_part(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
-constexpr size_t kStaticHistWords = 2048 * (kSortFewMost / 512 + 4);  // at least sort_hist_words(kStaticMaxIds): checked below
+constexpr size_t kStaticHistWords = sort_hist_words(kStaticMaxIds);
 constexpr uint64_t kStaticTiles = 2 * kTilesWanted;  // tiles of the reduction: reduce_tiles(kStaticMaxIds), checked below
 constexpr size_t kStaticPartFloats = 2 * ((kStaticMaxIds + 255) / 256) * kStaticMaxDim;  // for wide rows: tiles of 256 pairs
 constexpr size_t kStaticScratchBytes =
@@ -168,7 +168,6 @@ void* g_scratch_ptr[kMaxDevices] = {nullptr};
 std::mutex g_scratch_mutex;
 
 hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
-  if (sort_hist_words(kStaticMaxIds) > kStaticHistWords) return hipErrorInvalidValue;
   if (reduce_tiles(kStaticMaxIds) > kStaticTiles) return hipErrorInvalidValue;
   if (device < 0 || device >= kMaxDevices) return hipErrorInvalidDevice;
   void* base = nullptr;

@@ -568,9 +568,10 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
                                      uint32_t hwm_bound, hipStream_t stream, Profiler* prof) {
   if (n == 0 || n_bags == 0) return hipSuccess;
   uint32_t launched = 1, max_bits = 0;
-  hipError_t e = n > kSortSmall && n <= kSplitMost
-                     ? launch_split_pairs(t, ws, d_rows, n, d_offsets, n_bags, stream, prof)
-                     : launch_sort_pairs(t, ws, d_rows, n, d_offsets, n_bags, hwm_bound, &launched, &max_bits, stream, prof);
+  const hipError_t e =
+      sorts_in_one_block(n, n_bags) ? launch_sort_small(t, ws, d_rows, n, d_offsets, n_bags, stream, prof)
+      : n <= kSplitMost ? launch_split_pairs(t, ws, d_rows, n, d_offsets, n_bags, stream, prof)
+                        : launch_sort_pairs(t, ws, d_rows, n, d_offsets, n_bags, hwm_bound, &launched, &max_bits, stream, prof);
   if (e != hipSuccess) return e;
   uint32_t group_log2 = 0;
   while (group_log2 < 6 && (4u << group_log2) < t.dim) ++group_log2;

@@ -159,33 +159,44 @@ int main() {
 """)
 
 
-def test_two_wide_digits_only_where_they_are_faster_and_the_workspace_holds_every_shape(tmp_path):
-    """Two digits of up to 11 bits: batches of 2^17 pairs up to 2^20 rows in use (digits of 10 bits), 2^16 up to 2^21,
-    2^15 up to 2^22.  The histogram workspace for batches of n pairs holds what any shape of any smaller batch needs."""
+def test_the_workspace_holds_what_any_batch_needs_and_the_split_its_units(tmp_path):
+    """The histogram workspace for batches of n pairs holds the shares and turns of every split and the histograms of every
+    radix shape of any smaller batch; a block of the split's second kernel has a thread for every unit of the first; buckets
+    of evenly spread rows are an eighth of what a block sorts at once; digits of nine bits from 2^24 rows in use on."""
     _run(tmp_path, r"""
 #include "kernels.h"
 using namespace mono;
+static uint64_t words_of(uint64_t n, uint32_t rows) {
+  if (n <= kSplitMost) {
+    const SplitShape s = split_shape_for(n);
+    const uint64_t hot = kSplitSamples[s.size] / kSplitHits;
+    return sort_units(n, kSplitItems[s.size]) * (kSplitBuckets[s.size] + hot) + 2 + 2 * (hot + n / kSplitTurn);
+  }
+  const SortShape s = sort_shape_for(rows);
+  const uint64_t groups = sort_groups(n, s.items);
+  return (groups * kSortGroupUnits << s.max_bits) + (groups << s.max_bits) + (1ull << s.max_bits);
+}
 int main() {
   int wrong = 0;
-  struct { uint32_t rows; uint64_t most; } few[] = {{1u << 16, 0}, {(1u << 16) + 1, 1u << 17}, {1u << 20, 1u << 17},
-      {(1u << 20) + 1, 1u << 16}, {1u << 21, 1u << 16}, {(1u << 21) + 1, 1u << 15}, {1u << 22, 1u << 15}, {(1u << 22) + 1, 0}};
-  for (auto f : few)
-    for (uint64_t n : {1ull, 1ull << 15, (1ull << 15) + 1, 1ull << 16, (1ull << 16) + 1, 1ull << 17, (1ull << 17) + 1, 1ull << 20})
-      if ((sort_shape_for(f.rows, n).max_bits == kSortFewBits) != (n <= f.most))
-        printf("%u rows, %llu pairs\n", f.rows, (unsigned long long)n), ++wrong;
   uint64_t sizes[200];
   int k = 0;
   for (double n = 1; n < 3e8; n *= 1.2) sizes[k++] = (uint64_t)n;
-  for (uint64_t n : {1ull << 15, 1ull << 16, 1ull << 17, 1ull << 18, 400000ull, 400001ull, 1ull << 20, (1ull << 20) + 1}) sizes[k++] = n;
+  for (uint64_t n : {1ull << 12, (1ull << 12) + 1, 1ull << 16, (1ull << 16) + 1, 1ull << 17, (1ull << 17) + 1, 1ull << 18, 1ull << 19, (1ull << 19) + 1, 1ull << 20, (1ull << 20) + 1, 1ull << 28}) sizes[k++] = n;
   for (int i = 0; i < k; ++i)
     for (int j = 0; j < k; ++j)
-      for (uint32_t rows : {1u, 1u << 16, (1u << 16) + 1, 1u << 20, 1u << 21, 1u << 22, (1u << 22) + 1, 1u << 24, (1u << 24) + 1, 1u << 30})
-        if (sizes[j] <= sizes[i]) {
-          const SortShape s = sort_shape_for(rows, sizes[j]);
-          const uint64_t stride = sort_stride(sort_units(sizes[j], s.items)), groups = s.items > kSortGroupedAbove ? stride / kSortGroupUnits : 0;
-          if (((stride + groups + 1) << s.max_bits) > sort_hist_words(sizes[i]))
-            printf("%llu pairs in a workspace for %llu, %u rows\n", (unsigned long long)sizes[j], (unsigned long long)sizes[i], rows), ++wrong;
-        }
+      for (uint32_t rows : {1u, 1u << 24, (1u << 24) + 1, 1u << 30})
+        if (sizes[j] <= sizes[i] && words_of(sizes[j], rows) > sort_hist_words(sizes[i]))
+          printf("%llu pairs in a workspace for %llu, %u rows\n", (unsigned long long)sizes[j], (unsigned long long)sizes[i], rows), ++wrong;
+  for (uint64_t n = 1; n <= kSplitMost; n += 1 + n / 200) {
+    const SplitShape s = split_shape_for(n);
+    const uint64_t units = sort_units(n, kSplitItems[s.size]), most = sort_units(kSplitUpTo[s.size], kSplitItems[s.size]);
+    if (n > kSplitUpTo[s.size] || units > most || most > 512 || 1u << s.buckets_log2 > kSplitBuckets[s.size]) printf("%llu: %llu units\n", (unsigned long long)n, (unsigned long long)units), ++wrong;
+    if ((n >> s.buckets_log2) > 1024) printf("%llu pairs in %u buckets\n", (unsigned long long)n, 1u << s.buckets_log2), ++wrong;
+  }
+  for (uint32_t rows : {1u, 1u << 16, 1u << 22, 1u << 24, (1u << 24) + 1, 1u << 30}) {
+    const SortShape s = sort_shape_for(rows);
+    if (s.max_bits != (rows > 1u << 24 ? 9u : 8u) || s.items != 8u << s.max_bits) printf("%u rows\n", rows), ++wrong;
+  }
   return wrong ? 1 : 0;
 }
 """)

@@ -1,6 +1,6 @@
-"""The update's sort takes its shape from the size of the batch (one block in LDS, blocks of 512 / 1024 / 2048 elements)
-and from the rows in use (8- or 9-bit digits): batches at the edges of each, with hot rows, dropped occurrences and
-bags of every length, against the oracle."""
+"""How the update groups its pairs follows from the size of the batch (one block in LDS up to 4096 pairs, the split up to 2^20,
+radix passes beyond) and, of the radix passes, from the rows in use (8- or 9-bit digits): batches at the edges of each, with
+hot rows, dropped occurrences and bags of every length, against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,7 @@ from tests import table_checks as tc
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 1025, 8191, 8192, 8193, 50001, 400000, 400001, 1 << 20, (1 << 20) + 1])
+@pytest.mark.parametrize("n", [1, 2, 63, 1025, 4095, 4096, 4097, 8191, 8192, 8193, 50001, 400000, 400001, 1 << 20, (1 << 20) + 1])
 def test_update_at_the_edges_of_the_sort_shapes(n):
     from paper_2209_07663_amd.binding import Table
     dev, seed, cap, dim = torch.device("cuda:0"), 11, 1 << 18, 8
@@ -41,9 +41,10 @@ def test_update_at_the_edges_of_the_sort_shapes(n):
     tab.close()
 
 
-@pytest.mark.parametrize("n", [9000, (1 << 20) + 5])
+@pytest.mark.parametrize("n", [3000, 9000, (1 << 20) + 5])
 def test_wide_digits_in_small_and_large_batches(n):
-    """More than 2^24 rows in use: two batches of 9 M new keys raise the mark, then a small update is compared."""
+    """More than 2^24 rows in use: two batches of 9 M new keys raise the mark, then an update is compared that one block sorts
+    (in four digits), one that is split and one of nine-bit digits."""
     from paper_2209_07663_amd.binding import Table
     dev, seed, cap, dim = torch.device("cuda:0"), 13, 1 << 25, 4
     tab = Table(cap, dim, seed, 1, 0, max_ids=9 << 20, max_bags=9 << 20, device=dev)
