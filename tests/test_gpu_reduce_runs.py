@@ -44,5 +44,11 @@ def test_runs_of_all_lengths(dim, bf16):
         # run's pieces; the ratio of a sum and the root of its mean square doubles that, and the result is rounded once
         rel = 2 * (272 + count[at] / 256) * 2.0 ** -24
         assert ((got - want).abs() <= rel * move[at] + want.abs() * (2.0 ** -8 if bf16 else 2.0 ** -23)).all(), (case, dim)
+        # a row's move says little of the length of its sum, its accumulator does: twice the error of the sums, and at
+        # most twenty roundings of a mean of squares (four pieces of four elements a lane, six levels of lanes)
+        dump = tab.mono_table_export()
+        acc = (total ** 2).mean(1).cpu().numpy()
+        assert (dump["keys"] == stored.cpu().numpy()).all()
+        assert (abs(dump["acc"] - acc) <= (2 * (272 + count[:, 0].cpu().numpy() / 256) + 20) * 2.0 ** -24 * acc).all(), (case, dim)
         assert tab.mono_table_stats()["n_lost"] == 0
         tab.close()
