@@ -149,9 +149,9 @@ int mono_apply_grad_adagrad(mono_table* t, const int32_t* d_rows, uint64_t n, co
 
 /* mono_apply_grad_adagrad for callers that must not allocate device memory and cannot bring a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and
- * same result as mono_apply_grad_adagrad, but the per-call workspace (bag indices, the two buffers of
- * sorted (row, bag) pairs, radix histograms, partial sums) is a fixed array inside the library instead of
- * the table's arena: about 16 MB of device memory per GPU the library runs on, held until the process
+ * same result as mono_apply_grad_adagrad, but the per-call workspace (the two buffers of (row, bag) pairs,
+ * the shares of their bins, partial sums) is a fixed array inside the library instead of
+ * the table's arena: about 13 MB of device memory per GPU the library runs on, held until the process
  * ends.  The call allocates nothing (no hipMalloc / hipFree, no event creation) and never synchronises.
  *   limit   n <= mono_noalloc_max_ids() (262144) IDs per call, any dim the table can have; a larger batch
  *           is refused with MONO_ELIMIT and nothing is done (split the batch by whole bags, or use

@@ -8,7 +8,7 @@
 // 64 lanes hold are walked in segments by the whole wave.  A bag longer than kIdsInRegs goes on in steps
 // of kIdsInRegs indices, the next step's indices requested before this step's rows are waited for (bags
 // of 23 IDs on average, dim 36: 144 us per launch when the rest of a long bag was read one row at a time,
-// 20 us so).  A wave whose bags all hold at most two IDs (one-hot slots) issues four rounds of row reads
+// 20 us so).  A wave whose bags all hold at most two IDs (one-hot slots) issues several rounds of row reads
 // together instead (81 -> 69 us on the workload with one ID per bag).
 //
 // How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   const uint32_t group = 1u << group_log2, l = lane & (group - 1u), g = lane >> group_log2;
   const uint32_t bags_per_round = 64u >> group_log2, rounds = (1u << bags_log2) >> (6u - group_log2);
   // Short bags (one or two IDs each, as in one-hot slots): a round keeps only one or two rows per
-  // lane in flight, so four rounds are issued together instead.
+  // lane in flight, so four rounds (two, where four IDs are in flight) are issued together instead.
   constexpr int kShort = 2, kRoundsTogether = kIds / kShort;
   int longest = len;
 #pragma unroll

@@ -46,8 +46,9 @@ constexpr size_t static_part(size_t bytes) { return (bytes + 255) & ~(size_t)255
 constexpr size_t kStaticHistWords = sort_hist_words(kStaticMaxIds);
 constexpr uint64_t kStaticTiles = 2 * kTilesWanted;  // tiles of the reduction: reduce_tiles(kStaticMaxIds), checked below
 constexpr size_t kStaticPartFloats = 2 * ((kStaticMaxIds + 255) / 256) * kStaticMaxDim;  // for wide rows: tiles of 256 pairs
+static_assert(kStaticMaxIds <= kSplitMost, "no batch takes the radix passes, which need unit_bag");
 constexpr size_t kStaticScratchBytes =
-    static_part(kStaticMaxIds * 4) + 2 * static_part(kStaticMaxIds * sizeof(uint2)) +
+    2 * static_part(kStaticMaxIds * sizeof(uint2)) +
     static_part(kStaticHistWords * 4) +
     static_part(kStaticPartFloats * sizeof(float)) + static_part(2 * kStaticTiles * sizeof(uint32_t));
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -192,7 +193,7 @@ hipError_t static_workspace(int device, uint32_t dim, UpdateWorkspace* ws) {
     at += static_part(bytes);
     return p;
   };
-  ws->unit_bag = (uint32_t*)take(kStaticMaxIds * 4);
+  ws->unit_bag = nullptr;
   ws->pair_a = (uint2*)take(kStaticMaxIds * sizeof(uint2));
   ws->pair_b = (uint2*)take(kStaticMaxIds * sizeof(uint2));
   ws->hist = (uint32_t*)take(kStaticHistWords * 4);
