@@ -71,7 +71,7 @@ __device__ inline uint32_t split_turns(uint32_t hits, uint32_t n) {
   return 1 + (uint32_t)((uint64_t)hits * n / kSamples / kSplitTurn);
 }
 
-template <int kBlock, uint32_t kItems, uint32_t kSamples, uint32_t kBuckets>
+template <int kBlock, uint32_t kItems, uint32_t kSamples, uint32_t kBuckets, bool kSearch>
 __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict__ ctl, const int32_t* __restrict__ rows,
                                                             uint32_t n, const int64_t* __restrict__ offsets,
                                                             uint64_t n_bags, uint32_t buckets_log2, uint32_t group_log2,
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   __shared__ Lds s;
   __shared__ __align__(4) uint16_t cnt[kWaves][kBins];
   __shared__ uint32_t hot_row[kHot], hot_hits[kHot], hot_turns[kHot], hot_key[kHotSlots], hot_bin[kHotSlots];
-  __shared__ uint32_t n_hot, wave_sum[kWaves], wave_last[kWaves], bags_before[2];
+  __shared__ uint32_t n_hot, wave_sum[kWaves], wave_last[kWaves], bags_before[2], bags_left;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
   const uint32_t unit = blockIdx.x, ubase = unit * kItems, uend = ubase + kItems < n ? ubase + kItems : n;
   const uint32_t base = ubase + wave * kPerWave;
@@ -134,6 +134,7 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   static_assert(kWaves * kBins % 2 == 0, "whole words");
   for (uint32_t b = tid; b < kWaves * kBins / 2; b += kBlock) reinterpret_cast<uint32_t*>(cnt)[b] = 0;
   if (tid == 0) n_hot = 0;
+  if (kSearch && tid == 0) bags_left = 0;
   if (tid < 2) bags_before[tid] = 0;
   __syncthreads();
   report(yes, 0);
@@ -284,8 +285,11 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   }
   // The bag of every occurrence: every bag leaves its number at its first occurrence, an occurrence takes the number left
   // at or before it (as in the radix sort's first pass; whatever the offsets hold, every write stays inside the unit and
-  // every bag number that is used is one of the batch).
-  for (bool more = true; more;) {
+  // every bag number that is used is one of the batch).  With kSearch a unit whose occurrences lie in very many bags ends this
+  // after kBagTurns turns, of 0.6 us each, and every occurrence searches the other bags, which takes about as long as those turns.
+  constexpr uint32_t kBagTurns = 16;
+  bool more = true;
+  for (uint32_t turn = 0; more && (!kSearch || turn < kBagTurns); ++turn) {
 #pragma unroll
     for (uint32_t q = 0; q < kBagsAhead; ++q) {
       const uint64_t b = bag + q * kBlock;
@@ -296,6 +300,7 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
     bag += (uint64_t)kBlock * kBagsAhead;
     if (more) ask();
   }
+  if (kSearch && more) bags_left = 1;  // (the threads that say so agree)
   __syncthreads();
   uint32_t carry = 0;  // the last number left in the wave's earlier elements
 #pragma unroll
@@ -315,8 +320,27 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   for (uint32_t r = 0; r < kRounds; ++r) {
     const uint32_t b = kv[r].y ? kv[r].y : before;
     kv[r].y = min(b ? b - 1u : 0u, last_bag);
-    if (kv[r].x != kNoSplitRow) s.stage[cnt[wave][rank[r] >> 16] + (rank[r] & 0xFFFFu)] = kv[r];
   }
+  if constexpr (kSearch) {
+    const uint64_t walked = lo + (uint64_t)kBagTurns * kBagsAhead * kBlock;
+    if (bags_left && walked < n_bags) {  // block-uniform: how many of the other bags are not behind an occurrence
+      const uint32_t left = (uint32_t)(n_bags - walked);
+      uint32_t k[kRounds] = {};
+      for (uint32_t step = 1u << (31 - __clz(left)); step; step >>= 1) {
+#pragma unroll
+        for (uint32_t r = 0; r < kRounds; ++r) {
+          const uint32_t p = k[r] + step;  // (no more than twice `left`, and a batch has at most 2^28 + 1 bags)
+          if (p <= left && bounded_offset(offsets, walked + p - 1, n) <= base + r * 64 + lane) k[r] = p;
+        }
+      }
+#pragma unroll
+      for (uint32_t r = 0; r < kRounds; ++r)
+        if (k[r]) kv[r].y = (uint32_t)walked + k[r] - 1;
+    }
+  }
+#pragma unroll
+  for (uint32_t r = 0; r < kRounds; ++r)
+    if (kv[r].x != kNoSplitRow) s.stage[cnt[wave][rank[r] >> 16] + (rank[r] & 0xFFFFu)] = kv[r];
   __syncthreads();
   for (uint32_t p = tid; p < total; p += kBlock) dst[ubase + p] = s.stage[p];
 }
@@ -611,7 +635,7 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
   }
 }
 
-template <int kThreads, uint32_t kItems, uint32_t kSamples, uint32_t kBuckets, uint32_t kUnits>
+template <int kThreads, uint32_t kItems, uint32_t kSamples, uint32_t kBuckets, uint32_t kUnits, bool kSearch>
 static void queue_split(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                         const int64_t* d_offsets, uint64_t n_bags, const SplitShape& sh, hipStream_t stream, Profiler* prof) {
   constexpr int kBlock = kUnits <= 256 ? 256 : 512;  // (a thread per unit)
@@ -622,7 +646,7 @@ static void queue_split(const TableView& t, const UpdateWorkspace& ws, const int
   uint2* turns = reinterpret_cast<uint2*>(turns_n + 2);
   uint32_t pow2 = 1;
   while (pow2 < units) pow2 <<= 1;
-  MONO_LAUNCH(prof, K_SORT_SPLIT, stream, (sort_split_kernel<kThreads, kItems, kSamples, kBuckets>), dim3(units),
+  MONO_LAUNCH(prof, K_SORT_SPLIT, stream, (sort_split_kernel<kThreads, kItems, kSamples, kBuckets, kSearch>), dim3(units),
               dim3(kThreads), t.ctl, d_rows, (uint32_t)n, d_offsets, n_bags, sh.buckets_log2, sh.group_log2, ws.hist, turns_n,
               turns, ws.pair_a);
   MONO_LAUNCH(prof, K_SORT_BUCKET, stream, sort_bucket_kernel<kBlock>, dim3((1u << sh.buckets_log2) + most_turns),
@@ -633,14 +657,19 @@ static void queue_split(const TableView& t, const UpdateWorkspace& ws, const int
 hipError_t launch_split_pairs(const TableView& t, const UpdateWorkspace& ws, const int32_t* d_rows, uint64_t n,
                               const int64_t* d_offsets, uint64_t n_bags, hipStream_t stream, Profiler* prof) {
   const SplitShape sh = split_shape_for(n);
-#define MONO_SPLIT(i)                                                                           \
+#define MONO_SPLIT(i, search)                                                                   \
   queue_split<kSplitThreads[i], kSplitItems[i], kSplitSamples[i], kSplitBuckets[i],             \
-              sort_units(kSplitUpTo[i], kSplitItems[i])>(t, ws, d_rows, n, d_offsets, n_bags, sh, stream, prof)
+              sort_units(kSplitUpTo[i], kSplitItems[i]), search>(t, ws, d_rows, n, d_offsets, n_bags, sh, stream, prof)
   switch (sh.size) {
-    case 0: MONO_SPLIT(0); break;
-    case 1: MONO_SPLIT(1); break;
-    case 2: MONO_SPLIT(2); break;
-    default: MONO_SPLIT(3); break;
+    case 0:
+      if (split_searches_bags(n, n_bags))
+        MONO_SPLIT(0, true);
+      else
+        MONO_SPLIT(0, false);
+      break;
+    case 1: MONO_SPLIT(1, false); break;
+    case 2: MONO_SPLIT(2, false); break;
+    default: MONO_SPLIT(3, false); break;
   }
 #undef MONO_SPLIT
   return hipGetLastError();

@@ -50,3 +50,42 @@ def test_updates_on_both_sides_of_the_lines(used):
         assert ((after - ref).abs() <= 2e-5 * (ref.abs() + 0.05)).all(), (n, bags)
     assert tab.mono_table_stats()["n_lost"] == 0
     tab.close()
+
+
+@pytest.mark.parametrize("n,bags", [(60, 16385), (500, 1 << 20), (4000, 32 * 4000 + 31), (4000, 32 * 4001), (4000, 300000),
+                                    (60000, 32 * 60001), (65536, 32 * 65537), (65537, 32 * 65538)])
+def test_bags_beyond_those_that_a_unit_walks(n, bags):
+    """Occurrences in few of many bags, of the sizes where the split searches bags and of the next ones: on both sides of the
+    last bag that the first unit walks over (16 turns of two bags a thread, from bag 0 on here), in the batch's last bag, and
+    in bags that span units."""
+    from paper_2209_07663_amd.binding import Table
+    dev, dim, used, walked = torch.device("cuda:0"), 4, 1 << 16, 8192
+    g = torch.Generator(device=dev).manual_seed(n)
+    tab = Table(1 << 18, dim, 5, max_ids=1 << 22, max_bags=1 << 22, device=dev)
+    tab.mono_lookup_or_insert(torch.arange(used, device=dev), 0)
+    acc = torch.zeros(1 << 18, dtype=torch.float64, device=dev)
+    edges = torch.tensor([0, walked - 1, walked, walked + 1, 2 * walked, bags - 1], device=dev)
+    for few in (True, False):
+        bag = torch.randint(0, bags, (n,), device=dev, generator=g)
+        if few:
+            bag = edges[torch.randint(0, edges.numel(), (n,), device=dev, generator=g)]
+        bag[: edges.numel()] = edges
+        bag = torch.sort(bag)[0]
+        offs = torch.searchsorted(bag, torch.arange(bags + 1, device=dev))
+        rows = tab.mono_lookup_or_insert(torch.randint(0, used, (n,), device=dev, generator=g), 1)
+        rows[n // 3] = -1
+        # whole numbers below 2^24 in every sum: a pair in a wrong bag shows whatever the order of the sums
+        grad = torch.randint(-3, 4, (bags, dim), device=dev, generator=g).float()
+        kept = rows >= 0
+        at = torch.unique(rows[kept])
+        one = torch.arange(at.numel() + 1, device=dev)
+        before = tab.mono_gather_pool(at, one).double()
+        tab.mono_apply_grad_adagrad(rows, offs, grad, 0.05, 1e-6)
+        after = tab.mono_gather_pool(at, one).double()
+        total = torch.zeros(1 << 18, dim, dtype=torch.float64, device=dev)
+        total.index_add_(0, rows[kept].long(), grad[bag][kept].double())
+        acc += total.pow(2).mean(dim=1)
+        ref = before - 0.05 * total[at.long()] / (acc[at.long()].sqrt()[:, None] + 1e-6)
+        assert ((after - ref).abs() <= 2e-5 * (ref.abs() + 0.05)).all(), few
+    assert tab.mono_table_stats()["n_lost"] == 0
+    tab.close()
