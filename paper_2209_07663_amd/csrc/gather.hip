@@ -311,11 +311,23 @@ hipError_t launch_gather_pool(const TableView& t, const int32_t* d_rows, uint64_
 // Shorter bags of fp32 rows that share a wave with three others or more, where there are so many that the chip is full twice
 // over: bags of eight, uniform IDs, 500 K of dim 32 164 and 171, 250 K of dim 64 153 and 160 (90 K of dim 128 142 and 134, 66 K
 // of dim 64 57 and 45).
+// And of rows of more than two pieces of a wave's width, which a wave takes bag by bag: bags of eight, eight and four: bf16 of dim
+// 1024, 1000 bags 9.0 and 10.0 us, 32 K 159 and 165, fp32 16.9 and 17.5, 430 and 445, at worst (2 to 4 K bags) 3 % the other way.  Bags
+// of nine to eleven, two steps of eight or three of four, there too only where there are many: 100 bags 13.6 and 12.9 us.
+// Of two pieces only fp32 rows of such many waves (dim 512, 64 K bags 301 and 311 us, 12 K 65 and 61).
 constexpr uint64_t kQrBag = 12, kQrBagNarrow = 3, kQrBagMany = 6;
 inline bool qr_takes_eight(uint64_t n, uint64_t n_bags, uint32_t dim, bool bf16) {
-  if (bf16) return n / n_bags >= (dim <= 32 ? kQrBagNarrow : kQrBag);
   const GatherShape four(dim, 4, n_bags, 4);
-  return n / n_bags >= (four.group_log2 <= 4 && four.waves >= 2 * QuotRemRows<float, 4, 4>::kHeld ? kQrBagMany : kQrBag);
+  const bool many = four.waves >= 2 * QuotRemRows<float, 4, 4>::kHeld;
+  uint64_t bag = kQrBag;
+  if (dim > 2 * 64 * 4) {
+    if (many || n <= kIdsInRegs * n_bags) bag = kQrBagMany;
+  } else if (bf16) {
+    if (dim <= 32) bag = kQrBagNarrow;
+  } else if (many && (four.group_log2 <= 4 || dim > 64 * 4)) {
+    bag = kQrBagMany;
+  }
+  return n / n_bags >= bag;
 }
 
 hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t log2_rows, uint32_t dim, bool bf16,

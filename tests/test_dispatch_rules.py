@@ -117,22 +117,24 @@ int main() {
 
 
 def test_two_tables_eight_rows_in_flight_for_long_bags_and_for_many_of_six(tmp_path):
-    """Of fp32 rows, from 12 IDs a bag on, or from 6 where four rows or more share a wave and four IDs in flight would be more
-    than twice the 6144 waves that the chip holds; and the latter are never a little more than those."""
+    """From 12 IDs a bag on (3 of narrow bf16 rows), or from 6 of rows of more than two pieces (to 8 in few
+    bags) and of fp32 rows of which four or more share a wave or that are two pieces, where four IDs in flight would be more than twice the 6144 waves that the chip
+    holds; and the latter are never a little more than those."""
     _run(tmp_path, r"""
 #include "gather.hip"
 using namespace mono;
 int main() {
   int bad = 0;
-  for (unsigned dim : {4u, 16u, 32u, 36u, 64u, 100u, 128u, 256u, 512u})
+  for (unsigned dim : {4u, 16u, 32u, 36u, 64u, 100u, 128u, 256u, 512u, 768u, 1024u})
     for (unsigned long long bags = 1; bags < 3000000; bags += 1 + bags / 300) {
       const unsigned lanes_log2 = dim <= 4 ? 0 : dim <= 16 ? 2 : dim <= 32 ? 3 : dim <= 64 ? 4 : dim <= 128 ? 5 : 6;
-      const unsigned long long usual = lanes_log2 < 3 ? 64 : lanes_log2 == 3 ? 32 : 16;
-      const bool many = lanes_log2 <= 4 && bags / usual >= 12288;
-      for (unsigned long long each : {1ull, 5ull, 6ull, 11ull, 12ull, 40ull}) {
-        if (qr_takes_eight(bags * each, bags, dim, true) != (each >= (dim <= 32 ? 3u : 12u))) printf("bf16 %u %llu %llu\n", dim, bags, each), ++bad;
-        if (many != (lanes_log2 <= 4 && (bags + usual - 1) / usual >= 12288)) continue;
-        if (qr_takes_eight(bags * each, bags, dim, false) != (each >= 12 || (each >= 6 && many))) printf("%u %llu %llu\n", dim, bags, each), ++bad;
+      const unsigned long long usual = lanes_log2 < 3 ? 64 : lanes_log2 == 3 ? 32 : dim == 512 ? 2 : dim > 512 ? 1 : 16;
+      const bool some = lanes_log2 <= 4 || dim >= 512, many = some && bags / usual >= 12288;
+      for (unsigned long long each : {1ull, 5ull, 6ull, 8ull, 9ull, 11ull, 12ull, 40ull}) {
+        const unsigned long long from = many || (dim > 512 && each <= 8) ? 6 : 12;
+        if (qr_takes_eight(bags * each, bags, dim, true) != (each >= (dim <= 32 ? 3 : dim > 512 ? from : 12))) printf("bf16 %u %llu %llu\n", dim, bags, each), ++bad;
+        if (many != (some && (bags + usual - 1) / usual >= 12288)) continue;
+        if (qr_takes_eight(bags * each, bags, dim, false) != (each >= from)) printf("%u %llu %llu\n", dim, bags, each), ++bad;
       }
       using Four = QuotRemRows<float, 4, 4>;
       const GatherShape s(dim, 4, bags, Four::kIds, Four::kHeld);
