@@ -25,40 +25,74 @@
 
 namespace mono {
 
-// Cooperative probe.  A lane owns one key; the eight lanes of a group then visit the group's eight
-// buckets one after another, each lane reading 16 bytes, so that a bucket line (eight keys + eight
-// meta words) is ONE 128-byte access: lanes 0-3 of the group hold the keys two by two, lanes 4-7 the
-// meta words.  (Four 16-byte loads by one lane on the same line cost ~2.5x more once the line comes
-// from beyond the L2: measured.)  The eight loads of a lane are independent and in flight together.
-// side = 0 probes T0 for the keys flagged `want`, side = 1 probes T1.
-__device__ inline void probe_side(const TableView& t, uint64_t k, uint64_t bucket, bool want, uint32_t gi,
-                                  uint32_t gbase, unsigned long long* meta_out, int* slot_out) {
-  ulonglong2 d[kBucket];
-#pragma unroll
-  for (int r = 0; r < kBucket; ++r) {
-    const int src = (int)gbase + r;
-    const int need = __shfl((int)want, src);
-    const uint64_t bb = __shfl(bucket, src);
-    d[r] = make_ulonglong2(0ull, 0ull);
-    if (need) d[r] = reinterpret_cast<const ulonglong2*>(t.buckets + bb)[gi];
+// The value of lane R of the quad, in all of its lanes; the value of the lane whose number differs by X (1 or 2, xor).
+// (Moves inside a quad are operands of vector instructions; a shuffle goes through LDS.)
+template <int R>
+__device__ inline uint32_t quad_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, R * 0x55, 0xF, 0xF, true);
+}
+template <int X>
+__device__ inline uint32_t quad_xor(uint32_t v) {
+  static_assert(X == 1 || X == 2, "quad_perm 1,0,3,2 or 2,3,0,1");
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, true);
+}
+
+// Cooperative probe.  A lane owns one key; the four lanes of a quad visit the quad's four buckets one after another, and a
+// lane reads two keys of the bucket (16 bytes) and their two meta words: a bucket line (eight keys, eight meta words) is two
+// 64-byte accesses side by side, and the lane that finds the key has its row and stamp at hand.  The eight loads of a lane
+// are independent and in flight together.
+// Called by whole waves.  The bucket is looked at where `want`; found: the row, and kProbeFound | the slot, with
+// kProbeStamp if its last-seen step is not `step`; else 0.
+constexpr uint32_t kProbeStamp = 8, kProbeFound = 16;
+struct ProbePiece {
+  uint64_t key[2];
+  uint32_t row[2], seen[2];
+};
+template <int R>
+__device__ inline void probe_load(const TableView& t, uint32_t bucket, uint32_t q, ProbePiece& d) {
+  const uint32_t b = quad_lane<R>(bucket);
+  if (b != kNoRow) {
+    const ulonglong2* line = reinterpret_cast<const ulonglong2*>(t.buckets + b);
+    const ulonglong2 key = line[q];
+    const uint4 meta = reinterpret_cast<const uint4*>(line)[4 + q];
+    d.key[0] = key.x;
+    d.key[1] = key.y;
+    d.row[0] = meta.x;
+    d.seen[0] = meta.y;
+    d.row[1] = meta.z;
+    d.seen[1] = meta.w;
   }
-#pragma unroll
-  for (int r = 0; r < kBucket; ++r) {
-    const int src = (int)gbase + r;
-    const int need = __shfl((int)want, src);
-    const uint64_t kr = __shfl(k, src);
-    const bool is_key_lane = gi < 4;
-    const uint64_t m0 = __ballot(need && is_key_lane && d[r].x == kr);
-    const uint64_t m1 = __ballot(need && is_key_lane && d[r].y == kr);
-    const uint32_t g0 = (uint32_t)(m0 >> gbase) & 0xFu, g1 = (uint32_t)(m1 >> gbase) & 0xFu;
-    const int s = g0 ? 2 * (__ffs((int)g0) - 1) : (g1 ? 2 * (__ffs((int)g1) - 1) + 1 : -1);
-    const int ml = (int)gbase + 4 + ((s < 0 ? 0 : s) >> 1);
-    const unsigned long long mx = __shfl(d[r].x, ml), my = __shfl(d[r].y, ml);
-    if ((int)gi == r && s >= 0) {
-      *meta_out = (s & 1) ? my : mx;
-      *slot_out = s;
-    }
-  }
+}
+template <int R>
+__device__ inline void probe_match(uint64_t k, uint32_t q, uint32_t step, const ProbePiece& d, uint32_t& row, uint32_t& found) {
+  const uint64_t kr = (uint64_t)quad_lane<R>((uint32_t)(k >> 32)) << 32 | quad_lane<R>((uint32_t)k);
+  const bool hit0 = d.key[0] == kr, hit1 = d.key[1] == kr;
+  row = hit0 ? d.row[0] : (hit1 ? d.row[1] : 0u);
+  const uint32_t seen = hit0 ? d.seen[0] : d.seen[1];
+  const uint32_t code = (kProbeFound | 2 * q) + (hit1 ? 1u : 0u) + (seen != step ? kProbeStamp : 0u);
+  found |= (hit0 || hit1 ? code : 0u) << (8 * R);
+}
+__device__ inline uint32_t probe_bucket(const TableView& t, uint64_t k, uint64_t bucket, bool want, uint32_t step,
+                                        uint32_t* row_out) {
+  const uint32_t lane = lane_id(), q = lane & 3u, b = want ? (uint32_t)bucket : kNoRow;  // (buckets: at most 2^28)
+  ProbePiece d[4] = {};
+  probe_load<0>(t, b, q, d[0]);
+  probe_load<1>(t, b, q, d[1]);
+  probe_load<2>(t, b, q, d[2]);
+  probe_load<3>(t, b, q, d[3]);
+  uint32_t row[4], found = 0;
+  probe_match<0>(k, q, step, d[0], row[0], found);
+  probe_match<1>(k, q, step, d[1], row[1], found);
+  probe_match<2>(k, q, step, d[2], row[2], found);
+  probe_match<3>(k, q, step, d[3], row[3], found);
+  // at most one lane of the quad has found key r: lane r takes the words that the four have for it, together
+  found |= quad_xor<1>(found);
+  found |= quad_xor<2>(found);
+  const bool odd = q & 1u, high = q & 2u;
+  const uint32_t low01 = (odd ? row[1] : row[0]) | quad_xor<1>(odd ? row[0] : row[1]);
+  const uint32_t low23 = (odd ? row[3] : row[2]) | quad_xor<1>(odd ? row[2] : row[3]);
+  *row_out = (high ? low23 : low01) | quad_xor<2>(high ? low01 : low23);
+  return want ? (found >> (8 * q)) & 0xFFu : 0u;
 }
 
 // Threads (= keys of a turn) per block of probe_count.  The block's missing keys are gathered in an LDS set with
@@ -99,7 +133,6 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
     miss_cnt[s] = 0;
   }
   __syncthreads();  // the LDS set is cleared
-  const uint32_t lane = lane_id(), gi = lane & 7u, gbase = lane & ~7u;
   bool sparse = false;  // (tables with expiry) less than a quarter full: the occupancy bitmap is worth a look
   if (t.expire_steps != 0) {
     const int32_t free_n = t.ctl->free_n;
@@ -133,24 +166,28 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
       look0 = (t.occupied[b0 >> 6] >> (b0 & 63)) & 1ull;
       look1 = (t.occupied[b1 >> 6] >> (b1 & 63)) & 1ull;
     }
-    unsigned long long m = kNoMeta;
-    int slot = -1;
+    uint32_t row = 0, found = 0;
     uint64_t where = b0;
     if (__ballot(look0))  // wave-uniform
-      probe_side(t, k, b0, look0, gi, gbase, &m, &slot);
-    const bool again = look1 && slot < 0;
+      found = probe_bucket(t, k, b0, look0, step, &row);
+    const bool again = look1 && found == 0;
     if (__ballot(again)) {  // wave-uniform
-      probe_side(t, k, b1, again, gi, gbase, &m, &slot);
-      if (again) where = b1;
+      uint32_t row1;
+      const uint32_t found1 = probe_bucket(t, k, b1, again, step, &row1);
+      if (again) {
+        where = b1;
+        row = row1;
+        found = found1;
+      }
     }
     bool miss = false;
     if (i < n) {
       if (!live) {
         rows_out[i] = kRowAbsent;
-      } else if (slot >= 0) {
-        rows_out[i] = restore ? kRowAbsent : (int32_t)meta_row(m);
-        if (!restore && meta_seen(m) != step)
-          reinterpret_cast<uint32_t*>(&t.buckets[where].meta[slot])[1] = step;  // stamp
+      } else if (found) {
+        rows_out[i] = restore ? kRowAbsent : (int32_t)row;
+        if (!restore && (found & kProbeStamp))
+          reinterpret_cast<uint32_t*>(&t.buckets[where].meta[found & (kBucket - 1)])[1] = step;  // stamp
       } else {
         miss = true;
         const uint32_t sn = t.ctl->stash_n;
