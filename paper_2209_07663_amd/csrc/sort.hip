@@ -221,7 +221,7 @@ __global__ __launch_bounds__(1 << kBits) void sort_scatter_kernel(Control* __res
   const uint64_t unit = ((uint64_t)(turn / kSortChunk) * 8 + blockIdx.x % 8) * kSortChunk + turn % kSortChunk;
   if (unit * kItems >= n) return;  // (the grid is a whole number of chunks)
   const uint32_t last_bag = (uint32_t)(n_bags - 1);
-  const uint32_t shift = plan.shift(pass), bits = plan.width(pass), nbins = 1u << bits, mask = nbins - 1;
+  const uint32_t shift = plan.shift(pass), nbins = 1u << plan.width(pass), mask = nbins - 1;
 
   // 0. what step 3 needs from memory is asked for first: it arrives while the elements are loaded
   const uint32_t bin = threadIdx.x;  // the thread's bin
@@ -279,10 +279,11 @@ __global__ __launch_bounds__(1 << kBits) void sort_scatter_kernel(Control* __res
     for (uint32_t r = 0; r < S::kRounds; ++r) {
       const bool valid = kv[r].x != 0xFFFFFFFFu;
       const uint32_t digit = (kv[r].x >> shift) & mask;
-      const uint64_t peers = same_digit_lanes<kBits>(digit, bits, valid);
-      rank[r] = (digit << 16) | (wave_load(off + digit) + (uint32_t)__popcll(peers & lanes_below()));
+      const uint64_t peers = same_digit_lanes<kBits>(digit, valid);
+      const uint32_t before = lanes_before(peers);
+      rank[r] = (digit << 16) | (wave_load(off + digit) + before);
       wave_order();
-      if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, (rank[r] & 0xFFFFu) + (uint32_t)__popcll(peers));
+      if (valid && before == 0) wave_store(off + digit, (rank[r] & 0xFFFFu) + (uint32_t)__popcll(peers));
       wave_order();
     }
   }
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
   uint32_t count = n;  // elements that the pass reads: all occurrences, then the pairs that remain
 #pragma unroll 1
   for (uint32_t pass = 0; pass < plan.passes; ++pass) {
-    const uint32_t shift = plan.shift(pass), bits = plan.width(pass), mask = (1u << bits) - 1;
+    const uint32_t shift = plan.shift(pass), mask = (1u << plan.width(pass)) - 1;
     if (pass > 0) {
 #pragma unroll
       for (uint32_t r = 0; r < kSmallRounds; ++r)
@@ -445,10 +446,11 @@ __global__ __launch_bounds__(kSmallBlock) void sort_small_kernel(Control* __rest
       if (r < rounds) {  // block-uniform
         const bool valid = kv[r].x != 0xFFFFFFFFu;
         const uint32_t digit = (kv[r].x >> shift) & mask;
-        const uint64_t peers = same_digit_lanes<kSortNarrowBits>(digit, bits, valid);
-        rank[r] = (digit << 16) | (wave_load(off + digit) + (uint32_t)__popcll(peers & lanes_below()));
+        const uint64_t peers = same_digit_lanes<kSortNarrowBits>(digit, valid);
+        const uint32_t before = lanes_before(peers);
+        rank[r] = (digit << 16) | (wave_load(off + digit) + before);
         wave_order();
-        if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, (rank[r] & 0xFFFFu) + (uint32_t)__popcll(peers));
+        if (valid && before == 0) wave_store(off + digit, (rank[r] & 0xFFFFu) + (uint32_t)__popcll(peers));
         wave_order();
       }
     }

@@ -224,16 +224,16 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
     }
   }
   {
-    const uint32_t bits = 32 - __clz(bins);
     uint16_t* off = cnt[wave];
 #pragma unroll
     for (uint32_t r = 0; r < kRounds; ++r) {
       const bool valid = kv[r].x != kNoSplitRow;
       const uint32_t bin = rank[r];
-      const uint64_t peers = same_digit_lanes<kDigit>(bin, bits, valid);
-      rank[r] = (bin << 16) | (wave_load(off + bin) + (uint32_t)__popcll(peers & lanes_below()));
+      const uint64_t peers = same_digit_lanes<kDigit>(bin, valid);
+      const uint32_t before = lanes_before(peers);
+      rank[r] = (bin << 16) | (wave_load(off + bin) + before);
       wave_order();
-      if (valid && (peers & lanes_below()) == 0) wave_store(off + bin, (uint16_t)(rank[r] + (uint32_t)__popcll(peers)));
+      if (valid && before == 0) wave_store(off + bin, (uint16_t)(rank[r] + (uint32_t)__popcll(peers)));
       wave_order();
     }
   }
@@ -440,11 +440,11 @@ __device__ inline const T* sort_bucket(BucketLds<kBlock>& s, T* first, T* second
       const bool valid = i0 + lane < end;
       const T e = valid ? from[i0 + lane] : T{};
       const uint32_t digit = (sort_key(e) >> shift) & mask;
-      const uint64_t peers = same_digit_lanes<kBucketDigit>(digit, width, valid);
-      const uint32_t at = wave_load(off + digit);
-      if (valid) to[at + (uint32_t)__popcll(peers & lanes_below())] = e;
+      const uint64_t peers = same_digit_lanes<kBucketDigit>(digit, valid);
+      const uint32_t at = wave_load(off + digit), before = lanes_before(peers);
+      if (valid) to[at + before] = e;
       wave_order();
-      if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
+      if (valid && before == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
       wave_order();
     }
     __syncthreads();
