@@ -51,7 +51,7 @@ constexpr int kMissTag = 7;                 // Control::scratch slots: tag of th
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
 constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
-constexpr int kInsertDone = 14;             // Control::scratch slot: sub-lists whose blocks of the insertion are done (zero between calls)
+constexpr int kFreeBefore = 14;             // Control::scratch slot: rows that were free when the running call began
 constexpr int kHotBins = 13;                // Control::scratch slot: rows with a bin of their own (see sort_split.hip)
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists, or blocks, that are done; of sweep_small also the keys
                                             // removed so far << 32 (zero between calls)
@@ -98,8 +98,7 @@ struct TableView {
   StashEntry* stash;         // [kStashCap]
   unsigned long long* dset;  // [dset_size] per-call dedup set: epoch << 32 | occurrence index
   Winner* win_list;          // [kWinLists * win_cap] elected occurrences
-  uint32_t* win_cnt;         // [kWinLists * kWinStride] fill of each sub-list, and in the word beside it the blocks that are
-                             // done with the insertion (all zero between calls)
+  uint32_t* win_cnt;         // [kWinLists * kWinStride] fill of each sub-list (the call's first kernel clears them)
   uint64_t win_cap;
   // (tables with expiry) per bucket, for the sweep: a lower bound of the last-seen steps of its keys, in units of
   // 1 << sweep_q steps (see sweep_unit); kAgeEmpty: the bucket holds nothing; kAgeLook: nothing is known.

@@ -72,14 +72,19 @@ __device__ inline void probe_match(uint64_t k, uint32_t q, uint32_t step, const 
   const uint32_t code = (kProbeFound | 2 * q) + (hit1 ? 1u : 0u) + (seen != step ? kProbeStamp : 0u);
   found |= (hit0 || hit1 ? code : 0u) << (8 * R);
 }
-__device__ inline uint32_t probe_bucket(const TableView& t, uint64_t k, uint64_t bucket, bool want, uint32_t step,
-                                        uint32_t* row_out) {
-  const uint32_t lane = lane_id(), q = lane & 3u, b = want ? (uint32_t)bucket : kNoRow;  // (buckets: at most 2^28)
+struct QuadBuckets {
   ProbePiece d[4] = {};
-  probe_load<0>(t, b, q, d[0]);
-  probe_load<1>(t, b, q, d[1]);
-  probe_load<2>(t, b, q, d[2]);
-  probe_load<3>(t, b, q, d[3]);
+};
+__device__ inline void probe_ask(const TableView& t, uint64_t bucket, bool want, QuadBuckets& x) {
+  const uint32_t q = lane_id() & 3u, b = want ? (uint32_t)bucket : kNoRow;  // (buckets: at most 2^28)
+  probe_load<0>(t, b, q, x.d[0]);
+  probe_load<1>(t, b, q, x.d[1]);
+  probe_load<2>(t, b, q, x.d[2]);
+  probe_load<3>(t, b, q, x.d[3]);
+}
+__device__ inline uint32_t probe_find(uint64_t k, bool want, uint32_t step, const QuadBuckets& x, uint32_t* row_out) {
+  const uint32_t q = lane_id() & 3u;
+  const ProbePiece(&d)[4] = x.d;
   uint32_t row[4], found = 0;
   probe_match<0>(k, q, step, d[0], row[0], found);
   probe_match<1>(k, q, step, d[1], row[1], found);
@@ -110,12 +115,20 @@ __device__ inline uint32_t probe_bucket(const TableView& t, uint64_t k, uint64_t
 //   keys are hot, 228 us now, 272 with sixteen turns; 372 -> 349 us, 325 with sixteen, where the hot set drifts.)
 constexpr int kProbeBlock = 256;
 constexpr uint64_t kProbeBlocksWanted = 1024, kProbeMaxTurns = 8;
+// Largest batch for which both buckets and the counter are asked for at once.  lookup_or_insert of uniform keys in a table of
+// 2^24 slots, one access after the other and at once, us: a third unknown and kept out, counters that age 20 K 15.1 / 11.8, 60 K
+// 16.3 / 14.4, 120 K 18.2 / 20.3, that do not 60 K 16.4 / 14.4, 120 K 19.2 / 18.4, 200 K 25.0 / 26.1; all known 20 K 8.8 / 9.0,
+// 60 K 12.5 / 13.0, 120 K 14.0 / 15.9, 200 K 16.2 / 22.4.
+constexpr uint64_t kProbeSmall = 1u << 16;
+static_assert(kProbeSmall < 2 * kProbeBlock * kProbeBlocksWanted, "a key per thread");
 constexpr int kProbeTries = 8;  // slots of the set that a missing key looks at
 
 // restore != 0: the keys are snapshot records; a stored key is marked absent (its record is refused)
 // and nothing is stamped or counted.
 // A block owns kProbeBlock * turns consecutive keys and takes them in turns of one key per thread.
-template <bool kManyTurns>
+// kSmall (batches of at most kProbeSmall): the kernel is a chain of dependent accesses and has no bandwidth to save, so that
+// both buckets, and the counter of a key that turns out to miss, are asked for at once.
+template <bool kManyTurns, bool kSmall>
 __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, const int64_t* __restrict__ keys,
                                                                   uint64_t n, uint32_t step,
                                                                   int32_t* __restrict__ rows_out, int restore,
@@ -127,6 +140,16 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   __shared__ int any_miss;
   // Are counters worth a look before the buckets?  (Counters that age prove nothing; see MissSample.)
   const bool counters_first = t.expire_steps == 0 && !restore && t.ctl->scratch[kCountersFirst] != 0;
+  static_assert(!(kSmall && kManyTurns), "a small batch has a key per thread");
+  const uint64_t at = (uint64_t)blockIdx.x * kProbeBlock + threadIdx.x;
+  // (kSmall) the thread's key, the place in the set that it was the first to take, or none, and its counter as it was before
+  const uint64_t first_key = kSmall && at < n ? (uint64_t)keys[at] : kEmptyKey;
+  uint32_t first_at = kMissSlots;
+  unsigned long long first_guess = 0;
+  if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // for the election and the insertion
+    t.win_cnt[threadIdx.x * kWinStride] = 0;
+    if (threadIdx.x == 0) t.ctl->scratch[kFreeBefore] = (unsigned long long)(uint32_t)t.ctl->free_n;
+  }
   if (threadIdx.x == 0) any_miss = 0;
   for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock) {
     miss_key[s] = kEmptyKey;
@@ -141,7 +164,7 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
 #pragma unroll 1
   for (uint32_t turn = 0; turn < turns; ++turn) {
     const uint64_t i = ((uint64_t)blockIdx.x * turns + turn) * kProbeBlock + threadIdx.x;
-    const uint64_t k = i < n ? (uint64_t)keys[i] : kEmptyKey;
+    const uint64_t k = kSmall ? first_key : (i < n ? (uint64_t)keys[i] : kEmptyKey);
     const bool live = k != kEmptyKey;
     // Negative lookup through the admission counters.  When nothing ages (expire_steps == 0) a
     // counter never decreases, and a stored key reached freq_threshold on its counter when it was
@@ -168,12 +191,23 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
     }
     uint32_t row = 0, found = 0;
     uint64_t where = b0;
-    if (__ballot(look0))  // wave-uniform
-      found = probe_bucket(t, k, b0, look0, step, &row);
+    QuadBuckets side1;
+    if (kSmall) {
+      QuadBuckets side0;
+      probe_ask(t, b0, look0, side0);
+      probe_ask(t, b1, look1, side1);
+      if (t.expire_steps != 0 && live && !restore) first_guess = t.filter[filter_index(t, k)];
+      found = probe_find(k, look0, step, side0, &row);
+    } else if (__ballot(look0)) {  // wave-uniform
+      QuadBuckets side0;
+      probe_ask(t, b0, look0, side0);
+      found = probe_find(k, look0, step, side0, &row);
+    }
     const bool again = look1 && found == 0;
     if (__ballot(again)) {  // wave-uniform
       uint32_t row1;
-      const uint32_t found1 = probe_bucket(t, k, b1, again, step, &row1);
+      if (!kSmall) probe_ask(t, b1, again, side1);
+      const uint32_t found1 = probe_find(k, again, step, side1, &row1);
       if (again) {
         where = b1;
         row = row1;
@@ -209,6 +243,7 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
       int tries = 0;
       for (; tries < kProbeTries; ++tries) {
         const unsigned long long old = atomicCAS(&miss_key[pos], (unsigned long long)kEmptyKey, (unsigned long long)k);
+        if (kSmall && old == kEmptyKey) first_at = pos;
         if (old == kEmptyKey || old == k) break;
         pos = (pos + 1) & (kMissSlots - 1);
       }
@@ -223,6 +258,10 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   // 1.5 ms)
   if (threadIdx.x == 0 && any_miss) t.ctl->scratch[kMissTag] = epoch;
   if (restore || !any_miss) return;  // block-uniform
+  if (kSmall) {
+    if (first_at != kMissSlots) touch_counter(t, first_key, step, miss_cnt[first_at], &first_guess);
+    return;
+  }
   for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock)
     if (miss_cnt[s]) touch_counter(t, miss_key[s], step, miss_cnt[s]);
 }
@@ -257,10 +296,12 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   for (int j = 0; j < kPer; ++j) {
     const uint64_t i = i0 + (uint64_t)j * kElectBlock;
     miss[j] = i < n && rows_out[i] == kRowMiss;
+    if (kPer == 1) k[j] = i < n ? (uint64_t)keys[i] : kEmptyKey;  // (side by side with its word: latency is all that counts)
   }
   for (int s = threadIdx.x; s < kElectSlots; s += kElectBlock) s_key[s] = kEmptyKey;
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) k[j] = miss[j] ? (uint64_t)keys[i0 + (uint64_t)j * kElectBlock] : kEmptyKey;
+  for (int j = 0; j < kPer; ++j)
+    if (kPer > 1) k[j] = miss[j] ? (uint64_t)keys[i0 + (uint64_t)j * kElectBlock] : kEmptyKey;
   if (kPer > 1) {
     __syncthreads();
   } else if (!__syncthreads_or(miss[0])) {
@@ -284,9 +325,13 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   }
   // A snapshot record is admitted whatever its counter says, and with a threshold of 0 or 1 every
   // missing key is admissible (its count is at least 1 by now): no counter is read for either.
+  // (Small batches ask for the key's position in the dedup set beside its counters.)
   bool admissible[kPer];
+  unsigned long long e[kPer], old[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
+    e[j] = 0;
+    if (kPer == 1 && leader[j]) e[j] = ld_agent(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask]);
     uint32_t cnt = leader[j] ? 255u : 0u;
     if (!restore && leader[j] && t.freq_threshold > 1u) {
       for (uint32_t h = 0; h < t.filter_hashes; ++h) {  // smallest of the key's counters
@@ -298,11 +343,9 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   }
   // one occurrence per distinct key wins its position of the per-call dedup set: a first look and a first exchange
   // for all of the thread's leaders together, then whatever is left to do for each
-  unsigned long long e[kPer], old[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    e[j] = 0;
-    if (admissible[j]) e[j] = ld_agent(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask]);
+    if (kPer > 1 && admissible[j]) e[j] = ld_agent(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask]);
   }
   const unsigned long long tag = (unsigned long long)epoch << 32;
 #pragma unroll
@@ -354,7 +397,7 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     }
     missed += (uint32_t)__popcll(__ballot(kPer > 1 ? miss[j] : found == kRowAbsent));
   }
-  if (__ballot(duplicate) && lane_id() == 0) t.ctl->scratch[kDuplicateTag] = epoch;
+  if (kPer > 1 && __ballot(duplicate) && lane_id() == 0) t.ctl->scratch[kDuplicateTag] = epoch;
   // block-aggregated append to sub-list (blockIdx mod kWinLists)
   const uint32_t wave = threadIdx.x >> 6;
   uint32_t mine = 0;
@@ -399,7 +442,9 @@ __device__ inline void note_sample(const TableView& t, uint64_t enough) {
 // kAll (batches of at most kElectSmall): the duplicates of admitted keys take their rows here too.  The elected
 // occurrence's word in rows_out tells its place in its sub-list until it holds the row (stored and read at agent scope: its
 // block and the duplicates' run together), and the number of a winner follows from its place, so that nobody waits for
-// anybody; the block that finishes last settles the counters.  A kernel of its own for that is a launch more, 3 us of a
+// anybody.  Nor does the thread that settles the counters: all others know the free rows from kFreeBefore.  The kernel is a
+// chain of dependent accesses, and with the duplicates after the insertion, in a pass of their own, and a block that
+// finishes last and settles, it was one of ten.  A kernel of its own for duplicates and counters is a launch more, 3 us of a
 // call that has no miss (steps of 5 to 200 K known IDs 23 -> 19, 30 -> 28, 64 -> 60 us).  Large batches have it: the
 // winners' places are a write more per new key (6.8 M IDs, a million new: election and
 // insertion 276 us, with resolve_kernel 267).
@@ -411,10 +456,15 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   // (The list has room for all the keys of four rounds, after which it is worked off.)
   constexpr uint32_t kListRounds = 4, kLeastSpan = 8;
   __shared__ unsigned long long s_key[256 * kListRounds], s_meta[256 * kListRounds];
-  __shared__ uint32_t s_waiting, s_last;
+  __shared__ uint32_t s_waiting;
   if (threadIdx.x == 0) s_waiting = 0;
   __syncthreads();
   const uint32_t lane = lane_id();
+  // (kAll) an occurrence for every thread, at the end of the grid where the others have elected ones (the launch has a thread
+  // for every occurrence at least).  What is left of an earlier state of the word does no harm here.
+  const uint64_t i = (uint64_t)(gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x;
+  int32_t mine = kRowAbsent;
+  if (kAll && i < n) mine = rows_out[i];
   const uint32_t unit = src.seen ? kAgeLook : sweep_unit(step, t.sweep_q);
   // inclusive prefix of the sub-list fills, one list per lane
   const uint32_t inc = wave_sums(t.win_cnt[lane * kWinStride]), total = __shfl(inc, 63);
@@ -425,11 +475,30 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
     }
     return;
   }
-  const int32_t free0 = t.ctl->free_n;  // settled when all blocks are done, constant until then
-  const uint32_t hwm0 = t.ctl->hwm;
+  const int32_t free0 = (int32_t)(uint32_t)t.ctl->scratch[kFreeBefore];
+  if (kAll && blockIdx.x == 0 && threadIdx.x == 0) {
+    settle_call(t, total, free0, t.ctl->hwm, epoch);
+    note_sample(t, enough);
+  }
   // all of the call's new keys fit under the fill limit, or none of them is placed
   const bool room = (int64_t)total <= rows_on_offer(t.capacity, free0);
-  const uint32_t stride = gridDim.x * blockDim.x;
+  if constexpr (kAll) {
+    const bool duplicate = mine <= -3 && mine > kRowElected;
+    if (__ballot(duplicate)) {
+      const uint64_t owner = duplicate ? (uint64_t)(-(int64_t)mine - 3) : 0;
+      const int32_t o = duplicate ? ld_agent(&rows_out[owner]) : kRowAbsent;
+      const uint32_t list = (uint32_t)(owner / kElectBlock) & (kWinLists - 1);  // (a block of the election appends to one)
+      const uint32_t before = __shfl(inc, (int)(list > 0 ? list - 1 : 0));
+      if (duplicate) {
+        int32_t row = o;  // the row, or kRowAbsent, if the elected occurrence has it by now
+        if (o <= kRowElected) {
+          const uint32_t w = (list > 0 ? before : 0u) + (uint32_t)(kRowElected - o);
+          row = room ? (int32_t)t.free_rows[free0 - 1 - (int32_t)w] : kRowAbsent;
+        }
+        rows_out[i] = row;
+      }
+    }
+  }
   // How many winners a wave takes at a time: fewer than 64 where that would leave waves without any.  A new row's values
   // are hashes, 130 cycles of a wave for 64 of them, so that 64 rows of dim 128 hold one wave for 10 us while others have
   // none.  Training steps with 64 throughout and with this: 4.3 K IDs, most new, dim 128 79 -> 62 us; 26 K of dim 64
@@ -493,45 +562,6 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
       round = 0;
     }
   }
-  if constexpr (!kAll) return;
-  if (t.ctl->scratch[kDuplicateTag] == epoch) {  // (else every missing key of the call occurred once, or was not admitted)
-    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ((n + 63) & ~63ull); i += stride) {  // wave-uniform
-      const int32_t v = i < n ? ld_agent(&rows_out[i]) : kRowAbsent;
-      const bool duplicate = v <= -3 && v > kRowElected;
-      if (!__ballot(duplicate)) continue;
-      const uint64_t owner = duplicate ? (uint64_t)(-(int64_t)v - 3) : 0;
-      const int32_t o = duplicate ? ld_agent(&rows_out[owner]) : kRowAbsent;
-      const uint32_t list = (uint32_t)(owner / kElectBlock) & (kWinLists - 1);  // (a block of the election appends to one)
-      const uint32_t before = __shfl(inc, (int)(list > 0 ? list - 1 : 0));
-      if (duplicate) {
-        int32_t row = o;  // the row, or kRowAbsent, if the elected occurrence has it by now
-        if (o <= kRowElected) {
-          const uint32_t w = (list > 0 ? before : 0u) + (uint32_t)(kRowElected - o);
-          row = room ? (int32_t)t.free_rows[free0 - 1 - (int32_t)w] : kRowAbsent;
-        }
-        rows_out[i] = row;
-      }
-    }
-  }
-  // (Many blocks count themselves on the lists' 64 lines first, and the last of each line on one word: one word alone would
-  // serialise thousands of them at ~12 ns each.)
-  constexpr uint32_t kCountedAtOnce = 128;
-  __syncthreads();  // every wave has read the counters
-  if (threadIdx.x == 0) {
-    const uint32_t lines = gridDim.x <= kCountedAtOnce ? 1u : kWinLists, line = blockIdx.x & (lines - 1);
-    const uint32_t blocks = (gridDim.x - line + lines - 1) / lines;  // that count themselves here
-    s_last = atomicAdd(&t.win_cnt[line * kWinStride + 1], 1u) == blocks - 1 &&
-             (lines == 1 || atomicAdd(&t.ctl->scratch[kInsertDone], 1ull) == (unsigned long long)lines - 1);
-  }
-  __syncthreads();
-  if (!s_last || threadIdx.x >= kWinLists) return;
-  t.win_cnt[lane * kWinStride] = 0;
-  t.win_cnt[lane * kWinStride + 1] = 0;
-  if (threadIdx.x == 0) {
-    t.ctl->scratch[kInsertDone] = 0;
-    settle_call(t, total, free0, hwm0, epoch);
-    note_sample(t, enough);
-  }
 }
 
 // (large batches) Duplicates of admitted keys, and what insert_kernel settles for the others.
@@ -546,7 +576,6 @@ __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, i
   }
   if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // (the insert kernel has finished)
     const uint32_t total = __shfl(wave_sums(t.win_cnt[threadIdx.x * kWinStride]), 63);
-    t.win_cnt[threadIdx.x * kWinStride] = 0;
     if (threadIdx.x == 0) {
       settle_call(t, total, t.ctl->free_n, t.ctl->hwm, epoch);
       note_sample(t, enough);
@@ -569,17 +598,22 @@ hipError_t launch_lookup_or_insert(const TableView& t, const int64_t* d_keys, ui
   const dim3 block(256), grid((unsigned)((n + 255) / 256));
   // (insertion: a wave for 16 IDs, all of which may be new; see insert_kernel's span)
   const uint64_t iblocks = (n + 63) / 64;
-  const dim3 igrid((unsigned)(iblocks < 2048 ? iblocks : 2048));
+  constexpr uint64_t kInsertBlocks = 2048;
+  static_assert(kInsertBlocks * 256 >= kElectSmall, "a thread for every occurrence of a batch that has no resolve_kernel");
+  const dim3 igrid((unsigned)(iblocks < kInsertBlocks ? iblocks : kInsertBlocks));
   {
     uint64_t turns = t.expire_steps == 0 ? 1 : n / ((uint64_t)kProbeBlock * kProbeBlocksWanted);
     turns = turns < 1 ? 1 : (turns > kProbeMaxTurns ? kProbeMaxTurns : turns);
     const uint64_t per_block = (uint64_t)kProbeBlock * turns;
     const dim3 pgrid((unsigned)((n + per_block - 1) / per_block));
-    if (turns == 1)
-      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, probe_count_kernel<false>, pgrid, dim3(kProbeBlock), t, d_keys, n, step,
+    if (n <= kProbeSmall)
+      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, (probe_count_kernel<false, true>), pgrid, dim3(kProbeBlock), t, d_keys, n, step,
+                  d_rows_out, restore, 1u, epoch);
+    else if (turns == 1)
+      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, (probe_count_kernel<false, false>), pgrid, dim3(kProbeBlock), t, d_keys, n, step,
                   d_rows_out, restore, 1u, epoch);
     else
-      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, probe_count_kernel<true>, pgrid, dim3(kProbeBlock), t, d_keys, n, step,
+      MONO_LAUNCH(prof, K_PROBE_COUNT, stream, (probe_count_kernel<true, false>), pgrid, dim3(kProbeBlock), t, d_keys, n, step,
                   d_rows_out, restore, (uint32_t)turns, epoch);
   }
   const uint64_t elect_per_block = n <= kElectSmall ? kElectBlock : 4 * kElectBlock;

@@ -20,8 +20,10 @@ namespace mono {
 // Counts are kept unsaturated in the low half of a counter word and read as min(count, 255).  Where
 // counters age, the first touch of a batch cuts the count back to 255; where they do not, the host has all counts cut
 // back (launch_filter_cut) before they could have taken more than kCountMost occurrences since the last time.
-// one counter word: `times` occurrences at `step`
-__device__ inline void touch_word(const TableView& t, unsigned long long* w, uint32_t step, uint32_t times) {
+// one counter word: `times` occurrences at `step`; `guess`: what it held a moment ago, if the caller has looked (an ordinary
+// load will do, the exchange tells whether it still holds that)
+__device__ inline void touch_word(const TableView& t, unsigned long long* w, uint32_t step, uint32_t times,
+                                  const unsigned long long* guess) {
   if (t.expire_steps == 0) {
     // nothing ever ages: the stamp only moves forward and the count only grows, so two atomics
     // whose results nobody waits for do it (low half = count, high half = last step)
@@ -30,7 +32,7 @@ __device__ inline void touch_word(const TableView& t, unsigned long long* w, uin
     atomicAdd(half, times);
     return;
   }
-  unsigned long long cur = ld_agent(w);
+  unsigned long long cur = guess ? *guess : ld_agent(w);
   for (;;) {
     if ((uint32_t)(cur >> 32) == step) {  // already touched in this batch: increments only
       atomicAdd(w, (unsigned long long)times);  // unsaturated; read as min(count, 255)
@@ -49,8 +51,10 @@ __device__ inline void touch_word(const TableView& t, unsigned long long* w, uin
 
 // every counter of the key (section 2.1's probabilistic filter read as a counting filter with
 // filter_hashes hashes; two hashes of a key that fall on one counter touch it twice, as the oracle does)
-__device__ inline void touch_counter(const TableView& t, uint64_t key, uint32_t step, uint32_t times) {
-  for (uint32_t j = 0; j < t.filter_hashes; ++j) touch_word(t, &t.filter[filter_index(t, key, j)], step, times);
+__device__ inline void touch_counter(const TableView& t, uint64_t key, uint32_t step, uint32_t times,
+                                     const unsigned long long* first_guess = nullptr) {
+  for (uint32_t j = 0; j < t.filter_hashes; ++j)
+    touch_word(t, &t.filter[filter_index(t, key, j)], step, times, j == 0 ? first_guess : nullptr);
 }
 
 __device__ inline void wait_all_memory_ops() {
