@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace mono {
 
 constexpr uint64_t kEmptyKey = ~0ull;       // reserved key: padding / free slot
@@ -244,6 +246,61 @@ __device__ inline uint32_t wave_sums(uint32_t x) {
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);  // last lane of the row before, rows 1 and 3
   x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);  // last lane of row 1, rows 2 and 3
+  return x;
+}
+// Inclusive maximum, the same way.
+__device__ inline uint32_t wave_maxima(uint32_t x) {
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));
+  return x;
+}
+// The value of one lane, the same for the whole wave, in all of them.
+__device__ inline uint32_t lane_value(uint32_t x, uint32_t lane) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, (int)lane);
+}
+
+// Element w of all sub-lists, one after the other: the list it is in, and how many elements come before that list.  inc: the
+// lists' inclusive prefix sums, one per lane; first: the smallest w of the wave (the same for all its lanes).  Called by whole
+// waves whose w, of the valid lanes, are neighbours: they are in one list or a few.
+__device__ inline uint32_t list_holding(uint32_t inc, uint32_t w, uint32_t first, bool valid, uint32_t* before) {
+  uint32_t list = (uint32_t)__popcll(__ballot(inc <= first));  // (no list is left behind the last element)
+  *before = list > 0 ? lane_value(inc, list - 1) : 0u;
+  uint32_t mine = list;
+  for (; list < 64; ++list) {
+    const uint32_t end = lane_value(inc, list);
+    const bool past = valid && w >= end;
+    if (!__ballot(past)) break;
+    if (past) {
+      mine = list + 1;
+      *before = end;
+    }
+  }
+  return mine;
+}
+
+// Sum over the lanes of a group of `group` (a power of two, the same for the whole wave), in all of them: moves between
+// registers again.  Whole groups call it.  (The partners of a step hold equal sums, so that a mirror image will do for the
+// lane whose number differs in one bit; of two copies of a register the swaps leave one with either half's.)
+__device__ inline float group_sum(float x, uint32_t group) {
+  const auto mate = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+  if (group > 1) x += mate(x, std::integral_constant<int, 0xB1>{});   // quad_perm 1,0,3,2
+  if (group > 2) x += mate(x, std::integral_constant<int, 0x4E>{});   // quad_perm 2,3,0,1
+  if (group > 4) x += mate(x, std::integral_constant<int, 0x141>{});  // row_half_mirror
+  if (group > 8) x += mate(x, std::integral_constant<int, 0x140>{});  // row_mirror
+  if (group > 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  if (group > 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
   return x;
 }
 

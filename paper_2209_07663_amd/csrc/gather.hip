@@ -187,10 +187,7 @@ __global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t
   // Short bags (one or two IDs each, as in one-hot slots): a round keeps only one or two rows per
   // lane in flight, so four rounds (two, where four IDs are in flight) are issued together instead.
   constexpr int kShort = 2, kRoundsTogether = kIds / kShort;
-  int longest = len;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) longest = max(longest, __shfl_xor(longest, d));
-  if (longest <= kShort && dim <= 64 * N) {  // wave-uniform
+  if (!__ballot(len > kShort) && dim <= 64 * N) {  // wave-uniform
     const bool active = l * N < dim;
     for (uint32_t q0 = 0; q0 < rounds; q0 += kRoundsTogether) {
       Row v[kRoundsTogether][kShort];

@@ -459,7 +459,7 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   __shared__ uint32_t s_waiting;
   if (threadIdx.x == 0) s_waiting = 0;
   __syncthreads();
-  const uint32_t lane = lane_id();
+  const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   // (kAll) an occurrence for every thread, at the end of the grid where the others have elected ones (the launch has a thread
   // for every occurrence at least).  What is left of an earlier state of the word does no harm here.
   const uint64_t i = (uint64_t)(gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x;
@@ -467,7 +467,7 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   if (kAll && i < n) mine = rows_out[i];
   const uint32_t unit = src.seen ? kAgeLook : sweep_unit(step, t.sweep_q);
   // inclusive prefix of the sub-list fills, one list per lane
-  const uint32_t inc = wave_sums(t.win_cnt[lane * kWinStride]), total = __shfl(inc, 63);
+  const uint32_t inc = wave_sums(t.win_cnt[lane * kWinStride]), total = lane_value(inc, 63);
   if (total == 0) {  // nothing to place or to settle (a duplicate needs an elected occurrence)
     if (kAll && blockIdx.x == 0 && threadIdx.x == 0) {
       if (t.hwm_mail && epoch % kPostEvery == 0) post_hwm(t, epoch, t.ctl->hwm);
@@ -507,24 +507,14 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   while (span > kLeastSpan && total <= gridDim.x * 2 * span) span >>= 1;
   uint32_t round = 0;
   for (uint32_t b0 = blockIdx.x * 4 * span; b0 < total; b0 += gridDim.x * 4 * span) {  // block-uniform
-    const uint32_t w = b0 + (threadIdx.x >> 6) * span + lane;
+    const uint32_t w = b0 + wave * span + lane;
     const bool valid = lane < span && w < total;
-    // sub-list of w: the first list whose inclusive prefix exceeds w
-    uint32_t lo = 0, hi = 64;
-#pragma unroll
-    for (int it = 0; it < 7; ++it) {  // 65 possible answers: seven halvings
-      const uint32_t mid = (lo + hi) >> 1 < 63u ? (lo + hi) >> 1 : 63u;
-      const uint32_t v = __shfl(inc, (int)mid);
-      if (lo < hi) {
-        if (v <= w) lo = mid + 1; else hi = mid;
-      }
-    }
-    const uint32_t before = __shfl(inc, (int)(lo > 0 ? lo - 1 : 0));
+    uint32_t before;
+    const uint32_t list = list_holding(inc, w, b0 + wave * span, valid, &before);
     uint64_t k = 0;
     uint32_t row = kNoRow, occ = 0;
     if (valid) {
-      const uint32_t p = w - (lo > 0 ? before : 0u);
-      const Winner e = t.win_list[(uint64_t)lo * t.win_cap + p];
+      const Winner e = t.win_list[(uint64_t)list * t.win_cap + (w - before)];
       occ = e.occ;
       k = e.key;
       if (room) row = t.free_rows[free0 - 1 - (int32_t)w];
@@ -575,7 +565,7 @@ __global__ __launch_bounds__(256) void resolve_kernel(TableView t, uint64_t n, i
     }
   }
   if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // (the insert kernel has finished)
-    const uint32_t total = __shfl(wave_sums(t.win_cnt[threadIdx.x * kWinStride]), 63);
+    const uint32_t total = lane_value(wave_sums(t.win_cnt[threadIdx.x * kWinStride]), 63);
     if (threadIdx.x == 0) {
       settle_call(t, total, t.ctl->free_n, t.ctl->hwm, epoch);
       note_sample(t, enough);

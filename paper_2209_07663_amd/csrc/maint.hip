@@ -94,7 +94,7 @@ __device__ inline uint32_t list_old_buckets(const uint32_t (&word)[kWords], cons
     wave_store(list + at++, (uint16_t)(lane_id() * (4 * kWords) + ((i >> 1) & 7u) * 4u + (i >> 4) * 2u + (i & 1u)));
   }
   wave_order();
-  return __shfl(inc, 63);
+  return lane_value(inc, 63);
 }
 
 // Looks at 8 * kSweepTurns buckets of the list, from e0 on, and writes their new bounds.  m: meta words; gone: the lanes whose
@@ -293,25 +293,16 @@ __global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, uint32_t
                                                            uint64_t max_expired, uint64_t* n_expired) {
   const uint32_t lane = lane_id();
   const uint32_t inc = wave_sums(t.sweep_cnt[lane * kWinStride]);
-  const uint32_t total = __shfl(inc, 63);
+  const uint32_t total = lane_value(inc, 63);
   const int32_t free0 = t.ctl->free_n;                     // settled by the last block, constant until then
   const unsigned long long out0 = t.ctl->scratch[kSweepRemoved];       // keys already reported from the stash
   const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t w0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); w0 < total; w0 += stride) {
+  for (uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * blockDim.x + (threadIdx.x & ~63u))); w0 < total; w0 += stride) {
     const uint32_t w = w0 + lane;
-    uint32_t lo = 0, hi = 64;
-#pragma unroll
-    for (int it = 0; it < 7; ++it) {  // 65 possible answers: seven halvings
-      const uint32_t mid = (lo + hi) >> 1 < 63u ? (lo + hi) >> 1 : 63u;
-      const uint32_t v = __shfl(inc, (int)mid);
-      if (lo < hi) {
-        if (v <= w) lo = mid + 1; else hi = mid;
-      }
-    }
-    const uint32_t before = __shfl(inc, (int)(lo > 0 ? lo - 1 : 0));
+    uint32_t before;
+    const uint32_t list = list_holding(inc, w, w0, w < total, &before);
     if (w < total) {
-      const uint32_t p = w - (lo > 0 ? before : 0u);
-      uint32_t g = t.sweep_list[(uint64_t)lo * t.sweep_cap + p];
+      uint32_t g = t.sweep_list[(uint64_t)list * t.sweep_cap + (w - before)];
       if (expired_keys) {
         Bucket* b = &t.buckets[g >> 3];
         const int l = (int)(g & 7);

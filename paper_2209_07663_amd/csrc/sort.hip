@@ -341,10 +341,8 @@ __global__ __launch_bounds__(1 << kBits) void sort_scatter_kernel(Control* __res
 #pragma unroll
     for (uint32_t r = 0; r < S::kRounds; ++r) {
       const uint32_t mark = bag_here[wave * S::kPerWave + r * 64 + lane];
-      const uint64_t upto = __ballot(mark != 0) & (lanes_below() | (1ull << lane));
-      const uint32_t v = __shfl(mark, upto ? 63 - (int)__clzll((long long)upto) : 0);
-      kv[r].y = upto ? v : carry;
-      carry = __shfl(kv[r].y, 63);
+      kv[r].y = max(wave_maxima(mark), carry);
+      carry = lane_value(kv[r].y, 63);
     }
     if (lane == 0) wave_last[wave] = carry;
     __syncthreads();

@@ -306,10 +306,8 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
 #pragma unroll
   for (uint32_t r = 0; r < kRounds; ++r) {
     const uint32_t mark = s.bag_here[wave * kPerWave + r * 64 + lane];
-    const uint64_t upto = __ballot(mark != 0) & (lanes_below() | (1ull << lane));
-    const uint32_t v = __shfl(mark, upto ? 63 - (int)__clzll((long long)upto) : 0);
-    kv[r].y = upto ? v : carry;
-    carry = __shfl(kv[r].y, 63);
+    kv[r].y = max(wave_maxima(mark), carry);
+    carry = lane_value(kv[r].y, 63);
   }
   if (lane == 0) wave_last[wave] = carry;
   __syncthreads();
