@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   const uint32_t unit = blockIdx.x, ubase = unit * kItems, uend = ubase + kItems < n ? ubase + kItems : n;
   const uint32_t base = ubase + wave * kPerWave;
 
-  // The bag that holds the unit's first occurrence: the last one whose offset is not behind it.  A thread looks at
+  // The bag that holds the unit's first occurrence, or one not far before it: the last one whose offset is not behind.  A thread looks at
   // one bag a step; the steps lie between the barriers of what else is to be done.  (Whatever the offsets hold, `lo`
   // stays below n_bags.)
   uint64_t lo = 0, hi = n_bags;
@@ -116,6 +116,9 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
     hi = lo + (k + 1) * step < hi ? lo + (k + 1) * step : hi;
     lo += k * step;
   };
+  // (The walk over the unit's bags may begin as many bags too early as the block has threads: those say that they begin at the
+  // unit's first occurrence, where the last of all that say so counts.)
+  const auto near = [&]() { return hi - lo <= (uint64_t)kBlock; };
   // asked for at once: the unit's rows, the sample, the first step of the search
   uint32_t mine[kRounds], drawn[kDrawn];
 #pragma unroll
@@ -156,7 +159,8 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   }
   __syncthreads();
   narrow(0);
-  yes = not_behind();
+  const bool found = near();  // (block-uniform)
+  if (!found) yes = not_behind();
 #pragma unroll
   for (uint32_t b = 0; b < kSeen; b += kBlock)
     if (s.seen.hits[b + tid] >= kSplitHits) {
@@ -164,9 +168,9 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
       hot_row[i] = s.seen.row[b + tid];
       hot_hits[i] = s.seen.hits[b + tid];
     }
-  report(yes, 1);
+  if (!found) report(yes, 1);
   __syncthreads();
-  narrow(1);
+  if (!found) narrow(1);
   const uint32_t hot = n_hot, bins = split.buckets + hot;
   if (hot) {  // block-uniform.  Numbered in the order of the rows: the list's own order is that of the block's atomics
     for (uint32_t i = tid; i < hot; i += kBlock) {
@@ -180,7 +184,7 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
     }
     __syncthreads();
   }
-  while (hi - lo > 1) {  // (more bags than the square of the block's threads)
+  while (!near()) {  // (more bags than the cube of the block's threads)
     if (tid == 0) bags_before[0] = 0;
     __syncthreads();
     report(not_behind(), 0);

@@ -65,32 +65,38 @@ __device__ inline void wait_all_memory_ops() {
 
 // Notes for the sweep that bucket b has taken a key (tables with expiry).  `unit`: the unit of the current step if the
 // key's last-seen step is that (no key can be newer, so a bucket that holds something keeps its bound), or
-// kAgeLook for a key that was seen earlier or at an unknown time.  The byte is read first, with an ordinary load:
+// kAgeLook for a key that was seen earlier or at an unknown time.  `word`: the byte, in its word, read with an ordinary load:
 // a stale copy can only show kAgeEmpty where another compute unit has noted a key in this very kernel
 // (bytes become kAgeEmpty in the sweep alone, in a kernel of its own).  Bits are only ever cleared here: all who
 // note the current unit write the same one, and kAgeLook wins over any.
-__device__ inline void note_key(const TableView& t, const Bucket* b, uint32_t unit) {
+__device__ inline void note_key(const TableView& t, const Bucket* b, uint32_t unit, uint32_t word) {
   if (t.expire_steps == 0) return;
   const uint64_t idx = (uint64_t)(b - t.buckets);
-  const uint32_t at = 8u * (uint32_t)(idx & 3);
-  uint32_t* w = &t.oldest[idx >> 2];
-  const uint32_t have = (*w >> at) & 0xFFu;
+  const uint32_t at = 8u * (uint32_t)(idx & 3), have = (word >> at) & 0xFFu;
   if (have == kAgeEmpty) atomicOr(&t.occupied[idx >> 6], 1ull << (idx & 63));
-  if (have == kAgeEmpty || (unit == kAgeLook && have != kAgeLook)) atomicAnd(w, (unit << at) | ~(0xFFu << at));
+  if (have == kAgeEmpty || (unit == kAgeLook && have != kAgeLook)) atomicAnd(&t.oldest[idx >> 2], (unit << at) | ~(0xFFu << at));
+}
+// The word of `oldest` that note_key wants, asked for before it is known whether the bucket takes the key.
+__device__ inline uint32_t age_word(const TableView& t, const Bucket* b) {
+  return t.expire_steps == 0 ? 0u : t.oldest[(uint64_t)(b - t.buckets) >> 2];
 }
 
 __device__ inline bool try_claim(const TableView& t, Bucket* b, uint64_t k, unsigned long long meta, uint32_t unit) {
   // snapshot of the eight keys (may be stale: a slot seen free may be taken by now; the CAS decides)
   const ulonglong2* kp = reinterpret_cast<const ulonglong2*>(b->key);
   const ulonglong2 a0 = kp[0], a1 = kp[1], a2 = kp[2], a3 = kp[3];
+  const uint32_t word = age_word(t, b);
   const uint64_t snap[kBucket] = {a0.x, a0.y, a1.x, a1.y, a2.x, a2.y, a3.x, a3.y};
+  uint32_t open = 0;
 #pragma unroll
-  for (int l = 0; l < kBucket; ++l) {
-    if (snap[l] != kEmptyKey) continue;
+  for (int l = 0; l < kBucket; ++l) open |= snap[l] == kEmptyKey ? 1u << l : 0u;
+#pragma unroll 1
+  for (; open; open &= open - 1) {
+    const uint32_t l = (uint32_t)__ffs((int)open) - 1u;
     if (atomicCAS((unsigned long long*)&b->key[l], (unsigned long long)kEmptyKey, (unsigned long long)k) ==
         (unsigned long long)kEmptyKey) {
       st_agent(&b->meta[l], meta);  // issued after the CAS has returned: publishes the slot
-      note_key(t, b, unit);
+      note_key(t, b, unit, word);
       return true;
     }
   }
@@ -150,7 +156,7 @@ __device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long
       const uint64_t vk = atomicExch((unsigned long long*)&b->key[l], (unsigned long long)k);
       wait_all_memory_ops();  // the key exchange is performed before the slot is published again
       st_agent(&b->meta[l], meta);
-      if (unit == kAgeLook) note_key(t, b, unit);  // (a key of the current step leaves the bound of a full bucket as it is)
+      if (unit == kAgeLook) note_key(t, b, unit, age_word(t, b));  // (a key of the current step leaves the bound of a full bucket as it is)
       k = vk;
       meta = old;
       unit = kAgeLook;
