@@ -97,6 +97,7 @@ template <typename E, int N_>
 struct TableRows {
   static constexpr int N = N_, kIds = kIdsInRegs;
   static constexpr uint64_t kHeld = 8192;  // waves that run at a time; 0: does not matter
+  static constexpr int kSimdWaves = N_ == 4 && sizeof(E) == 4 ? 7 : 1;
   using Id = int32_t;
   const E* rows;
   const int32_t* idx;
@@ -119,6 +120,7 @@ template <typename E, int N_, int kIds_>
 struct QuotRemRows {
   static constexpr int N = N_, kIds = kIds_;
   static constexpr uint64_t kHeld = kIds_ == 4 && sizeof(E) == 4 ? 6144 : 0;
+  static constexpr int kSimdWaves = 1;
   using Id = int64_t;
   const E* rem;    // E_r: 2^m rows
   const E* quot;   // E_q: 2^m rows
@@ -158,7 +160,7 @@ __device__ inline void store_pooled(float* out, const float* a, bool past_caches
 // group_log2: log2 of the lanes that share a row; bags_log2: log2 of the bags a wave owns (64 >> group_log2 at
 // least); past_caches: how the pooled rows are stored (GatherShape)
 template <typename Src>
-__global__ __launch_bounds__(256) void gather_pool_kernel(Src src, const int64_t* __restrict__ offsets,
+__global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src src, const int64_t* __restrict__ offsets,
                                                           uint64_t n_bags, uint64_t n, uint32_t dim,
                                                           uint32_t group_log2, uint32_t bags_log2,
                                                           bool past_caches, float* __restrict__ out) {
