@@ -227,7 +227,8 @@ struct ExportWorkspace {
 uint64_t export_sort_units(uint64_t n);
 // leaves OR and AND of the keys found in the control block's scratch
 hipError_t launch_export_bits(const TableView& t, const ExportWorkspace& ws, uint64_t max_n, hipStream_t stream);
-// varying: the bits in which the keys differ
+// varying: the bits in which the keys differ (of more than kRangesMost of them)
+constexpr uint64_t kRangesMost = 1u << 17;
 hipError_t launch_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t varying, int64_t* d_keys, int32_t* d_row,
                               uint32_t* d_last_seen, int64_t* d_slot, hipStream_t stream);
 

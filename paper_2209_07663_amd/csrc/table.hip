@@ -538,7 +538,8 @@ int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t
                     max_n, touched_only != 0, s) != hipSuccess)
     return MONO_EHIP;
   Control c;
-  if (launch_export_bits(t->view, ws, max_n, s) != hipSuccess || read_control(t, &c, s) != hipSuccess) return MONO_EHIP;
+  if (max_n > kRangesMost && launch_export_bits(t->view, ws, max_n, s) != hipSuccess) return MONO_EHIP;
+  if (read_control(t, &c, s) != hipSuccess) return MONO_EHIP;
   const unsigned long long n = c.scratch[kExportCount];
   *h_n = n;
   if (n > max_n) return MONO_OK;  // the caller's buffers are too small: nothing is written, a window stays open

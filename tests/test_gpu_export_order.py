@@ -67,3 +67,30 @@ def test_exports_around_the_edges_of_both_unit_sizes(kind, n):
     assert (d["rows"] == tc.init_rows(d["keys"], 4, 5).astype(np.float32)).all() and (d["last_seen"] == 3).all()
     tc.check_placement(d, tab.capacity, 8, 5)
     tab.close()
+
+
+@pytest.mark.parametrize("kind", ["all", "low", "top"])
+@pytest.mark.parametrize("n", [3, 4095, 4096, 4097, 8191, 33333, 65537, 131071, 131072, 131073])
+def test_exports_that_are_ranked(kind, n):
+    """Up to 4096 keys are ranked against all others, up to 131072 within ranges that a sample of them bounds: all
+    attributes stay with their key, for keys in clusters of very different sizes too."""
+    from paper_2209_07663_amd.binding import Table
+    dev, rng = torch.device("cuda:0"), np.random.default_rng(n)
+    tab = Table(1 << 18, 4, 7, max_ids=1 << 18, device=dev)
+    keys = _keys("all" if kind == "top" else kind, n, rng)
+    if kind == "top":                                                   # most keys in a few narrow clusters, the others anywhere
+        near = np.unique(rng.integers(0, 3, n).astype(np.uint64) * np.uint64(1 << 62) + rng.integers(0, 4 * n, n).astype(np.uint64))
+        keys = np.unique(np.concatenate([near, keys]))[:n]
+    keys = rng.permutation(keys).astype(np.int64)
+    first = rng.random(keys.size) < 0.5
+    where = {}
+    for step, part in enumerate((keys[first], keys[~first])):
+        if part.size:
+            where.update(zip(part.tolist(), tab.mono_lookup_or_insert(torch.from_numpy(part).to(dev), step).tolist()))
+    d = tab.mono_table_export()
+    order = np.sort(keys.view(np.uint64)).view(np.int64)
+    assert np.array_equal(d["keys"], order) and d["row"].tolist() == [where[k] for k in order.tolist()]
+    assert np.array_equal(d["last_seen"], 1 - np.isin(order, keys[first]).astype(np.uint32))
+    assert (d["rows"] == tc.init_rows(d["keys"], 4, 7).astype(np.float32)).all()
+    tc.check_placement(d, tab.capacity, 8, 7)
+    tab.close()
