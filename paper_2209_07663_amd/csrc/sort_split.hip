@@ -362,19 +362,23 @@ template <int kBlock>
 struct BucketLds {
   static constexpr int kWaves = kBlock / 64;
   uint32_t first[kBlock];  // pairs of the bin in the units before this one
-  uint32_t from[kBlock];   // where the unit's share of the bin lies
+  uint16_t from[kBlock];   // where the unit's share of the bin lies in the unit
   union {
-    uint2 pairs[2][kBucketMost];
-    uint32_t words[2][kBucketWords];  // key within the bucket << kPlaceBits | place in the bin
+    uint16_t cnt[kWaves][kBucketBins];
+    uint32_t in_range[kBucketBins];
   };
-  uint32_t cnt[kWaves][kBucketBins];
+  union {
+    uint2 pairs[kBucketMost];
+    uint32_t words[kBucketWords];  // key within the bucket << kPlaceBits | place in the bin
+  };
   uint32_t wave_sum[2 * kWaves];
   uint32_t range[3];
 };
+static_assert(sizeof(BucketLds<512>) <= 160 * 1024 / 4 && kSplitItems[kSplitSizes - 1] < 0x10000, "four blocks to a compute unit");
 
 // The pairs at kTogether places of the bin, which is in the order of the batch; those at places from `end` on are left as they are.
 template <int kBlock>
-__device__ inline void pairs_at(const BucketLds<kBlock>& s, uint32_t units_pow2, const uint2* __restrict__ src,
+__device__ inline void pairs_at(const BucketLds<kBlock>& s, uint32_t units_pow2, uint32_t items, const uint2* __restrict__ src,
                                 const uint32_t (&at)[kTogether], uint32_t end, uint2 (&p)[kTogether]) {
   uint32_t u[kTogether];
 #pragma unroll
@@ -385,40 +389,59 @@ __device__ inline void pairs_at(const BucketLds<kBlock>& s, uint32_t units_pow2,
   }
 #pragma unroll
   for (uint32_t j = 0; j < kTogether; ++j)
-    if (at[j] < end) p[j] = src[s.from[u[j]] + (at[j] - s.first[u[j]])];
+    if (at[j] < end) p[j] = src[u[j] * items + s.from[u[j]] + (at[j] - s.first[u[j]])];
 }
 // q, q + step, ...
 template <int kBlock>
-__device__ inline void pairs_of_bin(const BucketLds<kBlock>& s, uint32_t units_pow2, const uint2* __restrict__ src,
-                                    uint32_t q, uint32_t step, uint32_t end, uint2 (&p)[kTogether]) {
+__device__ inline void pairs_of_bin(const BucketLds<kBlock>& s, uint32_t units_pow2, uint32_t items,
+                                    const uint2* __restrict__ src, uint32_t q, uint32_t step, uint32_t end,
+                                    uint2 (&p)[kTogether]) {
   uint32_t at[kTogether];
 #pragma unroll
   for (uint32_t j = 0; j < kTogether; ++j) at[j] = q + j * step;
-  pairs_at(s, units_pow2, src, at, end, p);
+  pairs_at(s, units_pow2, items, src, at, end, p);
 }
 
 __device__ inline uint32_t sort_key(uint2 pair) { return pair.x; }
 __device__ inline uint32_t sort_key(uint32_t word) { return word >> kPlaceBits; }
 
-// Stable sort of first[0 .. count) by the low `bits` bits of the keys, with room in `second`; returns which holds the result.
-// Per digit two walks over the elements, 64 at a time: one counts, one ranks and places.
-template <int kBlock, typename T>
-__device__ inline const T* sort_bucket(BucketLds<kBlock>& s, T* first, T* second, uint32_t count, uint32_t bits) {
+// Stable sort of `count` elements by the low `bits` bits of their keys, into `room`.  A wave owns 64 * rounds consecutive ones;
+// they are in registers: e[r] of lane l is the wave's element 64 r + l.  A digit is one walk over them, which ranks; what it leaves behind
+// are the waves' counts.
+template <int kBlock, typename T, uint32_t kRounds>
+__device__ inline void sort_bucket(BucketLds<kBlock>& s, T (&e)[kRounds], T* room, uint32_t count, uint32_t bits) {
   constexpr int kWaves = kBlock / 64;
   const uint32_t tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
-  const uint32_t passes = (bits + kBucketDigit - 1) / kBucketDigit, per = passes ? (bits + passes - 1) / passes : 0;
-  const uint32_t share = (count + kBlock - 1) / kBlock * 64, end = min((wave + 1) * share, count);
-  uint32_t* off = s.cnt[wave];
+  const uint32_t passes = bits > kBucketDigit ? (bits + kBucketDigit - 1) / kBucketDigit : 1, per = (bits + passes - 1) / passes;
+  const uint32_t rounds = (count + kBlock - 1) / kBlock, i0 = wave * 64 * rounds + lane;
+  uint16_t* off = s.cnt[wave];
 #pragma unroll 1
   for (uint32_t pass = 0; pass < passes; ++pass) {
     const uint32_t shift = pass * per, width = min(bits - shift, per), mask = (1u << width) - 1;
-    const T* from = pass & 1 ? second : first;
-    T* to = pass & 1 ? first : second;
+    uint32_t rank[kRounds / 2];  // two to a word
+    static_assert(kRounds % 2 == 0 && kBucketWords <= 0x10000, "halves of a word");
+    uint32_t i = i0;
+    __asm__ volatile("" : "+v"(i));  // (else which lanes have an element is kept for all rounds, in more registers than there are)
 #pragma unroll
-    for (uint32_t b = 0; b < kBucketBins; b += 64) wave_store(off + b + lane, 0u);
+    for (uint32_t b = 0; b < kBucketBins; b += 128) wave_store(reinterpret_cast<uint32_t*>(off + b) + lane, 0u);
     wave_order();
-    for (uint32_t i = wave * share + lane; i < end; i += 64) atomicAdd(&s.cnt[wave][(sort_key(from[i]) >> shift) & mask], 1u);
-    __syncthreads();
+#pragma unroll
+    for (uint32_t r = 0; r < kRounds; ++r) {
+      if (r % 2 == 0) rank[r / 2] = 0;
+      if (r < rounds) {  // block-uniform
+        const bool valid = i + r * 64 < count;
+        if (pass > 0 && valid) e[r] = room[i + r * 64];
+        const uint32_t digit = (sort_key(e[r]) >> shift) & mask;
+        const uint64_t peers = same_digit_lanes<kBucketDigit>(digit, valid);
+        const uint32_t before = lanes_before(peers);
+        const uint32_t there = wave_load(off + digit);
+        rank[r / 2] |= (there + before) << (r % 2 * 16);
+        wave_order();
+        if (valid && before == 0) wave_store(off + digit, (uint16_t)(there + (uint32_t)__popcll(peers)));
+        wave_order();
+      }
+    }
+    __syncthreads();  // every wave has counted, and has its elements in registers
     uint32_t c[kWaves], mine = 0;  // a bin per thread
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
@@ -434,28 +457,25 @@ __device__ inline const T* sort_bucket(BucketLds<kBlock>& s, T* first, T* second
       if (w < wave) at += s.wave_sum[w];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      if (tid < kBucketBins) s.cnt[w][tid] = at;
+      if (tid < kBucketBins) s.cnt[w][tid] = (uint16_t)at;
       at += c[w];
     }
     __syncthreads();
-    for (uint32_t i0 = wave * share; i0 < end; i0 += 64) {  // wave-uniform
-      const bool valid = i0 + lane < end;
-      const T e = valid ? from[i0 + lane] : T{};
-      const uint32_t digit = (sort_key(e) >> shift) & mask;
-      const uint64_t peers = same_digit_lanes<kBucketDigit>(digit, valid);
-      const uint32_t at = wave_load(off + digit), before = lanes_before(peers);
-      if (valid) to[at + before] = e;
-      wave_order();
-      if (valid && before == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
-      wave_order();
-    }
+    __asm__ volatile("" : "+v"(i));
+#pragma unroll
+    for (uint32_t r = 0; r < kRounds; ++r)
+      if (i + r * 64 < count && r < rounds) room[off[(sort_key(e[r]) >> shift) & mask] + (rank[r / 2] >> (r % 2 * 16) & 0xFFFFu)] = e[r];
     __syncthreads();
   }
-  return passes & 1 ? second : first;
 }
 
+// A chain of dependent steps in every block, so that what counts is how many blocks run at a time and how few steps there are.
+// The pairs are in registers between the digits and in one LDS buffer, so that four blocks fit a compute unit (a million pairs
+// have 1024 ordinary bins, all of which run at a time then), and a digit is one walk over them.  With two LDS buffers, two blocks
+// to a compute unit and a walk more to count, us: a million pairs 27.4 -> 20.2, 690 K 16.0 -> 13.0, 204 K 11.0 -> 9.5, 26 K 6.0
+// either way.
 template <int kBlock>
-__global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict__ ctl, const uint2* __restrict__ src,
+__global__ __launch_bounds__(kBlock, kBlock == 512 ? 8 : 4) void sort_bucket_kernel(Control* __restrict__ ctl, const uint2* __restrict__ src,
                                                              uint32_t items, uint32_t units, uint32_t units_pow2,
                                                              uint32_t buckets_log2, uint32_t group_log2, uint32_t stride,
                                                              const uint32_t* __restrict__ shares,
@@ -498,7 +518,7 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
   }
   if (tid < units_pow2) {  // (units past the last one begin behind every pair)
     s.first[tid] = tid < units ? before : 0xFFFFFFFFu;
-    s.from[tid] = tid * items + from;
+    s.from[tid] = (uint16_t)from;
   }
   // the last bin ends where all pairs do
   if (bin == split.buckets + hot - 1 && turn >> 16 == 0 && tid == 0)
@@ -509,7 +529,7 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
     const uint32_t a = (uint32_t)((uint64_t)count * part / parts), e = (uint32_t)((uint64_t)count * (part + 1) / parts);
     for (uint32_t q = a + tid; q < e; q += kBlock * kTogether) {
       uint2 p[kTogether];
-      pairs_of_bin(s, units_pow2, src, q, kBlock, e, p);
+      pairs_of_bin(s, units_pow2, items, src, q, kBlock, e, p);
 #pragma unroll
       for (uint32_t j = 0; j < kTogether; ++j)
         if (q + j * kBlock < e) dst[base + q + j * kBlock] = make_uint2(split.row(p[j].x, inv), p[j].y);
@@ -517,85 +537,89 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
     return;
   }
   const uint32_t all = 1u << split.rest, keys = all - 1;
-  if (count > kBucketMost && count <= kBucketWords && split.rest <= 32 - kPlaceBits) {
-    for (uint32_t q = tid; q < count; q += kBlock * kTogether) {
-      uint2 p[kTogether];
-      pairs_of_bin(s, units_pow2, src, q, kBlock, count, p);
+  const uint32_t rounds = (count + kBlock - 1) / kBlock;  // a wave sorts 64 * rounds consecutive pairs
+  const uint32_t i0 = wave * 64 * rounds + lane;
+  constexpr uint32_t kPairRounds = kBucketMost / kBlock;
+  if (count <= kBucketMost) {
+    uint2 pair[kPairRounds];
 #pragma unroll
-      for (uint32_t j = 0; j < kTogether; ++j) {
-        const uint32_t at = q + j * kBlock;
-        if (at < count) s.words[0][at] = (p[j].x & keys) << kPlaceBits | at;
-      }
+    for (uint32_t r = 0; r < kPairRounds; r += kTogether) {
+      uint2 p[kTogether] = {};
+      if (r < rounds) pairs_of_bin(s, units_pow2, items, src, i0 + r * 64, 64, count, p);
+#pragma unroll
+      for (uint32_t j = 0; j < kTogether; ++j) pair[r + j] = p[j];
     }
-    __syncthreads();
-    const uint32_t* sorted = sort_bucket(s, s.words[0], s.words[1], count, split.rest);
+    sort_bucket(s, pair, s.pairs, count, split.rest);
+    for (uint32_t q = tid; q < count; q += kBlock) dst[base + q] = make_uint2(split.row(s.pairs[q].x, inv), s.pairs[q].y);
+    return;
+  }
+  if (count <= kBucketWords && split.rest <= 32 - kPlaceBits) {
+    constexpr uint32_t kRounds = kBucketWords / kBlock;
+    uint32_t word[kRounds];
+#pragma unroll
+    for (uint32_t r = 0; r < kRounds; r += kTogether) {
+      uint2 p[kTogether] = {};
+      if (r < rounds) pairs_of_bin(s, units_pow2, items, src, i0 + r * 64, 64, count, p);
+#pragma unroll
+      for (uint32_t j = 0; j < kTogether; ++j) word[r + j] = (p[j].x & keys) << kPlaceBits | ((i0 + (r + j) * 64) & (kBucketWords - 1));
+    }
+    sort_bucket(s, word, s.words, count, split.rest);
     for (uint32_t q = tid; q < count; q += kBlock * kTogether) {
       uint32_t at[kTogether];
       uint2 p[kTogether];
 #pragma unroll
       for (uint32_t j = 0; j < kTogether; ++j)
-        at[j] = q + j * kBlock < count ? sorted[q + j * kBlock] & (kBucketWords - 1) : 0xFFFFFFFEu;
-      pairs_at(s, units_pow2, src, at, count, p);
+        at[j] = q + j * kBlock < count ? s.words[q + j * kBlock] & (kBucketWords - 1) : 0xFFFFFFFEu;
+      pairs_at(s, units_pow2, items, src, at, count, p);
 #pragma unroll
       for (uint32_t j = 0; j < kTogether; ++j)
         if (q + j * kBlock < count) dst[base + q + j * kBlock] = make_uint2(split.row(p[j].x, inv), p[j].y);
     }
     return;
   }
-  // Ranges [low, high) of the keys within the bucket, one after the other, each with no more pairs than fit into LDS: all
-  // keys at once, nearly always.  A key with more pairs than that is copied.
+  // Ranges [low, high) of the keys within the bucket, one after the other, each with no more pairs than fit into LDS.  A key
+  // with more pairs than that is copied.
   uint32_t done = 0, low = 0;
   while (low < all && done < count) {
-    uint32_t high = all, here = count;
-    bool copy = false;
-    if (count > kBucketMost) {
-      uint32_t width = (all - low + kBucketBins - 1) / kBucketBins;  // of a bin of the histogram
-      for (;;) {
-        if (tid < kBucketBins) s.cnt[0][tid] = 0;
-        __syncthreads();
-        for (uint32_t q = tid; q < count; q += kBlock * kTogether) {
-          uint2 p[kTogether];
-          pairs_of_bin(s, units_pow2, src, q, kBlock, count, p);
+    uint32_t width = (all - low + kBucketBins - 1) / kBucketBins;  // of a bin of the histogram
+    for (;;) {
+      if (tid < kBucketBins) s.in_range[tid] = 0;
+      __syncthreads();
+      for (uint32_t q = tid; q < count; q += kBlock * kTogether) {
+        uint2 p[kTogether];
+        pairs_of_bin(s, units_pow2, items, src, q, kBlock, count, p);
 #pragma unroll
-          for (uint32_t j = 0; j < kTogether; ++j) {
-            const uint32_t k = p[j].x & keys;
-            if (q + j * kBlock < count && k >= low && (k - low) / width < kBucketBins) atomicAdd(&s.cnt[0][(k - low) / width], 1u);
-          }
+        for (uint32_t j = 0; j < kTogether; ++j) {
+          const uint32_t k = p[j].x & keys;
+          if (q + j * kBlock < count && k >= low && (k - low) / width < kBucketBins) atomicAdd(&s.in_range[(k - low) / width], 1u);
         }
-        __syncthreads();
-        // how many of its bins fit together, and the pairs in them
-        const uint32_t mine = tid < kBucketBins ? s.cnt[0][tid] : 0u, sum = wave_sums(mine);
-        if (lane == 63) s.wave_sum[wave] = sum;
-        if (tid < 2) s.range[tid] = 0;
-        if (tid == 0) s.range[2] = mine;
-        __syncthreads();
-        uint32_t upto = sum;
-        for (uint32_t w = 0; w < wave; ++w) upto += s.wave_sum[w];
-        if (tid < kBucketBins && upto <= kBucketMost) {
-          atomicAdd(&s.range[0], 1u);
-          atomicMax(&s.range[1], upto);
-        }
-        __syncthreads();
-        if (s.range[0] || width == 1) break;
-        width = (width + kBucketBins - 1) / kBucketBins;  // closer
-        __syncthreads();
       }
-      copy = s.range[0] == 0;
-      high = low + (copy ? 1u : s.range[0] * width);
-      here = copy ? s.range[2] : s.range[1];
+      __syncthreads();
+      // how many of its bins fit together, and the pairs in them
+      const uint32_t mine = tid < kBucketBins ? s.in_range[tid] : 0u, sum = wave_sums(mine);
+      if (lane == 63) s.wave_sum[wave] = sum;
+      if (tid < 2) s.range[tid] = 0;
+      if (tid == 0) s.range[2] = mine;
+      __syncthreads();
+      uint32_t upto = sum;
+      for (uint32_t w = 0; w < wave; ++w) upto += s.wave_sum[w];
+      if (tid < kBucketBins && upto <= kBucketMost) {
+        atomicAdd(&s.range[0], 1u);
+        atomicMax(&s.range[1], upto);
+      }
+      __syncthreads();
+      if (s.range[0] || width == 1) break;
+      width = (width + kBucketBins - 1) / kBucketBins;  // closer
+      __syncthreads();
     }
+    const bool copy = s.range[0] == 0;
+    const uint32_t high = low + (copy ? 1u : s.range[0] * width), here = copy ? s.range[2] : s.range[1];
     // the range's pairs in order: to LDS, or where they belong
     uint32_t taken = 0;
     for (uint32_t q0 = 0; q0 < count; q0 += kBlock * kTogether) {
       uint2 p[kTogether];
       const uint32_t q = q0 + wave * 64 * kTogether + lane;  // (a wave takes consecutive pairs)
-      pairs_of_bin(s, units_pow2, src, q, 64, count, p);
-      if (count <= kBucketMost) {
-#pragma unroll
-        for (uint32_t j = 0; j < kTogether; ++j)
-          if (q + j * 64 < count) s.pairs[0][q + j * 64] = p[j];
-        continue;
-      }
+      pairs_of_bin(s, units_pow2, items, src, q, 64, count, p);
       uint64_t m[kTogether];
       uint32_t found = 0;
 #pragma unroll
@@ -620,16 +644,19 @@ __global__ __launch_bounds__(kBlock) void sort_bucket_kernel(Control* __restrict
           if (copy)
             dst[base + done + to] = make_uint2(split.row(p[j].x, inv), p[j].y);
           else
-            s.pairs[0][to] = p[j];
+            s.pairs[to] = p[j];
         }
         at += (uint32_t)__popcll(m[j]);
       }
     }
     __syncthreads();
     if (!copy) {
-      const uint2* sorted = sort_bucket(s, s.pairs[0], s.pairs[1], here, split.rest);
-      for (uint32_t q = tid; q < here; q += kBlock)
-        dst[base + done + q] = make_uint2(split.row(sorted[q].x, inv), sorted[q].y);
+      const uint32_t many = (here + kBlock - 1) / kBlock, i = wave * 64 * many + lane;
+      uint2 pair[kPairRounds];
+#pragma unroll
+      for (uint32_t r = 0; r < kPairRounds; ++r) pair[r] = r < many && i + r * 64 < here ? s.pairs[i + r * 64] : make_uint2(0u, 0u);
+      sort_bucket(s, pair, s.pairs, here, split.rest);
+      for (uint32_t q = tid; q < here; q += kBlock) dst[base + done + q] = make_uint2(split.row(s.pairs[q].x, inv), s.pairs[q].y);
       __syncthreads();
     }
     done += here;
