@@ -60,7 +60,10 @@ __device__ inline uint32_t bag_holding(const int64_t* offsets, uint64_t n_bags, 
   return (uint32_t)lo;
 }
 
-constexpr int kGroupBlock = 512;     // threads of a block of sort_hist_kernel
+// Threads of a block of sort_hist_kernel.  The wide shape's groups are few: 417 blocks of 6.8 M pairs, whose 13 waves a compute
+// unit with 512 threads each left the memory idle (17.7 -> 15.5 us a pass; 43 at 26 M either way).
+template <uint32_t kBits>
+constexpr int kGroupBlock = kBits > 8 ? 1024 : 512;
 constexpr uint32_t kSortChunk = 16;  // see sort_scatter_kernel
 
 // Digit histograms of a group of consecutive units: a unit's words are what the units before it in the group hold, to
@@ -75,7 +78,7 @@ constexpr uint32_t kSortChunk = 16;  // see sort_scatter_kernel
 // in 9-bit ones, and 39.6 -> 36.8 and 153 -> 146 in the scatter kernel.  A unit per block instead of four takes 5 us
 // less here at 26 M but 11 more in the scan.
 template <uint32_t kBits, uint32_t kItems>
-__global__ __launch_bounds__(kGroupBlock) void sort_hist_kernel(const Control* __restrict__ ctl, uint32_t pass,
+__global__ __launch_bounds__(kGroupBlock<kBits>) void sort_hist_kernel(const Control* __restrict__ ctl, uint32_t pass,
                                                                const int32_t* __restrict__ rows,
                                                                const uint2* __restrict__ src, uint64_t n,
                                                                uint32_t* __restrict__ hist,
@@ -85,7 +88,7 @@ __global__ __launch_bounds__(kGroupBlock) void sort_hist_kernel(const Control* _
                                                                uint32_t search_blocks) {
   const SortPlan plan = make_sort_plan(ctl->hwm, kBits);
   if (pass >= plan.passes) return;
-  constexpr uint32_t kBins = 1u << kBits, kBlock = kGroupBlock, kUnits = kSortGroupUnits, kCopies = 4;
+  constexpr uint32_t kBins = 1u << kBits, kBlock = kGroupBlock<kBits>, kUnits = kSortGroupUnits, kCopies = 4;
   __shared__ uint4 words[kUnits * kBins * kCopies / 4];
   uint32_t* cnt = reinterpret_cast<uint32_t*>(words);  // [unit][bin][copy]
   if (blockIdx.x < search_blocks) {
@@ -501,8 +504,8 @@ static void queue_sort_passes(const TableView& t, const UpdateWorkspace& ws, con
   for (uint32_t p = 0; p < passes; ++p) {
     const uint2* src = p % 2 == 0 ? ws.pair_a : ws.pair_b;
     uint2* dst = p % 2 == 0 ? ws.pair_b : ws.pair_a;
-    const uint32_t search = p == 0 ? (uint32_t)((units + kGroupBlock / 64 - 1) / (kGroupBlock / 64)) : 0u;
-    MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kItems>), dim3((unsigned)groups + search), dim3(kGroupBlock),
+    const uint32_t search = p == 0 ? (uint32_t)((units + kGroupBlock<kBits> / 64 - 1) / (kGroupBlock<kBits> / 64)) : 0u;
+    MONO_LAUNCH(prof, K_SORT_HIST, stream, (sort_hist_kernel<kBits, kItems>), dim3((unsigned)groups + search), dim3(kGroupBlock<kBits>),
                 t.ctl, p, d_rows, src, n, ws.hist, sums, d_offsets, n_bags, ws.unit_bag, search);
     MONO_LAUNCH(prof, K_SORT_SCAN, stream, sort_scan_kernel<kBits>, dim3((1u << kBits) / 4), dim3(kScanBlock), t.ctl, p, sums,
                 groups, totals);
