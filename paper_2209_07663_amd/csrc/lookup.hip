@@ -137,6 +137,9 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   const uint32_t turns = kManyTurns ? turns_ : 1u;
   __shared__ unsigned long long miss_key[kMissSlots];
   __shared__ uint32_t miss_cnt[kMissSlots];
+  // what the first counter of a missing key held, where it was looked at (see touch_word)
+  constexpr bool kHolds = !kManyTurns && !kSmall;
+  __shared__ unsigned long long miss_held[kHolds ? kMissSlots : 1];
   __shared__ int any_miss;
   // Are counters worth a look before the buckets?  (Counters that age prove nothing; see MissSample.)
   const bool counters_first = t.expire_steps == 0 && !restore && t.ctl->scratch[kCountersFirst] != 0;
@@ -145,7 +148,8 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   // (kSmall) the thread's key, the place in the set that it was the first to take, or none, and its counter as it was before
   const uint64_t first_key = kSmall && at < n ? (uint64_t)keys[at] : kEmptyKey;
   uint32_t first_at = kMissSlots;
-  unsigned long long first_guess = 0;
+  unsigned long long first_held = 0;
+  const bool marks = kHolds && marks_reached(t, n);
   if (blockIdx.x == 0 && threadIdx.x < kWinLists) {  // for the election and the insertion
     t.win_cnt[threadIdx.x * kWinStride] = 0;
     if (threadIdx.x == 0) t.ctl->scratch[kFreeBefore] = (unsigned long long)(uint32_t)t.ctl->free_n;
@@ -171,13 +175,16 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
     // admitted: a counter below the threshold proves the key absent, and both bucket probes are saved.
     // Counts added by this very batch can only make the test err on the side of probing.
     bool maybe = live;
+    unsigned long long held = 0;
     if (counters_first && live) {
       uint32_t cnt = 0xFFFFFFFFu;
       for (uint32_t j = 0; j < t.filter_hashes; ++j) {  // the key's count is the smallest of its counters
-        const uint32_t c = reinterpret_cast<const uint32_t*>(&t.filter[filter_index(t, k, j)])[0];
-        cnt = c < cnt ? c : cnt;
+        const unsigned long long w = t.filter[filter_index(t, k, j)];
+        if (j == 0) held = w;
+        cnt = (uint32_t)w < cnt ? (uint32_t)w : cnt;
       }
       maybe = cnt >= (t.freq_threshold > 1u ? t.freq_threshold : 1u);
+      if (kSmall) first_held = held;
     }
     const uint64_t b0 = bucket_index(t, 0, k), b1 = bucket_index(t, 1, k);
     // Where counters age nothing above could prove a key absent.  On a sparsely filled table the
@@ -196,7 +203,7 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
       QuadBuckets side0;
       probe_ask(t, b0, look0, side0);
       probe_ask(t, b1, look1, side1);
-      if (t.expire_steps != 0 && live && !restore) first_guess = t.filter[filter_index(t, k)];
+      if (t.expire_steps != 0 && live && !restore) first_held = t.filter[filter_index(t, k)];
       found = probe_find(k, look0, step, side0, &row);
     } else if (__ballot(look0)) {  // wave-uniform
       QuadBuckets side0;
@@ -244,13 +251,14 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
       for (; tries < kProbeTries; ++tries) {
         const unsigned long long old = atomicCAS(&miss_key[pos], (unsigned long long)kEmptyKey, (unsigned long long)k);
         if (kSmall && old == kEmptyKey) first_at = pos;
+        if (kHolds && old == kEmptyKey) miss_held[pos] = held;
         if (old == kEmptyKey || old == k) break;
         pos = (pos + 1) & (kMissSlots - 1);
       }
       if (tries < kProbeTries)
         atomicAdd(&miss_cnt[pos], 1u);
       else
-        touch_counter(t, k, step, 1u);
+        marks ? touch_counter<true>(t, k, step, 1u, false, 0, epoch) : touch_counter<false>(t, k, step, 1u);
     }
   }
   __syncthreads();
@@ -259,11 +267,19 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
   if (threadIdx.x == 0 && any_miss) t.ctl->scratch[kMissTag] = epoch;
   if (restore || !any_miss) return;  // block-uniform
   if (kSmall) {
-    if (first_at != kMissSlots) touch_counter(t, first_key, step, miss_cnt[first_at], &first_guess);
+    if (first_at != kMissSlots)
+      touch_counter<false>(t, first_key, step, miss_cnt[first_at], t.expire_steps != 0 || counters_first, first_held);
     return;
   }
-  for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock)
-    if (miss_cnt[s]) touch_counter(t, miss_key[s], step, miss_cnt[s]);
+  const bool known = kHolds && counters_first;
+  for (int s = threadIdx.x; s < kMissSlots; s += kProbeBlock) {
+    if (miss_cnt[s] == 0) continue;
+    const unsigned long long held = kHolds ? miss_held[s] : 0;
+    if (marks)
+      touch_counter<true>(t, miss_key[s], step, miss_cnt[s], known, held, epoch);
+    else
+      touch_counter<false>(t, miss_key[s], step, miss_cnt[s], known, held);
+  }
 }
 
 // ---- election ------------------------------------------------------------------------------------
@@ -274,9 +290,9 @@ __global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, c
 // leaders meet at one position of the dedup set.  One for batches of at most kElectSmall, which are short of blocks.
 constexpr int kElectBlock = 256;
 template <int kPer>
-__global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, const int64_t* __restrict__ keys,
-                                                                  uint64_t n, uint32_t epoch, int32_t* rows_out,
-                                                                  int restore, uint32_t sample_every) {
+__global__ __launch_bounds__(kElectBlock, 8) void admit_elect_kernel(TableView t, const int64_t* __restrict__ keys,
+                                                                     uint64_t n, uint32_t epoch, int32_t* rows_out,
+                                                                     int restore, uint32_t sample_every) {
   constexpr int kElectSlots = 2 * kElectBlock * kPer;  // slots of a block's LDS set of missing keys
   constexpr int kElectWaves = kElectBlock / 64;
   __shared__ uint32_t wave_cnt[kElectWaves];
@@ -284,8 +300,10 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   // The block's occurrences of one missing key are represented by one of them (the leader): a key
   // that turns hot before it is admitted arrives here in thousands of occurrences, and each of them
   // re-reading the counter and competing for the same position of the dedup set serialised.
+  // (When all have their places its keys make room for what the leaders find, kRowAbsent or the elected occurrence as
+  // -occ - 3: with an array for that, and 80 registers, six blocks shared a compute unit instead of eight.  6.8 M keys, a
+  // million of them new 92 -> 85 us, a million kept out 50 -> 44.)
   __shared__ unsigned long long s_key[kElectSlots];
-  __shared__ int32_t s_res[kElectSlots];  // what the leader found: kRowAbsent, or the elected occurrence as -occ - 3
   // A large batch without a miss ends here.  (A small one reads its occurrences at once: the tag before them is one more
   // round trip of a kernel that is hardly more than three.)
   if (kPer > 1 && t.ctl->scratch[kMissTag] != epoch) return;  // block-uniform
@@ -334,7 +352,11 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     if (kPer == 1 && leader[j]) e[j] = ld_agent(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask]);
     uint32_t cnt = leader[j] ? 255u : 0u;
     if (!restore && leader[j] && t.freq_threshold > 1u) {
-      for (uint32_t h = 0; h < t.filter_hashes; ++h) {  // smallest of the key's counters
+      bool look = true;
+      for (uint32_t h = 0; kPer > 1 && marks_reached(t, n) && h < t.filter_hashes; ++h)
+        look = look && t.reached[filter_index(t, k[j], h) & t.reached_mask] == reached_mark(epoch);
+      if (!look) cnt = 0;
+      for (uint32_t h = 0; look && h < t.filter_hashes; ++h) {  // smallest of the key's counters
         const uint32_t c = reinterpret_cast<const uint32_t*>(&t.filter[filter_index(t, k[j], h)])[0];
         cnt = c < cnt ? c : cnt;
       }
@@ -354,6 +376,7 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
     if (admissible[j] && (uint32_t)(e[j] >> 32) != epoch)
       old[j] = atomicCAS(&t.dset[mix64(k[j] ^ t.s_dedup) & t.dset_mask], e[j], tag | (i0 + (uint64_t)j * kElectBlock));
   }
+  __syncthreads();  // all have their places in the set
   bool winner[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
@@ -381,7 +404,7 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
       // (a second record of the same key in one restore call is refused like a stored key)
       found = restore ? kRowAbsent : -(int32_t)owner - 3;
     }
-    s_res[ls[j]] = found;
+    s_key[ls[j]] = (unsigned long long)(uint32_t)found;
     if (!winner[j]) rows_out[i] = found;  // (the winner's word is written with its place in the list, or by the insertion)
   }
   __syncthreads();
@@ -391,7 +414,7 @@ __global__ __launch_bounds__(kElectBlock) void admit_elect_kernel(TableView t, c
   for (int j = 0; j < kPer; ++j) {
     int32_t found = kRowMiss;
     if (miss[j] && !winner[j]) {
-      found = s_res[ls[j]];
+      found = (int32_t)(uint32_t)s_key[ls[j]];
       if (!leader[j]) rows_out[i0 + (uint64_t)j * kElectBlock] = found;
       duplicate = duplicate || found <= -3;
     }

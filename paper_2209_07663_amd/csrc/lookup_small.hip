@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kSmallThreads) void lookup_small_kernel(TableView t
   const uint32_t mine = s_count;
   if (mine) {  // block-uniform
     if (tid == 0) s_base = (uint32_t)atomicAdd(&t.ctl->scratch[kSmallMisses], (unsigned long long)mine);
-    if (tid < kSmallSet && s.p.miss_cnt[tid]) touch_counter(t, s.p.miss_key[tid], step, s.p.miss_cnt[tid]);
+    if (tid < kSmallSet && s.p.miss_cnt[tid]) touch_counter<false>(t, s.p.miss_key[tid], step, s.p.miss_cnt[tid]);
     __syncthreads();
     if (tid < mine) {
       unsigned long long* to = reinterpret_cast<unsigned long long*>(&t.win_list[s_base + tid]);

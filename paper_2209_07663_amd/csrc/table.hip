@@ -126,6 +126,8 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
   char* oldest = take((2 * n_buckets + 15) & ~15ull);
   char* sweep_list = take(kWinLists * sweep_cap * sizeof(uint32_t));
   char* sweep_cnt = take(kWinLists * kWinStride * sizeof(uint32_t));
+  const uint64_t n_reached = n_filter < kReachedMost ? n_filter : kReachedMost;
+  char* reached = take(n_reached);
   const uint64_t tiles = reduce_tiles(max_ids);
   char* unit_bag = take(max_ids * 4);
   char* pair_a = take(max_ids * sizeof(uint2));
@@ -152,6 +154,8 @@ size_t layout(mono_table* t, char* base, uint64_t capacity, uint32_t dim, uint32
     v.sweep_list = (uint32_t*)sweep_list;
     v.sweep_cnt = (uint32_t*)sweep_cnt;
     v.sweep_cap = sweep_cap;
+    v.reached = (uint8_t*)reached;  // (whatever it holds: see reached_mark)
+    v.reached_mask = n_reached - 1;
     t->ws.unit_bag = (uint32_t*)unit_bag;
     t->ws.pair_a = (uint2*)pair_a;
     t->ws.pair_b = (uint2*)pair_b;
