@@ -8,8 +8,8 @@
 // 64 lanes hold are walked in segments by the whole wave.  A bag longer than kIdsInRegs goes on in steps
 // of kIdsInRegs indices, the next step's indices requested before this step's rows are waited for (bags
 // of 23 IDs on average, dim 36: 144 us per launch when the rest of a long bag was read one row at a time,
-// 20 us so).  A wave whose bags all hold at most two IDs (one-hot slots) issues several rounds of row reads
-// together instead (81 -> 69 us on the workload with one ID per bag).
+// 20 us so).  A wave whose bags all hold at most two IDs, or one (one-hot slots), issues four or eight rounds of row reads
+// together instead (a million bags of one ID, bf16 of dim 64, us: 81 round by round, 67 four together, 61 eight).
 //
 // How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
 // thousand of them: 64, where that still leaves kWavesWanted waves (the index loads are then as coalesced as they can be),
@@ -35,6 +35,8 @@
 //   QuotRemRows     int64 IDs into the two dense tables of the quotient-remainder decomposition
 //                   (the paper's hashing baseline, section 3.1): E = E_r[ID mod 2^m] + E_q[ID div 2^m];
 //                   an ID outside [0, 2^(2m)) counts as absent
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -186,10 +188,9 @@ __global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src s
   // phase 2: group <-> bag, one bag per group and round
   const uint32_t group = 1u << group_log2, l = lane & (group - 1u), g = lane >> group_log2;
   const uint32_t bags_per_round = 64u >> group_log2, rounds = (1u << bags_log2) >> (6u - group_log2);
-  // Short bags (one or two IDs each, as in one-hot slots): a round keeps only one or two rows per
-  // lane in flight, so four rounds (two, where four IDs are in flight) are issued together instead.
-  constexpr int kShort = 2, kRoundsTogether = kIds / kShort;
-  if (!__ballot(len > kShort) && dim <= 64 * N) {  // wave-uniform
+  // Short bags: a round keeps only one or two rows per lane in flight, so as many rounds are issued together as have kIds rows.
+  const auto short_bags = [&](auto longest) {
+    constexpr int kShort = decltype(longest)::value, kRoundsTogether = kIds / kShort;
     const bool active = l * N < dim;
     for (uint32_t q0 = 0; q0 < rounds; q0 += kRoundsTogether) {
       Row v[kRoundsTogether][kShort];
@@ -206,13 +207,16 @@ __global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src s
 #pragma unroll
       for (int rr = 0; rr < kRoundsTogether; ++rr) {
         float acc[N] = {0.f};
-        v[rr][0].add_to(acc);
-        v[rr][1].add_to(acc);
+#pragma unroll
+        for (int j = 0; j < kShort; ++j) v[rr][j].add_to(acc);
         const uint64_t bag = bag_base + (q0 + rr) * bags_per_round + g;
         if (q0 + rr < rounds && bag < n_bags && active) store_pooled<N>(out + bag * dim + l * N, acc, past_caches);
       }
     }
-    return;
+  };
+  if (dim <= 64 * N) {  // (all of this is wave-uniform)
+    if (!__ballot(len > 1)) return short_bags(std::integral_constant<int, 1>{});
+    if (!__ballot(len > 2)) return short_bags(std::integral_constant<int, 2>{});
   }
   for (uint32_t q = 0; q < rounds; ++q) {
     const int from = (int)(q * bags_per_round + g);

@@ -129,7 +129,7 @@ constexpr int kProbeTries = 8;  // slots of the set that a missing key looks at
 // kSmall (batches of at most kProbeSmall): the kernel is a chain of dependent accesses and has no bandwidth to save, so that
 // both buckets, and the counter of a key that turns out to miss, are asked for at once.
 template <bool kManyTurns, bool kSmall>
-__global__ __launch_bounds__(kProbeBlock) void probe_count_kernel(TableView t, const int64_t* __restrict__ keys,
+__global__ __launch_bounds__(kProbeBlock, kSmall ? 1 : 8) void probe_count_kernel(TableView t, const int64_t* __restrict__ keys,
                                                                   uint64_t n, uint32_t step,
                                                                   int32_t* __restrict__ rows_out, int restore,
                                                                   uint32_t turns_, uint32_t epoch) {

@@ -56,3 +56,32 @@ def test_one_table(dim, bf16):
         inside = ((at >= 0) & (at < 1 << 12))[:, None]
         _check(got, rows[at.clamp(0, (1 << 12) - 1)] * inside, lens)
     tab.close()
+
+
+@pytest.mark.parametrize("longest", [1, 2])
+@pytest.mark.parametrize("dim,bf16", [(4, False), (36, False), (64, True), (256, False), (512, True), (512, False)])
+def test_bags_of_one_or_two(dim, bf16, longest):
+    """Waves whose bags all hold at most `longest` IDs, some of them none, beside one whose first bag holds one more."""
+    from paper_2209_07663_amd.binding import Table, mono_qr_gather_pool
+    dev, m = torch.device("cuda:0"), 6
+    g = torch.Generator(device=dev).manual_seed(dim + longest)
+    tab = Table(1 << 12, dim, 3, bf16=bf16, max_ids=1 << 18, max_bags=1 << 17, device=dev)
+    tab.mono_lookup_or_insert(torch.arange(3000, dtype=torch.int64, device=dev), 0)
+    d = tab.mono_table_export()
+    rows = torch.zeros((1 << 12, dim), dtype=torch.float64, device=dev)
+    rows[torch.from_numpy(d["row"].astype("int64")).to(dev)] = torch.from_numpy(d["rows"]).to(dev).double()
+    tabs = [torch.randn((1 << m, dim), device=dev, generator=g).to(torch.bfloat16 if bf16 else torch.float32) for _ in range(2)]
+    for bags in (1, 63, 65, 4099, 70001):
+        lens = torch.randint(0, longest + 1, (bags,), device=dev, generator=g)
+        lens[bags // 2] = longest + (bags > 4000)
+        offs = torch.zeros(bags + 1, dtype=torch.int64, device=dev)
+        torch.cumsum(lens, 0, out=offs[1:])
+        at = torch.randint(-1, 3000, (int(offs[-1]),), device=dev, generator=g)
+        inside = (at >= 0)[:, None]
+        _check(tab.mono_gather_pool(at.int(), offs), rows[at.clamp(min=0)] * inside, lens)
+        ids = torch.where(at % 5 == 0, 1 << 2 * m, at)
+        inside = ((ids >= 0) & (ids < 1 << 2 * m))[:, None]
+        ids_in = ids.clamp(0, (1 << 2 * m) - 1)
+        _check(mono_qr_gather_pool(tabs[0], tabs[1], ids, offs),
+               (tabs[0].double()[ids_in % (1 << m)] + tabs[1].double()[ids_in >> m]) * inside, lens)
+    tab.close()
