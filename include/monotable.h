@@ -250,6 +250,12 @@ int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t
                        int64_t* d_slot, float* d_values, float* d_acc, uint64_t max_n, void* d_work, size_t work_bytes,
                        uint64_t* h_n, void* stream);
 
+/* Copies `parts` arrays (at most MONO_COPY_PARTS) from the device to pinned host memory that the device can write
+ * (hipHostMalloc), all of them by one kernel, and waits for `stream`.  Sizes are whole 4-byte words, addresses 16-byte
+ * aligned; MONO_EINVAL otherwise, or if a destination is no such memory (nothing was done). */
+#define MONO_COPY_PARTS 8
+int mono_copy_to_host(const void* const* d_from, void* const* h_to, const size_t* bytes, uint32_t parts, void* stream);
+
 /* Occurrence counters [first, first + count) in canonical form (step & 0xFFFFFF) << 8 | min(count, 255).
  * There are 4 * capacity counters unless mono_table_create_ex said otherwise. */
 int mono_filter_export(mono_table* t, uint32_t* d_words, uint64_t first, uint64_t count, void* stream);

@@ -49,6 +49,7 @@ SYMBOLS = {
     "mono_table_import": (ctypes.c_int, [_vp, _vp, _vp, _vp, _vp, _u64, ctypes.POINTER(_u64), _vp]),
     "mono_filter_import": (ctypes.c_int, [_vp, _vp, _u64, _u64, _vp]),
     "mono_table_migrate": (ctypes.c_int, [_vp, _vp, _u32, _vp]),
+    "mono_copy_to_host": (ctypes.c_int, [ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(ctypes.c_size_t), _u32, _vp]),
     "mono_filter_export": (ctypes.c_int, [_vp, _vp, _u64, _u64, _vp]),
     "mono_profile_enable": (ctypes.c_int, [_vp, ctypes.c_int]),
     "mono_profile_read": (ctypes.c_int, [_vp, ctypes.POINTER(ctypes.c_char_p), ctypes.POINTER(ctypes.c_double),
@@ -156,19 +157,38 @@ def _pinned_like(tensors):
         return None
 
 
+COPY_PARTS = 8   # MONO_COPY_PARTS
+
+
+def _copy_to_host(tensors, host):
+    """The device tensors into the pinned ones by one kernel; False, and nothing done, where that is not for it to do."""
+    device, n = next(iter(tensors.values())).device, len(tensors)
+    if n > COPY_PARTS or device.type != "cuda" or not all(t.device == device and t.is_contiguous() for t in tensors.values()):
+        return False
+    rc = load_library().mono_copy_to_host((_vp * n)(*(t.data_ptr() for t in tensors.values())),
+                                          (_vp * n)(*(host[name].data_ptr() for name in tensors)),
+                                          (ctypes.c_size_t * n)(*(t.numel() * t.element_size() for t in tensors.values())),
+                                          n, _stream(device))
+    if rc == MONO_EINVAL:
+        return False
+    _check(rc, "mono_copy_to_host")
+    return True
+
+
 def _to_numpy(tensors):
     """Device tensors as host numpy arrays.  An answer of moderate size lands in pinned memory (torch's pool, which
-    takes it back with the arrays) by asynchronous copies: 0.2 ms for 11 MB where pageable copies took 1.3 ms.  A large
+    takes it back with the arrays), all its arrays by one kernel: 0.2 ms for 11 MB where pageable copies took 1.3 ms.  A large
     one takes the pageable way, and so does every one while the program holds PINNED_HELD bytes of earlier ones: it is no
     business of a dump to pin gigabytes of the host."""
     host = _pinned_like(tensors)
     if host is None:
         return {name: t.cpu().numpy() for name, t in tensors.items()}
     try:
-        for name, t in tensors.items():
-            host[name].copy_(t, non_blocking=True)
-        for device in {t.device for t in tensors.values()}:
-            torch.cuda.current_stream(device).synchronize()
+        if not _copy_to_host(tensors, host):
+            for name, t in tensors.items():
+                host[name].copy_(t, non_blocking=True)
+            for device in {t.device for t in tensors.values()}:
+                torch.cuda.current_stream(device).synchronize()
         out = {name: t.numpy() for name, t in host.items()}
     except BaseException:
         _pinned.release(sum(map(_pinned_bytes, host.values())))

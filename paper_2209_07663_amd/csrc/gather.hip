@@ -35,8 +35,6 @@
 //   QuotRemRows     int64 IDs into the two dense tables of the quotient-remainder decomposition
 //                   (the paper's hashing baseline, section 3.1): E = E_r[ID mod 2^m] + E_q[ID div 2^m];
 //                   an ID outside [0, 2^(2m)) counts as absent
-#include <type_traits>
-
 #include "common.h"
 #include "kernels.h"
 

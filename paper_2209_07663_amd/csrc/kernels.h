@@ -240,6 +240,14 @@ constexpr uint64_t kCountMost = 1ull << 31;
 hipError_t launch_filter_cut(const TableView& t, hipStream_t stream);
 hipError_t launch_filter_export(const TableView& t, uint32_t* d_words, uint64_t first, uint64_t count,
                                 hipStream_t stream);
+// Arrays on their way to the host (see mono_copy_to_host).
+constexpr uint32_t kCopyParts = 8;
+struct CopyParts {
+  const void* from[kCopyParts];
+  void* to[kCopyParts];
+  uint64_t words[kCopyParts];  // of four bytes
+};
+hipError_t launch_copy_to_host(const CopyParts& parts, uint32_t n, hipStream_t stream);
 hipError_t launch_filter_import(const TableView& t, const uint32_t* d_words, uint64_t first, uint64_t count,
                                 hipStream_t stream);
 hipError_t launch_table_init(const TableView& t, uint64_t dset_size, hipStream_t stream);

@@ -654,6 +654,28 @@ int mono_table_migrate(mono_table* dst, mono_table* src, uint32_t generation, vo
   return launch_migrate(b, a, c.free_n, s) == hipSuccess ? MONO_OK : MONO_EHIP;
 }
 
+int mono_copy_to_host(const void* const* d_from, void* const* h_to, const size_t* bytes, uint32_t parts, void* stream) {
+  static_assert(kCopyParts == MONO_COPY_PARTS, "the kernel takes what the interface says");
+  if (parts > MONO_COPY_PARTS || (parts && (!d_from || !h_to || !bytes))) return MONO_EINVAL;
+  CopyParts c = {};
+  uint32_t n = 0;
+  for (uint32_t p = 0; p < parts; ++p) {
+    if (bytes[p] == 0) continue;
+    if (bytes[p] % 4 || !d_from[p] || !h_to[p] || ((uintptr_t)d_from[p] | (uintptr_t)h_to[p]) % 16) return MONO_EINVAL;
+    hipPointerAttribute_t at;
+    if (hipPointerGetAttributes(&at, h_to[p]) != hipSuccess) {
+      (void)hipGetLastError();  // (memory that the runtime does not know: the error is answered here)
+      return MONO_EINVAL;
+    }
+    if (at.type != hipMemoryTypeHost || !at.devicePointer) return MONO_EINVAL;
+    c.from[n] = d_from[p];
+    c.to[n] = at.devicePointer;
+    c.words[n++] = bytes[p] / 4;
+  }
+  if (n && launch_copy_to_host(c, n, (hipStream_t)stream) != hipSuccess) return MONO_EHIP;
+  return hipStreamSynchronize((hipStream_t)stream) == hipSuccess ? MONO_OK : MONO_EHIP;
+}
+
 int mono_filter_export(mono_table* t, uint32_t* d_words, uint64_t first, uint64_t count, void* stream) {
   if (!t || first + count > t->view.n_filter || (count && !d_words)) return MONO_EINVAL;
   if (launch_filter_export(t->view, d_words, first, count, (hipStream_t)stream) != hipSuccess) return MONO_EHIP;

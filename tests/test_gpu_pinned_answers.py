@@ -24,3 +24,30 @@ def test_kept_exports_do_not_pin_the_host_without_bound(monkeypatch):
     gc.collect()
     assert pinned(tab.mono_table_export())
     tab.close()
+
+
+@pytest.mark.parametrize("words", [(1,), (3, 0, 4), (5, 1023, 1024, 4097), (262145, 7, 1, 2, 3, 4, 8, 65536)])
+def test_arrays_reach_the_host_whole_and_nothing_beside_them(words):
+    from paper_2209_07663_amd import binding
+    dev = torch.device("cuda:0")
+    names = ["a%d" % i for i in range(len(words))]
+    src = {k: torch.randint(-2 ** 31, 2 ** 31, (n,), dtype=torch.int32, device=dev) for k, n in zip(names, words)}
+    room = {k: torch.full((n + 16,), 77, dtype=torch.int32, pin_memory=True) for k, n in zip(names, words)}
+    assert binding._copy_to_host(src, room)
+    for k, n in zip(names, words):
+        assert (room[k][:n] == src[k].cpu()).all() and (room[k][n:] == 77).all()
+
+
+def test_what_the_copy_does_not_take_goes_the_other_way():
+    from paper_2209_07663_amd import binding
+    dev = torch.device("cuda:0")
+    x = torch.arange(64, dtype=torch.int32, device=dev)
+    pinned, pageable = torch.zeros(65, dtype=torch.int32, pin_memory=True), torch.zeros(65, dtype=torch.int32)
+    small = torch.zeros(7, dtype=torch.uint8, device=dev)
+    for src, to in ((x, pageable), (x[1:], pinned), (x, pinned[1:]), (small, pinned), (x[::2], pinned)):
+        assert not binding._copy_to_host({"x": src}, {"x": to})
+    assert not binding._copy_to_host({str(i): x for i in range(9)}, {str(i): pinned for i in range(9)})
+    torch.cuda.synchronize()
+    assert not pinned.any() and not pageable.any()
+    got = binding._to_numpy({"x": x[1:]})["x"]
+    assert (got == torch.arange(1, 64).numpy()).all()
