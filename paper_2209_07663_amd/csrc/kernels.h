@@ -46,7 +46,9 @@ constexpr SortShape sort_shape_for(uint32_t hwm_bound) {
 // (Large tiles only hold more LDS and leave fewer blocks to a compute unit: seg_reduce + combine of 5.8 M pairs of
 // dim 32 take 225 / 228 / 214 / 220 us with tiles of 4096 / 2048 / 1024 / 512 pairs.)
 constexpr uint32_t kReduceTile = 1024;
-constexpr uint64_t kTilesWanted = 2048;
+// (2048 blocks are a little more than the 1792 that run at a time, whose last ones ran alone: a million pairs of bf16 dim 64 in
+// 2048 tiles 74 us, in 4096 58.  But not many more than it takes: 690 K of dim 36 in 2700 20 us, in 5400 25.)
+constexpr uint64_t kTilesWanted = 2560;
 inline uint32_t reduce_tile(uint64_t n, uint32_t gpb) {
   const uint32_t least = 8 * gpb < 256 ? 8 * gpb : 256;
   uint32_t tile = kReduceTile;

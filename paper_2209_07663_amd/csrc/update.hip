@@ -29,6 +29,7 @@ namespace mono {
 
 constexpr uint32_t kHeadFlag = 0x80000000u;
 constexpr uint32_t kReduceWaves = 4;  // waves of a block of seg_reduce
+constexpr uint64_t kReduceFew = 1024; // (see seg_reduce_kernel)
 
 // seg_reduce reads and writes embedding rows past the caches where the batch's occurrences come to more bytes of
 // rows than the 256 MB cache behind the L2s holds: each row is used once and would not be there for the next
@@ -275,7 +276,9 @@ __device__ inline uint32_t tile_of_block(const uint32_t* __restrict__ order, uin
 // GLOG = log2(lanes per row), SEG = pieces of four elements per lane (1 unless GLOG == 6).  A block of 256
 // threads owns a tile of `tile` consecutive sorted pairs, a group an equal chunk of it; the host picks the size
 // of the tile so that small batches still fill the machine.
-template <typename E, int GLOG, int SEG, bool PAST>
+// FEW: there are no more tiles than kReduceFew, which all run at a time with either number of waves a SIMD, so that a chunk's
+// pairs are all asked for together (26 K pairs of dim 32 8.6 and 9.2 us, 1600 of bf16 dim 48 1.2 less).
+template <typename E, int GLOG, int SEG, bool PAST, bool FEW>
 __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint2* __restrict__ pair_a,
                                                          const uint2* __restrict__ pair_b, uint64_t n,
                                                          const float* __restrict__ grad, float lr, float eps,
@@ -287,11 +290,19 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
   using Vec = RowVec<SEG>;
   constexpr uint32_t group = 1u << GLOG, gpb = 256u >> GLOG;  // groups (= chunks) per block
   const uint32_t chunk = tile >> (8 - GLOG);
-  // gradient rows in flight per lane, each with the embedding row it may end in.  Rows in pieces: four, bf16 two (update of
-  // 400 K pairs with two and with four, of dim 512, 768, 1024: fp32 309 / 307, 474 / 466, 628 / 610 us, with hot rows
+  // Gradient rows in flight per lane, each with the embedding row it may end in.  Eight where rows go past the caches, which is
+  // bound by memory; else four, which leave registers for seven waves a SIMD instead of four: such a kernel waits and computes
+  // in turn (with eight and with four, us: 500 K pairs of bf16 dim 128 54 and 43, 945 K of dim 64 82 and 72, 755 K of dim 36 91
+  // and 84; past the caches 6.8 M of fp32 dim 32 188 and 193, 26 M of dim 64 1500 and 1527).  Rows in pieces: four, bf16 two
+  // (update of 400 K pairs with two and with four, of dim 512, 768, 1024: fp32 309 / 307, 474 / 466, 628 / 610 us, with hot rows
   // 267 / 260, 382 / 365, 498 / 476; bf16 255 / 314, 387 / 473, 535 / 738.  Batches of up to 98 K pairs the same way or
   // within 2 us)
-  constexpr int kBatch = SEG > 1 ? (sizeof(E) == 2 ? 2 : 4) : ((int)group < 8 ? (int)group : 8);
+  constexpr int kMany = PAST || FEW ? 8 : 4;
+  constexpr int kBatch = SEG > 1 ? (sizeof(E) == 2 ? 2 : 4) : ((int)group < kMany ? (int)group : kMany);
+  // Gradient rows in flight where no run ends among them, and no embedding row is wanted: what hot rows are, mostly (690 K
+  // pairs of dim 36, many of them of hot rows: 23.3 -> 20.4 us; 26 M of dim 64 1524 -> 1500).  Not for rows in pieces (98 K
+  // pairs of bf16 dim 512 48 -> 50), nor of up to 16 elements, whose chunks are short (204 K of dim 16 11.9 -> 12.8).
+  constexpr int kLong = SEG > 1 || group < 8 || FEW ? 0 : 8;
   // The tile's sorted pairs, and the rows of the pairs before and after it.  Where neither the place of the sort's result nor the
   // order of the tiles is the device's to say they are asked for beside the words that tell how many pairs remain: what lies
   // behind those is read, and left out below.
@@ -366,7 +377,24 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     bool head_in = first_head_in;
     E* rows = reinterpret_cast<E*>(t.rows);
     const float inv_dim = 1.0f / (float)t.dim;
-    for (uint32_t p0 = 0; p0 < count; p0 += kBatch) {  // position of the batch in the chunk
+    for (uint32_t p0 = 0; p0 < count;) {  // position of the batch in the chunk
+      // nothing ends in the next kLong pairs of any group of the wave (rows ascend): only gradients are read
+      const uint32_t row = mine[p0].x;
+      if (kLong > 0 && !__ballot(p0 + kLong > count || row != (p0 + kLong < count ? mine[p0 + kLong].x : after))) {
+        Vec v[kLong > 0 ? kLong : 1];
+#pragma unroll
+        for (int u = 0; u < kLong; ++u)
+          v[u] = load_vec<SEG>(g4 + (uint64_t)mine[p0 + u].y * dim4, l, row < hwm && active);
+        if (row != run) {
+          run = row;
+          head_in = true;
+          sum.zero();
+        }
+#pragma unroll
+        for (int u = 0; u < kLong; ++u) sum.add(v[u]);
+        p0 += kLong;
+        continue;
+      }
       uint32_t kx[kBatch + 1], ky[kBatch];
       Vec v[kBatch], w[kBatch];
       float a[kBatch];
@@ -414,6 +442,7 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
           }
         }
       }
+      p0 += kBatch;
     }
     if (after == run && run < hwm) {
       b_row = run;
@@ -608,14 +637,16 @@ hipError_t launch_apply_grad_adagrad(const TableView& t, const UpdateWorkspace& 
                 dim3(kOrderThreads), t.ctl, ws.pair_a, ws.pair_b, (uint32_t)n_tiles, tile, n_bags, launched, max_bits, ws.hist,
                 order);
   }
-#define MONO_SEG_REDUCE_AS(E, GLOG, SEG, PAST)                                                                        \
-  MONO_LAUNCH_SMEM(prof, K_SEG_REDUCE, stream, (seg_reduce_kernel<E, GLOG, SEG, PAST>), grid, block, lds_reduce, t,     \
+#define MONO_SEG_REDUCE_AS(E, GLOG, SEG, PAST, FEW)                                                                   \
+  MONO_LAUNCH_SMEM(prof, K_SEG_REDUCE, stream, (seg_reduce_kernel<E, GLOG, SEG, PAST, FEW>), grid, block, lds_reduce, t, \
                    ws.pair_a, ws.pair_b, n, d_grad, lr, eps, ws.part, ws.part_row, tile, launched, max_bits, order)
 #define MONO_SEG_REDUCE(E, GLOG, SEG)                                       \
   if (n * t.dim * sizeof(E) > kRowsCached) {                                \
-    MONO_SEG_REDUCE_AS(E, GLOG, SEG, true);                                 \
+    MONO_SEG_REDUCE_AS(E, GLOG, SEG, true, false);                          \
+  } else if (n_tiles <= kReduceFew) {                                       \
+    MONO_SEG_REDUCE_AS(E, GLOG, SEG, false, (SEG == 1 && GLOG >= 3));       \
   } else {                                                                  \
-    MONO_SEG_REDUCE_AS(E, GLOG, SEG, false);                                \
+    MONO_SEG_REDUCE_AS(E, GLOG, SEG, false, false);                         \
   }
 #define MONO_COMBINE(E, SEG, BLOCK)                                                                                     \
   MONO_LAUNCH_SMEM(prof, K_COMBINE, stream, (combine_kernel<E, SEG, BLOCK>), grid, dim3(BLOCK), lds_combine, t, n_tiles, \
