@@ -51,6 +51,7 @@ constexpr int kOrderDone = 17;              // Control::scratch slots: blocks of
 constexpr int kOrdered = 18;                // row (zero between calls); 1 + tiles of several rows if seg_reduce is to take that order
 constexpr int kMissTag = 7;                 // Control::scratch slots: tag of the latest call in which an occurrence missed,
 constexpr int kDuplicateTag = 8;            // and of the latest one that has duplicates of admitted keys to resolve
+constexpr int kElectedTag = 19;             // Control::scratch slot: tag of the latest call in which an occurrence was elected
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
 constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
 constexpr int kFreeBefore = 14;             // Control::scratch slot: rows that were free when the running call began

@@ -435,6 +435,7 @@ __global__ __launch_bounds__(kElectBlock, 8) void admit_elect_kernel(TableView t
     uint32_t total = 0;  // (both halves: at most kElectBlock * kPer each)
     for (int w = 0; w < kElectWaves; ++w) total += wave_cnt[w];
     block_base = total & 0xFFFFu ? atomicAdd(&t.win_cnt[list * kWinStride], total & 0xFFFFu) : 0u;
+    if (total & 0xFFFFu) t.ctl->scratch[kElectedTag] = epoch;  // (an ordinary store, as of kMissTag)
     if (sample_every && blockIdx.x % sample_every == 0 && total >> 16)
       atomicAdd(&t.ctl->scratch[kSampledMisses], (unsigned long long)(total >> 16));
   }
@@ -485,6 +486,13 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   if (threadIdx.x == 0) s_waiting = 0;
   __syncthreads();
   const uint32_t lane = lane_id(), wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (t.ctl->scratch[kElectedTag] != epoch) {  // nothing to place or to settle (a duplicate needs an elected occurrence)
+    if (kAll && blockIdx.x == 0 && threadIdx.x == 0) {
+      if (t.hwm_mail && epoch % kPostEvery == 0) post_hwm(t, epoch, t.ctl->hwm);
+      note_sample(t, enough);
+    }
+    return;
+  }
   // (kAll) an occurrence for every thread, at the end of the grid where the others have elected ones (the launch has a thread
   // for every occurrence at least).  What is left of an earlier state of the word does no harm here.
   const uint64_t i = (uint64_t)(gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x;
@@ -493,13 +501,6 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
   const uint32_t unit = src.seen ? kAgeLook : sweep_unit(step, t.sweep_q);
   // inclusive prefix of the sub-list fills, one list per lane
   const uint32_t inc = wave_sums(t.win_cnt[lane * kWinStride]), total = lane_value(inc, 63);
-  if (total == 0) {  // nothing to place or to settle (a duplicate needs an elected occurrence)
-    if (kAll && blockIdx.x == 0 && threadIdx.x == 0) {
-      if (t.hwm_mail && epoch % kPostEvery == 0) post_hwm(t, epoch, t.ctl->hwm);
-      note_sample(t, enough);
-    }
-    return;
-  }
   const int32_t free0 = (int32_t)(uint32_t)t.ctl->scratch[kFreeBefore];
   if (kAll && blockIdx.x == 0 && threadIdx.x == 0) {
     settle_call(t, total, free0, t.ctl->hwm, epoch);
