@@ -551,7 +551,7 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
         rows_out[e.occ] = found;
       if (row != kNoRow) {
         const unsigned long long meta = make_meta(row, src.seen ? src.seen[e.occ] : step);
-        if (!claim_free(t, k, meta, unit)) {
+        if (!claim_free<kAll>(t, k, meta, unit)) {
           const uint32_t at = atomicAdd(&s_waiting, 1u);
           s_key[at] = k;
           s_meta[at] = meta;
