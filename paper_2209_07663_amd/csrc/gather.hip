@@ -186,9 +186,10 @@ __global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src s
   // phase 2: group <-> bag, one bag per group and round
   const uint32_t group = 1u << group_log2, l = lane & (group - 1u), g = lane >> group_log2;
   const uint32_t bags_per_round = 64u >> group_log2, rounds = (1u << bags_log2) >> (6u - group_log2);
-  // Short bags: a round keeps only one or two rows per lane in flight, so as many rounds are issued together as have kIds rows.
+  // Short bags: a round keeps only one or two rows per lane in flight, so as many rounds are issued together as have kIds rows
+  // (four where two are in flight else: the registers are there, and one-hot bags of uniform IDs took 2 to 5 % longer with two).
   const auto short_bags = [&](auto longest) {
-    constexpr int kShort = decltype(longest)::value, kRoundsTogether = kIds / kShort;
+    constexpr int kShort = decltype(longest)::value, kRoundsTogether = (kIds < 4 ? 4 : kIds) / kShort;
     const bool active = l * N < dim;
     for (uint32_t q0 = 0; q0 < rounds; q0 += kRoundsTogether) {
       Row v[kRoundsTogether][kShort];
@@ -331,6 +332,17 @@ inline bool qr_takes_eight(uint64_t n, uint64_t n_bags, uint32_t dim, bool bf16)
   return n / n_bags >= bag;
 }
 
+// Two IDs' rows in flight, of fp32 rows that eight lanes or more share, where the chip is full twice over: each read is random, and
+// eight waves a SIMD that wait for four rows each come further than six that wait for eight.  Bags of one, zero to three and
+// four on average, four IDs and two, us: 2 M Zipf IDs of dim 32 108 / 103, 161 / 145, 93 / 85, of dim 128 366 / 353, 460 / 395,
+// 252 / 241, uniform ones 142 / 140, 171 / 159, 129 / 129 and 477 / 484, 502 / 480, 375 / 376; 300 K of dim 512, Zipf, 251 / 220,
+// 273 / 231, 155 / 153; 6.8 M of dim 32 in bags of four 281 / 262.  Fewer waves: 300 K of dim 32 18.7 / 20.0, 16.5 / 17.1; rows of
+// fewer lanes: 6 M of dim 16 in bags of four 253 / 261.
+inline bool qr_takes_two(uint64_t n_bags, uint32_t dim) {
+  const GatherShape four(dim, 4, n_bags, 4);
+  return four.group_log2 >= 3 && four.waves >= 2 * QuotRemRows<float, 4, 4>::kHeld;
+}
+
 hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t log2_rows, uint32_t dim, bool bf16,
                                  const int64_t* d_ids, uint64_t n, const int64_t* d_offsets, uint64_t n_bags,
                                  float* d_out, hipStream_t stream) {
@@ -339,8 +351,9 @@ hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t
   const auto queue = [&](const auto& src) { return queue_gather(src, d_offsets, n_bags, n, dim, d_out, stream, nullptr); };
   if (!bf16) {
     const float *rem = (const float*)d_rem, *quot = (const float*)d_quot;
-    return eight ? queue(QuotRemRows<float, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows})
-               : queue(QuotRemRows<float, 4, 4>{rem, quot, d_ids, log2_rows});
+    if (eight) return queue(QuotRemRows<float, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows});
+    return qr_takes_two(n_bags, dim) ? queue(QuotRemRows<float, 4, 2>{rem, quot, d_ids, log2_rows})
+                                     : queue(QuotRemRows<float, 4, 4>{rem, quot, d_ids, log2_rows});
   }
   const uint16_t *rem = (const uint16_t*)d_rem, *quot = (const uint16_t*)d_quot;
   return eight ? queue(QuotRemRows<uint16_t, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows})

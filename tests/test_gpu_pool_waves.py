@@ -85,3 +85,18 @@ def test_bags_of_one_or_two(dim, bf16, longest):
         _check(mono_qr_gather_pool(tabs[0], tabs[1], ids, offs),
                (tabs[0].double()[ids_in % (1 << m)] + tabs[1].double()[ids_in >> m]) * inside, lens)
     tab.close()
+
+
+@pytest.mark.parametrize("dim,bags", [(32, 12288 * 32 - 31), (64, 12288 * 16 - 16), (256, 12288 * 4 + 3)])
+def test_two_tables_full_chip(dim, bags):
+    """On either side of the size from which two IDs of a bag are in flight."""
+    from paper_2209_07663_amd.binding import mono_qr_gather_pool
+    dev, m = torch.device("cuda:0"), 9
+    g = torch.Generator(device=dev).manual_seed(dim)
+    tabs = [torch.randn((1 << m, dim), device=dev, generator=g) for _ in range(2)]
+    for average in (1, 2, 5):
+        lens, offs, ids = _batch(bags, average, 1 << 2 * m, dev)
+        inside = ((ids >= 0) & (ids < 1 << 2 * m))[:, None]
+        at = ids.clamp(0, (1 << 2 * m) - 1)
+        _check(mono_qr_gather_pool(tabs[0], tabs[1], ids, offs),
+               (tabs[0].double()[at % (1 << m)] + tabs[1].double()[at >> m]) * inside, lens)
