@@ -115,7 +115,7 @@ struct TableRows {
 
 // kIds_: IDs of a bag whose rows, two each, are in flight together.  Four: with eight their registers leave four waves to
 // a SIMD instead of six (bf16: five and eight).  Eight where bags are long, on average, since each step of the walk waits
-// for the one before (see kQrBag).
+// for the one before (see kQrBag); two in large calls (see qr_takes_two).
 template <typename E, int N_, int kIds_>
 struct QuotRemRows {
   static constexpr int N = N_, kIds = kIds_;
