@@ -9,7 +9,9 @@
 // of kIdsInRegs indices, the next step's indices requested before this step's rows are waited for (bags
 // of 23 IDs on average, dim 36: 144 us per launch when the rest of a long bag was read one row at a time,
 // 20 us so).  A wave whose bags all hold at most two IDs, or one (one-hot slots), issues four or eight rounds of row reads
-// together instead (a million bags of one ID, bf16 of dim 64, us: 81 round by round, 67 four together, 61 eight).
+// together instead (a million bags of one ID, bf16 of dim 64, us: 81 round by round, 67 four together, 61 eight; fp32 rows, 4 M
+// uniform ones, of dim 32 52 two by two, 49 one by one, which is what eight rounds are if the rows are not held, and 44
+// together, of dim 64 97, 89 and 83; bags of two, dim 32, 78 two by two and 65; 300 K bags of one 15.8, 14.5 and 15.0).
 //
 // How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
 // thousand of them: 64, where that still leaves kWavesWanted waves (the index loads are then as coalesced as they can be),
@@ -56,6 +58,22 @@ template <>
 struct Piece<float, 4> {
   float4 v;
   __device__ void clear() { v = make_float4(0.f, 0.f, 0.f, 0.f); }
+  __device__ void hold() {}
+  __device__ void add_to(float* a) const {
+    a[0] += v.x;
+    a[1] += v.y;
+    a[2] += v.z;
+    a[3] += v.w;
+  }
+};
+// The same, held between the read and the sum: the compiler must not know any more that an absent row is zero.  Where it knows,
+// and the sum begins with the row, it adds the row up in the branch that reads it, which waits for it there: reads that were to
+// be in flight together wait for one another.  (One value of four elements, which is read into where it stays.)
+struct HeldPiece {
+  typedef float Bits __attribute__((ext_vector_type(4)));
+  Bits v;
+  __device__ void clear() { v = Bits(0.f); }
+  __device__ void hold() { __asm__ volatile("" : "+v"(v)); }
   __device__ void add_to(float* a) const {
     a[0] += v.x;
     a[1] += v.y;
@@ -71,6 +89,7 @@ template <>
 struct Piece<uint16_t, 4> {
   uint2 v;
   __device__ void clear() { v = make_uint2(0u, 0u); }
+  __device__ void hold() {}  // (bf16 elements are widened before they are added, outside the branch)
   __device__ void add_to(float* a) const {
     add_bf16_pair(v.x, a);
     add_bf16_pair(v.y, a + 2);
@@ -80,6 +99,7 @@ template <>
 struct Piece<uint16_t, 8> {
   uint4 v;
   __device__ void clear() { v = make_uint4(0u, 0u, 0u, 0u); }
+  __device__ void hold() {}
   __device__ void add_to(float* a) const {
     add_bf16_pair(v.x, a);
     add_bf16_pair(v.y, a + 2);
@@ -88,8 +108,8 @@ struct Piece<uint16_t, 8> {
   }
 };
 
-template <typename E, int N>
-__device__ inline void load_piece(Piece<E, N>& p, const E* rows, uint64_t row, uint32_t dim, uint32_t col) {
+template <typename P, typename E>
+__device__ inline void load_piece(P& p, const E* rows, uint64_t row, uint32_t dim, uint32_t col) {
   p.v = *reinterpret_cast<const decltype(p.v)*>(rows + row * dim + col);
 }
 
@@ -103,8 +123,9 @@ struct TableRows {
   const int32_t* idx;
   uint32_t cap;
   struct Row {
-    Piece<E, N> p;
+    std::conditional_t<sizeof(E) == 4, HeldPiece, Piece<E, N>> p;
     __device__ void clear() { p.clear(); }
+    __device__ void hold() { p.hold(); }
     __device__ void add_to(float* a) const { p.add_to(a); }
   };
   __device__ Id none() const { return -1; }
@@ -131,6 +152,10 @@ struct QuotRemRows {
     __device__ void clear() {
       r.clear();
       q.clear();
+    }
+    __device__ void hold() {
+      r.hold();
+      q.hold();
     }
     __device__ void add_to(float* a) const {  // E_r + E_q first, then the bag's sum
       float e[N];
@@ -207,7 +232,10 @@ __global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src s
       for (int rr = 0; rr < kRoundsTogether; ++rr) {
         float acc[N] = {0.f};
 #pragma unroll
-        for (int j = 0; j < kShort; ++j) v[rr][j].add_to(acc);
+        for (int j = 0; j < kShort; ++j) {
+          v[rr][j].hold();
+          v[rr][j].add_to(acc);
+        }
         const uint64_t bag = bag_base + (q0 + rr) * bags_per_round + g;
         if (q0 + rr < rounds && bag < n_bags && active) store_pooled<N>(out + bag * dim + l * N, acc, past_caches);
       }
@@ -243,7 +271,10 @@ __global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src s
           for (int j = 0; j < kIds; ++j) rid[j] = c + j < blen ? src.at(bs + c + j) : src.none();
         }
 #pragma unroll
-        for (int j = 0; j < kIds; ++j) v[j].add_to(acc);
+        for (int j = 0; j < kIds; ++j) {
+          v[j].hold();
+          v[j].add_to(acc);
+        }
         if (!more) break;
       }
       if (bag < n_bags && active) store_pooled<N>(out + bag * dim + col, acc, past_caches);
