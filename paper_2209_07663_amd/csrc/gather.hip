@@ -134,11 +134,13 @@ struct TableRows {
   __device__ void fetch(Row& x, Id r, uint32_t dim, uint32_t col) const { load_piece(x.p, rows, (uint32_t)r, dim, col); }
 };
 
-// kIds_: IDs of a bag whose rows, two each, are in flight together.  Four: with eight their registers leave four waves to
-// a SIMD instead of six (bf16: five and eight).  Eight where bags are long, on average, since each step of the walk waits
-// for the one before (see kQrBag); two in large calls (see qr_takes_two).
-template <typename E, int N_, int kIds_>
+// kIds_: IDs of a bag whose rows, two each, are asked for in a step of the walk.  Four: with eight their registers leave four
+// waves to a SIMD instead of six (bf16: five and eight).  Eight where bags are long, on average, since each step of the walk
+// waits for the one before (see kQrBag).  HELD: they are in flight together (see HeldPiece); fp32 rows that are not wait for one
+// another, ID by ID, and only the IDs of the next step come beside them (see qr_holds).
+template <typename E, int N_, int kIds_, bool HELD = false>
 struct QuotRemRows {
+  static_assert(!HELD || (sizeof(E) == 4 && N_ == 4), "bf16 rows are in flight together anyway");
   static constexpr int N = N_, kIds = kIds_;
   static constexpr uint64_t kHeld = kIds_ == 4 && sizeof(E) == 4 ? 6144 : 0;
   static constexpr int kSimdWaves = 1;
@@ -148,7 +150,7 @@ struct QuotRemRows {
   const int64_t* ids;
   uint32_t m;
   struct Row {
-    Piece<E, N> r, q;
+    std::conditional_t<HELD, HeldPiece, Piece<E, N>> r, q;
     __device__ void clear() {
       r.clear();
       q.clear();
@@ -211,10 +213,9 @@ __global__ __launch_bounds__(256, Src::kSimdWaves) void gather_pool_kernel(Src s
   // phase 2: group <-> bag, one bag per group and round
   const uint32_t group = 1u << group_log2, l = lane & (group - 1u), g = lane >> group_log2;
   const uint32_t bags_per_round = 64u >> group_log2, rounds = (1u << bags_log2) >> (6u - group_log2);
-  // Short bags: a round keeps only one or two rows per lane in flight, so as many rounds are issued together as have kIds rows
-  // (four where two are in flight else: the registers are there, and one-hot bags of uniform IDs took 2 to 5 % longer with two).
+  // Short bags: a round keeps only one or two rows per lane in flight, so as many rounds are issued together as have kIds rows.
   const auto short_bags = [&](auto longest) {
-    constexpr int kShort = decltype(longest)::value, kRoundsTogether = (kIds < 4 ? 4 : kIds) / kShort;
+    constexpr int kShort = decltype(longest)::value, kRoundsTogether = kIds / kShort;
     const bool active = l * N < dim;
     for (uint32_t q0 = 0; q0 < rounds; q0 += kRoundsTogether) {
       Row v[kRoundsTogether][kShort];
@@ -363,13 +364,17 @@ inline bool qr_takes_eight(uint64_t n, uint64_t n_bags, uint32_t dim, bool bf16)
   return n / n_bags >= bag;
 }
 
-// Two IDs' rows in flight, of fp32 rows that eight lanes or more share, where the chip is full twice over: each read is random, and
-// eight waves a SIMD that wait for four rows each come further than six that wait for eight.  Bags of one, zero to three and
-// four on average, four IDs and two, us: 2 M Zipf IDs of dim 32 108 / 103, 161 / 145, 93 / 85, of dim 128 366 / 353, 460 / 395,
-// 252 / 241, uniform ones 142 / 140, 171 / 159, 129 / 129 and 477 / 484, 502 / 480, 375 / 376; 300 K of dim 512, Zipf, 251 / 220,
-// 273 / 231, 155 / 153; 6.8 M of dim 32 in bags of four 281 / 262.  Fewer waves: 300 K of dim 32 18.7 / 20.0, 16.5 / 17.1; rows of
-// fewer lanes: 6 M of dim 16 in bags of four 253 / 261.
-inline bool qr_takes_two(uint64_t n_bags, uint32_t dim) {
+// fp32 rows that eight lanes or more share are held where the chip is full twice over.  Bags of one, of zero to three, of four,
+// Poisson(5), and of one but for every 512th, which holds 200; not held and held, us.  1.6 M of dim 32: uniform IDs 95 / 92, 126 /
+// 121, 268 / 271, 340 / 338, 452 / 297, Zipf 70 / 69, 89 / 87, 176 / 173, 250 / 217, 379 / 260.  197 K of dim 128: 55 / 48, 78 / 73,
+// 169 / 153, 207 / 191, 190 / 140 and 42 / 39, 62 / 55, 109 / 95, 138 / 117, 160 / 116.  98 K of dim 512: 94 / 93, 113 / 111,
+// 255 / 256, 313 / 314, 609 / 455 and 73 / 73, 97 / 91, 182 / 172, 223 / 214, 488 / 370.  6.8 M IDs in bags of four, dim 32, Zipf,
+// 217 / 206.  The most that is lost is 3 %, of uniform IDs (197 K bags of two, dim 256, 141 / 146).  (Two IDs a step, not held, let
+// eight waves share a SIMD: 6 % less than four for Poisson bags of Zipf IDs, but 5 to 8 % more for the few long ones.)
+// Elsewhere rows are not held: fewer waves take up to 5 % longer so where rows are wide and IDs uniform (6 K bags of five, dim
+// 1024, 42.7 / 43.0, Zipf 30.4 / 32.0), and rows of fewer lanes up to 2 %; long bags of few waves would gain (3333 of 30, dim 32,
+// 15.0 / 9.4).
+inline bool qr_holds(uint64_t n_bags, uint32_t dim) {
   const GatherShape four(dim, 4, n_bags, 4);
   return four.group_log2 >= 3 && four.waves >= 2 * QuotRemRows<float, 4, 4>::kHeld;
 }
@@ -383,8 +388,8 @@ hipError_t launch_qr_gather_pool(const void* d_rem, const void* d_quot, uint32_t
   if (!bf16) {
     const float *rem = (const float*)d_rem, *quot = (const float*)d_quot;
     if (eight) return queue(QuotRemRows<float, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows});
-    return qr_takes_two(n_bags, dim) ? queue(QuotRemRows<float, 4, 2>{rem, quot, d_ids, log2_rows})
-                                     : queue(QuotRemRows<float, 4, 4>{rem, quot, d_ids, log2_rows});
+    return qr_holds(n_bags, dim) ? queue(QuotRemRows<float, 4, 4, true>{rem, quot, d_ids, log2_rows})
+                                 : queue(QuotRemRows<float, 4, 4>{rem, quot, d_ids, log2_rows});
   }
   const uint16_t *rem = (const uint16_t*)d_rem, *quot = (const uint16_t*)d_quot;
   return eight ? queue(QuotRemRows<uint16_t, 4, kIdsInRegs>{rem, quot, d_ids, log2_rows})

@@ -89,7 +89,7 @@ def test_bags_of_one_or_two(dim, bf16, longest):
 
 @pytest.mark.parametrize("dim,bags", [(32, 12288 * 32 - 31), (64, 12288 * 16 - 16), (256, 12288 * 4 + 3)])
 def test_two_tables_full_chip(dim, bags):
-    """On either side of the size from which two IDs of a bag are in flight."""
+    """On either side of the size from which the rows of four IDs are held in flight together."""
     from paper_2209_07663_amd.binding import mono_qr_gather_pool
     dev, m = torch.device("cuda:0"), 9
     g = torch.Generator(device=dev).manual_seed(dim)

@@ -38,6 +38,7 @@ def _reads_together(code):
 
 @pytest.mark.parametrize("source,runs", [
     ("9TableRowsIfLi4E", [8, 8, 8]),             # bags of any length, of up to two IDs, of one: eight rows each
+    ("11QuotRemRowsIfLi4ELi4ELb1E", [8, 8, 8]),  # four IDs, two rows each
 ])
 def test_fp32_rows_are_read_together(gather, source, runs):
     code = [text for name, text in gather.items() if source in name]
