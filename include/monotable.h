@@ -252,7 +252,8 @@ int mono_export_sorted(mono_table* t, int touched_only, int64_t* d_keys, int32_t
 
 /* Copies `parts` arrays (at most MONO_COPY_PARTS) from the device to pinned host memory that the device can write
  * (hipHostMalloc), all of them by one kernel, and waits for `stream`.  Sizes are whole 4-byte words, addresses 16-byte
- * aligned; MONO_EINVAL otherwise, or if a destination is no such memory (nothing was done). */
+ * aligned; MONO_EINVAL otherwise, or if a source is no memory of the stream's device, a destination no such memory, or the
+ * allocation of either ends before the array does (nothing was done). */
 #define MONO_COPY_PARTS 8
 int mono_copy_to_host(const void* const* d_from, void* const* h_to, const size_t* bytes, uint32_t parts, void* stream);
 

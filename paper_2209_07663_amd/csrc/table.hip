@@ -257,6 +257,20 @@ hipError_t read_control(mono_table* t, Control* c, hipStream_t stream) {
   return e;
 }
 
+// Does one allocation of this type that the device can reach hold all `bytes` from `p` on?  (The runtime's errors about memory
+// that it does not know are answered here.)
+bool holds(const void* p, size_t bytes, hipMemoryType type, hipPointerAttribute_t* at) {
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (hipPointerGetAttributes(at, p) != hipSuccess || at->type != type || !at->devicePointer ||
+      hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)at->devicePointer) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const size_t before = (size_t)((const char*)at->devicePointer - (const char*)base);
+  return before <= size && bytes <= size - before;
+}
+
 void note_stream(mono_table* t, void* stream) {
   t->last_stream = (hipStream_t)stream;
   t->used_stream = true;
@@ -657,19 +671,19 @@ int mono_table_migrate(mono_table* dst, mono_table* src, uint32_t generation, vo
 int mono_copy_to_host(const void* const* d_from, void* const* h_to, const size_t* bytes, uint32_t parts, void* stream) {
   static_assert(kCopyParts == MONO_COPY_PARTS, "the kernel takes what the interface says");
   if (parts > MONO_COPY_PARTS || (parts && (!d_from || !h_to || !bytes))) return MONO_EINVAL;
+  hipDevice_t device = 0;
+  if (parts && hipStreamGetDevice((hipStream_t)stream, &device) != hipSuccess) return MONO_EHIP;
   CopyParts c = {};
   uint32_t n = 0;
   for (uint32_t p = 0; p < parts; ++p) {
     if (bytes[p] == 0) continue;
     if (bytes[p] % 4 || !d_from[p] || !h_to[p] || ((uintptr_t)d_from[p] | (uintptr_t)h_to[p]) % 16) return MONO_EINVAL;
-    hipPointerAttribute_t at;
-    if (hipPointerGetAttributes(&at, h_to[p]) != hipSuccess) {
-      (void)hipGetLastError();  // (memory that the runtime does not know: the error is answered here)
+    hipPointerAttribute_t from, to;
+    if (!holds(d_from[p], bytes[p], hipMemoryTypeDevice, &from) || from.device != device ||
+        !holds(h_to[p], bytes[p], hipMemoryTypeHost, &to))
       return MONO_EINVAL;
-    }
-    if (at.type != hipMemoryTypeHost || !at.devicePointer) return MONO_EINVAL;
     c.from[n] = d_from[p];
-    c.to[n] = at.devicePointer;
+    c.to[n] = to.devicePointer;
     c.words[n++] = bytes[p] / 4;
   }
   if (n && launch_copy_to_host(c, n, (hipStream_t)stream) != hipSuccess) return MONO_EHIP;

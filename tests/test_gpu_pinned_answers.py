@@ -1,4 +1,5 @@
 """Deltas that a program keeps stop taking pinned memory at the allowance, and start again once it lets go of them."""
+import ctypes
 import gc
 
 import pytest
@@ -51,3 +52,25 @@ def test_what_the_copy_does_not_take_goes_the_other_way():
     assert not pinned.any() and not pageable.any()
     got = binding._to_numpy({"x": x[1:]})["x"]
     assert (got == torch.arange(1, 64).numpy()).all()
+
+
+def test_what_is_too_short_or_in_the_wrong_place_is_refused_before_anything_runs():
+    from paper_2209_07663_amd import binding
+    lib, dev, most = binding.load_library(), torch.device("cuda:0"), 64 << 20
+    large, small = torch.full((most // 4,), 5, dtype=torch.int32, device=dev), torch.full((256,), 5, dtype=torch.int32, device=dev)
+    room, little, first = (torch.full((n,), 77, dtype=torch.int32, pin_memory=True) for n in (most // 4, 256, 256))
+    host, pageable = torch.full((256,), 5, dtype=torch.int32, pin_memory=True), torch.full((256,), 5, dtype=torch.int32)
+
+    def copy(src, to, nbytes):                                    # behind a part that is as it should be
+        pair = ctypes.c_void_p * 2
+        return lib.mono_copy_to_host(pair(small.data_ptr(), src.data_ptr()), pair(first.data_ptr(), to.data_ptr()),
+                                     (ctypes.c_size_t * 2)(1024, nbytes), 2, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    for src, to, nbytes in ((large, little, most), (small, room, most), (large, room, most + 4), (large, room, (1 << 64) - 4),
+                            (large[4:], room, most), (large, room[4:], most), (host, room, 1024), (pageable, room, 1024),
+                            (large, pageable, 1024), (large, small, 1024)):
+        assert copy(src, to, nbytes) == binding.MONO_EINVAL
+    torch.cuda.synchronize()
+    assert (first == 77).all() and (little == 77).all() and (room == 77).all()
+    assert copy(large[4:], room[4:], most - 16) == binding.MONO_OK
+    assert (first == 5).all() and (room[:4] == 77).all() and (room[4:] == 5).all()
