@@ -84,7 +84,9 @@ __global__ __launch_bounds__(kRangeThreads) void export_ranges_kernel(ExportWork
   const bool last = blockIdx.x == ranges - 1;
   const uint64_t end = last ? ~0ull : bounds[blockIdx.x + 1];  // (~0 is no key)
   uint64_t high = end;
-  while (low < end) {  // once, unless a range holds eight times the keys that it should: it is halved then
+  // Once, unless a range holds more keys than there is room for, eight times what a range of 64 K keys should and four times
+  // of 128 K: it is halved then, for as long as that takes.
+  while (low < end) {
     if (threadIdx.x == 0) s_count = s_below = 0;
     __syncthreads();
     uint32_t below = 0;

@@ -1,6 +1,6 @@
-"""Exports come sorted by key as unsigned numbers, by a radix sort on the device over the bits in which the keys
-differ: numbers of elements at the edges of its units (512 elements, or 2048), keys that differ everywhere, in the low bits only, in the
-top bits only, and a single key; attributes and rows stay with their key."""
+"""Exports come sorted by key as unsigned numbers: up to 131072 keys by counting, more by a radix sort over the bits in which
+the keys differ.  Numbers of elements at the edges of either and of the sort's units (512 elements, or 2048), keys that differ
+everywhere, in the low bits only, in the top bits only, and a single key; attributes and rows stay with their key."""
 import numpy as np
 import pytest
 import torch
@@ -17,13 +17,14 @@ def _keys(kind, n, rng):
     if kind == "low":
         return (np.arange(n, dtype=np.uint64) * np.uint64(3)) | np.uint64(1 << 62)
     if kind == "top":
-        return np.arange(n, dtype=np.uint64) << np.uint64(64 - 17)
+        return np.arange(n, dtype=np.uint64) << np.uint64(64 - max(17, (n - 1).bit_length()))
     return k ^ (k << np.uint64(1))                                      # all 64 bits
 
 
 @pytest.mark.parametrize("kind", ["all", "low", "top"])
 @pytest.mark.parametrize("n", [0, 1, 2, 2047, 2048, 2049, 70001])
 def test_exports_are_in_key_order(kind, n):
+    """Against the oracle, and what was trained against the whole.  (All of these are ranked.)"""
     from paper_2209_07663_amd.binding import Table
     dev, seed = torch.device("cuda:0"), 5
     tab = Table(1 << 17, 8, seed, max_ids=1 << 17, device=dev)
@@ -54,7 +55,7 @@ def test_exports_are_in_key_order(kind, n):
 @pytest.mark.parametrize("kind", ["all", "low"])
 @pytest.mark.parametrize("n", [511, 512, 513, 400000, 400001, 524289])
 def test_exports_around_the_edges_of_both_unit_sizes(kind, n):
-    """Units of 512 elements up to 400 000 exported keys, of 2048 beyond."""
+    """Units of 512 elements up to 400 000 exported keys, of 2048 beyond.  (512 keys and one more or less are ranked.)"""
     from paper_2209_07663_amd.binding import Table
     dev = torch.device("cuda:0")
     tab = Table(1 << 20, 4, 5, max_ids=1 << 20, device=dev)
@@ -93,4 +94,60 @@ def test_exports_that_are_ranked(kind, n):
     assert np.array_equal(d["last_seen"], 1 - np.isin(order, keys[first]).astype(np.uint32))
     assert (d["rows"] == tc.init_rows(d["keys"], 4, 7).astype(np.float32)).all()
     tc.check_placement(d, tab.capacity, 8, 7)
+    tab.close()
+
+
+@pytest.mark.parametrize("kind", ["all", "low", "top"])
+@pytest.mark.parametrize("n", [131073, 131584, 131585])
+def test_exports_that_are_just_too_large_to_be_ranked(kind, n):
+    """Whole units of 512 elements, one element more, and one beyond what is ranked: the keys that were trained, with room
+    for all but one of them and for all, and the whole table."""
+    from paper_2209_07663_amd.binding import Table
+    dev, rng = torch.device("cuda:0"), np.random.default_rng(n)
+    tab = Table(1 << 18, 4, 7, max_ids=1 << 18, device=dev)
+    keys = rng.permutation(_keys(kind, n, rng)).astype(np.int64)
+    rows = tab.mono_lookup_or_insert(torch.from_numpy(keys).to(dev), 3)
+    more = torch.from_numpy(_keys("low", 1001, rng).astype(np.int64) + 1).to(dev)     # (multiples of three and one; never trained)
+    tab.mono_lookup_or_insert(more, 4)
+    offs = torch.arange(n + 1, dtype=torch.int64, device=dev)
+    tab.mono_apply_grad_adagrad(rows, offs, torch.ones((n, 4), device=dev), 0.1, 1e-8)
+    order = np.argsort(keys.view(np.uint64))
+    assert tab.mono_export_touched(max_n=n - 1) == {"n": n}
+    touched, dump = tab.mono_export_touched(), tab.mono_table_export()
+    assert np.array_equal(touched["keys"], keys[order]) and np.array_equal(touched["row"], rows.cpu().numpy()[order])
+    assert (touched["acc"] == 1).all()
+    assert (dump["keys"].view(np.uint64)[1:] > dump["keys"].view(np.uint64)[:-1]).all() and dump["keys"].size == n + 1001
+    trained = np.isin(dump["keys"], keys)
+    assert np.array_equal(dump["keys"][trained], touched["keys"]) and np.array_equal(dump["rows"][trained], touched["rows"])
+    assert np.array_equal(dump["last_seen"], np.where(trained, 3, 4)) and (dump["acc"] == trained).all()
+    tc.check_placement(dump, tab.capacity, 8, 7)
+    tab.close()
+
+
+@pytest.mark.parametrize("spread", [20, 62])
+def test_a_range_with_more_keys_than_a_block_holds(spread):
+    """The sample that bounds the ranges is every 32nd of 8192 keys in the order of their slots: where those are the largest
+    keys of the table, the first range holds the 6144 others, three times what a block has room for, near together or not.
+    (All buckets of the first sub-table are full, and the other one is empty, so that the order is known.)"""
+    from paper_2209_07663_amd.binding import Table
+    dev, rng, capacity, seed = torch.device("cuda:0"), np.random.default_rng(spread), 1 << 14, 7
+    buckets = capacity // 16
+    small = np.unique(rng.integers(0, 1 << spread, 1 << 16).astype(np.uint64))
+    large = np.unique(rng.integers(1 << 62, 1 << 63, 1 << 16).astype(np.uint64) << np.uint64(1))
+    keys = []
+    for group, here in ((large, np.arange(0, buckets, 4)), (small, np.setdiff1d(np.arange(buckets), np.arange(0, buckets, 4)))):
+        group = rng.permutation(group)
+        at = tc.bucket_of(0, group, capacity, 8, seed).astype(np.int64)
+        keys += [group[at == b][:8] for b in here]
+    assert all(k.size == 8 for k in keys)
+    keys = rng.permutation(np.concatenate(keys)).view(np.int64)
+    tab = Table(capacity, 4, seed, max_ids=1 << 14, device=dev)
+    rows = tab.mono_lookup_or_insert(torch.from_numpy(keys).to(dev), 3).cpu().numpy()
+    d = tab.mono_table_export()
+    slot_of = dict(zip(d["keys"].tolist(), d["slot"].tolist()))
+    assert sorted(slot_of.values()) == list(range(8 * buckets))                       # (so no key is missing either)
+    assert all(k < 0 for k, slot in slot_of.items() if slot % 32 == 0) and (keys >= 0).sum() == 6144
+    order = np.argsort(keys.view(np.uint64))
+    assert np.array_equal(d["keys"], keys[order]) and np.array_equal(d["row"], rows[order])
+    assert (d["rows"] == tc.init_rows(d["keys"], 4, seed).astype(np.float32)).all() and (d["last_seen"] == 3).all()
     tab.close()
