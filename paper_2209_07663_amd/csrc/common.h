@@ -54,7 +54,8 @@ constexpr int kDuplicateTag = 8;            // and of the latest one that has du
 constexpr int kElectedTag = 19;             // Control::scratch slot: tag of the latest call in which an occurrence was elected
 constexpr int kSampledMisses = 11;          // Control::scratch slots: missing occurrences in the running call's sample (see
 constexpr int kCountersFirst = 12;          // MissSample); is the next call to look at counters before buckets?
-constexpr int kFreeBefore = 14;             // Control::scratch slot: rows that were free when the running call began
+constexpr int kFreeBefore = 14;             // Control::scratch slot: rows that were free when the running call began (free_n itself
+                                            // may be settled by one thread of insert_kernel while the others run)
 constexpr int kHotBins = 13;                // Control::scratch slot: rows with a bin of their own (see sort_split.hip)
 constexpr int kSweepDone = 6;               // Control::scratch slot: sub-lists, or blocks, that are done; of sweep_small also the keys
                                             // removed so far << 32 (zero between calls)

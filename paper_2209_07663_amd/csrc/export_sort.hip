@@ -7,8 +7,8 @@
 //   up to kRankMost    `rank`: sixteen lanes compare a key with all others, which lie in LDS, and it is written where it belongs
 //   up to kRangesMost  `rank` puts a sample in order, every eighth key of which begins a range of about 256 keys; `ranges`: a
 //                      block per range reads all keys, counts those before the range, collects the range's in LDS and ranks them
-// One launch and two, where the passes below are three for every eight bits: 42 K keys of a 2^40 space 51 -> 22 us; deltas of 125 to 17 K
-// keys, whole calls, 200-250 -> 115-165 us.
+// One launch and two, where the passes below are three for every eight bits: 42 K keys of a 2^40 space 51 -> 22 us; deltas of
+// 125 to 17 K keys, whole calls, 200-250 -> 115-165 us.
 // Larger ones by a stable LSD radix sort of (key, index) pairs, eight bits a pass, over the bits in which the keys differ at all
 // (IDs of a 2^40 space: five passes).  Per pass:
 //   hist     digit histogram of every unit of elements, bin-major
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(kThreads) void export_rank_kernel(ExportWorkspace w
 }
 
 // Range r holds the keys from bounds[r] on (the first: all) that are below bounds[r + 1] (the last: all).  A block reads all
-// keys from the L2, bound by the latency of that: sixteen waves, eight keys of a lane in flight (42 K keys, 256 blocks: 16 us, with
-// four waves 31).
+// keys from the L2, bound by the latency of that: sixteen waves, eight keys of a lane in flight (42 K keys, 256 blocks: 16 us,
+// with four waves 31).
 constexpr int kRangeThreads = 1024;
 __global__ __launch_bounds__(kRangeThreads) void export_ranges_kernel(ExportWorkspace ws, uint32_t n, uint32_t ranges,
                                                                  const uint64_t* __restrict__ bounds, ExportOut out) {
@@ -345,8 +345,8 @@ hipError_t launch_export_sort(const ExportWorkspace& ws, uint64_t n, uint64_t va
   const uint32_t ranked = ranges > 1 ? ranges * kOversample : (uint32_t)n;
   uint64_t* bounds = ranges > 1 ? ws.key[1] : nullptr;
   const uint32_t per_block = kThreads / kRankLanes;
-  hipLaunchKernelGGL(export_rank_kernel, dim3((ranked + per_block - 1) / per_block), dim3(kThreads), 0, stream, ws, (uint32_t)n / ranked, ranked, out,
-                     bounds);
+  hipLaunchKernelGGL(export_rank_kernel, dim3((ranked + per_block - 1) / per_block), dim3(kThreads), 0, stream, ws,
+                     (uint32_t)n / ranked, ranked, out, bounds);
   if (ranges > 1)
     hipLaunchKernelGGL(export_ranges_kernel, dim3(ranges), dim3(kRangeThreads), 0, stream, ws, (uint32_t)n, ranges, bounds, out);
   return hipGetLastError();

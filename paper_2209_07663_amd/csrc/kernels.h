@@ -46,8 +46,12 @@ constexpr SortShape sort_shape_for(uint32_t hwm_bound) {
 // (Large tiles only hold more LDS and leave fewer blocks to a compute unit: seg_reduce + combine of 5.8 M pairs of
 // dim 32 take 225 / 228 / 214 / 220 us with tiles of 4096 / 2048 / 1024 / 512 pairs.)
 constexpr uint32_t kReduceTile = 1024;
-// (2048 blocks are a little more than the 1792 that run at a time, whose last ones ran alone: a million pairs of bf16 dim 64 in
-// 2048 tiles 74 us, in 4096 58.  But not many more than it takes: 690 K of dim 36 in 2700 20 us, in 5400 25.)
+// (One number for kernels of which 1024 to 2048 blocks run at a time: of rows of 17 to 256 elements 1792 in bf16, seven waves a
+// SIMD, 1536 in fp32, and 1024 past the caches.  2048 tiles are a little more than the first, and their last blocks ran alone: a
+// million pairs of bf16 dim 64 in 2048 tiles 74 us, in 4096 58.  But not many more than it takes: 690 K of dim 36 in 2700 20
+// us, in 5400 25.  Where tiles are as small as they get there is a step beyond the blocks that run at a time all the same.
+// Updates of uniform rows, us: fp32 dim 32 in 1524 tiles, 390 K pairs, 49 and in 1563, 400 K, 53, bf16 dim 64 in 1641, 420 K,
+// 66 and in 1797, 460 K, 75.)
 constexpr uint64_t kTilesWanted = 2560;
 inline uint32_t reduce_tile(uint64_t n, uint32_t gpb) {
   const uint32_t least = 8 * gpb < 256 ? 8 * gpb : 256;

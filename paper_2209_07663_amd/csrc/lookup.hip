@@ -12,8 +12,8 @@
 //                 table's fill limit (else none is placed): take a row from the free stack by rank
 //                 (no atomics), insert the key (CAS on 64-bit key slots, eviction chain), note it
 //                 in its bucket's bound for the sweep, initialise the row with the whole wave
-//   resolve       (in batches of at most kElectSmall at the end of insert) duplicates of an admitted key pick up its
-//                 row, the counters are settled and the high-water mark of rows is reported to the host
+//   resolve       duplicates of an admitted key pick up its row, the counters are settled and the high-water mark of
+//                 rows is reported to the host (in batches of at most kElectSmall by insert, beside the placement)
 //
 // The same kernels restore snapshot records (RestoreSource): every record is a forced
 // admission whose row, accumulator and last-seen step come from the caller instead of from
@@ -118,7 +118,8 @@ constexpr uint64_t kProbeBlocksWanted = 1024, kProbeMaxTurns = 8;
 // Largest batch for which both buckets and the counter are asked for at once.  lookup_or_insert of uniform keys in a table of
 // 2^24 slots, one access after the other and at once, us: a third unknown and kept out, counters that age 20 K 15.1 / 11.8, 60 K
 // 16.3 / 14.4, 120 K 18.2 / 20.3, that do not 60 K 16.4 / 14.4, 120 K 19.2 / 18.4, 200 K 25.0 / 26.1; all known 20 K 8.8 / 9.0,
-// 60 K 12.5 / 13.0, 120 K 14.0 / 15.9, 200 K 16.2 / 22.4.
+// 60 K 12.5 / 13.0, 120 K 14.0 / 15.9, 200 K 16.2 / 22.4.  (The rule does not ask whether the call before missed: batches that are
+// all known lose 2 to 4 % of the kernel by it, of a call whose three launches take the host 12 us.)
 constexpr uint64_t kProbeSmall = 1u << 16;
 static_assert(kProbeSmall < 2 * kProbeBlock * kProbeBlocksWanted, "a key per thread");
 constexpr int kProbeTries = 8;  // slots of the set that a missing key looks at
@@ -468,12 +469,14 @@ __device__ inline void note_sample(const TableView& t, uint64_t enough) {
 // kAll (batches of at most kElectSmall): the duplicates of admitted keys take their rows here too.  The elected
 // occurrence's word in rows_out tells its place in its sub-list until it holds the row (stored and read at agent scope: its
 // block and the duplicates' run together), and the number of a winner follows from its place, so that nobody waits for
-// anybody.  Nor does the thread that settles the counters: all others know the free rows from kFreeBefore.  The kernel is a
+// anybody.  Nor does the thread that settles the counters, while other blocks run: it alone may touch free_n and hwm here, and
+// all others know the free rows from kFreeBefore, which the call's first kernel has noted.  The kernel is a
 // chain of dependent accesses, and with the duplicates after the insertion, in a pass of their own, and a block that
 // finishes last and settles, it was one of ten.  A kernel of its own for duplicates and counters is a launch more, 3 us of a
 // call that has no miss (steps of 5 to 200 K known IDs 23 -> 19, 30 -> 28, 64 -> 60 us).  Large batches have it: the
 // winners' places are a write more per new key (6.8 M IDs, a million new: election and
 // insertion 276 us, with resolve_kernel 267).
+// (Two or three registers of a lane are spilled to keep to eight waves a SIMD.)
 template <typename E, bool kAll>
 __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n, uint32_t step, uint32_t epoch,
                                                         int32_t* rows_out, RestoreSource src, uint64_t enough) {
@@ -545,7 +548,7 @@ __global__ __launch_bounds__(256, 8) void insert_kernel(TableView t, uint64_t n,
       k = e.key;
       if (room) row = t.free_rows[free0 - 1 - (int32_t)w];
       const int32_t found = row == kNoRow ? kRowAbsent : (int32_t)row;
-      if (kAll)  // (other blocks look for it below)
+      if (kAll)  // (the threads of its duplicates, in any block, may be looking for it)
         st_agent(&rows_out[e.occ], found);
       else
         rows_out[e.occ] = found;

@@ -13,6 +13,10 @@
 // with 1 % unknown 10 to 14 and 16 to 22, 5 % 12 to 16 and 18 to 24); from a third of them unknown on one block's work costs as
 // much as the launches it saves (30 % 16 to 30 and 21 to 26), and all of them, where they are admitted, twice as much (54 to 68
 // and 31; 27 and 24 where they are not).
+// (Lookups with 5, 30 and 100 % new keys, dim 16, 2^22 slots, us, with the eight exchanges of an insertion unrolled and every
+// bucket's age byte read, and as they are now, see try_claim: 200 IDs 12.4 / 11.0, 14.4 / 11.9, 15.7 / 13.2, 1000 14.0 / 11.6,
+// 15.6 / 12.9, 24.2 / 19.9, 4096 16.4 / 13.7, 29.3 / 22.9, 73 / 54; with expiry 13.8 / 12.1 to 17.3 / 14.5, 15.6 / 12.8 to
+// 27.3 / 21.5, 17.9 / 14.9 to 85 / 58.)
 //
 // Blocks run on different XCDs, whose L2s are not coherent for ordinary accesses.  What a block leaves for
 // the last one in this same kernel (missing occurrences, counters, last-seen stamps that an eviction may

@@ -297,7 +297,8 @@ __global__ __launch_bounds__(256) void sweep_remove_kernel(TableView t, uint32_t
   const int32_t free0 = t.ctl->free_n;                     // settled by the last block, constant until then
   const unsigned long long out0 = t.ctl->scratch[kSweepRemoved];       // keys already reported from the stash
   const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * blockDim.x + (threadIdx.x & ~63u))); w0 < total; w0 += stride) {
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * blockDim.x + (threadIdx.x & ~63u)));
+  for (uint32_t w0 = first; w0 < total; w0 += stride) {
     const uint32_t w = w0 + lane;
     uint32_t before;
     const uint32_t list = list_holding(inc, w, w0, w < total, &before);
@@ -440,8 +441,9 @@ hipError_t launch_export(const TableView& t, int64_t* d_keys, int32_t* d_row, ui
                          uint64_t max_n, bool touched_only, hipStream_t stream) {
   hipLaunchKernelGGL(export_begin_kernel, dim3(1), dim3(64), 0, stream, t);
   const uint64_t total = t.capacity + kStashCap;
-  hipLaunchKernelGGL(export_kernel, dim3((unsigned)((total + kExportBlock * kExportPer - 1) / (kExportBlock * kExportPer))), dim3(kExportBlock), 0,
-                     stream, t, d_keys, d_row, d_last_seen, d_slot, max_n, touched_only);
+  constexpr uint64_t kPerBlock = kExportBlock * kExportPer;
+  hipLaunchKernelGGL(export_kernel, dim3((unsigned)((total + kPerBlock - 1) / kPerBlock)), dim3(kExportBlock), 0, stream, t, d_keys,
+                     d_row, d_last_seen, d_slot, max_n, touched_only);
   return hipGetLastError();
 }
 
@@ -504,8 +506,8 @@ hipError_t launch_copy_to_host(const CopyParts& parts, uint32_t n, hipStream_t s
   for (uint32_t p = 0; p < n; ++p) most = parts.words[p] > most ? parts.words[p] : most;
   if (most == 0) return hipSuccess;
   const uint64_t blocks = (most + 4 * kCopyBlock - 1) / (4 * kCopyBlock);
-  hipLaunchKernelGGL(copy_to_host_kernel, dim3((unsigned)(blocks < kCopyBlocks ? blocks : kCopyBlocks)), dim3(kCopyBlock), 0, stream,
-                     parts, n);
+  hipLaunchKernelGGL(copy_to_host_kernel, dim3((unsigned)(blocks < kCopyBlocks ? blocks : kCopyBlocks)), dim3(kCopyBlock), 0,
+                     stream, parts, n);
   return hipGetLastError();
 }
 

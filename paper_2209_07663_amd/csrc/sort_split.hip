@@ -99,9 +99,9 @@ __global__ __launch_bounds__(kBlock) void sort_split_kernel(Control* __restrict_
   const uint32_t unit = blockIdx.x, ubase = unit * kItems, uend = ubase + kItems < n ? ubase + kItems : n;
   const uint32_t base = ubase + wave * kPerWave;
 
-  // The bag that holds the unit's first occurrence, or one not far before it: the last one whose offset is not behind.  A thread looks at
-  // one bag a step; the steps lie between the barriers of what else is to be done.  (Whatever the offsets hold, `lo`
-  // stays below n_bags.)
+  // The bag that holds the unit's first occurrence, or one not far before it: the last one whose offset is not behind.  A
+  // thread looks at one bag a step; the steps lie between the barriers of what else is to be done.  (Whatever the offsets
+  // hold, `lo` stays below n_bags.)
   uint64_t lo = 0, hi = n_bags;
   const auto not_behind = [&]() {
     const uint64_t step = (hi - lo + kBlock - 1) / kBlock, p = lo + (uint64_t)(tid + 1) * step;
@@ -473,7 +473,7 @@ __device__ inline void sort_bucket(BucketLds<kBlock>& s, T (&e)[kRounds], T* roo
 // The pairs are in registers between the digits and in one LDS buffer, so that four blocks fit a compute unit (a million pairs
 // have 1024 ordinary bins, all of which run at a time then), and a digit is one walk over them.  With two LDS buffers, two blocks
 // to a compute unit and a walk more to count, us: a million pairs 27.4 -> 20.2, 690 K 16.0 -> 13.0, 204 K 11.0 -> 9.5, 26 K 6.0
-// either way.
+// either way.  (Blocks of 512 threads spill two registers of a lane for eight waves a SIMD.)
 template <int kBlock>
 __global__ __launch_bounds__(kBlock, kBlock == 512 ? 8 : 4) void sort_bucket_kernel(Control* __restrict__ ctl, const uint2* __restrict__ src,
                                                              uint32_t items, uint32_t units, uint32_t units_pow2,

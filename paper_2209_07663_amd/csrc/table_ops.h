@@ -17,14 +17,14 @@
 
 namespace mono {
 
-// Counts are kept unsaturated in the low half of a counter word and read as min(count, 255).  Where
-// counters age, the first touch of a batch cuts the count back to 255; where they do not, the host has all counts cut
-// back (launch_filter_cut) before they could have taken more than kCountMost occurrences since the last time.
 // Are counters marked that are at the threshold (see reached_mark)?
 __device__ inline bool marks_reached(const TableView& t, uint64_t n) {
   return t.expire_steps == 0 && t.freq_threshold > 1u && n > kElectSmall;
 }
 
+// Counts are kept unsaturated in the low half of a counter word and read as min(count, 255).  Where
+// counters age, the first touch of a batch cuts the count back to 255; where they do not, the host has all counts cut
+// back (launch_filter_cut) before they could have taken more than kCountMost occurrences since the last time.
 // one counter word: `times` occurrences at `step`; `held`, if `known`: what it held a moment ago (an ordinary
 // load will do, the exchange tells whether it still holds that).  kMark (where nothing ages): notes a count that is at the
 // threshold now.
@@ -181,7 +181,8 @@ __device__ void cuckoo_insert(const TableView& t, uint64_t k, unsigned long long
       const uint64_t vk = atomicExch((unsigned long long*)&b->key[l], (unsigned long long)k);
       wait_all_memory_ops();  // the key exchange is performed before the slot is published again
       st_agent(&b->meta[l], meta);
-      if (unit == kAgeLook) note_key(t, b, unit, age_word(t, b));  // (a key of the current step leaves the bound of a full bucket as it is)
+      // (a key of the current step leaves the bound of a full bucket as it is)
+      if (unit == kAgeLook) note_key(t, b, unit, age_word(t, b));
       k = vk;
       meta = old;
       unit = kAgeLook;
@@ -267,8 +268,9 @@ __device__ inline void post_hwm(const TableView& t, uint32_t epoch, uint32_t hwm
                      __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Settles the counters of a call that elected `total` new keys when free0 rows were free and the mark was hwm0 (one
-// thread, after everybody has read free_n; it reads nothing itself, which would be one more trip to memory at the end).
+// Settles the counters of a call that elected `total` new keys when free0 rows were free and the mark was hwm0.  One thread,
+// when nobody reads free_n or hwm any more: after all others, or beside them where they go by kFreeBefore (insert_kernel).  It
+// reads nothing itself, which would be one more trip to memory at the end.
 __device__ inline void settle_call(const TableView& t, uint32_t total, int32_t free0, uint32_t hwm0, uint32_t epoch) {
   const uint32_t offer = (uint32_t)rows_on_offer(t.capacity, free0);
   const uint32_t got = total <= offer ? total : 0u;  // all of the call's new keys or none

@@ -7,7 +7,7 @@
 //   order_tiles  (many gradients, each of several occurrences) the order in which seg_reduce takes its tiles
 //   seg_reduce   the sorted sequence is cut into tiles, a block each, and a tile into chunks, one for each lane
 //                group of the block (dim/4 lanes, four elements each); the group loads its chunk's pairs at once, then walks
-//                them with eight gradient rows in flight, summing grad[bag] along each run.  A run that lies
+//                them with four or eight gradient rows in flight, summing grad[bag] along each run.  A run that lies
 //                inside the chunk is complete: Adagrad is applied at once.  A run that crosses a
 //                chunk border leaves a partial sum; a segmented scan over the block's chunks then joins the
 //                partials of runs that stay inside the block's tile (Adagrad again) and only runs
@@ -378,7 +378,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
     E* rows = reinterpret_cast<E*>(t.rows);
     const float inv_dim = 1.0f / (float)t.dim;
     for (uint32_t p0 = 0; p0 < count;) {  // position of the batch in the chunk
-      // nothing ends in the next kLong pairs of any group of the wave (rows ascend): only gradients are read
+      // nothing ends in the next kLong pairs of any group of the wave (a row's pairs are neighbours): only gradients are
+      // read
       const uint32_t row = mine[p0].x;
       if (kLong > 0 && !__ballot(p0 + kLong > count || row != (p0 + kLong < count ? mine[p0 + kLong].x : after))) {
         Vec v[kLong > 0 ? kLong : 1];
