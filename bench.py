@@ -42,9 +42,9 @@ BUCKET_LINE = 128       # bytes of a bucket as this library stores it (keys + ro
 # profiled command, together with the name of the summary it comes from; otherwise `traffic` is null.
 TRAFFIC_FROM_PROFILE = {
     "cfg2": {"profile": "profiles/bench_cfg2_full_step.md", "fill_load": 0.5,
-             "step": 3458.6e6,
-             "kernels": {"probe_count": 970.0e6, "seg_reduce": 1126.9e6, "gather_pool": 531.4e6,
-                         "admit_elect": 280.2e6, "sort_scatter": 97.1e6, "sort_hist": 49.2e6, "insert": 76.0e6}},
+             "step": 3368.5e6,
+             "kernels": {"probe_count": 973.5e6, "seg_reduce": 1126.9e6, "gather_pool": 531.9e6,
+                         "admit_elect": 183.4e6, "sort_scatter": 96.7e6, "sort_hist": 49.2e6, "insert": 80.0e6}},
 }
 
 

@@ -9,9 +9,10 @@
 // of kIdsInRegs indices, the next step's indices requested before this step's rows are waited for (bags
 // of 23 IDs on average, dim 36: 144 us per launch when the rest of a long bag was read one row at a time,
 // 20 us so).  A wave whose bags all hold at most two IDs, or one (one-hot slots), issues four or eight rounds of row reads
-// together instead (a million bags of one ID, bf16 of dim 64, us: 81 round by round, 67 four together, 61 eight; fp32 rows, 4 M
-// uniform ones, of dim 32 52 two by two, 49 one by one, which is what eight rounds are if the rows are not held, and 44
-// together, of dim 64 97, 89 and 83; bags of two, dim 32, 78 two by two and 65; 300 K bags of one 15.8, 14.5 and 15.0).
+// together instead (a million bags of one ID, bf16 of dim 64, us: 81 round by round, 67 four together; eight 61 there, and within
+// 3 % of four with other tables and dims.  fp32 rows, 4 M uniform ones: of dim 32 52 two by two, 49 one by one, which is what
+// eight rounds are if the rows are not held, and 44 together, of dim 64 97, 89 and 83; bags of two, dim 32, 78 two by two and
+// 65.  In training steps of a million Zipf IDs of dim 64: 93, 88 and 76, in bags of two 65 and 49).
 //
 // How many bags a wave owns decides how many waves there are, and the kernel is latency-bound below a few
 // thousand of them: 64, where that still leaves kWavesWanted waves (the index loads are then as coalesced as they can be),

@@ -409,7 +409,8 @@ __global__ __launch_bounds__(256) void seg_reduce_kernel(TableView t, const uint
       kx[kBatch] = p0 + kBatch < count ? mine[p0 + kBatch].x : after;
       // everything the batch needs from memory is requested before anything is consumed: the
       // gradient row of every pair and, for every run that ends in the batch and lies inside the
-      // chunk, its embedding row and accumulator
+      // chunk, its embedding row and accumulator.  (bf16 rows are widened in the branch that reads them, which
+      // waits for them there: where several runs end, their reads follow one another.)
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) {
         const bool in = p0 + (uint32_t)u < count;
