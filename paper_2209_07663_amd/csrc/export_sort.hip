@@ -19,6 +19,7 @@
 // element.
 #include "common.h"
 #include "kernels.h"
+#include "sort_ops.h"
 
 namespace mono {
 
@@ -270,21 +271,14 @@ __global__ __launch_bounds__(kThreads) void export_scatter_kernel(const uint64_t
   for (uint32_t r = 0; r < kRounds; ++r) {
     const bool valid = base + (uint64_t)r * 64 + lane < n;
     const uint32_t digit = (uint32_t)(key[r] >> shift) & 255u;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (uint32_t b = 0; b < 8; ++b) {
-      const bool bit = (digit >> b) & 1u;
-      const uint64_t vote = __ballot(bit);
-      peers &= bit ? vote : ~vote;
-    }
-    const uint32_t at = wave_load(off + digit);
+    const uint64_t peers = same_digit_lanes<8>(digit, valid);
+    const uint32_t before = lanes_before(peers), at = wave_load(off + digit);
     if (valid) {
-      const uint32_t p = at + (uint32_t)__popcll(peers & lanes_below());
-      s_key[p] = key[r];
-      s_idx[p] = idx[r];
+      s_key[at + before] = key[r];
+      s_idx[at + before] = idx[r];
     }
     wave_order();
-    if (valid && (peers & lanes_below()) == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
+    if (valid && before == 0) wave_store(off + digit, at + (uint32_t)__popcll(peers));
     wave_order();
   }
   __syncthreads();

@@ -1,4 +1,4 @@
-// Device functions that the kernels of the pair sort share.
+// Device functions that the sorts of pairs and of exported keys share.
 #pragma once
 
 #include "common.h"
