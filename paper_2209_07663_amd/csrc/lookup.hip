@@ -118,8 +118,10 @@ constexpr uint64_t kProbeBlocksWanted = 1024, kProbeMaxTurns = 8;
 // Largest batch for which both buckets and the counter are asked for at once.  lookup_or_insert of uniform keys in a table of
 // 2^24 slots, one access after the other and at once, us: a third unknown and kept out, counters that age 20 K 15.1 / 11.8, 60 K
 // 16.3 / 14.4, 120 K 18.2 / 20.3, that do not 60 K 16.4 / 14.4, 120 K 19.2 / 18.4, 200 K 25.0 / 26.1; all known 20 K 8.8 / 9.0,
-// 60 K 12.5 / 13.0, 120 K 14.0 / 15.9, 200 K 16.2 / 22.4.  (The rule does not ask whether the call before missed: batches that are
-// all known lose 2 to 4 % of the kernel by it, of a call whose three launches take the host 12 us.)
+// 60 K 12.5 / 13.0, 120 K 14.0 / 15.9, 200 K 16.2 / 22.4.  (The rule does not ask whether the call before missed.  With a
+// word for that, which the insertion writes, the three kernels of 5 K, 20 K and 60 K keys take, now and so, all known 9.9 / 9.7,
+// 10.2 / 10.0, 11.2 / 10.5, of a call whose launches take the host 12 us, a third unknown 18.8 / 18.8, 19.3 / 19.5, 21.1 / 21.2, where
+// counters age 18.5 / 18.8, 19.5 / 19.7, 21.1 / 21.6.)
 constexpr uint64_t kProbeSmall = 1u << 16;
 static_assert(kProbeSmall < 2 * kProbeBlock * kProbeBlocksWanted, "a key per thread");
 constexpr int kProbeTries = 8;  // slots of the set that a missing key looks at
